@@ -60,7 +60,7 @@ struct FineT {
     static DI u32 kstart(pkey_t k) { return (u32)(IDX) ~(IDX)k; }
     DI u64 *list_at(u32 place) const { return arena + ((size_t)place << gs); }
     // TH 0: ssz[] / swit[] / soff[] live in LDS.  TH 2: swit[] and soff[], TH 3: all three live in the
-    // trace's workspace slice: then they are read with device-scope loads and moved by gblk_shift_*;
+    // trace's workspace slice: then they are read with workgroup-scope loads and moved by gblk_shift_*;
     // IDX is 16 bits wide there
     // before the first read of these tables after they were written (the stores must have arrived)
     DI void tables_written() const

@@ -32,11 +32,14 @@ DI void wave_sync()
 // build that runs the lanes one after another switches lanes here.
 DI void wave_lockstep() {}
 
-// a 64-bit word of a list in global memory: read at device scope, past the compute unit's
-// vector cache (lists are written and read by the same wavefront, and read once)
-DI u64 ld_list(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// a 64-bit word of a list in global memory.  Lists and tables are written and read by one wavefront
+// only, so workgroup scope is enough: the compute unit's vector cache may answer (it is written
+// through, and the accesses of one wavefront pass it in order).  A hit there takes 133 cycles, the
+// device scope used before went to L2 every time, 303 cycles (both measured on a dependent chain);
+// the workloads with their tables in the workspace gain 1 to 2 % (scale-out, 320 traces: 16.97 -> 16.64 ms).
+DI u64 ld_list(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 // the same for one 16-bit element of a table kept in global memory
-DI u32 ld_tab(const uint16_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+DI u32 ld_tab(const uint16_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
 // The wavefront's priority at instruction issue (0, the default, to 3) from here on.  The stitching
 // kernels hold LDS for as long as they run and the splitting kernels beside them hold none, so the

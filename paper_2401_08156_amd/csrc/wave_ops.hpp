@@ -247,7 +247,7 @@ template <class K>
 struct Probe2 {
     K v0, v1;       // per lane
     u32 stride;     // wave-uniform
-    // G: the array is a table in global memory (16-bit keys, read past the vector cache)
+    // G: the array is a table in global memory (16-bit keys)
     template <bool G = false>
     DI K at(const K *a, u32 i) const
     {
@@ -395,7 +395,7 @@ DI void blk_shift_down(T *a, u32 pos, u32 n)
 }
 
 // The same moves for N arrays of 16-bit elements kept in GLOBAL memory (tables of the fine-grained
-// stitching kernel that do not fit the LDS budget).  Blocks are read with device-scope loads (other
+// stitching kernel that do not fit the LDS budget).  Blocks are read with workgroup-scope loads (other
 // lanes of this wavefront wrote them; tbl_fence() first, so that their stores have arrived), G steps of
 // 64 blocks are on their way before the first store.  A step never reads a block that an earlier step
 // of the same call has written.
