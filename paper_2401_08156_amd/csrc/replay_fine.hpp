@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
     V.sp.template refresh<TH == 3>(V.ssz, 0u);
     wave_sync();
 
-    u32 requested = 0, active = 0, peak_requested = 0, peak_active = 0;
+    u32 lost = 0;               // request of a FREE that outgrew a table: the trace ends there, the request counts as gone
     u32 sp_reserved = 0;        // small-request pool: units reserved so far
     bool stop = false;
     TileOut T;
@@ -1114,42 +1114,40 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
             const u64 x = pin64(ev_row[min(nx, n_ev - 1)]);
             ev_next = nx < n_ev ? x : 0;
         }
-        u32 v_dlo = 0, v_dhi = 0, v_act = 0, v_res = 0;
+        u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_act = 0, v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
         u32 done = tile, todo = tile;       // todo drops to 0 when an engine table overflows: the trace ends there
         // every path of an event ends by parking its results in lane j and going on to the next event
-#define EMIT(DLO, DHI)                                                     \
+#define EMIT(DLO, DHI, DREQ, DACT)                                         \
     {                                                                      \
-        write_lane4(v_dlo, v_dhi, v_act, v_res, (DLO), (DHI), active,      \
-                    sp_reserved + (V.n_chunks << P.chunk_shift), j);       \
+        write_lane4(v_dlo, v_dhi, v_req, v_act, (DLO), (DHI), (DREQ), (DACT), j); \
         wave_sync();                                                       \
         continue;                                                          \
     }
+        // memory was reserved: the events from this one on see the new total
+#define RESERVED_NOW() v_res = lane >= j ? sp_reserved + (V.n_chunks << P.chunk_shift) : v_res
         for (u32 j = 0; j < todo; j++) {
             const u32 w = from_lane(ev_lo, j), slot = from_lane(ev_hi, j);
-            if (UNLIKELY(slot >= P.max_slots)) EMIT((u32)C_INVALID, 0u)
+            if (UNLIKELY(slot >= P.max_slots)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
             const u32 req = S.get_req(slot);
             if ((int)w < 0) {
                 // ---- FREE.  Update (Sec. 3.3.2): only activity flips; memory stays with its pBlocks
                 if (UNLIKELY(req + 1u <= 1u)) {             // unbound, or bound to a request that failed
                     if (req == SLOT_OOM) {
                         S.set_req(slot, (u32)SLOT_UNBOUND);
-                        EMIT((u32)C_FREE_NOOP, 0u)
+                        EMIT((u32)C_FREE_NOOP, 0u, 0u, 0u)
                     }
-                    EMIT((u32)C_INVALID, 0u)
+                    EMIT((u32)C_INVALID, 0u, 0u, 0u)
                 }
                 const u32 a = S.get_a(slot), b = S.get_b(slot);
                 const u32 kind = b & 3;
                 S.set_req(slot, (u32)SLOT_UNBOUND);
-                requested -= req;
                 if (LIKELY((kind & KIND_SBLOCK) != 0)) {
                     fine_free_sblock(V, S.get_c(slot));
-                    active -= (b >> 2) << P.chunk_shift;
-                    EMIT(C_FREE | B_SBLOCK, a)
+                    EMIT(C_FREE | B_SBLOCK, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
                 }
                 if (kind == KIND_PBLOCK) {
                     bmp_fill(V.bmp, V.w_spare, a, b >> 2, false);
-                    active -= (b >> 2) << P.chunk_shift;
-                    EMIT((u32)C_FREE, a)
+                    EMIT((u32)C_FREE, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
                 }
                 if (LIKELY(P.small_regs)) {
                     // (each outcome parks its results and goes on from where it is found: handed back
@@ -1159,12 +1157,12 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                     A.idle = V.idle;
                     Q.release(a >> 2, req, a & 3, A, base + j,
                               [&](bool ml, bool mr) {
-                                  active -= req;
-                                  write_lane4(v_dlo, v_dhi, v_act, v_res, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                              a >> 2, active, sp_reserved + (V.n_chunks << P.chunk_shift), j);
+                                  write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
+                                              a >> 2, 0u - req, 0u - req, j);
                                   wave_sync();
                               },
                               [&]() {
+                                  lost = req;
                                   stop = true;
                                   done = j;
                                   todo = 0;
@@ -1174,17 +1172,17 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                 bool ml = false, mr = false;
                 small_free(lds, P, V.idle, a >> 2, req, a & 3, base + j, &ml, &mr);
                 if (UNLIKELY(ld_uni((u32 *)(lds + LDS_SCALARS), (u32)SC_STOP) != 0)) {
+                    lost = req;
                     stop = true;
                     done = j;
                     todo = 0;
                     continue;
                 }
-                active -= req;
-                EMIT(C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2)
+                EMIT(C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2, 0u - req, 0u - req)
             }
             // ---- ALLOC
             const u32 size = w;
-            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) EMIT((u32)C_INVALID, 0u)
+            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
             u32 dlo, dhi = 0, held_units = size;
             if (LIKELY(size >= P.small_limit_units)) {
                 const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
@@ -1193,11 +1191,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                 if (fine_s1_sblock(V, bsize, ref, place)) {
                     S.bind(slot, size, ref, KIND_SBLOCK | (bsize << 2), place);
                     if (!SLOT_REGS) S.set_c(slot, place);
-                    requested += size;
-                    active += bsize << P.chunk_shift;
-                    peak_requested = max(peak_requested, requested);
-                    peak_active = max(peak_active, active);
-                    EMIT(C_EXACT | B_SBLOCK | (1u << 8), ref)
+                    EMIT(C_EXACT | B_SBLOCK | (1u << 8), ref, size, bsize << P.chunk_shift)
                 }
                 // pool[lo_p, hi_p): the multi-chunk pBlocks of exactly bsize chunks
                 u32 lo_p, hi_p;
@@ -1205,11 +1199,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                 if (bsize > 1 ? fine_s1_pblock(V, lo_p, hi_p, ref) : s1_single(V, ref)) {
                     bmp_fill(V.bmp, V.w_spare, ref, bsize, true);
                     S.bind(slot, size, ref, KIND_PBLOCK | (bsize << 2), 0u);
-                    requested += size;
-                    active += bsize << P.chunk_shift;
-                    peak_requested = max(peak_requested, requested);
-                    peak_active = max(peak_active, active);
-                    EMIT(C_EXACT | (1u << 8), ref)
+                    EMIT(C_EXACT | (1u << 8), ref, size, bsize << P.chunk_shift)
                 }
                 // ---- no exact fit: states S2 to S5
                 VmsRes R;
@@ -1241,7 +1231,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                     Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
                             [&](u32 code, u32 addr, u32 flags, bool split) {
                                 sp_reserved = Q.reserved();
-                                u32 d_lo = C_OOM, d_hi = 0;
+                                u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
                                 if (code == C_OOM) {
                                     S.set_req(slot, (u32)SLOT_OOM);
                                     ColdState C;            // rare: note the first failed request
@@ -1252,15 +1242,12 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                                     S.set_a(slot, (addr << 2) | flags);
                                     S.set_b(slot, (u32)KIND_SMALL);
                                     S.set_req(slot, size);
-                                    requested += size;
-                                    active += size;
-                                    peak_requested = max(peak_requested, requested);
-                                    peak_active = max(peak_active, active);
+                                    if (code == C_GROW) RESERVED_NOW();
                                     d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
                                     d_hi = addr;
+                                    d_req = size;
                                 }
-                                write_lane4(v_dlo, v_dhi, v_act, v_res, d_lo, d_hi, active,
-                                            sp_reserved + (V.n_chunks << P.chunk_shift), j);
+                                write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
                                 wave_sync();
                             },
                             [&]() {
@@ -1291,17 +1278,15 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                 ColdState C;                                // rare: note the first failed request
                 C.load(lds);
                 if (C.get(SC_FIRST_OOM) == NONE32) st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                EMIT((u32)C_OOM, 0u)
+                EMIT((u32)C_OOM, 0u, 0u, 0u)
             }
             S.set_req(slot, size);
-            requested += size;
-            active += held_units;
-            peak_requested = max(peak_requested, requested);
-            peak_active = max(peak_active, active);
-            EMIT(dlo, dhi)
+            if ((dlo & 15) == C_GROW) RESERVED_NOW();
+            EMIT(dlo, dhi, size, held_units)
         }
 #undef EMIT
-        tile_emit(T, dec_row, base, done, v_dlo, v_dhi, v_act, v_res);
+#undef RESERVED_NOW
+        tile_emit<false>(T, dec_row, base, done, v_dlo, v_dhi, v_req, v_act, v_res);
         if (stop) break;
     }
 
@@ -1319,29 +1304,29 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
 #pragma unroll
         for (u32 c = 0; c < 8; c++) s.n_code[c] = n_code[c];
         const u64 reserved = sp_reserved + (V.n_chunks << P.chunk_shift);
-        s.peak_requested = (u64)peak_requested * 512;
-        s.peak_active = (u64)peak_active * 512;
+        s.peak_requested = (u64)T.peak_requested * 512;
+        s.peak_active = (u64)T.peak_active * 512;
         s.peak_reserved = reserved * 512;           // reserved memory never shrinks: its peak is its final value
-        s.final_requested = (u64)requested * 512;
-        s.final_active = (u64)active * 512;
+        s.final_requested = (u64)(T.requested - lost) * 512;
+        s.final_active = (u64)T.active * 512;
         s.final_reserved = reserved * 512;
         s.digest = digest;
-        s.n_split = sc[SC_N_SPLIT];
-        s.n_merge = sc[SC_N_MERGE];
+        s.n_split = sc[SC_N_SPLIT] + T.n_split;
+        s.n_merge = T.n_merge;
         s.n_sblock_created = sc[SC_N_CREATED];
         s.n_sblock_evicted = sc[SC_N_EVICTED];
         s.first_oom_event = sc[SC_FIRST_OOM];
         s.status = sc[SC_STATUS] | (n_code[7] ? VMS_ST_INVALID_EVENT : 0u);
         s.max_pblocks = sc[SC_HW_PBLOCKS];
         s.max_sblocks = sc[SC_HW_SBLOCKS];
-        s.max_free_blocks = sc[SC_HW_FREE];
+        s.max_free_blocks = max(sc[SC_HW_FREE], Q.most());
         s.max_members = sc[SC_HW_MEMBERS];
         s.max_runs = sc[SC_HW_RUNS];
         s.overflow_event = sc[SC_OVF_EVENT];
         s.max_multi_pblocks = sc[SC_HW_MULTI];
         s.reserved1 = 0;
         // Sec. 5.1: fragmentation = 1 - utilisation, utilisation = peak active / peak reserved
-        s.fragmentation = reserved ? 1.0 - (double)peak_active / (double)reserved : 0.0;
+        s.fragmentation = reserved ? 1.0 - (double)T.peak_active / (double)reserved : 0.0;
     }
     wave_sync();
     } while (P.retry);

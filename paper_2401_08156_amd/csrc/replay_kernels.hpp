@@ -34,7 +34,7 @@ enum {
     SC_SP_N,                                            // blocks in the splitting pool for requests below one chunk
     SC_NP_ALL,                                          // fine-grained variant: pBlocks of any size
     SC_STATE_COUNT,
-    SC_N_SPLIT = SC_STATE_COUNT, SC_N_MERGE, SC_N_CREATED, SC_N_EVICTED, SC_FIRST_OOM, SC_STATUS, SC_OVF_EVENT, SC_STOP,
+    SC_N_SPLIT = SC_STATE_COUNT, SC_N_CREATED, SC_N_EVICTED, SC_FIRST_OOM, SC_STATUS, SC_OVF_EVENT, SC_STOP,
     SC_HW_PBLOCKS, SC_HW_SBLOCKS, SC_HW_FREE, SC_HW_MEMBERS, SC_HW_RUNS, SC_HW_MULTI,
     SC_COUNT
 };
@@ -280,7 +280,6 @@ DI void sp_alloc(SplitPoolD &sp, u32 size, u32 seg, bool may_grow, AcctT &A, u32
         r.flags &= 2;
         r.split = true;
         if (r.code == C_EXACT) r.code = C_SPLIT;
-        A.add(SC_N_SPLIT, 1);
     }
 }
 
@@ -332,7 +331,6 @@ DI void sp_free(SplitPoolD &sp, u32 addr, u32 size, u32 flags, bool *ml, bool *m
         size += (u32)(lkey >> 32);
         flags = ((u32)lkey & 2) | (flags & 1);
     }
-    A.add(SC_N_MERGE, (*ml ? 1u : 0u) + (*mr ? 1u : 0u));
     const u64 key = ((u64)size << 32) | ((u64)addr << 2) | flags;
     if (*ml) {
         st_one(sp.fl, lidx, key);               // merged block takes the left neighbour's place
@@ -372,6 +370,7 @@ struct SplitLds {
         wave_sync();
     }
     DI u32 reserved() const { return sp.reserved; }
+    DI u32 most() const { return 0; }       // (kept in the counters)
     // done(code, addr, flags, split) once the request is decided (code C_OOM: it failed), ovf() if
     // the table is full instead (see SplitRegs)
     template <class AcctT, class Done, class Ovf>
@@ -400,15 +399,17 @@ template <u32 TILES>
 struct SplitRegs {
     u64 k[TILES];
     u32 n, cap, res;
+    u32 hw;                     // the most blocks held at once (cuts and merges are counted off the decisions)
     DI void init(char *, const KParams &P)
     {
 #pragma unroll
         for (u32 t = 0; t < TILES; t++) k[t] = 0;
-        n = 0;
+        n = hw = 0;
         cap = P.cap_free;
         res = 0;
     }
     DI u32 reserved() const { return res; }
+    DI u32 most() const { return hw; }
     // keys are unique (they contain the address): the place that holds `from` (not 0) takes `to`,
     // found by comparing every place with it, with no book-keeping of where a key sits
     DI void swap_key(u64 from, u64 to)
@@ -429,6 +430,7 @@ struct SplitRegs {
             todo = todo && !here;
         }
         n++;
+        hw = max(hw, n);
     }
     // Every outcome ends in a call of its own: done(code, addr, flags, split) once the request is
     // decided (code C_OOM: it failed) or ovf() if the table is full.  Results handed back through
@@ -460,8 +462,6 @@ struct SplitRegs {
                 // step 2: cut off what is not needed; it stays cached as the right neighbour, in the
                 // place the block had
                 swap_key(chosen, ((u64)(mhi - size) << 32) | ((u64)(addr + size) << 2) | (flags & 1));
-                A.peak(SC_HW_FREE, n);
-                A.add(SC_N_SPLIT, 1);
                 done((u32)C_SPLIT, addr, flags & 2, true);
                 return;
             }
@@ -483,8 +483,6 @@ struct SplitRegs {
                 return;
             }
             insert(((u64)(seg - size) << 32) | ((u64)(addr + size) << 2) | 1u);
-            A.peak(SC_HW_FREE, n);
-            A.add(SC_N_SPLIT, 1);
             done((u32)C_GROW, addr, 2u, true);
             return;
         }
@@ -521,7 +519,6 @@ struct SplitRegs {
             size += (u32)(lkey >> 32);
             flags = ((u32)lkey & 2) | (flags & 1);
         }
-        A.add(SC_N_MERGE, (*ml ? 1u : 0u) + (*mr ? 1u : 0u));
         const u64 key = ((u64)size << 32) | ((u64)addr << 2) | flags;
         if (UNLIKELY(*ml)) {
             swap_key(lkey, key);                // the merged block takes the left neighbour's place
@@ -538,7 +535,6 @@ struct SplitRegs {
                 return;
             }
             insert(key);
-            A.peak(SC_HW_FREE, n);
         }
         done(ml_, mr_);
     }
@@ -1360,15 +1356,24 @@ DI void small_free(char *lds, const KParams &P, u32 *idle, u32 addr, u32 size, u
     wave_sync();
 }
 
-// The per-tile work shared by both replay kernels: one event per lane.
+// The per-tile work shared by the replay kernels: one event per lane.  An event parks what it changed
+// (decision word, change of requested and active units) in its lane; the running totals, their peaks
+// and the split and merge counts are taken from the 64 lanes once per tile.  Kept per event they cost
+// eight scalar operations each time (4.4 cycles apiece on a wavefront alone) and four scalar registers
+// that the stitching kernels had to keep in vector lanes; two prefix sums and two maxima per tile cost
+// five cycles per event.
 struct TileOut {
     u32 n_code[8];              // events of this lane per decision code ([7]: invalid)
     u64 dig;                    // this lane's share of the digest
+    u32 requested, active;      // wave-uniform: after the tiles so far
+    u32 peak_requested, peak_active;
+    u32 n_split, n_merge;       // of the splitting pools: cuts and merges the decision words report
     DI void init()
     {
 #pragma unroll
         for (u32 c = 0; c < 8; c++) n_code[c] = 0;
         dig = 0;
+        requested = active = peak_requested = peak_active = n_split = n_merge = 0;
     }
 };
 
@@ -1378,7 +1383,10 @@ __device__ __attribute__((noinline)) void emit_partial(u64 *dst, u64 dec, u32 do
     if (lane_id() < done) dst[lane_id()] = dec;
 }
 
-DI void tile_emit(TileOut &T, u64 *dec_row, u32 base, u32 done, u32 v_dlo, u32 v_dhi, u32 v_act, u32 v_res)
+// v_req / v_act: what each event added to the requested and active units (modulo 2^32; lanes that hold no
+// event hold zeros), v_res: units reserved after it.  SAME: active is requested (splitting policy).
+template <bool SAME>
+DI void tile_emit(TileOut &T, u64 *dec_row, u32 base, u32 done, u32 v_dlo, u32 v_dhi, u32 v_req, u32 v_act, u32 v_res)
 {
     const u32 lane = lane_id();
     const bool valid = lane < done;
@@ -1390,8 +1398,22 @@ DI void tile_emit(TileOut &T, u64 *dec_row, u32 base, u32 done, u32 v_dlo, u32 v
     const u32 code = v_dlo & 15, cidx = !valid ? 8u : (code == C_INVALID ? 7u : code);
 #pragma unroll
     for (u32 c = 0; c < 8; c++) T.n_code[c] += cidx == c ? 1u : 0u;
+    // the totals only rise on an allocation, so their maximum over all events is their peak
+    u32 tot;
+    const u32 req = T.requested + wave_scan_add(v_req, &tot);
+    T.requested += tot;
+    T.peak_requested = max(T.peak_requested, ~wave_min_u32(~req));
+    u32 act = req;
+    if (!SAME) {
+        act = T.active + wave_scan_add(v_act, &tot);
+        T.active += tot;
+        T.peak_active = max(T.peak_active, ~wave_min_u32(~act));
+    }
+    const bool pool = valid && (SAME || (v_dlo & B_SMALL)) && code <= C_GROW;
+    T.n_split += popc64(ballot(pool && code != C_FREE && (v_dlo & B_6)));
+    T.n_merge += popc64(ballot(pool && code == C_FREE && (v_dlo & B_6))) + popc64(ballot(pool && code == C_FREE && (v_dlo & B_7)));
     // digest: sum over events i of (decision * K1 + (active << 32 | reserved)) * ((2 i + 1) * K2)
-    const u64 term = (dec * 0x9E3779B97F4A7C15ull + (((u64)v_act << 32) | v_res)) *
+    const u64 term = (dec * 0x9E3779B97F4A7C15ull + (((u64)act << 32) | v_res)) *
                      ((2ull * (base + lane) + 1ull) * 0xD6E8FEB86659FD93ull);
     T.dig += valid ? term : 0ull;
 }
@@ -1477,7 +1499,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
     st_one(V.bmp, (P.cap_chunks + 31) / 32, 0u);                // the spare word
     wave_sync();
 
-    u32 requested = 0, active = 0, peak_requested = 0, peak_active = 0;
+    u32 lost = 0;               // request of a FREE that outgrew a table: the trace ends there, the request counts as gone
     u32 sp_reserved = 0;        // small-request pool: units reserved so far
     bool stop = false;
     TileOut T;
@@ -1497,33 +1519,33 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
             const u64 x = pin64(ev_row[min(nx, n_ev - 1)]);
             ev_next = nx < n_ev ? x : 0;
         }
-        u32 v_dlo = 0, v_dhi = 0, v_act = 0, v_res = 0;
+        u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_act = 0, v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
         u32 done = tile, todo = tile;       // todo drops to 0 when an engine table overflows: the trace ends there
         // every path of an event ends by parking its results in lane j and going on to the next event
-#define EMIT(DLO, DHI)                                                     \
+#define EMIT(DLO, DHI, DREQ, DACT)                                         \
     {                                                                      \
-        write_lane4(v_dlo, v_dhi, v_act, v_res, (DLO), (DHI), active,      \
-                    sp_reserved + (V.n_chunks << P.chunk_shift), j);       \
+        write_lane4(v_dlo, v_dhi, v_req, v_act, (DLO), (DHI), (DREQ), (DACT), j); \
         wave_sync();                                                       \
         continue;                                                          \
     }
+        // memory was reserved: the events from this one on see the new total
+#define RESERVED_NOW() v_res = lane >= j ? sp_reserved + (V.n_chunks << P.chunk_shift) : v_res
         for (u32 j = 0; j < todo; j++) {
             const u32 w = from_lane(ev_lo, j), slot = from_lane(ev_hi, j);
-            if (UNLIKELY(slot >= P.max_slots)) EMIT((u32)C_INVALID, 0u)
+            if (UNLIKELY(slot >= P.max_slots)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
             const u32 req = S.get_req(slot);
             if ((int)w < 0) {
                 // ---- FREE.  Update (Sec. 3.3.2): only activity flips; memory stays with its pBlocks
                 if (UNLIKELY(req + 1u <= 1u)) {             // unbound, or bound to a request that failed
                     if (req == SLOT_OOM) {
                         S.set_req(slot, (u32)SLOT_UNBOUND);
-                        EMIT((u32)C_FREE_NOOP, 0u)
+                        EMIT((u32)C_FREE_NOOP, 0u, 0u, 0u)
                     }
-                    EMIT((u32)C_INVALID, 0u)
+                    EMIT((u32)C_INVALID, 0u, 0u, 0u)
                 }
                 const u32 a = S.get_a(slot), b = S.get_b(slot);
                 const u32 kind = b & 3;
                 S.set_req(slot, (u32)SLOT_UNBOUND);
-                requested -= req;
                 if (LIKELY((kind & KIND_SBLOCK) != 0)) {    // (a bit test: the usual case stays the fall-through)
                     if (USE_LIST) {
                         const u32 list = S.get_c(slot), off = list >> 16, cnt = list & 0xFFFFu;
@@ -1533,13 +1555,11 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                     } else {
                         vms_free_by_key(V, a, b >> 2);
                     }
-                    active -= (b >> 2) << P.chunk_shift;
-                    EMIT(C_FREE | B_SBLOCK, a)
+                    EMIT(C_FREE | B_SBLOCK, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
                 }
                 if (kind == KIND_PBLOCK) {
                     bmp_fill(V.bmp, ENT_WORD(V.e_skip), a, b >> 2, false);
-                    active -= (b >> 2) << P.chunk_shift;
-                    EMIT((u32)C_FREE, a)
+                    EMIT((u32)C_FREE, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
                 }
                 if (LIKELY(P.small_regs)) {
                     AcctLds A;
@@ -1547,12 +1567,12 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                     A.idle = V.idle;
                     Q.release(a >> 2, req, a & 3, A, base + j,
                               [&](bool ml, bool mr) {
-                                  active -= req;
-                                  write_lane4(v_dlo, v_dhi, v_act, v_res, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                              a >> 2, active, sp_reserved + (V.n_chunks << P.chunk_shift), j);
+                                  write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
+                                              a >> 2, 0u - req, 0u - req, j);
                                   wave_sync();
                               },
                               [&]() {
+                                  lost = req;
                                   stop = true;
                                   done = j;
                                   todo = 0;
@@ -1562,17 +1582,17 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                 bool ml, mr;
                 small_free(lds, P, V.idle, a >> 2, req, a & 3, base + j, &ml, &mr);
                 if (UNLIKELY(ld_uni((u32 *)(lds + LDS_SCALARS), (u32)SC_STOP) != 0)) {
+                    lost = req;
                     stop = true;
                     done = j;
                     todo = 0;
                     continue;
                 }
-                active -= req;
-                EMIT(C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2)
+                EMIT(C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2, 0u - req, 0u - req)
             }
             // ---- ALLOC
             const u32 size = w;
-            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) EMIT((u32)C_INVALID, 0u)
+            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
             if (LIKELY(size >= fast_limit)) {
                 const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
                 u32 ref, list = 0;
@@ -1580,11 +1600,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
 #define S1_SBLOCK_HIT                                                      \
     {                                                                      \
         S.bind(slot, size, ref, KIND_SBLOCK | (bsize << 2), list);         \
-        requested += size;                                                 \
-        active += bsize << P.chunk_shift;                                  \
-        peak_requested = max(peak_requested, requested);                   \
-        peak_active = max(peak_active, active);                            \
-        EMIT(C_EXACT | B_SBLOCK | (1u << 8), ref)                          \
+        EMIT(C_EXACT | B_SBLOCK | (1u << 8), ref, size, bsize << P.chunk_shift) \
     }
                 // S1 on stitched blocks, the usual way (see s1_sblock_from for the general route).  It is
                 // written out here, not called, so that the hit leaves for the next event from where it
@@ -1638,11 +1654,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
         S.set_a(slot, ref);                                                \
         S.set_b(slot, KIND_PBLOCK | (bsize << 2));                         \
         S.set_req(slot, size);                                             \
-        requested += size;                                                 \
-        active += bsize << P.chunk_shift;                                  \
-        peak_requested = max(peak_requested, requested);                   \
-        peak_active = max(peak_active, active);                            \
-        EMIT(C_EXACT | (1u << 8), ref)                                     \
+        EMIT(C_EXACT | (1u << 8), ref, size, bsize << P.chunk_shift)       \
     }
                 S1_PBLOCK_TRY
             } else if (UNLIKELY(size >= P.small_limit_units)) {
@@ -1695,7 +1707,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                     Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
                             [&](u32 code, u32 addr, u32 flags, bool split) {
                                 sp_reserved = Q.reserved();
-                                u32 d_lo = C_OOM, d_hi = 0;
+                                u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
                                 if (code == C_OOM) {
                                     S.set_req(slot, (u32)SLOT_OOM);
                                     ColdState C;            // rare: note the first failed request
@@ -1706,15 +1718,12 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                                     S.set_a(slot, (addr << 2) | flags);
                                     S.set_b(slot, (u32)KIND_SMALL);
                                     S.set_req(slot, size);
-                                    requested += size;
-                                    active += size;
-                                    peak_requested = max(peak_requested, requested);
-                                    peak_active = max(peak_active, active);
+                                    if (code == C_GROW) RESERVED_NOW();
                                     d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
                                     d_hi = addr;
+                                    d_req = size;
                                 }
-                                write_lane4(v_dlo, v_dhi, v_act, v_res, d_lo, d_hi, active,
-                                            sp_reserved + (V.n_chunks << P.chunk_shift), j);
+                                write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
                                 wave_sync();
                             },
                             [&]() {
@@ -1746,17 +1755,15 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                 ColdState C;                                // rare: note the first failed request
                 C.load(lds);
                 if (C.get(SC_FIRST_OOM) == NONE32) st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                EMIT((u32)C_OOM, 0u)
+                EMIT((u32)C_OOM, 0u, 0u, 0u)
             }
             S.set_req(slot, size);
-            requested += size;
-            active += held_units;
-            peak_requested = max(peak_requested, requested);
-            peak_active = max(peak_active, active);
-            EMIT(dlo, dhi)
+            if ((dlo & 15) == C_GROW) RESERVED_NOW();
+            EMIT(dlo, dhi, size, held_units)
         }
 #undef EMIT
-        tile_emit(T, dec_row, base, done, v_dlo, v_dhi, v_act, v_res);
+#undef RESERVED_NOW
+        tile_emit<false>(T, dec_row, base, done, v_dlo, v_dhi, v_req, v_act, v_res);
         if (stop) break;
     }
 
@@ -1774,29 +1781,29 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
 #pragma unroll
         for (u32 c = 0; c < 8; c++) s.n_code[c] = n_code[c];
         const u64 reserved = sp_reserved + (V.n_chunks << P.chunk_shift);
-        s.peak_requested = (u64)peak_requested * 512;
-        s.peak_active = (u64)peak_active * 512;
+        s.peak_requested = (u64)T.peak_requested * 512;
+        s.peak_active = (u64)T.peak_active * 512;
         s.peak_reserved = reserved * 512;           // reserved memory never shrinks: its peak is its final value
-        s.final_requested = (u64)requested * 512;
-        s.final_active = (u64)active * 512;
+        s.final_requested = (u64)(T.requested - lost) * 512;
+        s.final_active = (u64)T.active * 512;
         s.final_reserved = reserved * 512;
         s.digest = digest;
-        s.n_split = sc[SC_N_SPLIT];
-        s.n_merge = sc[SC_N_MERGE];
+        s.n_split = sc[SC_N_SPLIT] + T.n_split;
+        s.n_merge = T.n_merge;
         s.n_sblock_created = sc[SC_N_CREATED];
         s.n_sblock_evicted = sc[SC_N_EVICTED];
         s.first_oom_event = sc[SC_FIRST_OOM];
         s.status = sc[SC_STATUS] | (n_code[7] ? VMS_ST_INVALID_EVENT : 0u);
         s.max_pblocks = sc[SC_HW_PBLOCKS];
         s.max_sblocks = sc[SC_HW_SBLOCKS];
-        s.max_free_blocks = sc[SC_HW_FREE];
+        s.max_free_blocks = max(sc[SC_HW_FREE], Q.most());
         s.max_members = sc[SC_HW_MEMBERS];
         s.max_runs = sc[SC_HW_RUNS];
         s.overflow_event = sc[SC_OVF_EVENT];
         s.max_multi_pblocks = sc[SC_HW_MULTI];
         s.reserved1 = 0;
         // Sec. 5.1: fragmentation = 1 - utilisation, utilisation = peak active / peak reserved
-        s.fragmentation = reserved ? 1.0 - (double)peak_active / (double)reserved : 0.0;
+        s.fragmentation = reserved ? 1.0 - (double)T.peak_active / (double)reserved : 0.0;
     }
 }
 
@@ -1826,7 +1833,6 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
 
     AcctRegs A;
     A.init();
-    u32 requested = 0, peak_requested = 0;
     TileOut T;
     T.init();
     const u32 chunk_units = 1u << P.chunk_shift;
@@ -1843,7 +1849,7 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
             const u64 x = pin64(ev_row[min(nx, n_ev - 1)]);
             ev_next = nx < n_ev ? x : 0;
         }
-        u32 v_dlo = 0, v_dhi = 0, v_act = 0, v_res = 0;
+        u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_res = sp.reserved();
         u32 done = tile, todo = tile;       // todo drops to 0 when the free list overflows: the trace ends there
         u32 w_next = from_lane(ev_lo, 0), slot_next = from_lane(ev_hi, 0);     // one event ahead
         for (u32 j = 0; j < todo; j++) {
@@ -1852,8 +1858,8 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
             slot_next = from_lane(ev_hi, (j + 1) & 63);
             // every path of an event ends by parking its results in lane j; none hands a result to
             // a common tail (that would cost flags to test)
-            auto emit = [&](u32 dlo, u32 dhi) {
-                write_lane4(v_dlo, v_dhi, v_act, v_res, dlo, dhi, requested, sp.reserved(), j);
+            auto emit = [&](u32 dlo, u32 dhi, u32 dreq) {
+                write_lane3(v_dlo, v_dhi, v_req, dlo, dhi, dreq, j);
                 wave_sync();
             };
             auto overflow = [&]() {
@@ -1861,7 +1867,7 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
                 todo = 0;
             };
             if (UNLIKELY(slot >= P.max_slots)) {
-                emit((u32)C_INVALID, 0u);
+                emit((u32)C_INVALID, 0u, 0u);
                 continue;
             }
             const u32 req = S.get_req(slot);
@@ -1869,25 +1875,24 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
                 if (UNLIKELY(req + 1u <= 1u)) {             // unbound, or bound to a request that failed
                     if (req == SLOT_OOM) {
                         S.set_req(slot, (u32)SLOT_UNBOUND);
-                        emit((u32)C_FREE_NOOP, 0u);
+                        emit((u32)C_FREE_NOOP, 0u, 0u);
                         continue;
                     }
-                    emit((u32)C_INVALID, 0u);
+                    emit((u32)C_INVALID, 0u, 0u);
                     continue;
                 }
                 const u32 a = S.get_a(slot);
                 S.set_req(slot, (u32)SLOT_UNBOUND);
                 sp.release(a >> 2, req, a & 3, A, base + j,
                            [&](bool ml, bool mr) {
-                               requested -= req;
-                               emit(C_FREE | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2);
+                               emit(C_FREE | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2, 0u - req);
                            },
                            overflow);
                 continue;
             }
             const u32 size = w;
             if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) {
-                emit((u32)C_INVALID, 0u);
+                emit((u32)C_INVALID, 0u, 0u);
                 continue;
             }
             const u32 seg = ((size + chunk_units - 1) >> P.chunk_shift) << P.chunk_shift;
@@ -1896,19 +1901,18 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
                          if (code == C_OOM) {
                              S.set_req(slot, (u32)SLOT_OOM);
                              if (A.f[SC_FIRST_OOM] == NONE32) A.f[SC_FIRST_OOM] = base + j;
-                             emit((u32)C_OOM, 0u);
+                             emit((u32)C_OOM, 0u, 0u);
                              return;
                          }
                          S.set_a(slot, (addr << 2) | flags);
                          S.set_req(slot, size);
                          // blocks are cut to the request: active bytes are the requested bytes
-                         requested += size;
-                         peak_requested = max(peak_requested, requested);
-                         emit(code | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), addr);
+                         if (code == C_GROW) v_res = lane >= j ? sp.reserved() : v_res;
+                         emit(code | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), addr, size);
                      },
                      overflow);
         }
-        tile_emit(T, dec_row, base, done, v_dlo, v_dhi, v_act, v_res);
+        tile_emit<true>(T, dec_row, base, done, v_dlo, v_dhi, v_req, 0u, v_res);
         if (A.stop) break;
     }
 
@@ -1920,29 +1924,29 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
 #pragma unroll
         for (u32 c = 0; c < 8; c++) s.n_code[c] = n_code[c];
         const u64 reserved = sp.reserved();
-        s.peak_requested = (u64)peak_requested * 512;
-        s.peak_active = (u64)peak_requested * 512;
+        s.peak_requested = (u64)T.peak_requested * 512;
+        s.peak_active = (u64)T.peak_requested * 512;
         s.peak_reserved = reserved * 512;           // reserved memory never shrinks: its peak is its final value
-        s.final_requested = (u64)requested * 512;
-        s.final_active = (u64)requested * 512;
+        s.final_requested = (u64)T.requested * 512;
+        s.final_active = (u64)T.requested * 512;
         s.final_reserved = reserved * 512;
         s.digest = digest;
-        s.n_split = A.f[SC_N_SPLIT];
-        s.n_merge = A.f[SC_N_MERGE];
+        s.n_split = T.n_split;
+        s.n_merge = T.n_merge;
         s.n_sblock_created = 0;
         s.n_sblock_evicted = 0;
         s.first_oom_event = A.f[SC_FIRST_OOM];
         s.status = A.f[SC_STATUS] | (n_code[7] ? VMS_ST_INVALID_EVENT : 0u);
         s.max_pblocks = 0;
         s.max_sblocks = 0;
-        s.max_free_blocks = A.f[SC_HW_FREE];
+        s.max_free_blocks = max(A.f[SC_HW_FREE], sp.most());
         s.max_members = 0;
         s.max_runs = 0;
         s.overflow_event = A.f[SC_OVF_EVENT];
         s.max_multi_pblocks = 0;
         s.reserved1 = 0;
         // Sec. 5.1: fragmentation = 1 - utilisation, utilisation = peak active / peak reserved
-        s.fragmentation = reserved ? 1.0 - (double)peak_requested / (double)reserved : 0.0;
+        s.fragmentation = reserved ? 1.0 - (double)T.peak_requested / (double)reserved : 0.0;
     }
     wave_sync();
     } while (P.retry);

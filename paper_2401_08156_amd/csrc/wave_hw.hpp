@@ -140,6 +140,15 @@ DI void write_lane4(u32 &a, u32 &b, u32 &c, u32 &d, u32 va, u32 vb, u32 vc, u32 
         : "m0");
 }
 
+#define WAVE_WRITE_LANE3
+DI void write_lane3(u32 &a, u32 &b, u32 &c, u32 va, u32 vb, u32 vc, u32 lane)
+{
+    asm("s_mov_b32 m0, %6\n\ts_nop 0\n\tv_writelane_b32 %0, %3, m0\n\tv_writelane_b32 %1, %4, m0\n\tv_writelane_b32 %2, %5, m0"
+        : "+v"(a), "+v"(b), "+v"(c)
+        : "s"(uni(va)), "s"(uni(vb)), "s"(uni(vc)), "s"(uni(lane))
+        : "m0");
+}
+
 // which way a wave-uniform branch usually goes: the usual way becomes the fall-through
 #define LIKELY(x) __builtin_expect(!!(x), 1)
 #define UNLIKELY(x) __builtin_expect(!!(x), 0)
