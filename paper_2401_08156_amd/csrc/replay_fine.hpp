@@ -1105,15 +1105,11 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
     const u64 *ev_row = events + (size_t)trace * P.max_events;
     u64 *dec_row = decisions ? decisions + (size_t)trace * P.max_events : nullptr;
 
-    u64 ev_next = lane < n_ev ? ev_row[lane] : 0;
+    u64 ev = pin64(lane < n_ev ? ev_row[lane] : 0), ev_next = ev;
     for (u32 base = 0; base < n_ev; base += 64) {
         const u32 tile = min(64u, n_ev - base);
-        const u32 ev_lo = (u32)ev_next, ev_hi = (u32)(ev_next >> 32);
-        if (base + 64 < n_ev) {                             // prefetch; lanes past the end re-read the last event
-            const u32 nx = base + 64 + lane;
-            const u64 x = pin64(ev_row[min(nx, n_ev - 1)]);
-            ev_next = nx < n_ev ? x : 0;
-        }
+        const u32 ev_lo = (u32)ev, ev_hi = (u32)(ev >> 32);
+        if (base + 64 < n_ev) ev_next = ev_row[min(base + 64 + lane, n_ev - 1)];       // prefetch (see replay_split_kernel)
         u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_act = 0, v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
         u32 done = tile, todo = tile;       // todo drops to 0 when an engine table overflows: the trace ends there
         // every path of an event ends by parking its results in lane j and going on to the next event
@@ -1286,6 +1282,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
         }
 #undef EMIT
 #undef RESERVED_NOW
+        ev = pin64(ev_next);
         tile_emit<false>(T, dec_row, base, done, v_dlo, v_dhi, v_req, v_act, v_res);
         if (stop) break;
     }

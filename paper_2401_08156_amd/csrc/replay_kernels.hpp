@@ -1510,15 +1510,11 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
     u64 *dec_row = decisions ? decisions + (size_t)trace * P.max_events : nullptr;
 
     u32 fast_limit = P.small_limit_units;   // requests from this size on take the usual S1 route (renewed with the probe)
-    u64 ev_next = lane < n_ev ? ev_row[lane] : 0;
+    u64 ev = pin64(lane < n_ev ? ev_row[lane] : 0), ev_next = ev;
     for (u32 base = 0; base < n_ev; base += 64) {
         const u32 tile = min(64u, n_ev - base);
-        const u32 ev_lo = (u32)ev_next, ev_hi = (u32)(ev_next >> 32);
-        if (base + 64 < n_ev) {                             // prefetch; lanes past the end re-read the last event
-            const u32 nx = base + 64 + lane;
-            const u64 x = pin64(ev_row[min(nx, n_ev - 1)]);
-            ev_next = nx < n_ev ? x : 0;
-        }
+        const u32 ev_lo = (u32)ev, ev_hi = (u32)(ev >> 32);
+        if (base + 64 < n_ev) ev_next = ev_row[min(base + 64 + lane, n_ev - 1)];       // prefetch (see replay_split_kernel)
         u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_act = 0, v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
         u32 done = tile, todo = tile;       // todo drops to 0 when an engine table overflows: the trace ends there
         // every path of an event ends by parking its results in lane j and going on to the next event
@@ -1763,6 +1759,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
         }
 #undef EMIT
 #undef RESERVED_NOW
+        ev = pin64(ev_next);
         tile_emit<false>(T, dec_row, base, done, v_dlo, v_dhi, v_req, v_act, v_res);
         if (stop) break;
     }
@@ -1840,15 +1837,15 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
     const u64 *ev_row = events + (size_t)trace * P.max_events;
     u64 *dec_row = decisions ? decisions + (size_t)trace * P.max_events : nullptr;
 
-    u64 ev_next = lane < n_ev ? ev_row[lane] : 0;
+    u64 ev = pin64(lane < n_ev ? ev_row[lane] : 0), ev_next = ev;
     for (u32 base = 0; base < n_ev; base += 64) {
         const u32 tile = min(64u, n_ev - base);
-        const u32 ev_lo = (u32)ev_next, ev_hi = (u32)(ev_next >> 32);
-        if (base + 64 < n_ev) {                             // prefetch; lanes past the end re-read the last event
-            const u32 nx = base + 64 + lane;
-            const u64 x = pin64(ev_row[min(nx, n_ev - 1)]);
-            ev_next = nx < n_ev ? x : 0;
-        }
+        const u32 ev_lo = (u32)ev, ev_hi = (u32)(ev >> 32);
+        // the next tile, on its way while this one is replayed: nothing touches the value (a select on it
+        // would wait for memory here, once per 64 events) until this tile's results are stored, and it is
+        // taken over before that store, which would have to be waited for too (one counter).  Lanes past
+        // the end hold the last event, which no j reaches.
+        if (base + 64 < n_ev) ev_next = ev_row[min(base + 64 + lane, n_ev - 1)];
         u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_res = sp.reserved();
         u32 done = tile, todo = tile;       // todo drops to 0 when the free list overflows: the trace ends there
         u32 w_next = from_lane(ev_lo, 0), slot_next = from_lane(ev_hi, 0);     // one event ahead
@@ -1912,6 +1909,7 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
                      },
                      overflow);
         }
+        ev = pin64(ev_next);
         tile_emit<true>(T, dec_row, base, done, v_dlo, v_dhi, v_req, 0u, v_res);
         if (A.stop) break;
     }
