@@ -391,42 +391,52 @@ struct SplitLds {
     }
 };
 
-// The inactive blocks in registers: key t * 64 + l of the array is k[t] of lane l, 0 = empty place.
-// The order of the array means nothing (best fit and the neighbour searches look at every key), so a
-// block that leaves just zeroes its place and a new one takes the first empty place.  No LDS access
-// at all: a request is compares, one or two wave-wide minima and a few lane selects.
+// The inactive blocks in registers: place t * 64 + l of the array is h[t], w[t] of lane l: the two
+// halves of the key, size and address << 2 | flags; 0 in both = empty place.  The order of the array
+// means nothing (best fit and the neighbour searches look at every key), so a block that leaves just
+// zeroes its place and a new one takes the first empty place.  No LDS access at all: a request is
+// compares, one or two wave-wide minima and a few lane selects.
+// What bounds it is the chain of one event (two wavefronts per SIMD issue an instruction every nine
+// cycles), so the halves are searched apart, all tiles side by side: 64-bit minima went through the
+// tiles one after the other, compare, select, compare (2,048 traces of 20,000 events, three tiles:
+// 9.68 -> 8.93 ms; LoRA streams, five tiles: 113.4 -> 111.9 ms, with the stitching kernel beside it).
 template <u32 TILES>
 struct SplitRegs {
-    u64 k[TILES];
+    u32 h[TILES], w[TILES];
     u32 n, cap, res;
     u32 hw;                     // the most blocks held at once (cuts and merges are counted off the decisions)
     DI void init(char *, const KParams &P)
     {
 #pragma unroll
-        for (u32 t = 0; t < TILES; t++) k[t] = 0;
+        for (u32 t = 0; t < TILES; t++) h[t] = w[t] = 0;
         n = hw = 0;
         cap = P.cap_free;
         res = 0;
     }
     DI u32 reserved() const { return res; }
     DI u32 most() const { return hw; }
-    // keys are unique (they contain the address): the place that holds `from` (not 0) takes `to`,
-    // found by comparing every place with it, with no book-keeping of where a key sits
-    DI void swap_key(u64 from, u64 to)
+    // w is unique among the live blocks (it contains the address) and not 0 (the block at address 0 is
+    // the first of its segment): the place that holds `from` takes a new size and address
+    DI void swap_block(u32 from, u32 size, u32 to)
     {
 #pragma unroll
-        for (u32 q = 0; q < TILES; q++) k[q] = k[q] == from ? to : k[q];
+        for (u32 q = 0; q < TILES; q++) {
+            const bool here = w[q] == from;
+            h[q] = here ? size : h[q];
+            w[q] = here ? to : w[q];
+        }
     }
-    DI void insert(u64 key)                     // into an empty place (n < cap <= 64 * TILES: there is one)
+    DI void insert(u32 size, u32 to)            // into an empty place (n < cap <= 64 * TILES: there is one)
     {
         bool any = false;
 #pragma unroll
-        for (u32 q = 0; q < TILES; q++) any = any || k[q] == 0;
+        for (u32 q = 0; q < TILES; q++) any = any || h[q] == 0;
         bool todo = lane_id() == first_lane(ballot(any));       // the first lane with room, its first empty place
 #pragma unroll
         for (u32 q = 0; q < TILES; q++) {
-            const bool here = todo && k[q] == 0;
-            k[q] = here ? key : k[q];
+            const bool here = todo && h[q] == 0;
+            h[q] = here ? size : h[q];
+            w[q] = here ? to : w[q];
             todo = todo && !here;
         }
         n++;
@@ -438,34 +448,30 @@ struct SplitRegs {
     template <class AcctT, class Done, class Ovf>
     DI void alloc(u32 size, u32 seg, bool may_grow, AcctT &A, u32 ev, Done done, Ovf ovf)
     {
-        // step 1: best fit = smallest key not below (size, address 0); an empty place never fits
-        u64 best = ~0ull;
+        // step 1: best fit = smallest size not below the request.  Sizes have 31 bits, so what a block
+        // has beyond the request has bit 31 set exactly if the block is too small (or the place empty)
+        u32 d[TILES], mine = NONE32;
 #pragma unroll
         for (u32 t = 0; t < TILES; t++) {
-            const bool ok = (u32)(k[t] >> 32) >= size && k[t] < best;
-            best = ok ? k[t] : best;
+            d[t] = h[t] - size;
+            mine = min(mine, d[t]);
         }
-        const u32 hi = (u32)(best >> 32);
-        const u32 mhi = wave_min_u32(hi);
-        if (LIKELY(mhi != NONE32)) {
-            const u64 m = ballot(hi == mhi);
-            u32 owner = first_lane(m);
-            if (m & (m - 1)) {                  // several blocks of that size: lowest address
-                const u32 lo = hi == mhi ? (u32)best : NONE32;
-                const u32 mlo = wave_min_u32(lo);
-                owner = first_lane(ballot(lo == mlo));
-            }
-            const u32 blo = from_lane((u32)best, owner);
-            const u64 chosen = ((u64)mhi << 32) | blo;
+        const u32 rest = wave_min_u32(mine);
+        if (LIKELY((int)rest >= 0)) {
+            u32 c = NONE32;                     // lowest address of that size in this lane
+#pragma unroll
+            for (u32 t = 0; t < TILES; t++) c = min(c, d[t] == rest ? w[t] : NONE32);
+            const u64 m = ballot(mine == rest);
+            const u32 blo = UNLIKELY(m & (m - 1)) ? wave_min_u32(c) : from_lane(c, first_lane(m));
             const u32 addr = blo >> 2, flags = blo & 3;
-            if (LIKELY(mhi > size)) {
+            if (LIKELY(rest != 0)) {
                 // step 2: cut off what is not needed; it stays cached as the right neighbour, in the
                 // place the block had
-                swap_key(chosen, ((u64)(mhi - size) << 32) | ((u64)(addr + size) << 2) | (flags & 1));
+                swap_block(blo, rest, ((addr + size) << 2) | (flags & 1));
                 done((u32)C_SPLIT, addr, flags & 2, true);
                 return;
             }
-            swap_key(chosen, 0);
+            swap_block(blo, 0u, 0u);
             n--;
             done((u32)C_EXACT, addr, flags, false);
             return;
@@ -482,7 +488,7 @@ struct SplitRegs {
                 ovf();
                 return;
             }
-            insert(((u64)(seg - size) << 32) | ((u64)(addr + size) << 2) | 1u);
+            insert(seg - size, ((addr + size) << 2) | 1u);
             done((u32)C_GROW, addr, 2u, true);
             return;
         }
@@ -492,51 +498,51 @@ struct SplitRegs {
     template <class AcctT, class Done, class Ovf>
     DI void release(u32 addr, u32 size, u32 flags, AcctT &A, u32 ev, Done done, Ovf ovf)
     {
-        bool ml_, mr_;
-        bool *ml = &ml_, *mr = &mr_;
         const bool can_l = !(flags & 2), can_r = !(flags & 1);
         const u32 end = addr + size;
         // at most one block ends where this one starts and at most one starts where it ends: every
-        // lane folds its places into one candidate per side, two ballots decide
-        u64 lk = 0, rk = 0;
+        // lane folds its places into one candidate per side, two ballots decide.  Of the left block the
+        // address is enough (it ends at addr), the right one brings its size too
+        u32 lw = 0, rw = 0, rh = 0;
 #pragma unroll
         for (u32 t = 0; t < TILES; t++) {
             // an empty place matches nothing: no block ends at 0 that could merge, none starts at an end
-            const u32 ka = (u32)k[t] >> 2, ks = (u32)(k[t] >> 32);
-            lk = ka + ks == addr ? k[t] : lk;
-            rk = ka == end ? k[t] : rk;
+            const u32 ka = w[t] >> 2;
+            lw = ka + h[t] == addr ? w[t] : lw;
+            rw = ka == end ? w[t] : rw;
+            rh = ka == end ? h[t] : rh;
         }
-        const u64 mL = can_l ? ballot(lk != 0) : 0, mR = can_r ? ballot(rk != 0) : 0;
-        const u64 lkey = from_lane64(lk, first_lane(mL | (1ull << 63))), rkey = from_lane64(rk, first_lane(mR | (1ull << 63)));
-        *ml = mL != 0;
-        *mr = mR != 0;
-        if (*mr) {
-            size += (u32)(rkey >> 32);
-            flags = (flags & 2) | ((u32)rkey & 1);
+        const u64 mL = can_l ? ballot(lw != 0) : 0, mR = can_r ? ballot(rw != 0) : 0;
+        const bool ml = mL != 0, mr = mR != 0;
+        const u32 lown = first_lane(mL | (1ull << 63)), rown = first_lane(mR | (1ull << 63));
+        const u32 left = from_lane(lw, lown), right = from_lane(rw, rown), rsize = from_lane(rh, rown);
+        if (mr) {
+            size += rsize;
+            flags = (flags & 2) | (right & 1);
         }
-        if (*ml) {
-            addr = (u32)lkey >> 2;
-            size += (u32)(lkey >> 32);
-            flags = ((u32)lkey & 2) | (flags & 1);
+        if (ml) {
+            size += addr - (left >> 2);
+            addr = left >> 2;
+            flags = (left & 2) | (flags & 1);
         }
-        const u64 key = ((u64)size << 32) | ((u64)addr << 2) | flags;
-        if (UNLIKELY(*ml)) {
-            swap_key(lkey, key);                // the merged block takes the left neighbour's place
-            if (*mr) {
-                swap_key(rkey, 0);
+        const u32 to = (addr << 2) | flags;
+        if (UNLIKELY(ml)) {
+            swap_block(left, size, to);         // the merged block takes the left neighbour's place
+            if (mr) {
+                swap_block(right, 0u, 0u);
                 n--;
             }
-        } else if (*mr) {
-            swap_key(rkey, key);
+        } else if (mr) {
+            swap_block(right, size, to);
         } else {
             if (n == cap) {
                 A.overflow(ev, VMS_ST_OVF_FREE_BLOCKS);
                 ovf();
                 return;
             }
-            insert(key);
+            insert(size, to);
         }
-        done(ml_, mr_);
+        done(ml, mr);
     }
 };
 

@@ -73,3 +73,25 @@ def assert_parity(events, cfg, n_events=None, threads=8, label=""):
                 raise AssertionError("%s policy %d trace %d field %s: gpu %s oracle %s" % (
                     label, pol, t, f, gst[f][t], ost[f][t]))
     return st
+
+
+def equal_blocks_trace(blocks, small, seed):
+    """Fills a splitting pool to `blocks` inactive blocks of three sizes (ties inside a lane and across lanes,
+    every place taken), then allocates and frees at random: cuts, exact fits, merges to the left, to the right
+    and on both sides.  small: sizes below one chunk (the stitching policy's own pool).  Returns (events, slots)."""
+    from paper_2401_08156_amd import tracegen as tg
+    rng = np.random.default_rng(seed)
+    chunk = 2 << 20
+    # a block of its own segment each; small ones: the request and the rest of the chunk are two blocks
+    first = [("A", s, chunk - 512 * int(rng.integers(1, 4)) if small else chunk * int(rng.integers(1, 4))) for s in range(blocks)]
+    ops, live = first + [("F", s) for s in rng.permutation(blocks)], set()
+    for _ in range(1500):
+        s = int(rng.integers(0, blocks))
+        if s in live:
+            ops.append(("F", s))
+            live.discard(s)
+        elif len(live) < blocks // 2:
+            size = 512 * int(rng.choice((1, 2, 1024, 2047, 2048, 4095) if small else (1, 4096, 8192, 8191, 12288)))
+            ops.append(("A", s, min(size, chunk - 512) if small else size))
+            live.add(s)
+    return tg.make_events(ops)[None, :], blocks

@@ -59,6 +59,17 @@ def test_splitting_pool_in_registers():
     assert (st["status"][1] & binding.VMS_ST_OVF_FREE_BLOCKS).all() and (st["status"][0] == 0).all()
 
 
+@pytest.mark.parametrize("blocks,cap", [(1, 192), (65, 192), (170, 192), (300, 320)])
+@pytest.mark.parametrize("small", [False, True])
+def test_splitting_pool_of_equal_blocks(blocks, cap, small):
+    if small:
+        blocks = (blocks + 1) // 2          # each brings the rest of its chunk: two blocks while it is held
+    ev, ms = gpu_util.equal_blocks_trace(blocks, small, seed=blocks)
+    gpu_util.assert_parity(ev, gpu_util.make_cfg(1, ev.shape[1], ms, policy_mask=1, max_free_blocks=cap), label="%d equal blocks" % blocks)
+    if small and blocks <= 96:
+        gpu_util.assert_parity(ev, gpu_util.make_cfg(1, ev.shape[1], ms, variant=2, max_free_blocks=cap), label="pool for small requests")
+
+
 def test_worked_examples_on_gpu():
     import glob
     import os

@@ -66,6 +66,22 @@ def test_splitting_kernels():
     check(ev, gpu_util.make_cfg(1, 2000, ms, policy_mask=1, max_free_blocks=320), label="slot table and pool (five per lane) in registers")
 
 
+@pytest.mark.parametrize("blocks,cap", [(1, 64), (63, 192), (65, 192), (192, 192), (193, 320), (320, 320)])
+@pytest.mark.parametrize("small", [False, True])
+def test_splitting_pool_of_equal_blocks(blocks, cap, small):
+    ev, ms = gpu_util.equal_blocks_trace(blocks, small, seed=blocks)
+    cap = max(cap, 192 if small else 0)
+    cfg = gpu_util.make_cfg(1, ev.shape[1], ms, policy_mask=1, max_free_blocks=cap)
+    _, _, st = emu.replay(ev, cfg, binding.STATS_DTYPE)
+    if st["status"][0, 0] & binding.VMS_ST_TABLE_OVERFLOW:      # exactly full: the oracle holds more blocks than the table
+        _, ost = oracle.replay(ev, gpu_util.oracle_params(cfg), 0)
+        assert ost["max_free_blocks"][0] > cap
+        return
+    check(ev, cfg, label="%d equal blocks" % blocks)
+    if small and blocks <= 96:
+        check(ev, gpu_util.make_cfg(1, ev.shape[1], ms, variant=2, max_free_blocks=cap), label="pool for small requests")
+
+
 @pytest.mark.parametrize("kind,nt,ne,tables", [
     (1, 2, 2000, dict(max_runs=20000)),
     (2, 2, 3000, dict(max_runs=20000)),
