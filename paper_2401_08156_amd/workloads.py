@@ -26,9 +26,11 @@ TABLES = {
     # three, 153 against 179 ms per step)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432,
             variant=2, table_place=3),
-    # (the same for the 1,280 traces of the scale-out regime, 9,408 chunks at most: 22.9 KB, all traces resident
-    # at once, 20.0 against 25.8 ms)
-    6: dict(max_free_blocks=192, max_pblocks=512, max_sblocks=576, max_runs=3072, max_chunks=9728, variant=2, table_place=3),
+    # (the same for the 1,280 traces of the scale-out regime, 9,408 chunks at most: 23,040 B, which is 18 LDS granules
+    # of 1,280 bytes exactly, all traces resident at once, 20.0 against 25.8 ms.  pBlocks: 497 to 534 at most over 12
+    # seeds; with 512 places, in the same 18 granules, four of those seeds sent a trace through the second pass,
+    # alone and from its first event)
+    6: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3072, max_chunks=9728, variant=2, table_place=3),
 }
 # config 5 mixes the generators of configs 2, 3 and 4 (trace i uses kind 2 + i mod 3) with twice the
 # events; replayed as three batches, one per kind, each with tables of its own

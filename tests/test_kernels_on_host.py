@@ -12,7 +12,7 @@ import pytest
 import emu
 import gpu_util
 import oracle
-from paper_2401_08156_amd import binding
+from paper_2401_08156_amd import binding, workloads
 from paper_2401_08156_amd import tracegen as tg
 from test_oracle_examples import GOLDEN, load_fixture
 
@@ -149,6 +149,15 @@ def test_lists_are_compacted_under_a_slot_table_in_lds():
                                 max_pblocks=1024, max_sblocks=92, max_runs=700, max_chunks=20480)
         st = check(ev, cfg, label="compaction, slot table in LDS, tables %d" % place)
         assert st["n_sblock_created"][1, 0] > 400 and st["n_sblock_evicted"][1, 0] > 300
+
+
+@pytest.mark.parametrize("seed,trace", [(1, 300), (12345, 500)])
+def test_zero3_preset_holds_its_traces_in_the_first_pass(seed, trace):
+    # the traces with the most pBlocks of their seeds (534 and 527); without retry_traces an overflow stays flagged
+    ev, ms = tg.generate(6, n_traces=1, n_events=20000, first_trace=trace, seed=seed)
+    cfg = workloads.make_config(binding, 6, 1, 20000, ms, retry_traces=0, policy_mask=2)
+    st = check(ev, cfg, label="seed %d trace %d" % (seed, trace))
+    assert st["max_pblocks"][1, 0] > 512
 
 
 def test_table_overflow_is_flagged_not_fatal():
