@@ -1,11 +1,59 @@
 // Self-test of the wavefront primitives: each is compared, on the device, with a
-// serial evaluation of its definition by lane 0.  Every access is to a fixed
-// LDS array of 256 or 832 entries, so the test cannot touch memory it does not own.
+// serial evaluation of its definition.  Every access is to an LDS array of a fixed
+// length or to the SELFTEST_TABLES tables of SELFTEST_PLACES 16-bit elements behind
+// `tab` (16-byte aligned), so the test cannot touch memory it does not own.
 #pragma once
 #include "wave_ops.hpp"
 #include "../../include/vms_replay.h"
 
-__global__ __launch_bounds__(64) void selftest_kernel(u32 *fail)
+const u32 SELFTEST_TABLES = 3, SELFTEST_PLACES = 1216;
+
+// Moves of N tables in global memory: n elements (every length around a block of 8, a step of 64 blocks and
+// two steps), moved from the first, the last and inner places.
+template <int N>
+DI u32 selftest_gblk(uint16_t *tab)
+{
+    const u32 lane = lane_id();
+    uint16_t *a[N];
+#pragma unroll
+    for (int f = 0; f < N; f++) a[f] = tab + (u32)f * SELFTEST_PLACES;
+    const u32 lengths[] = { 1, 7, 8, 9, 15, 16, 511, 512, 513, 519, 520, 1016, 1023, 1024, 1025, 1032 };
+    u32 bad = 0;
+    for (u32 n : lengths) {
+        const u32 places[] = { 0, 6, 7, 8, n / 2, n - 1, n };
+        for (u32 pos : places) {
+            if (pos > n) continue;
+#pragma unroll
+            for (int f = 0; f < N; f++)
+                for (u32 i = lane; i < SELFTEST_PLACES; i += 64) a[f][i] = (uint16_t)(i < n ? (f + 1) * 20000 - 9 * i : 0);
+            wave_sync();
+            gblk_shift_up(a, pos, n);
+#pragma unroll
+            for (int f = 0; f < N; f++) st_one(a[f], pos, (uint16_t)(f + 1));
+            tbl_fence();
+#pragma unroll
+            for (int f = 0; f < N; f++)
+                for (u32 i = lane; i < SELFTEST_PLACES; i += 64) {
+                    const u32 from = i < pos ? i : i - 1;
+                    const uint16_t want = (uint16_t)(i == pos ? f + 1 : i <= n ? (f + 1) * 20000 - 9 * from : 0);
+                    if (ld_tab(a[f] + i) != want) bad |= 1u << 18;
+                }
+            wave_sync();
+            gblk_shift_down(a, pos, n + 1);
+            tbl_fence();
+#pragma unroll
+            for (int f = 0; f < N; f++)
+                for (u32 i = lane; i < SELFTEST_PLACES; i += 64) {
+                    const uint16_t want = (uint16_t)(i < n ? (f + 1) * 20000 - 9 * i : 0);
+                    if (ld_tab(a[f] + i) != want) bad |= 1u << 19;
+                }
+            wave_sync();
+        }
+    }
+    return bad;
+}
+
+__global__ __launch_bounds__(64) void selftest_kernel(u32 *fail, uint16_t *tab)
 {
     __shared__ u32 in[64], out[64];
     __shared__ u64 arr[256];
@@ -39,7 +87,42 @@ __global__ __launch_bounds__(64) void selftest_kernel(u32 *fail)
         for (u32 i = 0; i < lane; i++) below += in[i] & 1;
         if (rank_in(b) != below) bad |= 8;
         if (from_lane(v, (round * 9) & 63) != in[(round * 9) & 63]) bad |= 16;
+        // the prefix sum wraps around at 32 bits (it is taken over decreases too)
+        u32 wtot, ws = wave_scan_add(0u - v * 0x10001u, &wtot), wrun = 0;
+        out[lane] = ws;
         wave_sync();
+        for (int i = 0; i < 64; i++) {
+            wrun += 0u - in[i] * 0x10001u;
+            if (out[i] != wrun) bad |= 2;
+        }
+        if (wtot != wrun) bad |= 4;
+        wave_sync();
+    }
+    // the minimum in every lane in turn, and a single value to add in every lane in turn: whatever way across the
+    // rows a reduction takes, some lane's value needs each of its steps.  The others hold all ones, values with
+    // and without bit 31, neighbours of the minimum.
+    for (u32 l = 0; l < 64; l++) {
+        const u32 mixed = lane * 2654435761u + l;
+        const u32 others[] = { 0xFFFFFFFFu, mixed | 0x80000000u, mixed | 1u, 0x80000001u };
+        const u32 least[] = { 0xFFFFFFFEu, 0x7FFFFFFFu, 0u, 0x80000000u };
+        for (u32 k = 0; k < 4; k++)
+            if (wave_min_u32(lane == l ? least[k] : others[k]) != least[k]) bad |= 1;
+        u32 tot, s = wave_scan_add(lane == l ? 0x80000001u : 0u, &tot);
+        if (s != (lane >= l ? 0x80000001u : 0u)) bad |= 2;
+        if (tot != 0x80000001u) bad |= 4;
+        // writes of one lane leave the others as they are
+        u32 a = lane, b = lane + 100, c = lane + 200, d = lane + 300;
+        const u32 one = write_lane(a, 7000 + l, l);
+        if (one != (lane == l ? 7000 + l : lane)) bad |= 1u << 16;
+        write_lane4(a, b, c, d, 1000 + l, 2000 + l, 3000 + l, 4000 + l, l);
+        if (a != (lane == l ? 1000 + l : lane) || b != (lane == l ? 2000 + l : lane + 100) ||
+            c != (lane == l ? 3000 + l : lane + 200) || d != (lane == l ? 4000 + l : lane + 300))
+            bad |= 1u << 16;
+        write_lane3(b, c, d, 5000 + l, 6000 + l, 7000 + l, 63 - l);
+        if (b != (lane == 63 - l ? 5000 + l : lane == l ? 2000 + l : lane + 100) ||
+            c != (lane == 63 - l ? 6000 + l : lane == l ? 3000 + l : lane + 200) ||
+            d != (lane == 63 - l ? 7000 + l : lane == l ? 4000 + l : lane + 300))
+            bad |= 1u << 17;
     }
     // sorted-array helpers on a descending array of 150 keys, followed by zero keys as they require
     for (u32 i = lane; i < 256; i += 64) arr[i] = i < 150 ? (u64)(1000 - 3 * i) << 32 : 0;
@@ -133,6 +216,8 @@ __global__ __launch_bounds__(64) void selftest_kernel(u32 *fail)
             if (b0 > ref || ref - b0 >= 64) bad |= 32768;
         }
     }
+    bad |= selftest_gblk<2>(tab);
+    bad |= selftest_gblk<3>(tab);
     u64 any = ballot(bad != 0);
     if (lane == 0) *fail = any ? (bad | 0x80000000u) : 0;
     if (any && bad) atomicOr(fail, bad);

@@ -109,13 +109,15 @@ __global__ __launch_bounds__(64) void summary_kernel(const vms_trace_stats *__re
 static int selftest_run()
 {
     u32 *d = nullptr, h = 0xFFFFFFFFu;
-    if (hipMalloc((void **)&d, sizeof(u32)) != hipSuccess) return VMS_EHIP;
-    hipLaunchKernelGGL(selftest_kernel, dim3(1), dim3(64), 0, 0, d);
+    const size_t tab_bytes = (size_t)SELFTEST_TABLES * SELFTEST_PLACES * sizeof(uint16_t);     // (a multiple of 16)
+    if (hipMalloc((void **)&d, tab_bytes + sizeof(u32)) != hipSuccess) return VMS_EHIP;
+    u32 *fail = (u32 *)((char *)d + tab_bytes);
+    hipLaunchKernelGGL(selftest_kernel, dim3(1), dim3(64), 0, 0, fail, (uint16_t *)d);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpy(&h, d, sizeof h, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(&h, fail, sizeof h, hipMemcpyDeviceToHost);
     (void)hipFree(d);
     if (e != hipSuccess) return VMS_EHIP;
-    return h == 0 ? VMS_OK : -(int)(1000 + (h & 0xFFFF));
+    return h == 0 ? VMS_OK : -(int)(1000 + (h & 0xFFFFFF));
 }
 
 typedef void (*vms_fn)(KParams, const u64 *, const u32 *, u64 *, vms_trace_stats *, char *);

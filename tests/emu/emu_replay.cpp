@@ -129,7 +129,7 @@ void body_split(void *p)
 }
 
 u32 g_selftest_fail;
-void body_selftest(void *) { selftest_kernel(&g_selftest_fail); }
+void body_selftest(void *tab) { selftest_kernel(&g_selftest_fail, (uint16_t *)tab); }
 
 }  // namespace
 
@@ -189,12 +189,13 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
     return 0;
 }
 
-// the wave primitives' self-test kernel on the host lanes: 0, or its failure bits
+// the wave primitives' self-test kernel on the host lanes: 0, its failure bits, or 0xFFFFFFFF if a guard band was written
 unsigned emu_selftest(void)
 {
+    Guarded tab((size_t)SELFTEST_TABLES * SELFTEST_PLACES * sizeof(uint16_t));
     g_selftest_fail = 0xFFFFFFFFu;
-    emu::launch(body_selftest, nullptr, 0);
-    return g_selftest_fail;
+    emu::launch(body_selftest, tab.ptr(), 0);
+    return tab.intact() ? g_selftest_fail : 0xFFFFFFFFu;
 }
 
 }  // extern "C"
