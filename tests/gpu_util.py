@@ -95,3 +95,36 @@ def equal_blocks_trace(blocks, small, seed):
             ops.append(("A", s, min(size, chunk - 512) if small else size))
             live.add(s)
     return tg.make_events(ops)[None, :], blocks
+
+
+def alternate_frees_trace(n):
+    """2 n requests of 1 KiB out of one chunk, then every second one back: each FREE adds a block to the splitting
+    pool that merges with nothing, beside the rest of the chunk.  Returns (events, slots)."""
+    from paper_2401_08156_amd import tracegen as tg
+    ops = [("A", s, 1024) for s in range(2 * n)] + [("F", s) for s in range(0, 2 * n, 2)]
+    return tg.make_events(ops + [("A", 0, 512)])[None, :], 2 * n
+
+
+def assert_free_outgrows_pool(replay, cfg, ev, pol, flag):
+    """The last FREE of alternate_frees_trace(n) needs a place more than the pool has: the replay ends before it,
+    flagged, with the statistics of the events before it.  Under the stitching policy the request of that FREE is
+    gone (its slot is unbound before the pool is asked), its memory is still held."""
+    at = ev.shape[1] - 2
+    ds, dv, st = replay(ev, cfg)
+    dec, g = (ds, dv)[pol][0], st[pol][0]
+    P = oracle_params(cfg)
+    odec, ost = oracle.replay(ev, P, pol, n_events=[at])
+    assert g["status"] == binding.VMS_ST_TABLE_OVERFLOW | flag and g["overflow_event"] == at
+    assert np.array_equal(dec[:at], odec[0, :at]) and (dec[at:] == np.uint64(0xFFFFFFFFFFFFFFFF)).all()
+    for f in COMPARED_FIELDS:
+        if f not in ("status", "final_requested"):
+            assert np.array_equal(g[f], ost[0][f]), (f, g[f], ost[0][f])
+    assert g["final_requested"] == ost[0]["final_requested"] - (1024 if pol else 0)
+    # with one place more the whole trace fits
+    cfg.max_free_blocks += 1
+    cfg.max_small_blocks += 1 if cfg.max_small_blocks else 0
+    ds, dv, st = replay(ev, cfg)
+    odec, ost = oracle.replay(ev, P, pol)
+    assert np.array_equal((ds, dv)[pol], odec) and st[pol][0]["status"] == 0
+    for f in COMPARED_FIELDS:
+        assert np.array_equal(st[pol][0][f], ost[0][f]), f

@@ -70,6 +70,16 @@ def test_splitting_pool_of_equal_blocks(blocks, cap, small):
         gpu_util.assert_parity(ev, gpu_util.make_cfg(1, ev.shape[1], ms, variant=2, max_free_blocks=cap), label="pool for small requests")
 
 
+@pytest.mark.parametrize("pol,variant,blocks,small", [
+    (0, 0, 190, 0), (0, 0, 250, 0), (0, 0, 400, 0),                                     # three and five registers per lane, LDS
+    (1, binding.VMS_VARIANT_FINE, 190, 190), (1, binding.VMS_VARIANT_FINE, 250, 0),     # registers, LDS
+    (1, binding.VMS_VARIANT_FLAT, 190, 190), (1, binding.VMS_VARIANT_FLAT, 250, 0)])
+def test_free_that_outgrows_the_splitting_pool(pol, variant, blocks, small):
+    ev, ms = gpu_util.alternate_frees_trace(blocks)
+    cfg = gpu_util.make_cfg(1, ev.shape[1], ms, policy_mask=1 << pol, variant=variant, max_free_blocks=blocks, max_small_blocks=small)
+    gpu_util.assert_free_outgrows_pool(gpu_util.gpu_replay, cfg, ev, pol, binding.VMS_ST_OVF_FREE_BLOCKS)
+
+
 def test_worked_examples_on_gpu():
     import glob
     import os

@@ -72,14 +72,18 @@ def test_splitting_pool_of_equal_blocks(blocks, cap, small):
     ev, ms = gpu_util.equal_blocks_trace(blocks, small, seed=blocks)
     cap = max(cap, 192 if small else 0)
     cfg = gpu_util.make_cfg(1, ev.shape[1], ms, policy_mask=1, max_free_blocks=cap)
-    _, _, st = emu.replay(ev, cfg, binding.STATS_DTYPE)
-    if st["status"][0, 0] & binding.VMS_ST_TABLE_OVERFLOW:      # exactly full: the oracle holds more blocks than the table
-        _, ost = oracle.replay(ev, gpu_util.oracle_params(cfg), 0)
-        assert ost["max_free_blocks"][0] > cap
-        return
     check(ev, cfg, label="%d equal blocks" % blocks)
     if small and blocks <= 96:
         check(ev, gpu_util.make_cfg(1, ev.shape[1], ms, variant=2, max_free_blocks=cap), label="pool for small requests")
+
+
+# pools in three and five registers per lane and in LDS; the stitching policy's pool in registers and in LDS
+@pytest.mark.parametrize("pol,blocks,small", [(0, 64, 0), (0, 190, 0), (0, 250, 0), (0, 400, 0), (1, 64, 64), (1, 190, 190), (1, 250, 0)])
+def test_free_that_outgrows_the_splitting_pool(pol, blocks, small):
+    ev, ms = gpu_util.alternate_frees_trace(blocks)
+    cfg = gpu_util.make_cfg(1, ev.shape[1], ms, policy_mask=1 << pol, variant=binding.VMS_VARIANT_FINE if pol else 0,
+                            max_free_blocks=blocks, max_small_blocks=small)
+    gpu_util.assert_free_outgrows_pool(lambda e, c: emu.replay(e, c, binding.STATS_DTYPE), cfg, ev, pol, binding.VMS_ST_OVF_FREE_BLOCKS)
 
 
 @pytest.mark.parametrize("kind,nt,ne,tables", [
