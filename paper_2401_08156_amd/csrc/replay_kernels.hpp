@@ -398,8 +398,8 @@ struct SplitLds {
 // compares, one or two wave-wide minima and a few lane selects.
 // What bounds it is the chain of one event (two wavefronts per SIMD issue an instruction every nine
 // cycles), so the halves are searched apart, all tiles side by side: 64-bit minima went through the
-// tiles one after the other, compare, select, compare (2,048 traces of 20,000 events, three tiles:
-// 9.68 -> 8.93 ms; LoRA streams, five tiles: 113.4 -> 111.9 ms, with the stitching kernel beside it).
+// tiles one after the other, compare, select, compare (the splitting kernel alone on LoRA streams, five
+// tiles: 2048x20000 9.57 -> 8.84 ms, 4096x50000 35.6 -> 31.9 ms).
 template <u32 TILES>
 struct SplitRegs {
     u32 h[TILES], w[TILES];
@@ -1367,7 +1367,8 @@ DI void small_free(char *lds, const KParams &P, u32 *idle, u32 addr, u32 size, u
 // and the split and merge counts are taken from the 64 lanes once per tile.  Kept per event they cost
 // eight scalar operations each time (4.4 cycles apiece on a wavefront alone) and four scalar registers
 // that the stitching kernels had to keep in vector lanes; two prefix sums and two maxima per tile cost
-// five cycles per event.
+// five cycles per event.  The stitching kernel alone: LoRA 4096x50000 92.7 -> 84.3 ms, scale-out
+// 320x20000 17.0 -> 15.6 ms; on a single random trace, whose scalars were at hand, 1.58 -> 1.60 ms.
 struct TileOut {
     u32 n_code[8];              // events of this lane per decision code ([7]: invalid)
     u64 dig;                    // this lane's share of the digest
@@ -1460,10 +1461,12 @@ struct SecondPass {
 // Replay under the stitching policy (Sec. 3, Sec. 4.1), one wavefront per trace.
 // SLOT_REGS: slot table in registers (max_slots <= 64).
 //
-// Per event only the allocator runs; the decision word and the active / reserved totals after
-// the event are parked in lane j of four registers.  Once per tile of 64 events the lanes store
-// the decisions with one coalesced write, count the decision codes and fold their event into
-// the digest, all 64 events side by side.
+// Per event only the allocator runs; the decision word and what the event added to the requested
+// and active units are parked in lane j of four registers, and where memory was reserved the lanes
+// from j up take over the new reserved total.  Once per tile of 64 events the lanes store the
+// decisions with one coalesced write, take the totals after each event and their peaks by prefix
+// sums and maxima, count the decision codes and fold their event into the digest, all 64 events
+// side by side (tile_emit).
 // ---------------------------------------------------------------------------
 template <bool SLOT_REGS>
 __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__restrict__ events,
@@ -1847,7 +1850,8 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
     for (u32 base = 0; base < n_ev; base += 64) {
         const u32 tile = min(64u, n_ev - base);
         const u32 ev_lo = (u32)ev, ev_hi = (u32)(ev >> 32);
-        // the next tile, on its way while this one is replayed: nothing touches the value (a select on it
+        // the next tile, on its way while this one is replayed (the flat stitching kernel alone on
+        // recomputation traces 1024x20000: 8.56 -> 8.45 ms): nothing touches the value (a select on it
         // would wait for memory here, once per 64 events) until this tile's results are stored, and it is
         // taken over before that store, which would have to be waited for too (one counter).  Lanes past
         // the end hold the last event, which no j reaches.

@@ -36,7 +36,8 @@ DI void wave_lockstep() {}
 // only, so workgroup scope is enough: the compute unit's vector cache may answer (it is written
 // through, and the accesses of one wavefront pass it in order).  A hit there takes 133 cycles, the
 // device scope used before went to L2 every time, 303 cycles (both measured on a dependent chain);
-// the workloads with their tables in the workspace gain 1 to 2 % (scale-out, 320 traces: 16.97 -> 16.64 ms).
+// the workloads with their tables in the workspace gain 1 to 2 % (the stitching kernel alone on scale-out
+// 320x20000: 17.4 -> 17.0 ms).
 DI u64 ld_list(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 // the same for one 16-bit element of a table kept in global memory
 DI u32 ld_tab(const uint16_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
@@ -107,8 +108,8 @@ enum {
 
 // Across the four rows of 16 the reductions go by row broadcasts too: two DPP steps and one lane read.
 // (Four lane reads and scalar arithmetic took four instructions more, and the compiler put the result
-// into a vector register, where it was compared again.)  LoRA 4096x50000 111.9 -> 106.3 ms, ZeRO-3
-// 1280x20000 38.0 -> 36.3 ms, one random trace 1.66 -> 1.63 ms.
+// into a vector register, where it was compared again.)  The stitching kernel alone: LoRA 4096x50000
+// 82.7 -> 78.6 ms, ZeRO-3 1280x20000 17.4 -> 16.7 ms, one random trace 1.595 -> 1.567 ms.
 
 // minimum over the 64 lanes, returned wave-uniform
 DI u32 wave_min_u32(u32 v)

@@ -424,9 +424,10 @@ DI void gblk_store(uint16_t *a, u32 B, const Blk16 &v)
 
 // Groups of 64 blocks per step.  With all three tables in the workspace (N = 3) most moves are shorter than
 // one group of 512 records, and a second group that holds nothing costs its loads, selects and code all
-// the same: one group takes 103.5 instead of 106 ms on LoRA 4096x50000, 14.9 instead of 15.5 on scale-out
-// 320x20000, 35.1 instead of 36.1 on ZeRO-3 1280x20000.  The offloading tables with their sizes in LDS
-// (N = 2) move further and keep two: 526 against 535 ms on 4096x50000.
+// the same: the stitching kernel alone takes 77.7 instead of 79.8 ms on LoRA 4096x50000, 14.45 instead of
+// 14.97 on scale-out 320x20000, 16.0 instead of 16.6 on ZeRO-3 1280x20000, the mixture 16384x20000 250
+// instead of 256.  The offloading tables with their sizes in LDS (N = 2) move further and keep two: 383
+// against 398 ms on 4096x50000.
 template <int N>
 constexpr u32 GBLK_GROUPS = N == 2 ? 2 : 1;
 
