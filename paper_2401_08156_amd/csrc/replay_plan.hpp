@@ -211,8 +211,10 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
     return (uint32_t)(w < 32 ? w : 32);                     // a compute unit holds 32 wavefronts at most
 }
 
-// The plan for cfg.  With variant 0 the library chooses: a trace replays about twice as fast on the
-// flat variant (its lists are in LDS), but when the batch does not fit the compute units at once and
+// The plan for cfg.  With variant 0 the library chooses: a trace replays 1.3 to 2.5 times as fast on the
+// flat variant (its lists are in LDS; the stitching kernel alone, both with all tables in LDS: fragmentation
+// limit study 64x20000 8.8 against 11.8 ms, scale-out 320x20000 9.0 against 13.7, recomputation 1024x20000
+// 8.4 against 21.0), but when the batch does not fit the compute units at once and
 // the fine-grained variant holds at least 2.5 times as many traces per compute unit, the latter
 // finishes the batch sooner.  With table_place 0 it chooses where the fine-grained variant keeps the
 // tables of the sBlocks: throughput grows almost in proportion to the wavefronts per compute unit
@@ -235,7 +237,10 @@ inline int replay_plan_make(const vms_config *cfg, ReplayPlan &p)
     }
     if (p.fine && !p.wide && cfg->table_place == VMS_TABLES_AUTO) {
         // rounds of wavefronts the batch takes, times what a wavefront pays for tables in the workspace
-        // (measured on offloading traces: 1.2 with two tables there, 1.45 with all three)
+        // (1.2 with two tables there, 1.45 with all three: measured on offloading traces when these tables were
+        // read past the vector cache and moved in two groups.  Now, on scale-out 320x20000 with every trace
+        // resident, 1.11 and 1.06; offloading 4096x50000 takes 534 ms with the tables in LDS, 385 with two and
+        // 380 with all three in the workspace, where this rule chooses two.)
         auto cost = [&](const ReplayPlan &x, uint32_t tenths) {
             const uint64_t slots = (uint64_t)CUS * plan_waves_per_cu(x);
             return ((cfg->n_traces + slots - 1) / slots) * tenths;

@@ -18,18 +18,21 @@ TABLES = {
     2: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3840, max_chunks=4096),
     # offloading grinds pBlocks down to single chunks: thousands of pBlocks and sBlocks (the fine-grained kernel
     # variant: single chunks in bitmaps, a table for the pBlocks of two or more chunks, lists in the workspace)
-    # (31,680 B of LDS per wavefront: LDS is handed out in 1,280-byte granules, 128 per compute unit, so five
-    # wavefronts per compute unit need at most 32,000 B each; with 2,816 places for multi-chunk pBlocks it was four)
+    # (LDS is handed out in 1,280-byte granules, 128 per compute unit.  With all tables in LDS 30,960 B per wavefront,
+    # five per compute unit; with two tables in the workspace, as the library places them for this batch, 20,400 B,
+    # eight.  Multi-chunk pBlocks: 2,421 to 2,824 at most over 13 seeds; seven of them send one or two traces through
+    # the second pass.  Places for all would take a seventeenth granule: seven wavefronts per compute unit)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2592, max_sblocks=2560, max_runs=1 << 18, max_chunks=10240),
     # (the fine-grained kernel with its sBlock tables in the workspace, chunk tables for the 17,699 chunks the
     # largest trace reserves: 19.5 KB of LDS per wavefront, eight per compute unit instead of the flat kernel's
-    # three, 153 against 179 ms per step)
+    # three; the stitching kernel alone 79 ms, 97 with the tables in LDS, 125 on the flat kernel)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432,
             variant=2, table_place=3),
     # (the same for the 1,280 traces of the scale-out regime, 9,408 chunks at most: 23,040 B, which is 18 LDS granules
-    # of 1,280 bytes exactly, all traces resident at once, 20.0 against 25.8 ms.  pBlocks: 497 to 534 at most over 12
-    # seeds; with 512 places, in the same 18 granules, four of those seeds sent a trace through the second pass,
-    # alone and from its first event)
+    # exactly, all traces resident at once; the stitching kernel alone 16.1 ms, 18.4 on the flat kernel, and 15.2 with
+    # the tables in LDS, 26,976 B, which leave the splitting kernel beside it half the room.  pBlocks: 497 to 534 at
+    # most over 12 seeds; with 512 places, in the same 18 granules, four of those seeds sent a trace through the
+    # second pass, alone and from its first event)
     6: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3072, max_chunks=9728, variant=2, table_place=3),
 }
 # config 5 mixes the generators of configs 2, 3 and 4 (trace i uses kind 2 + i mod 3) with twice the
