@@ -325,8 +325,8 @@ typedef struct vms_peaks_report {
  * rounds each.  Synchronous, on the default stream.                                                */
 int vms_measure_peaks(vms_peaks_report *out);
 
-/* In-wavefront primitives self-test (reductions, scans, sorted insert): runs a
- * small kernel on the current device and returns VMS_OK if every lane layout
+/* In-wavefront primitives self-test (reductions, scans, lane writes, searches and
+ * moves of sorted arrays in LDS, moves of tables in global memory): runs a small kernel on the current device and returns VMS_OK if every lane layout
  * matches its definition.  Diagnostic; not part of a replay.                  */
 int vms_selftest(void);
 
