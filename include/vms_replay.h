@@ -326,8 +326,9 @@ typedef struct vms_peaks_report {
 int vms_measure_peaks(vms_peaks_report *out);
 
 /* In-wavefront primitives self-test (reductions, scans, lane writes, searches and
- * moves of sorted arrays in LDS, moves of tables in global memory): runs a small kernel on the current device and returns VMS_OK if every lane layout
- * matches its definition.  Diagnostic; not part of a replay.                  */
+ * moves of sorted arrays in LDS, moves of tables in global memory): runs a small
+ * kernel on the current device and returns VMS_OK if every lane layout matches its
+ * definition.  Diagnostic; not part of a replay.                               */
 int vms_selftest(void);
 
 #ifdef __cplusplus

@@ -3,8 +3,8 @@
 Table sizes (per trace) are capacity settings of the replay engine, not parameters of the
 allocators: a trace that outgrows them is replayed a second time with doubled tables (up to
 retry_traces traces per run), and flagged VMS_ST_TABLE_OVERFLOW, never replayed wrongly, if that
-does not suffice.  The values below hold the high-water marks measured on the full workloads of the default seed with
-headroom (what other seeds need is said beside the table where they were counted);
+does not suffice.  The values below hold the high-water marks measured on the full workloads of the
+default seed with headroom (what other seeds need is said beside the table where they were counted);
 smaller tables mean less LDS per wavefront and therefore more resident wavefronts per compute unit.
 """
 from . import tracegen
