@@ -1187,10 +1187,10 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                     AcctLds A;
                     A.sc = (u32 *)(lds + LDS_SCALARS);
                     A.idle = V.idle;
-                    Q.release(a >> 2, req, a & 3, A, base + j,
+                    Q.release(a, req, A, base + j,
                               [&](bool ml, bool mr) {
                                   write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                              a >> 2, 0u - req, 0u - req, j);
+                                              Q.addr(a), 0u - req, 0u - req, j);
                                   wave_sync();
                               },
                               [&]() {
@@ -1261,7 +1261,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                     A.sc = (u32 *)(lds + LDS_SCALARS);
                     A.idle = V.idle;
                     Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
-                            [&](u32 code, u32 addr, u32 flags, bool split) {
+                            [&](u32 code, u32 ref, bool split) {
                                 sp_reserved = Q.reserved();
                                 u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
                                 if (code == C_OOM) {
@@ -1271,12 +1271,12 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                                     if (C.get(SC_FIRST_OOM) == NONE32)
                                         st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
                                 } else {
-                                    S.set_a(slot, (addr << 2) | flags);
+                                    S.set_a(slot, ref);
                                     S.set_b(slot, (u32)KIND_SMALL);
                                     S.set_req(slot, size);
                                     if (code == C_GROW) RESERVED_NOW();
                                     d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
-                                    d_hi = addr;
+                                    d_hi = Q.addr(ref);
                                     d_req = size;
                                 }
                                 write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);

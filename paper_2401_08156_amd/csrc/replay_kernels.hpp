@@ -371,62 +371,71 @@ struct SplitLds {
     }
     DI u32 reserved() const { return sp.reserved; }
     DI u32 most() const { return 0; }       // (kept in the counters)
-    // done(code, addr, flags, split) once the request is decided (code C_OOM: it failed), ovf() if
-    // the table is full instead (see SplitRegs)
+    static DI u32 addr(u32 ref) { return ref >> 2; }            // ref: address << 2 | flags, what its slot keeps
+    // done(code, ref, split) once the request is decided (code C_OOM: it failed), ovf() if the table
+    // is full instead (see SplitRegs)
     template <class AcctT, class Done, class Ovf>
     DI void alloc(u32 size, u32 seg, bool may_grow, AcctT &A, u32 ev, Done done, Ovf ovf)
     {
         SplitRes r;
         sp_alloc(sp, size, seg, may_grow, A, ev, r);
         if (UNLIKELY(A.stop)) ovf();
-        else done(r.code, r.addr, r.flags, r.split);
+        else done(r.code, (r.addr << 2) | r.flags, r.split);
     }
     template <class AcctT, class Done, class Ovf>
-    DI void release(u32 addr, u32 size, u32 flags, AcctT &A, u32 ev, Done done, Ovf ovf)
+    DI void release(u32 ref, u32 size, AcctT &A, u32 ev, Done done, Ovf ovf)
     {
         bool ml, mr;
-        sp_free(sp, addr, size, flags, &ml, &mr, A, ev);
+        sp_free(sp, ref >> 2, size, ref & 3, &ml, &mr, A, ev);
         if (UNLIKELY(A.stop)) ovf();
         else done(ml, mr);
     }
 };
 
-// The inactive blocks in registers: place t * 64 + l of the array is h[t], w[t] of lane l: the two
-// halves of the key, size and address << 2 | flags; 0 in both = empty place.  The order of the array
-// means nothing (best fit and the neighbour searches look at every key), so a block that leaves just
-// zeroes its place and a new one takes the first empty place.  No LDS access at all: a request is
-// compares, one or two wave-wide minima and a few lane selects.
+// The inactive blocks in registers: place t * 64 + l of the array is at[t], h[t] of lane l: where the
+// block is and its size; 0 in both = empty place.  The order of the array means nothing (best fit and
+// the neighbour searches look at every block), so a block that leaves just zeroes its place and a new
+// one takes the first empty place.  No LDS access at all: a request is compares, one or two wave-wide
+// minima and a few lane selects.
+// at = address << 1 | segment parity (1 for the first segment, then 0, 1, ...).  Segments follow each
+// other without a gap, so only neighbouring ones could touch, and theirs differ in the low bit: block x
+// ends where y starts, in the same segment, iff at_x + 2 h_x == at_y.  One compare per side and place
+// answers what took two segment flags their own tests, masks and merging before (the splitting kernel
+// alone: LoRA 2048x20000 8.74 -> 7.22 ms, recomputation 1024x20000 6.33 -> 5.26; the stitching kernel on
+// LoRA 4096x50000, most of whose requests are small, 80.2 -> 74.2 ms).  No block is at 0 (the block at
+// address 0 has parity 1), so an empty place matches nothing.
 // What bounds it is the chain of one event (two wavefronts per SIMD issue an instruction every nine
 // cycles), so the halves are searched apart, all tiles side by side: 64-bit minima went through the
 // tiles one after the other, compare, select, compare (the splitting kernel alone on LoRA streams, five
 // tiles: 2048x20000 9.57 -> 8.84 ms, 4096x50000 35.6 -> 31.9 ms).
 template <u32 TILES>
 struct SplitRegs {
-    u32 h[TILES], w[TILES];
-    u32 n, cap, res;
+    u32 at[TILES], h[TILES];
+    u32 n, cap, res, parity;
     u32 hw;                     // the most blocks held at once (cuts and merges are counted off the decisions)
     DI void init(char *, const KParams &P)
     {
 #pragma unroll
-        for (u32 t = 0; t < TILES; t++) h[t] = w[t] = 0;
+        for (u32 t = 0; t < TILES; t++) at[t] = h[t] = 0;
         n = hw = 0;
         cap = P.cap_free;
         res = 0;
+        parity = 1;
     }
     DI u32 reserved() const { return res; }
     DI u32 most() const { return hw; }
-    // w is unique among the live blocks (it contains the address) and not 0 (the block at address 0 is
-    // the first of its segment): the place that holds `from` takes a new size and address
-    DI void swap_block(u32 from, u32 size, u32 to)
+    static DI u32 addr(u32 ref) { return ref >> 1; }            // ref: `at` of a block, what its slot keeps
+    // the block at `from` (one place holds it) takes a new place and size
+    DI void swap_block(u32 from, u32 to, u32 size)
     {
 #pragma unroll
         for (u32 q = 0; q < TILES; q++) {
-            const bool here = w[q] == from;
+            const bool here = at[q] == from;
+            at[q] = here ? to : at[q];
             h[q] = here ? size : h[q];
-            w[q] = here ? to : w[q];
         }
     }
-    DI void insert(u32 size, u32 to)            // into an empty place (n < cap <= 64 * TILES: there is one)
+    DI void insert(u32 to, u32 size)            // into an empty place (n < cap <= 64 * TILES: there is one)
     {
         bool any = false;
 #pragma unroll
@@ -435,16 +444,16 @@ struct SplitRegs {
 #pragma unroll
         for (u32 q = 0; q < TILES; q++) {
             const bool here = todo && h[q] == 0;
+            at[q] = here ? to : at[q];
             h[q] = here ? size : h[q];
-            w[q] = here ? to : w[q];
             todo = todo && !here;
         }
         n++;
         hw = max(hw, n);
     }
-    // Every outcome ends in a call of its own: done(code, addr, flags, split) once the request is
-    // decided (code C_OOM: it failed) or ovf() if the table is full.  Results handed back through
-    // one return would meet again in flags that the caller has to test, event after event.
+    // Every outcome ends in a call of its own: done(code, ref, split) once the request is decided
+    // (code C_OOM: it failed) or ovf() if the table is full.  Results handed back through one return
+    // would meet again in flags that the caller has to test, event after event.
     template <class AcctT, class Done, class Ovf>
     DI void alloc(u32 size, u32 seg, bool may_grow, AcctT &A, u32 ev, Done done, Ovf ovf)
     {
@@ -460,87 +469,86 @@ struct SplitRegs {
         if (LIKELY((int)rest >= 0)) {
             u32 c = NONE32;                     // lowest address of that size in this lane
 #pragma unroll
-            for (u32 t = 0; t < TILES; t++) c = min(c, d[t] == rest ? w[t] : NONE32);
+            for (u32 t = 0; t < TILES; t++) c = min(c, d[t] == rest ? at[t] : NONE32);
             const u64 m = ballot(mine == rest);
-            const u32 blo = UNLIKELY(m & (m - 1)) ? wave_min_u32(c) : from_lane(c, first_lane(m));
-            const u32 addr = blo >> 2, flags = blo & 3;
+            const u32 ref = UNLIKELY(m & (m - 1)) ? wave_min_u32(c) : from_lane(c, first_lane(m));
             if (LIKELY(rest != 0)) {
                 // step 2: cut off what is not needed; it stays cached as the right neighbour, in the
                 // place the block had
-                swap_block(blo, rest, ((addr + size) << 2) | (flags & 1));
-                done((u32)C_SPLIT, addr, flags & 2, true);
+                swap_block(ref, ref + 2 * size, rest);
+                done((u32)C_SPLIT, ref, true);
                 return;
             }
-            swap_block(blo, 0u, 0u);
+            swap_block(ref, 0u, 0u);
             n--;
-            done((u32)C_EXACT, addr, flags, false);
+            done((u32)C_EXACT, ref, false);
             return;
         }
         if (!may_grow) {
-            done((u32)C_OOM, 0u, 0u, false);
+            done((u32)C_OOM, 0u, false);
             return;
         }
-        const u32 addr = res;                   // "native allocation": a fresh segment
+        const u32 ref = 2 * res + parity;       // "native allocation": a fresh segment
         res += seg;
+        parity ^= 1;
         if (seg > size) {                       // the rest of a fresh segment
             if (n == cap) {
                 A.overflow(ev, VMS_ST_OVF_FREE_BLOCKS);
                 ovf();
                 return;
             }
-            insert(seg - size, ((addr + size) << 2) | 1u);
-            done((u32)C_GROW, addr, 2u, true);
+            insert(ref + 2 * size, seg - size);
+            done((u32)C_GROW, ref, true);
             return;
         }
-        done((u32)C_GROW, addr, 3u, false);
+        done((u32)C_GROW, ref, false);
     }
     // steps 3 and 4: the block becomes inactive and absorbs inactive neighbours of its segment
     template <class AcctT, class Done, class Ovf>
-    DI void release(u32 addr, u32 size, u32 flags, AcctT &A, u32 ev, Done done, Ovf ovf)
+    DI void release(u32 ref, u32 size, AcctT &A, u32 ev, Done done, Ovf ovf)
     {
-        const bool can_l = !(flags & 2), can_r = !(flags & 1);
-        const u32 end = addr + size;
-        // at most one block ends where this one starts and at most one starts where it ends: every
-        // lane folds its places into one candidate per side, two ballots decide.  Of the left block the
-        // address is enough (it ends at addr), the right one brings its size too
-        u32 lw = 0, rw = 0, rh = 0;
+        // at most one block ends where this one starts and at most one starts where it ends
+        const u32 end = ref + 2 * size;
+        bool l[TILES], r[TILES], any_l = false, any_r = false;
 #pragma unroll
         for (u32 t = 0; t < TILES; t++) {
-            // an empty place matches nothing: no block ends at 0 that could merge, none starts at an end
-            const u32 ka = w[t] >> 2;
-            lw = ka + h[t] == addr ? w[t] : lw;
-            rw = ka == end ? w[t] : rw;
-            rh = ka == end ? h[t] : rh;
+            l[t] = at[t] + 2 * h[t] == ref;
+            r[t] = at[t] == end;
+            any_l = any_l || l[t];
+            any_r = any_r || r[t];
         }
-        const u64 mL = can_l ? ballot(lw != 0) : 0, mR = can_r ? ballot(rw != 0) : 0;
+        const u64 mL = ballot(any_l), mR = ballot(any_r);
         const bool ml = mL != 0, mr = mR != 0;
-        const u32 lown = first_lane(mL | (1ull << 63)), rown = first_lane(mR | (1ull << 63));
-        const u32 left = from_lane(lw, lown), right = from_lane(rw, rown), rsize = from_lane(rh, rown);
         if (mr) {
-            size += rsize;
-            flags = (flags & 2) | (right & 1);
-        }
-        if (ml) {
-            size += addr - (left >> 2);
-            addr = left >> 2;
-            flags = (left & 2) | (flags & 1);
-        }
-        const u32 to = (addr << 2) | flags;
-        if (UNLIKELY(ml)) {
-            swap_block(left, size, to);         // the merged block takes the left neighbour's place
-            if (mr) {
-                swap_block(right, 0u, 0u);
+            u32 x = 0;                          // the right neighbour's size
+#pragma unroll
+            for (u32 t = 0; t < TILES; t++) x = r[t] ? h[t] : x;
+            size += from_lane(x, first_lane(mR));
+            if (UNLIKELY(ml)) {
+                // the merged block takes the left neighbour's place
+#pragma unroll
+                for (u32 t = 0; t < TILES; t++) {
+                    at[t] = r[t] ? 0u : at[t];
+                    h[t] = r[t] ? 0u : (l[t] ? h[t] + size : h[t]);
+                }
                 n--;
+            } else {
+#pragma unroll
+                for (u32 t = 0; t < TILES; t++) {
+                    at[t] = r[t] ? ref : at[t];
+                    h[t] = r[t] ? size : h[t];
+                }
             }
-        } else if (mr) {
-            swap_block(right, size, to);
+        } else if (UNLIKELY(ml)) {
+#pragma unroll
+            for (u32 t = 0; t < TILES; t++) h[t] = l[t] ? h[t] + size : h[t];
         } else {
             if (n == cap) {
                 A.overflow(ev, VMS_ST_OVF_FREE_BLOCKS);
                 ovf();
                 return;
             }
-            insert(size, to);
+            insert(ref, size);
         }
         done(ml, mr);
     }
@@ -1570,10 +1578,10 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                     AcctLds A;
                     A.sc = (u32 *)(lds + LDS_SCALARS);
                     A.idle = V.idle;
-                    Q.release(a >> 2, req, a & 3, A, base + j,
+                    Q.release(a, req, A, base + j,
                               [&](bool ml, bool mr) {
                                   write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                              a >> 2, 0u - req, 0u - req, j);
+                                              Q.addr(a), 0u - req, 0u - req, j);
                                   wave_sync();
                               },
                               [&]() {
@@ -1710,7 +1718,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                     A.sc = (u32 *)(lds + LDS_SCALARS);
                     A.idle = V.idle;
                     Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
-                            [&](u32 code, u32 addr, u32 flags, bool split) {
+                            [&](u32 code, u32 ref, bool split) {
                                 sp_reserved = Q.reserved();
                                 u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
                                 if (code == C_OOM) {
@@ -1720,12 +1728,12 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                                     if (C.get(SC_FIRST_OOM) == NONE32)
                                         st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
                                 } else {
-                                    S.set_a(slot, (addr << 2) | flags);
+                                    S.set_a(slot, ref);
                                     S.set_b(slot, (u32)KIND_SMALL);
                                     S.set_req(slot, size);
                                     if (code == C_GROW) RESERVED_NOW();
                                     d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
-                                    d_hi = addr;
+                                    d_hi = Q.addr(ref);
                                     d_req = size;
                                 }
                                 write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
@@ -1890,9 +1898,9 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
                 }
                 const u32 a = S.get_a(slot);
                 S.set_req(slot, (u32)SLOT_UNBOUND);
-                sp.release(a >> 2, req, a & 3, A, base + j,
+                sp.release(a, req, A, base + j,
                            [&](bool ml, bool mr) {
-                               emit(C_FREE | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2, 0u - req);
+                               emit(C_FREE | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), sp.addr(a), 0u - req);
                            },
                            overflow);
                 continue;
@@ -1904,18 +1912,18 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
             }
             const u32 seg = ((size + chunk_units - 1) >> P.chunk_shift) << P.chunk_shift;
             sp.alloc(size, seg, sp.reserved() + seg <= P.capacity_units, A, base + j,
-                     [&](u32 code, u32 addr, u32 flags, bool split) {
+                     [&](u32 code, u32 ref, bool split) {
                          if (code == C_OOM) {
                              S.set_req(slot, (u32)SLOT_OOM);
                              if (A.f[SC_FIRST_OOM] == NONE32) A.f[SC_FIRST_OOM] = base + j;
                              emit((u32)C_OOM, 0u, 0u);
                              return;
                          }
-                         S.set_a(slot, (addr << 2) | flags);
+                         S.set_a(slot, ref);
                          S.set_req(slot, size);
                          // blocks are cut to the request: active bytes are the requested bytes
                          if (code == C_GROW) v_res = lane >= j ? sp.reserved() : v_res;
-                         emit(code | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), addr, size);
+                         emit(code | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), sp.addr(ref), size);
                      },
                      overflow);
         }

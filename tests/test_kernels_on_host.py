@@ -77,6 +77,22 @@ def test_splitting_pool_of_equal_blocks(blocks, cap, small):
         check(ev, gpu_util.make_cfg(1, ev.shape[1], ms, variant=2, max_free_blocks=cap), label="pool for small requests")
 
 
+# whole segments freed side by side do not merge, their own pieces do, up to the last address of 512 GiB
+@pytest.mark.parametrize("cap", [64, 320])
+def test_segments_that_touch_do_not_merge(cap):
+    rng, ops, live, n = np.random.default_rng(cap), [], [], 0
+    for i in range(400):
+        if live and rng.random() < (0.2 if i % 100 < 50 else 0.8):
+            ops.append(("F", live.pop(rng.integers(len(live)))))
+        else:
+            ops.append(("A", n, int(rng.choice([1, 2, 8, 32, 64])) << int(rng.choice([21, 30]))))
+            live.append(n)
+            n += 1
+    ev = tg.make_events(ops)[None, :]
+    st = check(ev, gpu_util.make_cfg(1, ev.shape[1], n, policy_mask=1, max_free_blocks=cap), label="segments side by side")
+    assert st["n_code"][0, 0, 5] > 0 and st["n_merge"][0, 0] > 20 and st["peak_reserved"][0, 0] > 500 << 30
+
+
 # pools in three and five registers per lane and in LDS; the stitching policy's pool in registers and in LDS
 @pytest.mark.parametrize("pol,blocks,small", [(0, 64, 0), (0, 190, 0), (0, 250, 0), (0, 400, 0), (1, 64, 64), (1, 190, 190), (1, 250, 0)])
 def test_free_that_outgrows_the_splitting_pool(pol, blocks, small):
