@@ -1113,9 +1113,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
     V.np = V.ns = V.n_chunks = V.np_all = V.top = V.live = V.next_sid = V.clock = 0;
     for (u32 i = lane; i < P.bmp_words + 1; i += 64) V.bmp[i] = V.bnd[i] = 0;
     for (u32 i = lane; i < P.bmp_words + 64; i += 64) V.tmp[i] = 0;
-    if (!P.small_regs)
-        for (u32 i = lane; i < P.cap_free + 128; i += 64) ((u64 *)(lds + P.off_fl))[i] = 0;
-    SplitRegs<3> Q;                                         // the pool for small requests, if it fits registers
+    SplitPool<SMALL_TILES, true> Q;                               // the pool for small requests
     Q.init(lds, P);
     for (u32 i = lane; i < P.cap_pblocks + 80; i += 64) V.pool[i] = 0;
     for (u32 i = lane; i < P.cap_sblocks + 80; i += 64) {
@@ -1181,36 +1179,24 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                     bmp_fill(V.bmp, V.w_spare, a, b >> 2, false);
                     EMIT((u32)C_FREE, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
                 }
-                if (LIKELY(P.small_regs)) {
-                    // (each outcome parks its results and goes on from where it is found: handed back
-                    // through a record they would meet in flags that are tested again)
-                    AcctLds A;
-                    A.sc = (u32 *)(lds + LDS_SCALARS);
-                    A.idle = V.idle;
-                    Q.release(a, req, A, base + j,
-                              [&](bool ml, bool mr) {
-                                  write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                              Q.addr(a), 0u - req, 0u - req, j);
-                                  wave_sync();
-                              },
-                              [&]() {
-                                  lost = req;
-                                  stop = true;
-                                  done = j;
-                                  todo = 0;
-                              });
-                    continue;
-                }
-                bool ml = false, mr = false;
-                small_free(lds, P, V.idle, a >> 2, req, a & 3, base + j, &ml, &mr);
-                if (UNLIKELY(ld_uni((u32 *)(lds + LDS_SCALARS), (u32)SC_STOP) != 0)) {
-                    lost = req;
-                    stop = true;
-                    done = j;
-                    todo = 0;
-                    continue;
-                }
-                EMIT(C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2, 0u - req, 0u - req)
+                // (each outcome parks its results and goes on from where it is found: handed back
+                // through a record they would meet in flags that are tested again)
+                AcctLds A;
+                A.sc = (u32 *)(lds + LDS_SCALARS);
+                A.idle = V.idle;
+                Q.release(a, req, A, base + j,
+                          [&](bool ml, bool mr) {
+                              write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
+                                          Q.addr(a), 0u - req, 0u - req, j);
+                              wave_sync();
+                          },
+                          [&]() {
+                              lost = req;
+                              stop = true;
+                              done = j;
+                              todo = 0;
+                          });
+                continue;
             }
             // ---- ALLOC
             const u32 size = w;
@@ -1256,54 +1242,37 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                 // ---- a request below one chunk: the policy's own splitting pool (Sec. 3.1)
                 const u32 seg = ((size + chunk_units - 1) >> P.chunk_shift) << P.chunk_shift;
                 const u32 reserved = sp_reserved + (V.n_chunks << P.chunk_shift);
-                if (LIKELY(P.small_regs)) {
-                    AcctLds A;
-                    A.sc = (u32 *)(lds + LDS_SCALARS);
-                    A.idle = V.idle;
-                    Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
-                            [&](u32 code, u32 ref, bool split) {
-                                sp_reserved = Q.reserved();
-                                u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
-                                if (code == C_OOM) {
-                                    S.set_req(slot, (u32)SLOT_OOM);
-                                    ColdState C;            // rare: note the first failed request
-                                    C.load(lds);
-                                    if (C.get(SC_FIRST_OOM) == NONE32)
-                                        st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                                } else {
-                                    S.set_a(slot, ref);
-                                    S.set_b(slot, (u32)KIND_SMALL);
-                                    S.set_req(slot, size);
-                                    if (code == C_GROW) RESERVED_NOW();
-                                    d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
-                                    d_hi = Q.addr(ref);
-                                    d_req = size;
-                                }
-                                write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
-                                wave_sync();
-                            },
-                            [&]() {
-                                stop = true;
-                                done = j;
-                                todo = 0;
-                            });
-                    continue;
-                }
-                SplitRes r;
-                small_alloc(lds, P, V.idle, size, seg, reserved + seg <= P.capacity_units, base + j, r, sp_reserved);
-                if (UNLIKELY(ld_uni((u32 *)(lds + LDS_SCALARS), (u32)SC_STOP) != 0)) {
-                    stop = true;
-                    done = j;
-                    todo = 0;
-                    continue;
-                }
-                dlo = C_OOM;
-                if (r.code != C_OOM) {
-                    S.set_a(slot, (r.addr << 2) | r.flags);
-                    S.set_b(slot, (u32)KIND_SMALL);
-                    dlo = r.code | B_SMALL | (r.split ? B_6 : 0u) | ((r.code == C_GROW ? 0u : 1u) << 8);
-                    dhi = r.addr;
-                }
+                AcctLds A;
+                A.sc = (u32 *)(lds + LDS_SCALARS);
+                A.idle = V.idle;
+                Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
+                        [&](u32 code, u32 ref, bool split) {
+                            sp_reserved = Q.reserved();
+                            u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
+                            if (code == C_OOM) {
+                                S.set_req(slot, (u32)SLOT_OOM);
+                                ColdState C;            // rare: note the first failed request
+                                C.load(lds);
+                                if (C.get(SC_FIRST_OOM) == NONE32)
+                                    st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
+                            } else {
+                                S.set_a(slot, ref);
+                                S.set_b(slot, (u32)KIND_SMALL);
+                                S.set_req(slot, size);
+                                if (code == C_GROW) RESERVED_NOW();
+                                d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
+                                d_hi = Q.addr(ref);
+                                d_req = size;
+                            }
+                            write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
+                            wave_sync();
+                        },
+                        [&]() {
+                            stop = true;
+                            done = j;
+                            todo = 0;
+                        });
+                continue;
             }
             if (UNLIKELY((dlo & 15) == C_OOM)) {
                 S.set_req(slot, (u32)SLOT_OOM);
@@ -1352,7 +1321,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
         s.status = sc[SC_STATUS] | (n_code[7] ? VMS_ST_INVALID_EVENT : 0u);
         s.max_pblocks = sc[SC_HW_PBLOCKS];
         s.max_sblocks = sc[SC_HW_SBLOCKS];
-        s.max_free_blocks = max(sc[SC_HW_FREE], Q.most());
+        s.max_free_blocks = Q.most();
         s.max_members = sc[SC_HW_MEMBERS];
         s.max_runs = sc[SC_HW_RUNS];
         s.overflow_event = sc[SC_OVF_EVENT];

@@ -31,11 +31,10 @@ enum { KIND_SMALL = 0u, KIND_PBLOCK = 1u, KIND_SBLOCK = 2u };
 // when they end); the counters after them are only ever updated in place.
 enum {
     SC_TOP, SC_LIVE, SC_NEXT_SID,                       // arena top, live list entries, next creation number
-    SC_SP_N,                                            // blocks in the splitting pool for requests below one chunk
     SC_NP_ALL,                                          // fine-grained variant: pBlocks of any size
     SC_STATE_COUNT,
     SC_N_SPLIT = SC_STATE_COUNT, SC_N_CREATED, SC_N_EVICTED, SC_FIRST_OOM, SC_STATUS, SC_OVF_EVENT, SC_STOP,
-    SC_HW_PBLOCKS, SC_HW_SBLOCKS, SC_HW_FREE, SC_HW_MEMBERS, SC_HW_RUNS, SC_HW_MULTI,
+    SC_HW_PBLOCKS, SC_HW_SBLOCKS, SC_HW_MEMBERS, SC_HW_RUNS, SC_HW_MULTI,
     SC_COUNT
 };
 
@@ -181,222 +180,23 @@ struct SlotsT<false> {
 };
 
 // ---------------------------------------------------------------------------
-// Splitting pool (Sec. 2.2): the inactive blocks of the pool as an unordered
-// LDS array of 64-bit keys
-//     bits 32-62 size (units) | bits 2-31 address (units) | bit 1 first-in-segment | bit 0 last-in-segment
-// so that the minimum key >= (request << 32) is the best fit with the lowest
-// address.  Active blocks are not stored: a block's address, size and segment
-// flags travel with the slot that holds it.  The two flags replace neighbour
-// links: a block may merge to the right iff it is not last in its segment and
-// the block starting where it ends is in the array (inactive); same to the left.
-// The array is scanned four tiles of 64 keys at a time, all loads issued before
-// the first is used, so a scan of up to 256 keys costs one LDS round trip.
-// ---------------------------------------------------------------------------
-struct SplitPoolD {
-    u64 *fl;
-    u32 n, cap;
-    u32 reserved;               // units obtained so far = next segment address
-};
-
-struct SplitRes {
-    u32 code, addr, flags;
-    bool split;
-};
-
-// fl[] is followed by zero keys (128 places past cap): a scan reads whole tiles without
-// clamping, and a zero key neither fits a request nor neighbours a block.
-template <class AcctT>
-DI void sp_alloc(SplitPoolD &sp, u32 size, u32 seg, bool may_grow, AcctT &A, u32 ev, SplitRes &r)
-{
-    const u32 lane = lane_id();
-    r.split = false;
-    // step 1: best fit = smallest key not below (size, address 0)
-    u64 best = ~0ull;
-    u32 besti = 0;
-    const u32 last = sp.n - 1;
-    const u64 lastk = sp.fl[sp.n ? last : 0u];          // every lane reads the last key: it will fill the hole
-    for (u32 base = 0; base < sp.n; base += 256) {
-        u64 k[4];
-        k[0] = sp.fl[base + lane];
-        k[1] = sp.fl[base + 64 + lane];
-        k[2] = k[3] = 0;
-        if (base + 128 < sp.n) {
-            k[2] = sp.fl[base + 128 + lane];
-            k[3] = sp.fl[base + 192 + lane];
-        }
-#pragma unroll
-        for (u32 t = 0; t < 4; t++) {
-            if (t < 2 || base + 128 < sp.n) {
-                const bool ok = (u32)(k[t] >> 32) >= size && k[t] < best;
-                best = ok ? k[t] : best;
-                besti = ok ? base + t * 64 + lane : besti;
-            }
-        }
-    }
-    const u32 hi = (u32)(best >> 32);
-    const u32 mhi = sp.n ? wave_min_u32(hi) : NONE32;
-    u32 bsize;
-    if (mhi != NONE32) {
-        const u64 m = ballot(hi == mhi);
-        u32 owner = first_lane(m);
-        if (m & (m - 1)) {                      // several blocks of that size: lowest address
-            const u32 lo = hi == mhi ? (u32)best : NONE32;
-            const u32 mlo = wave_min_u32(lo);
-            owner = first_lane(ballot(lo == mlo));
-        }
-        const u32 blo = from_lane((u32)best, owner);
-        const u32 idx = from_lane(besti, owner);
-        bsize = mhi;
-        r.addr = blo >> 2;
-        r.flags = blo & 3;
-        r.code = C_EXACT;
-        if (idx != last) st_one(sp.fl, idx, lastk);     // unordered: the last key fills the hole, a zero its place
-        st_one(sp.fl, last, (u64)0);
-        sp.n = last;
-        wave_sync();
-    } else {
-        if (!may_grow) {
-            r.code = C_OOM;
-            r.addr = r.flags = 0;
-            return;
-        }
-        r.addr = sp.reserved;                   // "native allocation": a fresh segment
-        sp.reserved += seg;
-        bsize = seg;
-        r.flags = 3;
-        r.code = C_GROW;
-    }
-    // step 2: cut off what is not needed; it stays cached as the right neighbour
-    if (bsize > size) {
-        if (sp.n == sp.cap) {
-            A.overflow(ev, VMS_ST_OVF_FREE_BLOCKS);
-            return;
-        }
-        const u64 rest = ((u64)(bsize - size) << 32) | ((u64)(r.addr + size) << 2) | (r.flags & 1);
-        st_one(sp.fl, sp.n, rest);
-        sp.n++;
-        A.peak(SC_HW_FREE, sp.n);
-        wave_sync();
-        r.flags &= 2;
-        r.split = true;
-        if (r.code == C_EXACT) r.code = C_SPLIT;
-    }
-}
-
-// steps 3 and 4: the block becomes inactive and absorbs inactive neighbours of its segment
-template <class AcctT>
-DI void sp_free(SplitPoolD &sp, u32 addr, u32 size, u32 flags, bool *ml, bool *mr, AcctT &A, u32 ev)
-{
-    const u32 lane = lane_id();
-    const bool can_l = !(flags & 2), can_r = !(flags & 1);
-    const u32 end = addr + size;
-    u32 lidx = NONE32, ridx = NONE32;
-    u64 lkey = 0, rkey = 0;
-    if (can_l || can_r) {
-        for (u32 base = 0; base < sp.n; base += 256) {
-            u64 k[4];
-            k[0] = sp.fl[base + lane];
-            k[1] = sp.fl[base + 64 + lane];
-            k[2] = k[3] = 0;
-            if (base + 128 < sp.n) {
-                k[2] = sp.fl[base + 128 + lane];
-                k[3] = sp.fl[base + 192 + lane];
-            }
-#pragma unroll
-            for (u32 t = 0; t < 4; t++) {
-                if (t < 2 || base + 128 < sp.n) {
-                    // a zero key matches nothing: no block ends at 0 that could merge, none starts at an end
-                    const u32 ka = (u32)k[t] >> 2, ks = (u32)(k[t] >> 32);
-                    const u64 mL = ballot(ka + ks == addr), mR = ballot(ka == end);
-                    if (can_l && mL) {
-                        lidx = base + t * 64 + first_lane(mL);
-                        lkey = from_lane64(k[t], first_lane(mL));
-                    }
-                    if (can_r && mR) {
-                        ridx = base + t * 64 + first_lane(mR);
-                        rkey = from_lane64(k[t], first_lane(mR));
-                    }
-                }
-            }
-        }
-    }
-    *ml = lidx != NONE32;
-    *mr = ridx != NONE32;
-    if (*mr) {
-        size += (u32)(rkey >> 32);
-        flags = (flags & 2) | ((u32)rkey & 1);
-    }
-    if (*ml) {
-        addr = (u32)lkey >> 2;
-        size += (u32)(lkey >> 32);
-        flags = ((u32)lkey & 2) | (flags & 1);
-    }
-    const u64 key = ((u64)size << 32) | ((u64)addr << 2) | flags;
-    if (*ml) {
-        st_one(sp.fl, lidx, key);               // merged block takes the left neighbour's place
-        wave_sync();
-        if (*mr) {
-            const u32 last = sp.n - 1;
-            const u64 lastk = ld_uni(sp.fl, last);
-            if (ridx != last) st_one(sp.fl, ridx, lastk);
-            st_one(sp.fl, last, (u64)0);
-            sp.n = last;
-        }
-    } else if (*mr) {
-        st_one(sp.fl, ridx, key);
-    } else {
-        if (sp.n == sp.cap) {
-            A.overflow(ev, VMS_ST_OVF_FREE_BLOCKS);
-            return;
-        }
-        st_one(sp.fl, sp.n, key);
-        sp.n++;
-        A.peak(SC_HW_FREE, sp.n);
-    }
-    wave_sync();
-}
-
-// The two holders of a splitting pool behind one interface: the LDS array above, and, for pools of
-// at most 64 * TILES inactive blocks, registers.
-struct SplitLds {
-    SplitPoolD sp;
-    DI void init(char *lds, const KParams &P)
-    {
-        sp.fl = (u64 *)(lds + P.off_fl);
-        sp.n = 0;
-        sp.cap = P.cap_free;
-        sp.reserved = 0;
-        for (u32 i = lane_id(); i < P.cap_free + 128; i += 64) sp.fl[i] = 0;    // zero keys behind the live ones
-        wave_sync();
-    }
-    DI u32 reserved() const { return sp.reserved; }
-    DI u32 most() const { return 0; }       // (kept in the counters)
-    static DI u32 addr(u32 ref) { return ref >> 2; }            // ref: address << 2 | flags, what its slot keeps
-    // done(code, ref, split) once the request is decided (code C_OOM: it failed), ovf() if the table
-    // is full instead (see SplitRegs)
-    template <class AcctT, class Done, class Ovf>
-    DI void alloc(u32 size, u32 seg, bool may_grow, AcctT &A, u32 ev, Done done, Ovf ovf)
-    {
-        SplitRes r;
-        sp_alloc(sp, size, seg, may_grow, A, ev, r);
-        if (UNLIKELY(A.stop)) ovf();
-        else done(r.code, (r.addr << 2) | r.flags, r.split);
-    }
-    template <class AcctT, class Done, class Ovf>
-    DI void release(u32 ref, u32 size, AcctT &A, u32 ev, Done done, Ovf ovf)
-    {
-        bool ml, mr;
-        sp_free(sp, ref >> 2, size, ref & 3, &ml, &mr, A, ev);
-        if (UNLIKELY(A.stop)) ovf();
-        else done(ml, mr);
-    }
-};
-
-// The inactive blocks in registers: place t * 64 + l of the array is at[t], h[t] of lane l: where the
-// block is and its size; 0 in both = empty place.  The order of the array means nothing (best fit and
-// the neighbour searches look at every block), so a block that leaves just zeroes its place and a new
-// one takes the first empty place.  No LDS access at all: a request is compares, one or two wave-wide
-// minima and a few lane selects.
+// Splitting pool (Sec. 2.2).  Only the inactive blocks are stored; an active block's place and size
+// travel with the slot that holds it.
+//
+// They live in registers: place t * 64 + l of the array is at[t], h[t] of lane l: where the block is and
+// its size; 0 in both = empty place.  The order of the array means nothing (best fit and the neighbour
+// searches look at every block), so a block that leaves just zeroes its place and a new one takes the
+// first empty place.  No LDS access at all: a request is compares, one or two wave-wide minima and a few
+// lane selects.
+// A table of more than 64 * TILES blocks has the rest in LDS: the tail, used only while every place in
+// the registers is taken (most tables are sized for more blocks than their traces ever hold at once: the
+// default holds 512, the random traces 63 to 115, the LoRA streams 250 to 300).  An earlier version kept
+// every pool of a table of more than 320 (the small-request pool: 192) blocks in LDS as a whole and searched
+// it four tiles at a time (the splitting kernel alone: one random trace 1.067 -> 0.637 ms, LoRA 64x20000 with
+// a table of 1,024 blocks 12.05 -> 6.34; the stitching kernel, which had both kinds of pool in its code:
+// random 1.567 -> 1.093, ZeRO-3 1280x20000 15.8 -> 13.7, LoRA 4096x50000 74.2 -> 63.6).  A kernel that can
+// do without the tail is its own variant: with it the splitting kernel takes 7.75 instead of 7.25 ms on
+// LoRA 2048x20000.
 // at = address << 1 | segment parity (1 for the first segment, then 0, 1, ...).  Segments follow each
 // other without a gap, so only neighbouring ones could touch, and theirs differ in the low bit: block x
 // ends where y starts, in the same segment, iff at_x + 2 h_x == at_y.  One compare per side and place
@@ -408,16 +208,18 @@ struct SplitLds {
 // cycles), so the halves are searched apart, all tiles side by side: 64-bit minima went through the
 // tiles one after the other, compare, select, compare (the splitting kernel alone on LoRA streams, five
 // tiles: 2048x20000 9.57 -> 8.84 ms, 4096x50000 35.6 -> 31.9 ms).
-template <u32 TILES>
-struct SplitRegs {
+template <u32 TILES, bool TAIL>
+struct SplitPool {
     u32 at[TILES], h[TILES];
-    u32 n, cap, res, parity;
+    u64 *fl;                    // the tail: h << 32 | at
+    u32 n, n_tail, cap, res, parity;        // n: blocks, those in the tail among them
     u32 hw;                     // the most blocks held at once (cuts and merges are counted off the decisions)
-    DI void init(char *, const KParams &P)
+    DI void init(char *lds, const KParams &P)
     {
 #pragma unroll
         for (u32 t = 0; t < TILES; t++) at[t] = h[t] = 0;
-        n = hw = 0;
+        fl = (u64 *)(lds + P.off_fl);
+        n = n_tail = hw = 0;
         cap = P.cap_free;
         res = 0;
         parity = 1;
@@ -435,7 +237,7 @@ struct SplitRegs {
             h[q] = here ? size : h[q];
         }
     }
-    DI void insert(u32 to, u32 size)            // into an empty place (n < cap <= 64 * TILES: there is one)
+    DI void place(u32 to, u32 size)             // into an empty place of the registers (there is one)
     {
         bool any = false;
 #pragma unroll
@@ -448,8 +250,78 @@ struct SplitRegs {
             h[q] = here ? size : h[q];
             todo = todo && !here;
         }
+    }
+    DI void insert(u32 to, u32 size)            // (n < cap)
+    {
+        if (!TAIL || LIKELY(n - n_tail < 64 * TILES)) place(to, size);
+        else {
+            st_one(fl, n_tail++, ((u64)size << 32) | to);
+            wave_sync();
+        }
         n++;
         hw = max(hw, n);
+    }
+    // block i of the tail leaves, the last one takes its place; where block `other` is now
+    DI u32 tail_remove(u32 i, u32 other)
+    {
+        st_one(fl, i, ld_uni(fl, --n_tail));
+        wave_sync();
+        n--;
+        return other == n_tail ? i : other;
+    }
+    // The tail's part of a request: a block there that fits better than the best in the registers (which
+    // leaves `rest`) changes places with the one in this wavefront's first place, and the search is repeated
+    DI bool fetch_from_tail(u32 size, u32 rest, const u32 (&d)[TILES])
+    {
+        u32 bd = NONE32, ba = NONE32, bi = 0;
+        for (u32 base = 0; base < n_tail; base += 64) {
+            const u32 i = base + lane_id();
+            const u64 k = fl[i < n_tail ? i : 0u];
+            const u32 x = i < n_tail ? (u32)(k >> 32) - size : NONE32;
+            const bool better = x < bd || (x == bd && (u32)k < ba);
+            bd = better ? x : bd;
+            ba = better ? (u32)k : ba;
+            bi = better ? i : bi;
+        }
+        const u32 left = wave_min_u32(bd);
+        if ((int)left < 0 || left > rest) return false;
+        const u32 ref = wave_min_u32(bd == left ? ba : NONE32);
+        u32 c = NONE32;
+#pragma unroll
+        for (u32 t = 0; t < TILES; t++) c = min(c, d[t] == left ? at[t] : NONE32);
+        if (left == rest && wave_min_u32(c) < ref) return false;        // of equal sizes the lowest address goes
+        const u32 idx = from_lane(bi, first_lane(ballot(bd == left && ba == ref)));
+        const u64 out = ((u64)from_lane(h[0], 0) << 32) | from_lane(at[0], 0);
+        h[0] = write_lane(h[0], left + size, 0);
+        at[0] = write_lane(at[0], ref, 0);
+        if (out) st_one(fl, idx, out);
+        else st_one(fl, idx, ld_uni(fl, --n_tail));             // that place was empty
+        wave_sync();
+        return true;
+    }
+    // The tail's part of a release: neighbours that are there leave it and are taken into the block
+    DI void absorb_from_tail(u32 &ref, u32 &size, bool &ml, bool &mr)
+    {
+        u32 li = NONE32, ri = NONE32;
+        for (u32 base = 0; base < n_tail; base += 64) {
+            const u32 i = base + lane_id();
+            const u64 k = fl[i < n_tail ? i : 0u];
+            const u64 mL = ballot(i < n_tail && (u32)k + 2 * (u32)(k >> 32) == ref), mR = ballot(i < n_tail && (u32)k == ref + 2 * size);
+            if (mL) li = base + first_lane(mL);
+            if (mR) ri = base + first_lane(mR);
+        }
+        ml = li != NONE32;
+        mr = ri != NONE32;
+        if (mr) {
+            size += (u32)(ld_uni(fl, ri) >> 32);
+            li = tail_remove(ri, li);
+        }
+        if (ml) {
+            const u64 k = ld_uni(fl, li);
+            ref = (u32)k;
+            size += (u32)(k >> 32);
+            tail_remove(li, 0u);
+        }
     }
     // Every outcome ends in a call of its own: done(code, ref, split) once the request is decided
     // (code C_OOM: it failed) or ovf() if the table is full.  Results handed back through one return
@@ -459,13 +331,16 @@ struct SplitRegs {
     {
         // step 1: best fit = smallest size not below the request.  Sizes have 31 bits, so what a block
         // has beyond the request has bit 31 set exactly if the block is too small (or the place empty)
-        u32 d[TILES], mine = NONE32;
+        u32 d[TILES], mine, rest;
+        do {
+            mine = NONE32;
 #pragma unroll
-        for (u32 t = 0; t < TILES; t++) {
-            d[t] = h[t] - size;
-            mine = min(mine, d[t]);
-        }
-        const u32 rest = wave_min_u32(mine);
+            for (u32 t = 0; t < TILES; t++) {
+                d[t] = h[t] - size;
+                mine = min(mine, d[t]);
+            }
+            rest = wave_min_u32(mine);
+        } while (TAIL && UNLIKELY(n_tail != 0) && fetch_from_tail(size, rest, d));
         if (LIKELY((int)rest >= 0)) {
             u32 c = NONE32;                     // lowest address of that size in this lane
 #pragma unroll
@@ -507,6 +382,8 @@ struct SplitRegs {
     template <class AcctT, class Done, class Ovf>
     DI void release(u32 ref, u32 size, AcctT &A, u32 ev, Done done, Ovf ovf)
     {
+        bool tl = false, tr = false;
+        if (TAIL && UNLIKELY(n_tail != 0)) absorb_from_tail(ref, size, tl, tr);
         // at most one block ends where this one starts and at most one starts where it ends
         const u32 end = ref + 2 * size;
         bool l[TILES], r[TILES], any_l = false, any_r = false;
@@ -550,7 +427,7 @@ struct SplitRegs {
             }
             insert(ref, size);
         }
-        done(ml, mr);
+        done(ml || tl, mr || tr);
     }
 };
 
@@ -1334,42 +1211,6 @@ DI bool vms_alloc_cold(char *lds, VmsT &V, const KParams &P, u32 bsize, u32 rese
     return ld_uni(sc, (u32)SC_STOP) == 0;
 }
 
-// Requests below one chunk under the stitching policy: its private splitting pool (Sec. 3.1), whose
-// two scalars (blocks in the list, units reserved) wait in LDS between requests.
-DI void small_alloc(char *lds, const KParams &P, u32 *idle, u32 size, u32 seg, bool may_grow, u32 ev, SplitRes &r,
-                    u32 &sp_reserved)
-{
-    u32 *sc = (u32 *)(lds + LDS_SCALARS);
-    SplitPoolD sp;
-    sp.fl = (u64 *)(lds + P.off_fl);
-    sp.cap = P.cap_free;
-    sp.n = ld_uni(sc, (u32)SC_SP_N);
-    sp.reserved = sp_reserved;
-    AcctLds A;
-    A.sc = sc;
-    A.idle = idle;
-    sp_alloc(sp, size, seg, may_grow, A, ev, r);
-    st_one(sc, (u32)SC_SP_N, sp.n);
-    sp_reserved = sp.reserved;
-    wave_sync();
-}
-
-DI void small_free(char *lds, const KParams &P, u32 *idle, u32 addr, u32 size, u32 flags, u32 ev, bool *ml, bool *mr)
-{
-    u32 *sc = (u32 *)(lds + LDS_SCALARS);
-    SplitPoolD sp;
-    sp.fl = (u64 *)(lds + P.off_fl);
-    sp.cap = P.cap_free;
-    sp.n = ld_uni(sc, (u32)SC_SP_N);
-    sp.reserved = 0;            // not used by a release
-    AcctLds A;
-    A.sc = sc;
-    A.idle = idle;
-    sp_free(sp, addr, size, flags, ml, mr, A, ev);
-    st_one(sc, (u32)SC_SP_N, sp.n);
-    wave_sync();
-}
-
 // The per-tile work shared by the replay kernels: one event per lane.  An event parks what it changed
 // (decision word, change of requested and active units) in its lane; the running totals, their peaks
 // and the split and merge counts are taken from the 64 lanes once per tile.  Kept per event they cost
@@ -1502,9 +1343,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
     V.tmp[(P.cap_chunks + 31) / 32 + lane] = 0;             // 64 spare words: where idle lanes OR their zeros
     // the searches read up to 64 places past the live part of pool[], skey[], swit[] and arena[]
     // without clamping: zero keys there, and witnesses / entries on words that exist
-    if (!P.small_regs)
-        for (u32 i = lane; i < P.cap_free + 128; i += 64) ((u64 *)(lds + P.off_fl))[i] = 0;
-    SplitRegs<3> Q;                                         // the pool for small requests, if it fits registers
+    SplitPool<SMALL_TILES, true> Q;                               // the pool for small requests
     Q.init(lds, P);
     for (u32 i = lane; i < P.cap_pblocks + 64; i += 64) V.pool[i] = 0;
     for (u32 i = lane; i < P.cap_sblocks + 64; i += 64) {
@@ -1574,34 +1413,22 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                     bmp_fill(V.bmp, ENT_WORD(V.e_skip), a, b >> 2, false);
                     EMIT((u32)C_FREE, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
                 }
-                if (LIKELY(P.small_regs)) {
-                    AcctLds A;
-                    A.sc = (u32 *)(lds + LDS_SCALARS);
-                    A.idle = V.idle;
-                    Q.release(a, req, A, base + j,
-                              [&](bool ml, bool mr) {
-                                  write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                              Q.addr(a), 0u - req, 0u - req, j);
-                                  wave_sync();
-                              },
-                              [&]() {
-                                  lost = req;
-                                  stop = true;
-                                  done = j;
-                                  todo = 0;
-                              });
-                    continue;
-                }
-                bool ml, mr;
-                small_free(lds, P, V.idle, a >> 2, req, a & 3, base + j, &ml, &mr);
-                if (UNLIKELY(ld_uni((u32 *)(lds + LDS_SCALARS), (u32)SC_STOP) != 0)) {
-                    lost = req;
-                    stop = true;
-                    done = j;
-                    todo = 0;
-                    continue;
-                }
-                EMIT(C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), a >> 2, 0u - req, 0u - req)
+                AcctLds A;
+                A.sc = (u32 *)(lds + LDS_SCALARS);
+                A.idle = V.idle;
+                Q.release(a, req, A, base + j,
+                          [&](bool ml, bool mr) {
+                              write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
+                                          Q.addr(a), 0u - req, 0u - req, j);
+                              wave_sync();
+                          },
+                          [&]() {
+                              lost = req;
+                              stop = true;
+                              done = j;
+                              todo = 0;
+                          });
+                continue;
             }
             // ---- ALLOC
             const u32 size = w;
@@ -1713,55 +1540,37 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
             } else {
                 const u32 seg = ((size + chunk_units - 1) >> P.chunk_shift) << P.chunk_shift;
                 const u32 reserved = sp_reserved + (V.n_chunks << P.chunk_shift);
-                if (LIKELY(P.small_regs)) {
-                    AcctLds A;
-                    A.sc = (u32 *)(lds + LDS_SCALARS);
-                    A.idle = V.idle;
-                    Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
-                            [&](u32 code, u32 ref, bool split) {
-                                sp_reserved = Q.reserved();
-                                u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
-                                if (code == C_OOM) {
-                                    S.set_req(slot, (u32)SLOT_OOM);
-                                    ColdState C;            // rare: note the first failed request
-                                    C.load(lds);
-                                    if (C.get(SC_FIRST_OOM) == NONE32)
-                                        st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                                } else {
-                                    S.set_a(slot, ref);
-                                    S.set_b(slot, (u32)KIND_SMALL);
-                                    S.set_req(slot, size);
-                                    if (code == C_GROW) RESERVED_NOW();
-                                    d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
-                                    d_hi = Q.addr(ref);
-                                    d_req = size;
-                                }
-                                write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
-                                wave_sync();
-                            },
-                            [&]() {
-                                stop = true;
-                                done = j;
-                                todo = 0;
-                            });
-                    continue;
-                }
-                SplitRes r;
-                small_alloc(lds, P, V.idle, size, seg, reserved + seg <= P.capacity_units, base + j, r, sp_reserved);
-                if (UNLIKELY(ld_uni((u32 *)(lds + LDS_SCALARS), (u32)SC_STOP) != 0)) {
-                    stop = true;
-                    done = j;
-                    todo = 0;
-                    continue;
-                }
-                dlo = C_OOM;
-                if (r.code != C_OOM) {
-                    const u32 af = (r.addr << 2) | r.flags;
-                    S.set_a(slot, af);
-                    S.set_b(slot, (u32)KIND_SMALL);
-                    dlo = r.code | B_SMALL | (r.split ? B_6 : 0u) | ((r.code == C_GROW ? 0u : 1u) << 8);
-                    dhi = r.addr;
-                }
+                AcctLds A;
+                A.sc = (u32 *)(lds + LDS_SCALARS);
+                A.idle = V.idle;
+                Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
+                        [&](u32 code, u32 ref, bool split) {
+                            sp_reserved = Q.reserved();
+                            u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
+                            if (code == C_OOM) {
+                                S.set_req(slot, (u32)SLOT_OOM);
+                                ColdState C;            // rare: note the first failed request
+                                C.load(lds);
+                                if (C.get(SC_FIRST_OOM) == NONE32)
+                                    st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
+                            } else {
+                                S.set_a(slot, ref);
+                                S.set_b(slot, (u32)KIND_SMALL);
+                                S.set_req(slot, size);
+                                if (code == C_GROW) RESERVED_NOW();
+                                d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
+                                d_hi = Q.addr(ref);
+                                d_req = size;
+                            }
+                            write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
+                            wave_sync();
+                        },
+                        [&]() {
+                            stop = true;
+                            done = j;
+                            todo = 0;
+                        });
+                continue;
             }
             if (UNLIKELY((dlo & 15) == C_OOM)) {
                 S.set_req(slot, (u32)SLOT_OOM);
@@ -1810,7 +1619,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
         s.status = sc[SC_STATUS] | (n_code[7] ? VMS_ST_INVALID_EVENT : 0u);
         s.max_pblocks = sc[SC_HW_PBLOCKS];
         s.max_sblocks = sc[SC_HW_SBLOCKS];
-        s.max_free_blocks = max(sc[SC_HW_FREE], Q.most());
+        s.max_free_blocks = Q.most();
         s.max_members = sc[SC_HW_MEMBERS];
         s.max_runs = sc[SC_HW_RUNS];
         s.overflow_event = sc[SC_OVF_EVENT];
@@ -1825,7 +1634,7 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
 // Replay under the splitting policy (Sec. 2.2), one wavefront per trace.  Both of its paths are
 // hot, so everything is inline and its few scalars stay in registers.
 // ---------------------------------------------------------------------------
-template <bool SLOT_REGS, u32 FL_TILES>
+template <bool SLOT_REGS, u32 TILES, bool TAIL>
 __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *__restrict__ events,
                                                           const u32 *__restrict__ n_events, u64 *__restrict__ decisions,
                                                           vms_trace_stats *__restrict__ stats)
@@ -1841,8 +1650,7 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
 
     SlotsT<SLOT_REGS> S;
     S.init(lds, P);
-    // FL_TILES: the inactive blocks live in registers (pools of at most 64 * FL_TILES blocks), else in LDS
-    typename std::conditional<FL_TILES == 0, SplitLds, SplitRegs<(FL_TILES ? FL_TILES : 1u)>>::type sp;
+    SplitPool<TILES, TAIL> sp;
     sp.init(lds, P);
 
     AcctRegs A;
@@ -1955,7 +1763,7 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
         s.status = A.f[SC_STATUS] | (n_code[7] ? VMS_ST_INVALID_EVENT : 0u);
         s.max_pblocks = 0;
         s.max_sblocks = 0;
-        s.max_free_blocks = max(A.f[SC_HW_FREE], sp.most());
+        s.max_free_blocks = sp.most();
         s.max_members = 0;
         s.max_runs = 0;
         s.overflow_event = A.f[SC_OVF_EVENT];

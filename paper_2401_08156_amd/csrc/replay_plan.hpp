@@ -8,6 +8,9 @@
 
 #include "../../include/vms_replay.h"
 
+// places per lane of the stitching policy's pool for requests below one chunk (see SplitPool)
+const uint32_t SMALL_TILES = 3;
+
 // Launch-constant parameters (passed by value as a kernel argument).
 struct KParams {
     uint32_t n_traces, max_events;
@@ -22,7 +25,7 @@ struct KParams {
     uint32_t off_slot_req, off_slot_a, off_slot_b, off_slot_c, off_fl, off_pool, off_bmp, off_skey, off_smeta,
         off_sstamp, off_swit, off_tmp, off_arena;
     uint32_t lds_bytes;
-    uint32_t small_regs;             // stitching kernel: its pool for small requests is held in registers (cap_free <= 192)
+    uint32_t reserved_pad0;
     uint64_t ws_stride;              // workspace bytes per trace
     // fine-grained variant only (see replay_fine.hpp)
     uint32_t off_bnd, off_soff;      // block-start bitmap; list places of the sBlocks
@@ -44,8 +47,8 @@ struct ReplayPlan {
     bool wide;                       // fine-grained variant with 32-bit chunk numbers (more than 65,000 chunks)
     int tbl_ws;                      // fine-grained variant: 0 the sBlock tables in LDS; 2 witnesses and list places in the workspace; 3 sizes too
     bool slot_regs;                  // slot table in registers (at most 64 slots)
-    bool fl_regs;                    // splitting policy: inactive blocks in registers (at most 320)
-    uint32_t fl_tiles;               // ... in that many registers per lane: 3 (at most 192 blocks) or 5; 0: in LDS
+    uint32_t fl_tiles;               // splitting policy: places for inactive blocks in registers, per lane: 3 or 5 (see SplitPool)
+    bool fl_tail;                    // ... and the rest of them in LDS
     size_t ws_bytes;
     bool has_retry;                  // a second pass with the plan below follows the first
 };
@@ -56,6 +59,14 @@ const uint64_t UNIT = 512;
 const uint64_t ENGINE_MAX_BYTES = 1ull << 39;       // 30-bit block addresses in 512-byte units
 const uint64_t LDS_PER_CU = 160 * 1024;
 const uint32_t TABLE_MAX = 1u << 24;                // upper bound of every per-trace table size
+
+// what a pool whose blocks are not all in registers would take with all of them in LDS, beyond what it takes
+// there: counted against the compute unit's LDS, so that no table size is refused or accepted for where it lives
+inline uint64_t pool_bytes_saved(const KParams &k, int policy, const ReplayPlan &p)
+{
+    const uint32_t in_regs = 64 * (policy ? SMALL_TILES : p.fl_tiles);
+    return k.cap_free <= in_regs ? 0 : (128ull + in_regs) * 8;
+}
 
 inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 inline bool is_pow2(uint64_t x) { return x && !(x & (x - 1)); }
@@ -80,9 +91,9 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
         k.off_slot_b = policy ? take((uint64_t)c.max_slots * 4) : 0;
         k.off_slot_c = policy && p.fine ? take((uint64_t)c.max_slots * 2) : 0;   // 16-bit list places
     }
-    // the splitting policy keeps small pools in registers: no LDS array then
-    // (up to 320 blocks; the stitching policy's pool for small requests: up to 192)
-    k.off_fl = k.cap_free <= (policy ? 192u : 320u) ? 0 : take(((uint64_t)k.cap_free + 128) * 8);   // 128 spare places: scans read whole tiles
+    // inactive blocks of a splitting pool beyond those held in registers
+    const uint32_t in_regs = 64 * (policy ? SMALL_TILES : p.fl_tiles);
+    k.off_fl = k.cap_free <= in_regs ? 0 : take(((uint64_t)k.cap_free - in_regs) * 8);
     if (policy && p.fine) {
         const uint64_t idx = p.wide ? 4 : 2;                    // bytes of a chunk number
         k.off_pool = take(((uint64_t)k.cap_pblocks + 80) * 2 * idx);      // 64 spare places, and moves of whole 16-byte blocks
@@ -148,8 +159,8 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
     p.tbl_ws = p.fine && !p.wide && c.table_place >= VMS_TABLES_WORKSPACE ? (int)c.table_place : 0;
     if (c.table_place >= VMS_TABLES_WORKSPACE && p.fine && p.wide) return VMS_EINVAL;
     p.slot_regs = c.max_slots <= 64;
-    p.fl_tiles = c.max_free_blocks <= 192 ? 3u : c.max_free_blocks <= 320 ? 5u : 0u;
-    p.fl_regs = p.fl_tiles != 0;
+    p.fl_tiles = c.max_free_blocks <= 192 ? 3u : 5u;
+    p.fl_tail = c.max_free_blocks > 320;
     uint32_t shift = 0;
     while ((UNIT << shift) < c.chunk_bytes) shift++;
     const uint64_t cap = c.capacity_bytes ? (c.capacity_bytes < ENGINE_MAX_BYTES ? c.capacity_bytes : ENGINE_MAX_BYTES)
@@ -166,7 +177,6 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
         k.max_slots = c.max_slots;
         // the stitching policy's pool for small requests may be given a size of its own
         k.cap_free = pol && c.max_small_blocks ? c.max_small_blocks : c.max_free_blocks;
-        k.small_regs = pol && k.cap_free <= 192;
         k.cap_pblocks = c.max_pblocks;
         k.cap_sblocks = c.max_sblocks;
         k.cap_runs = c.max_runs;
@@ -194,7 +204,7 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
         } else if (pol) {
             k.ws_stride = align_up(((uint64_t)c.max_runs + 64) * 4, 256);     // where compaction copies the lists
         }
-        const uint64_t need = layout(k, pol, c, p);
+        const uint64_t need = layout(k, pol, c, p) + plan_detail::pool_bytes_saved(k, pol, p);
         if ((c.policy_mask & (1u << pol)) && need > LDS_PER_CU) return VMS_ETOOBIG;
     }
     p.ws_bytes = (c.policy_mask & VMS_POLICY_VMS) ? (size_t)p.kp[1].ws_stride * c.n_traces : 0;

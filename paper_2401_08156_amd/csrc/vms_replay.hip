@@ -135,12 +135,13 @@ vms_fn pick_vms(const ReplayPlan &p)
     }
     return p.slot_regs ? replay_vms_kernel<true> : replay_vms_kernel<false>;
 }
-// fl_tiles: the splitting pool's inactive blocks fit three or five registers per lane (at most 192 / 320 blocks)
-split_fn pick_split(bool slot_regs, uint32_t fl_tiles)
+// the splitting pool's inactive blocks: three or five register pairs per lane (tables of at most 192 or 320
+// blocks), or five and the rest in LDS
+split_fn pick_split(const ReplayPlan &p)
 {
-    if (fl_tiles == 3) return slot_regs ? replay_split_kernel<true, 3> : replay_split_kernel<false, 3>;
-    if (fl_tiles == 5) return slot_regs ? replay_split_kernel<true, 5> : replay_split_kernel<false, 5>;
-    return slot_regs ? replay_split_kernel<true, 0> : replay_split_kernel<false, 0>;
+    if (p.fl_tiles == 3) return p.slot_regs ? replay_split_kernel<true, 3, false> : replay_split_kernel<false, 3, false>;
+    if (!p.fl_tail) return p.slot_regs ? replay_split_kernel<true, 5, false> : replay_split_kernel<false, 5, false>;
+    return p.slot_regs ? replay_split_kernel<true, 5, true> : replay_split_kernel<false, 5, true>;
 }
 
 }  // namespace
@@ -204,13 +205,13 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     // LDS above 64 KB per workgroup has to be requested explicitly
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)pick_split(h->plan.slot_regs, h->plan.fl_tiles), hipFuncAttributeMaxDynamicSharedMemorySize,
+        e = hipFuncSetAttribute((const void *)pick_split(h->plan), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)LDS_PER_CU);
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)pick_vms(h->plan), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)LDS_PER_CU);
     if (e == hipSuccess && h->retry.has_retry)
-        e = hipFuncSetAttribute((const void *)pick_split(h->retry.slot_regs, h->retry.fl_tiles),
+        e = hipFuncSetAttribute((const void *)pick_split(h->retry),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
     if (e == hipSuccess && h->retry.has_retry)
         e = hipFuncSetAttribute((const void *)pick_vms(h->retry), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -264,13 +265,13 @@ int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_
     }
     HIP_TRY(h, hipEventRecord(h->ev[2], sst));
     if (c.policy_mask & VMS_POLICY_SPLIT) {
-        hipLaunchKernelGGL(pick_split(h->plan.slot_regs, h->plan.fl_tiles), dim3(c.n_traces), dim3(64), h->plan.kp[0].lds_bytes, sst, h->plan.kp[0],
+        hipLaunchKernelGGL(pick_split(h->plan), dim3(c.n_traces), dim3(64), h->plan.kp[0].lds_bytes, sst, h->plan.kp[0],
                            d_events, d_n_events, d_dec_split, h->d_stats);
         HIP_TRY(h, hipGetLastError());
     }
     HIP_TRY(h, hipEventRecord(h->ev[3], sst));
     if ((c.policy_mask & VMS_POLICY_SPLIT) && h->retry.has_retry) {
-        hipLaunchKernelGGL(pick_split(h->retry.slot_regs, h->retry.fl_tiles), dim3(second_pass_waves(c)), dim3(64),
+        hipLaunchKernelGGL(pick_split(h->retry), dim3(second_pass_waves(c)), dim3(64),
                            h->retry.kp[0].lds_bytes, sst, h->retry.kp[0], d_events, d_n_events, d_dec_split, h->d_stats);
         HIP_TRY(h, hipGetLastError());
     }

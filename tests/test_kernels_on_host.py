@@ -94,6 +94,36 @@ def test_segments_that_touch_do_not_merge(cap):
     assert st["n_merge"][0, 0] > 20 and st["peak_reserved"][0, 0] > 256 << 30
 
 
+# pools of more blocks than the registers hold (192 or 320): the rest is in LDS.  Rounds that fill the pool (every
+# other one of a row of blocks is freed), churn and drain it, with few sizes (equal ones in the registers and in LDS
+# at once) and with many
+@pytest.mark.parametrize("pol,row,sizes", [(0, 900, 4), (0, 900, 600), (1, 600, 4), (1, 600, 600)])
+def test_splitting_pool_beyond_the_registers(pol, row, sizes):
+    rng, ops, live, slots = np.random.default_rng(row + sizes), [], [], list(range(2000))
+    def alloc():
+        live.append(slots.pop(0))
+        ops.append(("A", live[-1], int(rng.integers(1, sizes + 1)) * 512))
+    def free(i):
+        slots.append(live.pop(i))
+        ops.append(("F", slots[-1]))
+    for _ in range(2):
+        for _ in range(row):
+            alloc()
+        for s in rng.permutation(live[::2]):
+            free(live.index(s))
+        for _ in range(500):
+            if rng.random() < 0.5:
+                alloc()
+            else:
+                free(int(rng.integers(len(live))))
+        while len(live) > 40:
+            free(int(rng.integers(len(live))))
+    ev = tg.make_events(ops)[None, :]
+    cfg = gpu_util.make_cfg(1, ev.shape[1], 2000, policy_mask=1 << pol, variant=binding.VMS_VARIANT_FINE if pol else 0, max_free_blocks=1024)
+    st = check(ev, cfg, label="a pool beyond the registers")
+    assert st["max_free_blocks"][pol, 0] > (192 if pol else 320) + 30
+
+
 # pools in three and five registers per lane and in LDS; the stitching policy's pool in registers and in LDS
 @pytest.mark.parametrize("pol,blocks,small", [(0, 64, 0), (0, 190, 0), (0, 250, 0), (0, 400, 0), (1, 64, 64), (1, 190, 190), (1, 250, 0)])
 def test_free_that_outgrows_the_splitting_pool(pol, blocks, small):
