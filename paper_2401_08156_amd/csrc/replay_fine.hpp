@@ -377,26 +377,27 @@ DI u32 list_put_run(const FineT<IDX, TH> &V, u32 place, u32 start, u32 len)
 }
 
 // Squeeze the lists of released sBlocks out: copy the live lists, in table order, to the other
-// half of the slice, which becomes the arena.  Slots that hold an sBlock learn its new place.
-template <class IDX, int TH, class Slots>
-DI void fine_compact(FineT<IDX, TH> &V, Slots &S)
+// half of the slice, which becomes the arena.  The first word at each old place then says where its list
+// is now: the slots that hold an sBlock look there (relist()) before anything else happens.
+template <class IDX, int TH>
+DI void fine_compact(FineT<IDX, TH> &V)
 {
     u32 top = 0;
     V.tables_written();
     for (u32 s = 0; s < V.ns; s++) {
         const u32 from = TH ? uni(V.off_at(s)) : ld_uni(V.soff, s);
-        const u64 *src = V.list_at(from);
+        u64 *src = V.list_at(from);
         const u32 cnt = (u32)(uni64(ld_list(src)) >> 32), words = cnt + 2;
         u64 *dst = V.bounce + ((size_t)top << V.gs);
         for (u32 rb = 0; rb < words; rb += 64) {                // lanes past the end copy the last word again
             const u32 r = min(rb + lane_id(), words - 1);
             dst[r] = ld_list(src + r);
         }
+        wave_lockstep();
+        st_one(src, 0u, (u64)top);
         st_one(V.soff, s, (u16)top);
-        S.relocate(from, top);
         top += V.grans(cnt);
     }
-    S.relocate_done();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");      // later reads are of other lanes' global writes
     wave_sync();
     u64 *t = V.arena;
@@ -405,10 +406,10 @@ DI void fine_compact(FineT<IDX, TH> &V, Slots &S)
     V.top = V.live = top;
 }
 
-template <class IDX, int TH, class Slots, class AcctT>
-DI bool fine_reserve(FineT<IDX, TH> &V, Slots &S, u32 need_grans, AcctT &A, u32 ev)
+template <class IDX, int TH, class AcctT>
+DI bool fine_reserve(FineT<IDX, TH> &V, u32 need_grans, AcctT &A, u32 ev)
 {
-    if (UNLIKELY(V.top + need_grans > V.cap_grans && V.live < V.top)) fine_compact(V, S);
+    if (UNLIKELY(V.top + need_grans > V.cap_grans && V.live < V.top)) fine_compact(V);
     if (UNLIKELY(V.top + need_grans > V.cap_grans)) {
         A.overflow(ev, VMS_ST_OVF_RUNS);
         return false;
@@ -686,8 +687,8 @@ DI void fine_free_sblock(const FineT<IDX, TH> &V, u32 place)
 
 // No block of exactly bsize chunks is free: BestFit's second loop and the post-processing of its
 // state (Algorithm 1; Sec. 4.1, Fig. 9, states S2 to S5).
-template <class IDX, int TH, class Slots, class AcctT>
-DI void fine_alloc_rest(FineT<IDX, TH> &V, Slots &S, u32 bsize, u32 lo_p, u32 hi_p, u32 reserved_units, const KParams &P,
+template <class IDX, int TH, class AcctT>
+DI void fine_alloc_rest(FineT<IDX, TH> &V, u32 bsize, u32 lo_p, u32 hi_p, u32 reserved_units, const KParams &P,
                         AcctT &A, u32 ev, VmsRes &R)
 {
     typedef typename FineT<IDX, TH>::pkey_t pkey_t;
@@ -720,7 +721,7 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, Slots &S, u32 bsize, u32 lo_p, u32 hi
                 return;
             }
             const u32 gr = V.grans(run_words(pstart, psize));
-            if (UNLIKELY(V.np + 1 > P.cap_pblocks || V.ns + 1 > P.cap_sblocks || !fine_reserve(V, S, gr, A, ev))) {
+            if (UNLIKELY(V.np + 1 > P.cap_pblocks || V.ns + 1 > P.cap_sblocks || !fine_reserve(V, gr, A, ev))) {
                 A.overflow(ev, (V.np + 1 > P.cap_pblocks ? VMS_ST_OVF_PBLOCKS : 0u) | (V.ns + 1 > P.cap_sblocks ? VMS_ST_OVF_SBLOCKS : 0u));
                 R.dec_lo = C_INVALID;
                 return;
@@ -923,7 +924,7 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, Slots &S, u32 bsize, u32 lo_p, u32 hi
         R.dec_lo = C_INVALID;
         return;
     }
-    if (UNLIKELY(!fine_reserve(V, S, V.grans((n_after + 31) >> 5) + q_gr, A, ev))) {
+    if (UNLIKELY(!fine_reserve(V, V.grans((n_after + 31) >> 5) + q_gr, A, ev))) {
         R.dec_lo = C_INVALID;
         return;
     }
@@ -1039,8 +1040,8 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, Slots &S, u32 bsize, u32 lo_p, u32 hi
 }
 
 // The rare path of the replay loop (see vms_alloc_cold): its scalars wait in the LDS header.
-template <class IDX, int TH, class Slots>
-DI bool fine_alloc_cold(char *lds, FineT<IDX, TH> &V, Slots &S, const KParams &P, u32 bsize, u32 lo_p, u32 hi_p,
+template <class IDX, int TH>
+DI bool fine_alloc_cold(char *lds, FineT<IDX, TH> &V, const KParams &P, u32 bsize, u32 lo_p, u32 hi_p,
                         u32 reserved_units, u32 ev, VmsRes &R)
 {
     u32 *sc = (u32 *)(lds + LDS_SCALARS);
@@ -1053,7 +1054,7 @@ DI bool fine_alloc_cold(char *lds, FineT<IDX, TH> &V, Slots &S, const KParams &P
     AcctLds A;
     A.sc = sc;
     A.idle = V.idle;
-    fine_alloc_rest(V, S, bsize, lo_p, hi_p, reserved_units, P, A, ev, R);
+    fine_alloc_rest(V, bsize, lo_p, hi_p, reserved_units, P, A, ev, R);
     st_one(sc, (u32)SC_TOP, V.top);
     st_one(sc, (u32)SC_LIVE, V.live);
     st_one(sc, (u32)SC_NEXT_SID, V.next_sid);
@@ -1088,7 +1089,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
         ws_slice = workspace + P.retry_ws_off + (size_t)blockIdx.x * P.ws_stride;
     }
 
-    SlotsT<SLOT_REGS> S;
+    SlotsT<SLOT_REGS, true, u16> S;
     S.init(lds, P);
     ((u32 *)(lds + LDS_SCALARS))[lane] = lane == SC_FIRST_OOM || lane == SC_OVF_EVENT ? NONE32 : 0u;     // LDS header
     FineT<IDX, TH> V;
@@ -1142,42 +1143,35 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
     u64 ev = pin64(lane < n_ev ? ev_row[lane] : 0), ev_next = ev;
     for (u32 base = 0; base < n_ev; base += 64) {
         const u32 tile = min(64u, n_ev - base);
-        const u32 ev_lo = (u32)ev, ev_hi = (u32)(ev >> 32);
+        u32 ev_lo = (u32)ev;
+        u32 ev_hi = (u32)(ev >> 32);
+        S.tile_begin(ev_lo, ev_hi, tile);
         if (base + 64 < n_ev) ev_next = ev_row[min(base + 64 + lane, n_ev - 1)];       // prefetch (see replay_split_kernel)
-        u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_act = 0, v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
+        u32 v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
         u32 done = tile, todo = tile;       // todo drops to 0 when an engine table overflows: the trace ends there
-        // every path of an event ends by parking its results in lane j and going on to the next event
-#define EMIT(DLO, DHI, DREQ, DACT)                                         \
-    {                                                                      \
-        write_lane4(v_dlo, v_dhi, v_req, v_act, (DLO), (DHI), (DREQ), (DACT), j); \
-        wave_sync();                                                       \
-        continue;                                                          \
-    }
+        // every path of an event ends by noting its results and going on to the next event
         // memory was reserved: the events from this one on see the new total
 #define RESERVED_NOW() v_res = lane >= j ? sp_reserved + (V.n_chunks << P.chunk_shift) : v_res
         for (u32 j = 0; j < todo; j++) {
-            const u32 w = from_lane(ev_lo, j), slot = from_lane(ev_hi, j);
-            if (UNLIKELY(slot >= P.max_slots)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
-            const u32 req = S.get_req(slot);
+            const u32 w = from_lane(ev_lo, j), at = S.at(ev_hi, j), req = S.get_req(at);
             if ((int)w < 0) {
                 // ---- FREE.  Update (Sec. 3.3.2): only activity flips; memory stays with its pBlocks
                 if (UNLIKELY(req + 1u <= 1u)) {             // unbound, or bound to a request that failed
-                    if (req == SLOT_OOM) {
-                        S.set_req(slot, (u32)SLOT_UNBOUND);
-                        EMIT((u32)C_FREE_NOOP, 0u, 0u, 0u)
-                    }
-                    EMIT((u32)C_INVALID, 0u, 0u, 0u)
+                    if (req == SLOT_OOM) S.failed(j, at, (u32)C_FREE_NOOP, SLOT_UNBOUND);
+                    else S.not_done(j, at);
+                    continue;
                 }
-                const u32 a = S.get_a(slot), b = S.get_b(slot);
-                const u32 kind = b & 3;
-                S.set_req(slot, (u32)SLOT_UNBOUND);
+                const u32 a = S.get_a(at), b = S.get_b(at);
+                const u32 kind = b & 3, held = (b >> 2) << P.chunk_shift;
                 if (LIKELY((kind & KIND_SBLOCK) != 0)) {
-                    fine_free_sblock(V, S.get_c(slot));
-                    EMIT(C_FREE | B_SBLOCK, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
+                    fine_free_sblock(V, S.get_c(at));
+                    S.free_done(j, at, C_FREE | B_SBLOCK, a, req, held);
+                    continue;
                 }
                 if (kind == KIND_PBLOCK) {
                     bmp_fill(V.bmp, V.w_spare, a, b >> 2, false);
-                    EMIT((u32)C_FREE, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
+                    S.free_done(j, at, (u32)C_FREE, a, req, held);
+                    continue;
                 }
                 // (each outcome parks its results and goes on from where it is found: handed back
                 // through a record they would meet in flags that are tested again)
@@ -1186,9 +1180,7 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                 A.idle = V.idle;
                 Q.release(a, req, A, base + j,
                           [&](bool ml, bool mr) {
-                              write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                          Q.addr(a), 0u - req, 0u - req, j);
-                              wave_sync();
+                              S.free_done(j, at, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), Q.addr(a), req, req);
                           },
                           [&]() {
                               lost = req;
@@ -1200,45 +1192,11 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
             }
             // ---- ALLOC
             const u32 size = w;
-            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
-            u32 dlo, dhi = 0, held_units = size;
-            if (LIKELY(size >= P.small_limit_units)) {
-                const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
-                u32 ref, place;
-                // S1: stitched blocks first, then primitive blocks (Algorithm 1, first loop)
-                if (fine_s1_sblock(V, bsize, ref, place)) {
-                    S.bind(slot, size, ref, KIND_SBLOCK | (bsize << 2), place);
-                    if (!SLOT_REGS) S.set_c(slot, place);
-                    EMIT(C_EXACT | B_SBLOCK | (1u << 8), ref, size, bsize << P.chunk_shift)
-                }
-                // pool[lo_p, hi_p): the multi-chunk pBlocks of exactly bsize chunks
-                u32 lo_p, hi_p;
-                rank_desc2_k(V.pool, V.np, V.key(bsize, 0), (pkey_t)(((pkey_t)bsize << V.W) - 1), &lo_p, &hi_p);
-                if (bsize > 1 ? fine_s1_pblock(V, lo_p, hi_p, ref) : s1_single(V, ref)) {
-                    bmp_fill(V.bmp, V.w_spare, ref, bsize, true);
-                    S.bind(slot, size, ref, KIND_PBLOCK | (bsize << 2), 0u);
-                    EMIT(C_EXACT | (1u << 8), ref, size, bsize << P.chunk_shift)
-                }
-                // ---- no exact fit: states S2 to S5
-                VmsRes R;
-                const bool went = fine_alloc_cold(lds, V, S, P, bsize, lo_p, hi_p, sp_reserved + (V.n_chunks << P.chunk_shift), base + j, R);
-                V.tables_written();
-                V.sp.template refresh<TH == 3>(V.ssz, V.ns);        // the sBlock table may have changed
-                if (UNLIKELY(!went)) {                      // an engine table overflowed: the trace ends here
-                    stop = true;
-                    done = j;
-                    todo = 0;
-                    continue;
-                }
-                dlo = R.dec_lo;
-                if (LIKELY((dlo & 15) != C_OOM)) {
-                    dhi = R.ref;
-                    S.set_a(slot, dhi);
-                    S.set_b(slot, R.kind | (R.held << 2));
-                    S.set_c(slot, R.list);
-                    held_units = R.held << P.chunk_shift;
-                }
-            } else {
+            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) {
+                S.not_done(j, at);
+                continue;
+            }
+            if (UNLIKELY(size < P.small_limit_units)) {
                 // ---- a request below one chunk: the policy's own splitting pool (Sec. 3.1)
                 const u32 seg = ((size + chunk_units - 1) >> P.chunk_shift) << P.chunk_shift;
                 const u32 reserved = sp_reserved + (V.n_chunks << P.chunk_shift);
@@ -1248,24 +1206,17 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                 Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
                         [&](u32 code, u32 ref, bool split) {
                             sp_reserved = Q.reserved();
-                            u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
-                            if (code == C_OOM) {
-                                S.set_req(slot, (u32)SLOT_OOM);
-                                ColdState C;            // rare: note the first failed request
+                            if (UNLIKELY(code == C_OOM)) {
+                                S.failed(j, at, (u32)C_OOM, SLOT_OOM);
+                                ColdState C;                // rare: note the first failed request
                                 C.load(lds);
                                 if (C.get(SC_FIRST_OOM) == NONE32)
                                     st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                            } else {
-                                S.set_a(slot, ref);
-                                S.set_b(slot, (u32)KIND_SMALL);
-                                S.set_req(slot, size);
-                                if (code == C_GROW) RESERVED_NOW();
-                                d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
-                                d_hi = Q.addr(ref);
-                                d_req = size;
+                                return;
                             }
-                            write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
-                            wave_sync();
+                            if (code == C_GROW) RESERVED_NOW();
+                            S.alloc_done(j, at, code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), Q.addr(ref),
+                                         size, size, ref, (u32)KIND_SMALL, 0u);
                         },
                         [&]() {
                             stop = true;
@@ -1274,21 +1225,49 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
                         });
                 continue;
             }
-            if (UNLIKELY((dlo & 15) == C_OOM)) {
-                S.set_req(slot, (u32)SLOT_OOM);
+            const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
+            u32 ref, place;
+            // S1: stitched blocks first, then primitive blocks (Algorithm 1, first loop)
+            if (fine_s1_sblock(V, bsize, ref, place)) {
+                S.alloc_done(j, at, C_EXACT | B_SBLOCK | (1u << 8), ref, size, bsize << P.chunk_shift, ref, KIND_SBLOCK | (bsize << 2), place);
+                continue;
+            }
+            // pool[lo_p, hi_p): the multi-chunk pBlocks of exactly bsize chunks
+            u32 lo_p, hi_p;
+            rank_desc2_k(V.pool, V.np, V.key(bsize, 0), (pkey_t)(((pkey_t)bsize << V.W) - 1), &lo_p, &hi_p);
+            if (bsize > 1 ? fine_s1_pblock(V, lo_p, hi_p, ref) : s1_single(V, ref)) {
+                bmp_fill(V.bmp, V.w_spare, ref, bsize, true);
+                S.alloc_done(j, at, C_EXACT | (1u << 8), ref, size, bsize << P.chunk_shift, ref, KIND_PBLOCK | (bsize << 2), 0u);
+                continue;
+            }
+            // ---- no exact fit: states S2 to S5
+            VmsRes R;
+            const u64 *const before = V.arena;
+            const bool went = fine_alloc_cold(lds, V, P, bsize, lo_p, hi_p, sp_reserved + (V.n_chunks << P.chunk_shift), base + j, R);
+            V.tables_written();
+            V.sp.template refresh<TH == 3>(V.ssz, V.ns);        // the sBlock table may have changed
+            if (UNLIKELY(V.arena != before))
+                S.relist([&](u32, u32, u32 place) { return (u32)ld_list(before + ((size_t)min(place, V.cap_grans - 1) << V.gs)); });
+            if (UNLIKELY(!went)) {                      // an engine table overflowed: the trace ends here
+                stop = true;
+                done = j;
+                todo = 0;
+                continue;
+            }
+            if (UNLIKELY((R.dec_lo & 15) == C_OOM)) {
+                S.failed(j, at, (u32)C_OOM, SLOT_OOM);
                 ColdState C;                                // rare: note the first failed request
                 C.load(lds);
                 if (C.get(SC_FIRST_OOM) == NONE32) st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                EMIT((u32)C_OOM, 0u, 0u, 0u)
+                continue;
             }
-            S.set_req(slot, size);
-            if ((dlo & 15) == C_GROW) RESERVED_NOW();
-            EMIT(dlo, dhi, size, held_units)
+            if ((R.dec_lo & 15) == C_GROW) RESERVED_NOW();
+            S.alloc_done(j, at, R.dec_lo, R.ref, size, R.held << P.chunk_shift, R.ref, R.kind | (R.held << 2), R.list);
         }
-#undef EMIT
 #undef RESERVED_NOW
         ev = pin64(ev_next);
-        tile_emit<false>(T, dec_row, base, done, v_dlo, v_dhi, v_req, v_act, v_res);
+        S.tile_end(done, P.chunk_shift, [&](u32 ref) { return Q.addr(ref); });
+        tile_emit<false>(T, dec_row, base, done, S.v_dlo, S.v_dhi, S.v_req, S.v_act, v_res);
         if (stop) break;
     }
 

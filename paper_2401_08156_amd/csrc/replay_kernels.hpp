@@ -81,101 +81,187 @@ struct AcctLds {
 // ---------------------------------------------------------------------------
 // Slot table: what each handle of the trace currently holds.
 //   req  request size in units; 0 = unbound; 0xFFFFFFFF = its ALLOC hit OOM
-//   a    splitting pools: address << 2 | segment flags; pBlock: first chunk; sBlock: creation number
+//   a    splitting pools: the block's `at` (see SplitPool); pBlock: first chunk; sBlock: creation number
 //   b    kind | chunks held << 2 (stitching policy only)
-//   c    sBlock: its chunk-run list in the arena, offset << 16 | entries (see VmsT)
-// IN_REGS: the table is four registers, slot s in lane s (traces with at most 64
-// slots): a lookup is a v_readlane, an update a compare-and-select, no LDS round trip.
+//   c    sBlock: where its list is (flat variant: offset << 16 | entries; fine-grained: its place)
+// An event asks at() where its slot's record is (readable with get_*() until the event ends) and ends in one
+// of free_done(), alloc_done(), failed() and not_done(), which also note what the decision word and the totals
+// of the event are made of; tile_end() hands these over once per 64 events.
+// With at most 64 slots (REGS) the table is four registers, slot s in lane s.  Else it is in LDS, and a
+// tile of events works on records in registers: lane j takes a copy of its event's record when the tile
+// begins, keeps what the event makes of it, and knows the last lane before it with the same slot (`prev`),
+// whose record is the current one then; the last event of each slot puts its record back when the tile ends.
+// So an event never waits for the table, and stores nothing; per event the look-ups cost three dependent
+// LDS round trips and up to seven stores before (alone: the splitting kernel on LoRA 2048x20000 7.25 -> 6.18 ms,
+// on one random trace 0.637 -> 0.529; the stitching kernel on ZeRO-3 1280x20000 13.4 -> 12.5, on LoRA
+// 4096x50000 62 -> 58).
 // ---------------------------------------------------------------------------
-template <bool IN_REGS>
-struct SlotsT;
-
-template <>
-struct SlotsT<true> {
-    u32 req, a, b, c;
-    DI void init(char *, const KParams &) { req = a = b = c = 0; }
-    DI u32 get_req(u32 s) const { return from_lane(req, s); }
-    DI u32 get_a(u32 s) const { return from_lane(a, s); }
-    DI u32 get_b(u32 s) const { return from_lane(b, s); }
-    DI u32 get_c(u32 s) const { return from_lane(c, s); }
-    DI void set_req(u32 s, u32 v) { req = write_lane(req, v, s); }
-    DI void set_a(u32 s, u32 v) { a = write_lane(a, v, s); }
-    DI void set_b(u32 s, u32 v) { b = write_lane(b, v, s); }
-    DI void set_c(u32 s, u32 v) { c = write_lane(c, v, s); }
-    DI void bind(u32 s, u32 vreq, u32 va, u32 vb, u32 vc) { write_lane4(req, a, b, c, vreq, va, vb, vc, s); }
-    // the arena was compacted: the list that was at `from` is now at `to`
-    // the lists of the sBlocks have moved: look each held sBlock up by its key (creation number a,
-    // b >> 2 chunks) in skey[0..ns) (descending) and take its new place from smeta[]
-    DI void relist(const u64 *skey, const u32 *smeta, u32 ns)
-    {
-        // every lane searches (13 halvings cover 4096 sBlocks), lanes without an sBlock for nothing:
-        // no lane is switched off, so the caller keeps its wave-uniform control flow
-        const bool holds = req + 1u > 1u && (b & 3) == KIND_SBLOCK;
-        const u64 key = ((u64)(b >> 2) << 32) | (u32)~a;
-        u32 lo = 0, hi = ns;                    // first index whose key is not greater than key
-#pragma unroll 1
-        for (u32 it = 0; it < 13; it++) {
-            const u32 mid = (lo + hi) >> 1;     // < ns while lo < hi; else a place that exists
-            const bool open = lo < hi, greater = skey[mid] > key;
-            lo = open && greater ? mid + 1 : lo;
-            hi = open && !greater ? mid : hi;
-        }
-        const u32 found = pin(smeta[lo]);
-        c = holds ? found : c;
-        wave_sync();
-    }
-    // fine-grained variant: c is the place of the held sBlock's list.  The list at `from` has moved
-    // to `to`; bit 31 marks a slot that has its new place already (places are reused as lists move)
-    DI void relocate(u32 from, u32 to)
-    {
-        const bool hit = req + 1u > 1u && (b & 3) == KIND_SBLOCK && c == from;
-        c = hit ? (to | 0x80000000u) : c;
-    }
-    DI void relocate_done() { c &= 0x7FFFFFFFu; }
-};
-
-template <>
-struct SlotsT<false> {
-    u32 *req, *a, *b;
-    uint16_t *c;                // fine-grained variant only: a list place (a 15-bit granule number) and the mark of relocate()
+template <bool REGS, bool VMS, class LIST>
+struct SlotsT {
+    u32 req, a, b, c;           // the table (REGS), or the records of the tile's events
+    u32 v_dlo, v_dhi, v_req, v_act;         // the events' decision words and what they added to the totals
+    u32 *t_req, *t_a, *t_b;     // the table in LDS
+    LIST *t_c;
+    u32 n_slots;
+    u32 prev, slot, old_req;    // per lane: see above; the slot; what req was when the tile began
     DI void init(char *lds, const KParams &P)
     {
-        req = (u32 *)(lds + P.off_slot_req);
-        a = (u32 *)(lds + P.off_slot_a);
-        b = (u32 *)(lds + P.off_slot_b);
-        c = (uint16_t *)(lds + P.off_slot_c);
+        req = a = b = c = 0;
         n_slots = P.max_slots;
-        for (u32 i = lane_id(); i < P.max_slots; i += 64) req[i] = SLOT_UNBOUND;
+        if constexpr (!REGS) {
+            t_req = (u32 *)(lds + P.off_slot_req);
+            t_a = (u32 *)(lds + P.off_slot_a);
+            t_b = (u32 *)(lds + P.off_slot_b);
+            t_c = (LIST *)(lds + P.off_slot_c);
+            for (u32 i = lane_id(); i < n_slots; i += 64) {
+                t_req[i] = SLOT_UNBOUND;
+                t_a[i] = 0;
+                if constexpr (VMS) {
+                    t_b[i] = 0;
+                    t_c[i] = 0;
+                }
+            }
+            wave_sync();
+        }
     }
-    DI u32 get_req(u32 s) const { return ld_uni(req, s); }
-    DI u32 get_a(u32 s) const { return ld_uni(a, s); }
-    DI u32 get_b(u32 s) const { return ld_uni(b, s); }
-    DI u32 get_c(u32 s) const { return ld_uni(c, s); }
-    DI void set_req(u32 s, u32 v) { st_one(req, s, v); }
-    DI void set_a(u32 s, u32 v) { st_one(a, s, v); }
-    DI void set_b(u32 s, u32 v) { st_one(b, s, v); }
-    DI void set_c(u32 s, u32 v) { st_one(c, s, (uint16_t)v); }
-    DI void bind(u32 s, u32 vreq, u32 va, u32 vb, u32)
+    // ev_lo, ev_hi: the tile's event words; n of them exist.  An event whose slot does not exist becomes an
+    // ALLOC of nothing: it is as invalid as that.
+    DI void tile_begin(u32 &ev_lo, u32 &ev_hi, u32 n)
     {
-        st_one(req, s, vreq);
-        st_one(a, s, va);
-        st_one(b, s, vb);           // c is not used with the table in LDS
+        const u32 lane = lane_id();
+        const bool exists = ev_hi < n_slots;
+        ev_lo = exists ? ev_lo : 0u;
+        if constexpr (REGS) ev_hi = exists ? ev_hi : 0u;
+        v_dlo = v_dhi = v_req = v_act = 0;
+        if constexpr (!REGS) {
+            slot = lane < n && exists ? ev_hi : n_slots;
+            // the last lane before this one with the same slot: key is slot * 128 + lane, so key - key' - 1 is
+            // below 63 exactly for the same slot in an earlier lane, and smallest for the last of those
+            const u32 key = (slot << 7) | lane;
+            // (written out it is 3 % of the splitting kernel; the stitching kernels are 2 % faster with a loop of
+            // nine a step, which leaves them the scalar registers)
+            constexpr int STEP = VMS ? 9 : 63;
+            u32 d = NONE32;
+#pragma unroll STEP
+            for (u32 i = 0; i < 63; i++) d = min(d, key - 1 - from_lane(key, i));
+            prev = d < 63 ? lane - 1 - d : lane;
+            const u32 i = min(slot, n_slots - 1);
+            req = t_req[i];
+            a = t_a[i];
+            if constexpr (VMS) {
+                b = t_b[i];
+                c = t_c[i];
+            }
+            old_req = req;
+        }
     }
-    DI void relist(const u64 *, const u32 *, u32) {}  // c is not used with the table in LDS
-    // fine-grained variant (c is used): see SlotsT<true>
-    u32 n_slots;
-    DI void relocate(u32 from, u32 to)
+    DI u32 at(u32 ev_hi, u32 j) const { return from_lane(REGS ? ev_hi : prev, j); }
+    DI u32 get_req(u32 at) const { return from_lane(req, at); }
+    DI u32 get_a(u32 at) const { return from_lane(a, at); }
+    DI u32 get_b(u32 at) const { return from_lane(b, at); }
+    DI u32 get_c(u32 at) const { return from_lane(c, at); }
+    // a FREE: the slot held r units, d units of memory
+    DI void free_done(u32 j, u32 at, u32 dlo, u32 dhi, u32 r, u32 d)
     {
-        for (u32 i = lane_id(); i < n_slots; i += 64) {
-            const bool hit = req[i] + 1u > 1u && (b[i] & 3) == KIND_SBLOCK && c[i] == from;
-            if (hit) c[i] = (uint16_t)(to | 0x8000u);
+        if constexpr (REGS) {
+            req = write_lane(req, SLOT_UNBOUND, at);
+            if constexpr (VMS) write_lane4(v_dlo, v_dhi, v_req, v_act, dlo, dhi, 0u - r, 0u - d, j);
+            else write_lane3(v_dlo, v_dhi, v_req, dlo, dhi, 0u - r, j);
+        } else {
+            write_lane2(v_dlo, req, dlo, SLOT_UNBOUND, j);
         }
         wave_sync();
     }
-    DI void relocate_done()
+    // an ALLOC of r units that was given d units of memory
+    DI void alloc_done(u32 j, u32 at, u32 dlo, u32 dhi, u32 r, u32 d, u32 va, u32 vb, u32 vc)
     {
-        for (u32 i = lane_id(); i < n_slots; i += 64) c[i] &= 0x7FFFu;
+        if constexpr (VMS) {
+            if constexpr (REGS) {
+                write_lane4(req, a, b, c, r, va, vb, vc, at);
+                write_lane4(v_dlo, v_dhi, v_req, v_act, dlo, dhi, r, d, j);
+            } else {
+                write_lane5(v_dlo, req, a, b, c, dlo, r, va, vb, vc, j);
+            }
+        } else {
+            if constexpr (REGS) {
+                write_lane2(req, a, r, va, at);
+                write_lane3(v_dlo, v_dhi, v_req, dlo, dhi, r, j);
+            } else {
+                write_lane3(v_dlo, req, a, dlo, r, va, j);
+            }
+        }
         wave_sync();
+    }
+    // the slot is left with `r` as its req and nothing changes hands (out of memory, a FREE after that)
+    DI void failed(u32 j, u32 at, u32 dlo, u32 r)
+    {
+        req = write_lane(req, r, REGS ? at : j);
+        v_dlo = write_lane(v_dlo, dlo, j);
+        wave_sync();
+    }
+    // an invalid event: the record stays as it is
+    DI void not_done(u32 j, u32 at)
+    {
+        if constexpr (!REGS) {
+            write_lane2(req, a, get_req(at), get_a(at), j);
+            if constexpr (VMS) write_lane2(b, c, get_b(at), get_c(at), j);
+        }
+        v_dlo = write_lane(v_dlo, (u32)C_INVALID, j);
+        wave_sync();
+    }
+    // the first `done` events have ended: v_dhi, v_req, v_act become theirs, and the table is up to date.
+    // place(a): the address of a block of a splitting pool; shift: log2 of a chunk in units
+    template <class Place>
+    DI void tile_end(u32 done, u32 shift, Place place)
+    {
+        if constexpr (!REGS) {
+            const u32 lane = lane_id(), code = v_dlo & 15;
+            const bool freed = lane < done && code == C_FREE, given = lane < done && code - C_EXACT <= C_GROW - C_EXACT;
+            // what a FREE let go of is the record it found: its own lane's or that of the event before it
+            const u32 pa = other_lane(a, prev), pr = other_lane(req, prev);
+            const u32 fa = freed ? pa : a, fr = freed ? (prev == lane ? old_req : pr) : req;
+            u32 held = fr;
+            bool whole = false;                                 // held in chunks
+            if constexpr (VMS) {
+                const u32 pb = other_lane(b, prev), fb = freed ? pb : b;
+                whole = (fb & 3) != KIND_SMALL;
+                held = whole ? (fb >> 2) << shift : fr;
+            }
+            const u32 sign = freed ? NONE32 : 0u, some = freed || given ? NONE32 : 0u;
+            v_dhi = (VMS && whole ? fa : place(fa)) & some;
+            v_req = ((fr ^ sign) - sign) & some;
+            v_act = ((held ^ sign) - sign) & some;
+            // a lane that a later one names as `prev` is not the last of its slot.  (No lane names lane 63: what
+            // arrives there is from the lanes that name none)
+            const u32 later = to_lane(prev != lane ? 1u : 0u, prev != lane ? prev : 63u);
+            if (slot < n_slots && (lane == 63 || later == 0)) {
+                t_req[slot] = req;
+                t_a[slot] = a;
+                if constexpr (VMS) {
+                    t_b[slot] = b;
+                    t_c[slot] = (LIST)c;
+                }
+            }
+            wave_sync();
+        }
+    }
+    // The lists of the held sBlocks have moved: moved_to(a, b, c) is the place now of the list a record
+    // describes (called by every lane, whatever its record holds).  Records that are no longer current get
+    // something as well, which nothing reads.
+    template <class MovedTo>
+    DI void relist(MovedTo moved_to)
+    {
+        const u32 to = moved_to(a, b, c);
+        c = req + 1u > 1u && (b & 3) == KIND_SBLOCK ? to : c;
+        if constexpr (!REGS) {
+            for (u32 base = 0; base < n_slots; base += 64) {
+                const u32 i = min(base + lane_id(), n_slots - 1);
+                const u32 r = t_req[i], tb = t_b[i], tc = t_c[i], now = moved_to(t_a[i], tb, tc);
+                wave_lockstep();
+                t_c[i] = (LIST)(r + 1u > 1u && (tb & 3) == KIND_SBLOCK ? now : tc);
+            }
+            wave_sync();
+        }
     }
 };
 
@@ -1136,15 +1222,6 @@ DI void vms_alloc_rest(VmsT &V, Slots &S, u32 bsize, u32 reserved_units, const K
     if (stitch_free(V, P, A)) R.dec_lo |= B_7;
 }
 
-// Update (Sec. 3.3.2) of an sBlock that is looked up by its key (slot table in LDS)
-DI void vms_free_by_key(VmsT &V, u32 ref, u32 held)
-{
-    const u64 key = ((u64)held << 32) | (u32)~ref;
-    const u32 idx = rank_fast<false>(V.sp, V.skey, V.ns, key);
-    const auto meta = ld_uni(V.smeta, idx);
-    bmp_fill_entries(V, V.off(meta), V.cnt(meta), false);
-}
-
 // ---------------------------------------------------------------------------
 // Hot and cold halves.  The replay loop keeps only what the two frequent paths need in registers
 // (exact hit on a cached block, free).  The states S2 to S5 and the splitting pool for requests below
@@ -1326,12 +1403,11 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
     WAVE_DYNAMIC_LDS(lds);
     const u32 lane = lane_id();
     const u32 trace = blockIdx.x;
-    constexpr bool USE_LIST = SLOT_REGS;
     char *ws_slice = workspace + (size_t)trace * P.ws_stride;
     // a second pass follows for traces that outgrow these tables: it counts the traces it takes on
     if (P.retry_slots && trace == 0) ((u32 *)&stats[2 * (size_t)P.n_traces])[1] = 0;     // the second pass counts from 0
 
-    SlotsT<SLOT_REGS> S;
+    SlotsT<SLOT_REGS, true, u32> S;
     S.init(lds, P);
     ((u32 *)(lds + LDS_SCALARS))[lane] = lane == SC_FIRST_OOM || lane == SC_OVF_EVENT ? NONE32 : 0u;     // LDS header
     VmsT V;
@@ -1369,58 +1445,45 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
     u64 ev = pin64(lane < n_ev ? ev_row[lane] : 0), ev_next = ev;
     for (u32 base = 0; base < n_ev; base += 64) {
         const u32 tile = min(64u, n_ev - base);
-        const u32 ev_lo = (u32)ev, ev_hi = (u32)(ev >> 32);
+        u32 ev_lo = (u32)ev;
+        u32 ev_hi = (u32)(ev >> 32);
+        S.tile_begin(ev_lo, ev_hi, tile);
         if (base + 64 < n_ev) ev_next = ev_row[min(base + 64 + lane, n_ev - 1)];       // prefetch (see replay_split_kernel)
-        u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_act = 0, v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
+        u32 v_res = sp_reserved + (V.n_chunks << P.chunk_shift);
         u32 done = tile, todo = tile;       // todo drops to 0 when an engine table overflows: the trace ends there
-        // every path of an event ends by parking its results in lane j and going on to the next event
-#define EMIT(DLO, DHI, DREQ, DACT)                                         \
-    {                                                                      \
-        write_lane4(v_dlo, v_dhi, v_req, v_act, (DLO), (DHI), (DREQ), (DACT), j); \
-        wave_sync();                                                       \
-        continue;                                                          \
-    }
+        // every path of an event ends by noting its results and going on to the next event
         // memory was reserved: the events from this one on see the new total
 #define RESERVED_NOW() v_res = lane >= j ? sp_reserved + (V.n_chunks << P.chunk_shift) : v_res
         for (u32 j = 0; j < todo; j++) {
-            const u32 w = from_lane(ev_lo, j), slot = from_lane(ev_hi, j);
-            if (UNLIKELY(slot >= P.max_slots)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
-            const u32 req = S.get_req(slot);
+            const u32 w = from_lane(ev_lo, j), at = S.at(ev_hi, j), req = S.get_req(at);
             if ((int)w < 0) {
                 // ---- FREE.  Update (Sec. 3.3.2): only activity flips; memory stays with its pBlocks
                 if (UNLIKELY(req + 1u <= 1u)) {             // unbound, or bound to a request that failed
-                    if (req == SLOT_OOM) {
-                        S.set_req(slot, (u32)SLOT_UNBOUND);
-                        EMIT((u32)C_FREE_NOOP, 0u, 0u, 0u)
-                    }
-                    EMIT((u32)C_INVALID, 0u, 0u, 0u)
+                    if (req == SLOT_OOM) S.failed(j, at, (u32)C_FREE_NOOP, SLOT_UNBOUND);
+                    else S.not_done(j, at);
+                    continue;
                 }
-                const u32 a = S.get_a(slot), b = S.get_b(slot);
-                const u32 kind = b & 3;
-                S.set_req(slot, (u32)SLOT_UNBOUND);
+                const u32 a = S.get_a(at), b = S.get_b(at);
+                const u32 kind = b & 3, held = (b >> 2) << P.chunk_shift;
                 if (LIKELY((kind & KIND_SBLOCK) != 0)) {    // (a bit test: the usual case stays the fall-through)
-                    if (USE_LIST) {
-                        const u32 list = S.get_c(slot), off = list >> 16, cnt = list & 0xFFFFu;
-                        // one list read, then the entries' bits cleared without waiting for anything
-                        if (LIKELY(cnt <= 64)) entries_apply(V, V.arena[off + lane], lane < cnt, false);
-                        else bmp_fill_entries(V, off, cnt, false);
-                    } else {
-                        vms_free_by_key(V, a, b >> 2);
-                    }
-                    EMIT(C_FREE | B_SBLOCK, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
+                    const u32 list = S.get_c(at), off = list >> 16, cnt = list & 0xFFFFu;
+                    // one list read, then the entries' bits cleared without waiting for anything
+                    if (LIKELY(cnt <= 64)) entries_apply(V, V.arena[off + lane], lane < cnt, false);
+                    else bmp_fill_entries(V, off, cnt, false);
+                    S.free_done(j, at, C_FREE | B_SBLOCK, a, req, held);
+                    continue;
                 }
                 if (kind == KIND_PBLOCK) {
                     bmp_fill(V.bmp, ENT_WORD(V.e_skip), a, b >> 2, false);
-                    EMIT((u32)C_FREE, a, 0u - req, 0u - ((b >> 2) << P.chunk_shift))
+                    S.free_done(j, at, (u32)C_FREE, a, req, held);
+                    continue;
                 }
                 AcctLds A;
                 A.sc = (u32 *)(lds + LDS_SCALARS);
                 A.idle = V.idle;
                 Q.release(a, req, A, base + j,
                           [&](bool ml, bool mr) {
-                              write_lane4(v_dlo, v_dhi, v_req, v_act, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u),
-                                          Q.addr(a), 0u - req, 0u - req, j);
-                              wave_sync();
+                              S.free_done(j, at, C_FREE | B_SMALL | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), Q.addr(a), req, req);
                           },
                           [&]() {
                               lost = req;
@@ -1432,15 +1495,18 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
             }
             // ---- ALLOC
             const u32 size = w;
-            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) EMIT((u32)C_INVALID, 0u, 0u, 0u)
+            if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) {
+                S.not_done(j, at);
+                continue;
+            }
             if (LIKELY(size >= fast_limit)) {
                 const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
                 u32 ref, list = 0;
                 // Sec. 5.1: active memory is recorded at its peak; the totals only rise on an allocation
 #define S1_SBLOCK_HIT                                                      \
     {                                                                      \
-        S.bind(slot, size, ref, KIND_SBLOCK | (bsize << 2), list);         \
-        EMIT(C_EXACT | B_SBLOCK | (1u << 8), ref, size, bsize << P.chunk_shift) \
+        S.alloc_done(j, at, C_EXACT | B_SBLOCK | (1u << 8), ref, size, bsize << P.chunk_shift, ref, KIND_SBLOCK | (bsize << 2), list); \
+        continue;                                                          \
     }
                 // S1 on stitched blocks, the usual way (see s1_sblock_from for the general route).  It is
                 // written out here, not called, so that the hit leaves for the next event from where it
@@ -1491,10 +1557,8 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
 #define S1_PBLOCK_TRY                                                      \
     if (s1_pblock(V, bsize, ref)) {                                        \
         bmp_fill(V.bmp, ENT_WORD(V.e_skip), ref, bsize, true);             \
-        S.set_a(slot, ref);                                                \
-        S.set_b(slot, KIND_PBLOCK | (bsize << 2));                         \
-        S.set_req(slot, size);                                             \
-        EMIT(C_EXACT | (1u << 8), ref, size, bsize << P.chunk_shift)       \
+        S.alloc_done(j, at, C_EXACT | (1u << 8), ref, size, bsize << P.chunk_shift, ref, KIND_PBLOCK | (bsize << 2), 0u); \
+        continue;                                                          \
     }
                 S1_PBLOCK_TRY
             } else if (UNLIKELY(size >= P.small_limit_units)) {
@@ -1509,35 +1573,8 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
 #undef S1_PBLOCK_TRY
 #undef S1_SBLOCK_HIT
             // ---- the rare cases: no exact fit (states S2 to S5), or a request below one chunk
-            u32 dlo, dhi = 0, held_units = size;
             wave_sync();
-            if (size >= P.small_limit_units) {
-                const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
-                VmsRes R;
-                bool compacted;
-                const bool went = vms_alloc_cold(lds, V, P, bsize, sp_reserved + (V.n_chunks << P.chunk_shift), base + j,
-                                                      R, compacted);
-                // the pools may have changed: renew the first search level of both
-                probe_refresh(V.sp, V.skey, V.ns);
-                probe_refresh(V.pp, V.pool, V.np);
-                fast_limit = V.sp.stride >= 64 ? NONE32 : P.small_limit_units;
-                // lists have moved: every slot holding an sBlock looks its list up again
-                if (USE_LIST && UNLIKELY(compacted)) S.relist(V.skey, (const u32 *)V.smeta, V.ns);
-                if (UNLIKELY(!went)) {                                // an engine table overflowed: the trace ends here
-                    stop = true;
-                    done = j;
-                    todo = 0;
-                    continue;
-                }
-                dlo = R.dec_lo;
-                if (LIKELY((dlo & 15) != C_OOM)) {
-                    dhi = R.ref;
-                    S.set_a(slot, dhi);
-                    S.set_b(slot, R.kind | (R.held << 2));
-                    if (USE_LIST) S.set_c(slot, R.list);
-                    held_units = R.held << P.chunk_shift;
-                }
-            } else {
+            if (size < P.small_limit_units) {
                 const u32 seg = ((size + chunk_units - 1) >> P.chunk_shift) << P.chunk_shift;
                 const u32 reserved = sp_reserved + (V.n_chunks << P.chunk_shift);
                 AcctLds A;
@@ -1546,24 +1583,17 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                 Q.alloc(size, seg, reserved + seg <= P.capacity_units, A, base + j,
                         [&](u32 code, u32 ref, bool split) {
                             sp_reserved = Q.reserved();
-                            u32 d_lo = C_OOM, d_hi = 0, d_req = 0;
-                            if (code == C_OOM) {
-                                S.set_req(slot, (u32)SLOT_OOM);
-                                ColdState C;            // rare: note the first failed request
+                            if (UNLIKELY(code == C_OOM)) {
+                                S.failed(j, at, (u32)C_OOM, SLOT_OOM);
+                                ColdState C;                // rare: note the first failed request
                                 C.load(lds);
                                 if (C.get(SC_FIRST_OOM) == NONE32)
                                     st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                            } else {
-                                S.set_a(slot, ref);
-                                S.set_b(slot, (u32)KIND_SMALL);
-                                S.set_req(slot, size);
-                                if (code == C_GROW) RESERVED_NOW();
-                                d_lo = code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8);
-                                d_hi = Q.addr(ref);
-                                d_req = size;
+                                return;
                             }
-                            write_lane4(v_dlo, v_dhi, v_req, v_act, d_lo, d_hi, d_req, d_req, j);
-                            wave_sync();
+                            if (code == C_GROW) RESERVED_NOW();
+                            S.alloc_done(j, at, code | B_SMALL | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), Q.addr(ref),
+                                         size, size, ref, (u32)KIND_SMALL, 0u);
                         },
                         [&]() {
                             stop = true;
@@ -1572,21 +1602,50 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
                         });
                 continue;
             }
-            if (UNLIKELY((dlo & 15) == C_OOM)) {
-                S.set_req(slot, (u32)SLOT_OOM);
+            const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
+            VmsRes R;
+            bool compacted;
+            const bool went = vms_alloc_cold(lds, V, P, bsize, sp_reserved + (V.n_chunks << P.chunk_shift), base + j, R, compacted);
+            // the pools may have changed: renew the first search level of both
+            probe_refresh(V.sp, V.skey, V.ns);
+            probe_refresh(V.pp, V.pool, V.np);
+            fast_limit = V.sp.stride >= 64 ? NONE32 : P.small_limit_units;
+            // lists have moved: every record of an sBlock looks its list up again
+            if (UNLIKELY(compacted))
+                S.relist([&](u32 sid, u32 b, u32) {
+                    // by its key (creation number, chunks) in skey[0..ns), descending; every lane searches (13 halvings
+                    // cover 4096 sBlocks), lanes without an sBlock for nothing: no lane is switched off
+                    const u64 key = ((u64)(b >> 2) << 32) | (u32)~sid;
+                    u32 lo = 0, hi = V.ns;          // first index whose key is not greater than key
+#pragma unroll 1
+                    for (u32 it = 0; it < 13; it++) {
+                        const u32 mid = (lo + hi) >> 1;         // < ns while lo < hi; else a place that exists
+                        const bool open = lo < hi, greater = V.skey[mid] > key;
+                        lo = open && greater ? mid + 1 : lo;
+                        hi = open && !greater ? mid : hi;
+                    }
+                    return pin(V.smeta[lo]);
+                });
+            if (UNLIKELY(!went)) {                                // an engine table overflowed: the trace ends here
+                stop = true;
+                done = j;
+                todo = 0;
+                continue;
+            }
+            if (UNLIKELY((R.dec_lo & 15) == C_OOM)) {
+                S.failed(j, at, (u32)C_OOM, SLOT_OOM);
                 ColdState C;                                // rare: note the first failed request
                 C.load(lds);
                 if (C.get(SC_FIRST_OOM) == NONE32) st_one((u32 *)(lds + LDS_SCALARS), (u32)SC_FIRST_OOM, base + j);
-                EMIT((u32)C_OOM, 0u, 0u, 0u)
+                continue;
             }
-            S.set_req(slot, size);
-            if ((dlo & 15) == C_GROW) RESERVED_NOW();
-            EMIT(dlo, dhi, size, held_units)
+            if ((R.dec_lo & 15) == C_GROW) RESERVED_NOW();
+            S.alloc_done(j, at, R.dec_lo, R.ref, size, R.held << P.chunk_shift, R.ref, R.kind | (R.held << 2), R.list);
         }
-#undef EMIT
 #undef RESERVED_NOW
         ev = pin64(ev_next);
-        tile_emit<false>(T, dec_row, base, done, v_dlo, v_dhi, v_req, v_act, v_res);
+        S.tile_end(done, P.chunk_shift, [&](u32 ref) { return Q.addr(ref); });
+        tile_emit<false>(T, dec_row, base, done, S.v_dlo, S.v_dhi, S.v_req, S.v_act, v_res);
         if (stop) break;
     }
 
@@ -1648,7 +1707,7 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
     do {        // once; the second pass: once per flagged trace this wavefront takes on
     if (P.retry && !W.next(P, stats, &taken[0], trace)) return;
 
-    SlotsT<SLOT_REGS> S;
+    SlotsT<SLOT_REGS, false, u32> S;
     S.init(lds, P);
     SplitPool<TILES, TAIL> sp;
     sp.init(lds, P);
@@ -1665,78 +1724,66 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
     u64 ev = pin64(lane < n_ev ? ev_row[lane] : 0), ev_next = ev;
     for (u32 base = 0; base < n_ev; base += 64) {
         const u32 tile = min(64u, n_ev - base);
-        const u32 ev_lo = (u32)ev, ev_hi = (u32)(ev >> 32);
+        u32 ev_lo = (u32)ev;
+        u32 ev_hi = (u32)(ev >> 32);
+        S.tile_begin(ev_lo, ev_hi, tile);
         // the next tile, on its way while this one is replayed (the flat stitching kernel alone on
         // recomputation traces 1024x20000: 8.56 -> 8.45 ms): nothing touches the value (a select on it
         // would wait for memory here, once per 64 events) until this tile's results are stored, and it is
         // taken over before that store, which would have to be waited for too (one counter).  Lanes past
         // the end hold the last event, which no j reaches.
         if (base + 64 < n_ev) ev_next = ev_row[min(base + 64 + lane, n_ev - 1)];
-        u32 v_dlo = 0, v_dhi = 0, v_req = 0, v_res = sp.reserved();
+        u32 v_res = sp.reserved();
         u32 done = tile, todo = tile;       // todo drops to 0 when the free list overflows: the trace ends there
-        u32 w_next = from_lane(ev_lo, 0), slot_next = from_lane(ev_hi, 0);     // one event ahead
+        u32 w_next = from_lane(ev_lo, 0), at_next = S.at(ev_hi, 0);            // one event ahead
         for (u32 j = 0; j < todo; j++) {
-            const u32 w = w_next, slot = slot_next;
+            const u32 w = w_next, at = at_next;
             w_next = from_lane(ev_lo, (j + 1) & 63);
-            slot_next = from_lane(ev_hi, (j + 1) & 63);
-            // every path of an event ends by parking its results in lane j; none hands a result to
-            // a common tail (that would cost flags to test)
-            auto emit = [&](u32 dlo, u32 dhi, u32 dreq) {
-                write_lane3(v_dlo, v_dhi, v_req, dlo, dhi, dreq, j);
-                wave_sync();
-            };
+            at_next = S.at(ev_hi, (j + 1) & 63);
+            // every path of an event ends by noting its results; none hands a result to a common tail
+            // (that would cost flags to test)
             auto overflow = [&]() {
                 done = j;
                 todo = 0;
             };
-            if (UNLIKELY(slot >= P.max_slots)) {
-                emit((u32)C_INVALID, 0u, 0u);
-                continue;
-            }
-            const u32 req = S.get_req(slot);
+            const u32 req = S.get_req(at);
             if ((int)w < 0) {
                 if (UNLIKELY(req + 1u <= 1u)) {             // unbound, or bound to a request that failed
-                    if (req == SLOT_OOM) {
-                        S.set_req(slot, (u32)SLOT_UNBOUND);
-                        emit((u32)C_FREE_NOOP, 0u, 0u);
-                        continue;
-                    }
-                    emit((u32)C_INVALID, 0u, 0u);
+                    if (req == SLOT_OOM) S.failed(j, at, (u32)C_FREE_NOOP, SLOT_UNBOUND);
+                    else S.not_done(j, at);
                     continue;
                 }
-                const u32 a = S.get_a(slot);
-                S.set_req(slot, (u32)SLOT_UNBOUND);
+                const u32 a = S.get_a(at);
                 sp.release(a, req, A, base + j,
                            [&](bool ml, bool mr) {
-                               emit(C_FREE | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), sp.addr(a), 0u - req);
+                               S.free_done(j, at, C_FREE | (ml ? B_6 : 0u) | (mr ? B_7 : 0u), sp.addr(a), req, req);
                            },
                            overflow);
                 continue;
             }
             const u32 size = w;
             if (UNLIKELY(size == 0 || req != SLOT_UNBOUND)) {
-                emit((u32)C_INVALID, 0u, 0u);
+                S.not_done(j, at);
                 continue;
             }
             const u32 seg = ((size + chunk_units - 1) >> P.chunk_shift) << P.chunk_shift;
             sp.alloc(size, seg, sp.reserved() + seg <= P.capacity_units, A, base + j,
                      [&](u32 code, u32 ref, bool split) {
                          if (code == C_OOM) {
-                             S.set_req(slot, (u32)SLOT_OOM);
+                             S.failed(j, at, (u32)C_OOM, SLOT_OOM);
                              if (A.f[SC_FIRST_OOM] == NONE32) A.f[SC_FIRST_OOM] = base + j;
-                             emit((u32)C_OOM, 0u, 0u);
                              return;
                          }
-                         S.set_a(slot, ref);
-                         S.set_req(slot, size);
                          // blocks are cut to the request: active bytes are the requested bytes
                          if (code == C_GROW) v_res = lane >= j ? sp.reserved() : v_res;
-                         emit(code | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), sp.addr(ref), size);
+                         S.alloc_done(j, at, code | (split ? B_6 : 0u) | ((code == C_GROW ? 0u : 1u) << 8), sp.addr(ref), size, size,
+                                      ref, 0u, 0u);
                      },
                      overflow);
         }
         ev = pin64(ev_next);
-        tile_emit<true>(T, dec_row, base, done, v_dlo, v_dhi, v_req, 0u, v_res);
+        S.tile_end(done, 0u, [&](u32 ref) { return sp.addr(ref); });
+        tile_emit<true>(T, dec_row, base, done, S.v_dlo, S.v_dhi, S.v_req, 0u, v_res);
         if (A.stop) break;
     }
 

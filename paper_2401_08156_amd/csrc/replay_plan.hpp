@@ -89,7 +89,7 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
         k.off_slot_req = take((uint64_t)c.max_slots * 4);
         k.off_slot_a = take((uint64_t)c.max_slots * 4);
         k.off_slot_b = policy ? take((uint64_t)c.max_slots * 4) : 0;
-        k.off_slot_c = policy && p.fine ? take((uint64_t)c.max_slots * 2) : 0;   // 16-bit list places
+        k.off_slot_c = policy ? take((uint64_t)c.max_slots * (p.fine ? 2 : 4)) : 0;     // 16-bit list places, or offset and length
     }
     // inactive blocks of a splitting pool beyond those held in registers
     const uint32_t in_regs = 64 * (policy ? SMALL_TILES : p.fl_tiles);
@@ -205,7 +205,16 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
             k.ws_stride = align_up(((uint64_t)c.max_runs + 64) * 4, 256);     // where compaction copies the lists
         }
         const uint64_t need = layout(k, pol, c, p) + plan_detail::pool_bytes_saved(k, pol, p);
-        if ((c.policy_mask & (1u << pol)) && need > LDS_PER_CU) return VMS_ETOOBIG;
+        if ((c.policy_mask & (1u << pol)) && need > LDS_PER_CU) {
+            // flat variant: the lists' places in a slot table in LDS are there for speed only; tables that fit
+            // without them are served by the fine-grained variant
+            const uint64_t lists = pol && !p.fine && !p.slot_regs ? 4ull * c.max_slots + 16 : 0;
+            if (need - lists > LDS_PER_CU) return VMS_ETOOBIG;
+            vms_config alt = c;
+            alt.variant = VMS_VARIANT_FINE;
+            alt.table_place = VMS_TABLES_AUTO;
+            return replay_plan_for(&alt, p);
+        }
     }
     p.ws_bytes = (c.policy_mask & VMS_POLICY_VMS) ? (size_t)p.kp[1].ws_stride * c.n_traces : 0;
     return VMS_OK;

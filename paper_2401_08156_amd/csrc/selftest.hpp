@@ -123,6 +123,20 @@ __global__ __launch_bounds__(64) void selftest_kernel(u32 *fail, uint16_t *tab)
             c != (lane == 63 - l ? 6000 + l : lane == l ? 3000 + l : lane + 200) ||
             d != (lane == 63 - l ? 7000 + l : lane == l ? 4000 + l : lane + 300))
             bad |= 1u << 17;
+        u32 e = lane + 400;
+        a = lane;
+        b = lane + 100;
+        c = lane + 200;
+        d = lane + 300;
+        write_lane2(a, e, 1000 + l, 2000 + l, l);
+        if (a != (lane == l ? 1000 + l : lane) || e != (lane == l ? 2000 + l : lane + 400)) bad |= 1u << 17;
+        write_lane5(a, b, c, d, e, 11, 22, 33, 44, 55, l);
+        if (lane == l ? a != 11 || b != 22 || c != 33 || d != 44 || e != 55 : a != lane || b != lane + 100 || c != lane + 200 || d != lane + 300 || e != lane + 400)
+            bad |= 1u << 17;
+        if (other_lane(lane + 7, (lane + l) & 63) != ((lane + l) & 63) + 7) bad |= 1u << 17;
+        // lanes below l hand a value to the lane after them, the others name lane 63 in vain
+        const u32 got = to_lane(lane < l ? lane + 9 : 0u, lane < l && lane < 62 ? lane + 1 : 63u);
+        if (lane < 63 && got != (lane > 0 && lane - 1 < l ? lane + 8 : 0u)) bad |= 1u << 17;
     }
     // sorted-array helpers on a descending array of 150 keys, followed by zero keys as they require
     for (u32 i = lane; i < 256; i += 64) arr[i] = i < 150 ? (u64)(1000 - 3 * i) << 32 : 0;

@@ -145,7 +145,21 @@ DI u32 write_lane(u32 vec, u32 val, u32 lane)
     asm("s_mov_b32 m0, %2\n\ts_nop 0\n\tv_writelane_b32 %0, %1, m0" : "+v"(vec) : "s"(uni(val)), "s"(uni(lane)) : "m0");
     return vec;
 }
-// four vectors, the same lane
+// several vectors, the same lane
+DI void write_lane2(u32 &a, u32 &b, u32 va, u32 vb, u32 lane)
+{
+    asm("s_mov_b32 m0, %4\n\ts_nop 0\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
+        : "+v"(a), "+v"(b)
+        : "s"(uni(va)), "s"(uni(vb)), "s"(uni(lane))
+        : "m0");
+}
+DI void write_lane3(u32 &a, u32 &b, u32 &c, u32 va, u32 vb, u32 vc, u32 lane)
+{
+    asm("s_mov_b32 m0, %6\n\ts_nop 0\n\tv_writelane_b32 %0, %3, m0\n\tv_writelane_b32 %1, %4, m0\n\tv_writelane_b32 %2, %5, m0"
+        : "+v"(a), "+v"(b), "+v"(c)
+        : "s"(uni(va)), "s"(uni(vb)), "s"(uni(vc)), "s"(uni(lane))
+        : "m0");
+}
 DI void write_lane4(u32 &a, u32 &b, u32 &c, u32 &d, u32 va, u32 vb, u32 vc, u32 vd, u32 lane)
 {
     asm("s_mov_b32 m0, %8\n\ts_nop 0\n\tv_writelane_b32 %0, %4, m0\n\tv_writelane_b32 %1, %5, m0\n\t"
@@ -154,15 +168,20 @@ DI void write_lane4(u32 &a, u32 &b, u32 &c, u32 &d, u32 va, u32 vb, u32 vc, u32 
         : "s"(uni(va)), "s"(uni(vb)), "s"(uni(vc)), "s"(uni(vd)), "s"(uni(lane))
         : "m0");
 }
-
-#define WAVE_WRITE_LANE3
-DI void write_lane3(u32 &a, u32 &b, u32 &c, u32 va, u32 vb, u32 vc, u32 lane)
+DI void write_lane5(u32 &a, u32 &b, u32 &c, u32 &d, u32 &e, u32 va, u32 vb, u32 vc, u32 vd, u32 ve, u32 lane)
 {
-    asm("s_mov_b32 m0, %6\n\ts_nop 0\n\tv_writelane_b32 %0, %3, m0\n\tv_writelane_b32 %1, %4, m0\n\tv_writelane_b32 %2, %5, m0"
-        : "+v"(a), "+v"(b), "+v"(c)
-        : "s"(uni(va)), "s"(uni(vb)), "s"(uni(vc)), "s"(uni(lane))
+    asm("s_mov_b32 m0, %10\n\ts_nop 0\n\tv_writelane_b32 %0, %5, m0\n\tv_writelane_b32 %1, %6, m0\n\t"
+        "v_writelane_b32 %2, %7, m0\n\tv_writelane_b32 %3, %8, m0\n\tv_writelane_b32 %4, %9, m0"
+        : "+v"(a), "+v"(b), "+v"(c), "+v"(d), "+v"(e)
+        : "s"(uni(va)), "s"(uni(vb)), "s"(uni(vc)), "s"(uni(vd)), "s"(uni(ve)), "s"(uni(lane))
         : "m0");
 }
+
+// v of lane `from` (each lane its own)
+DI u32 other_lane(u32 v, u32 from) { return (u32)__builtin_amdgcn_ds_bpermute((int)(from * 4), (int)v); }
+// v goes to lane `to`; a lane that nothing goes to receives 0.  Where several lanes name the same one, any of
+// their values arrives.
+DI u32 to_lane(u32 v, u32 to) { return (u32)__builtin_amdgcn_ds_permute((int)(to * 4), (int)v); }
 
 // which way a wave-uniform branch usually goes: the usual way becomes the fall-through
 #define LIKELY(x) __builtin_expect(!!(x), 1)

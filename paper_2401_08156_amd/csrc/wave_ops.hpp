@@ -276,15 +276,6 @@ struct Probe2 {
     }
 };
 
-#ifndef WAVE_WRITE_LANE3        // (a host build brings single lane writes only)
-DI void write_lane3(u32 &a, u32 &b, u32 &c, u32 va, u32 vb, u32 vc, u32 lane)
-{
-    a = write_lane(a, va, lane);
-    b = write_lane(b, vb, lane);
-    c = write_lane(c, vc, lane);
-}
-#endif
-
 // Moves of arrays of 2- or 4-byte elements, sixteen bytes (one block of E elements) per lane and
 // step.  The array starts on a 16-byte boundary, every place behind the n live ones is zero, and the
 // array is allocated two blocks beyond the one that holds place n.  A block is four 32-bit words;

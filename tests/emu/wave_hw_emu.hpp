@@ -110,9 +110,30 @@ DI u32 wave_scan_add(u32 v, u32 *total)
     return mine;
 }
 DI u32 write_lane(u32 vec, u32 val, u32 lane) { return lane_id() == lane ? val : vec; }
+DI void write_lane2(u32 &a, u32 &b, u32 va, u32 vb, u32 lane)
+{
+    if (lane_id() == lane) { a = va; b = vb; }
+}
+DI void write_lane3(u32 &a, u32 &b, u32 &c, u32 va, u32 vb, u32 vc, u32 lane)
+{
+    if (lane_id() == lane) { a = va; b = vb; c = vc; }
+}
 DI void write_lane4(u32 &a, u32 &b, u32 &c, u32 &d, u32 va, u32 vb, u32 vc, u32 vd, u32 lane)
 {
     if (lane_id() == lane) { a = va; b = vb; c = vc; d = vd; }
+}
+DI void write_lane5(u32 &a, u32 &b, u32 &c, u32 &d, u32 &e, u32 va, u32 vb, u32 vc, u32 vd, u32 ve, u32 lane)
+{
+    if (lane_id() == lane) { a = va; b = vb; c = vc; d = vd; e = ve; }
+}
+DI u32 other_lane(u32 v, u32 from) { return (u32)emu::all(v)[from & 63]; }
+DI u32 to_lane(u32 v, u32 to)
+{
+    const u64 *x = emu::all(((u64)to << 32) | v);
+    u32 got = 0;
+    for (int l = 0; l < emu::LANES; l++)
+        if ((x[l] >> 32) == lane_id()) got = (u32)x[l];
+    return got;
 }
 
 #define LIKELY(x) __builtin_expect(!!(x), 1)

@@ -97,6 +97,39 @@ def equal_blocks_trace(blocks, small, seed):
     return tg.make_events(ops)[None, :], blocks
 
 
+def slot_reuse_traces(slots, events, seed, traces=4):
+    """Traces that keep coming back to a few slots, so that most events of 64 in a row follow another one on the same
+    slot, with every kind of invalid event among them: slots that do not exist, an ALLOC of a held slot or of
+    nothing, a FREE of an unbound slot.  Lengths end just before, at and after a tile of 64 events."""
+    from paper_2401_08156_amd import tracegen as tg
+    rng = np.random.default_rng(seed)
+    out = np.zeros((traces, events), dtype=np.uint64)
+    for t in range(traces):
+        few = rng.choice(slots, size=min(slots, 3 + 12 * t), replace=False)
+        held = set()
+        ops = []
+        while len(ops) < events:
+            s = int(rng.choice(few)) if rng.random() < 0.8 else int(rng.integers(slots))
+            x = rng.random()
+            if x < 0.03:
+                ops.append(("A", int(rng.choice((slots, slots + 1, 0x7FFFFFFF, 0xFFFFFFFF))), 4096))
+            elif x < 0.05:
+                ops.append(("F", int(rng.choice((slots, 0xFFFFFFFF)))))
+            elif x < 0.07:
+                ops.append(("A", s, 0))
+            elif x < 0.10:
+                ops.append((("A", s, 512) if s in held else ("F", s)))
+            elif s in held:
+                ops.append(("F", s))
+                held.discard(s)
+            else:
+                big = int(rng.integers(1, 40)) << 20
+                ops.append(("A", s, int(rng.integers(1, 3000)) * 512 if rng.random() < 0.5 else big))
+                held.add(s)
+        out[t] = tg.make_events(ops)
+    return out, np.array([events, events - 1, events - 63, events - 64][:traces], dtype=np.uint32)
+
+
 def alternate_frees_trace(n):
     """2 n requests of 1 KiB out of one chunk, then every second one back: each FREE adds a block to the splitting
     pool that merges with nothing, beside the rest of the chunk.  Returns (events, slots)."""

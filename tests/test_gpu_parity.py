@@ -111,6 +111,14 @@ def test_invalid_events_and_oom():
     assert st["status"][0, 0] == 1 and st["n_code"][1, 0, 5] == 1
 
 
+@pytest.mark.parametrize("slots", [3, 64, 65, 300])
+@pytest.mark.parametrize("kw", [dict(variant=1), dict(variant=1, spool_threshold=4, max_sblocks=128, max_runs=900), dict(variant=2),
+                                dict(variant=2, table_place=binding.VMS_TABLES_WORKSPACE_ALL, spool_threshold=4, max_sblocks=128, max_runs=160)])
+def test_events_that_follow_each_other_on_a_slot(slots, kw):
+    ev, n = gpu_util.slot_reuse_traces(slots, 64 * 9, seed=slots)
+    gpu_util.assert_parity(ev, gpu_util.make_cfg(4, ev.shape[1], slots, **kw), n_events=n, label="%d slots" % slots)
+
+
 @pytest.mark.parametrize("cfg_id,nt,ne", [(2, 48, 4000), (4, 24, 6000)])
 def test_transformer_slices(cfg_id, nt, ne):
     ev, ms = tg.generate(cfg_id, n_traces=nt, n_events=ne)

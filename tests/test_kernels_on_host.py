@@ -154,6 +154,16 @@ def test_fine_grained_variant(kind, nt, ne, tables):
         check(ev, cfg, label="generator %d %s tables %d" % (kind, tables, place))
 
 
+# slot tables in registers (up to 64 slots) and in LDS; a capacity that is reached, and an arena that is squeezed often
+@pytest.mark.parametrize("slots", [3, 64, 65, 300])
+@pytest.mark.parametrize("kw", [dict(policy_mask=1), dict(variant=2, capacity_bytes=192 * MiB),
+                                dict(variant=2, table_place=binding.VMS_TABLES_WORKSPACE_ALL, spool_threshold=4, max_sblocks=128, max_runs=160)])
+def test_events_that_follow_each_other_on_a_slot(slots, kw):
+    ev, n = gpu_util.slot_reuse_traces(slots, 64 * 9, seed=slots)
+    st = check(ev, gpu_util.make_cfg(4, ev.shape[1], slots, **kw), n_events=n, label="%d slots" % slots)
+    assert (st["n_code"][:, :, 7][st["n_code"].sum(axis=2) > 0] > 20).all()
+
+
 def test_ragged_traces_and_nothing_written_past_the_end():
     ev, ms = tg.generate(1, n_traces=3, n_events=700, seed=11)
     check(ev, gpu_util.make_cfg(3, 700, ms, max_runs=20000), n_events=np.array([0, 333, 700], dtype=np.uint32), label="ragged")
