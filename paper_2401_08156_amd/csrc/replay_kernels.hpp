@@ -749,10 +749,12 @@ DI void spool_shift_up(VmsT &V, u32 pos, u32 n)
         const u64 k = V.skey[src];
         const auto m = V.smeta[src];
         const u32 st = V.sstamp[src], w = V.swit[src];
+        wave_lockstep();
         V.skey[i + 1] = k;
         V.smeta[i + 1] = m;
         V.sstamp[i + 1] = st;
         V.swit[i + 1] = w;
+        wave_lockstep();
         hi = lo;
     }
     wave_sync();
@@ -765,10 +767,12 @@ DI void spool_shift_down(VmsT &V, u32 pos, u32 n)
         const u64 k = V.skey[i];
         const auto m = V.smeta[i];
         const u32 st = V.sstamp[i], w = V.swit[i];
+        wave_lockstep();
         V.skey[dst] = k;
         V.smeta[dst] = m;
         V.sstamp[dst] = st;
         V.swit[dst] = w;
+        wave_lockstep();
     }
     wave_sync();
 }

@@ -220,64 +220,73 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
     return VMS_OK;
 }
 
-// Wavefronts of the stitching kernel that share a compute unit: LDS is handed out in granules of
-// 1,280 bytes, 128 of them per compute unit (measured: 31,680 B per wavefront gives five wavefronts
-// per compute unit, 32,576 B four).
+// LDS is handed out in granules of 1,280 bytes, 128 of them per compute unit (measured: 31,680 B per
+// wavefront gives five wavefronts per compute unit, 32,576 B four).
+const uint32_t PLAN_CUS = 256, PLAN_GRANULES = 128;
+inline uint32_t plan_granules(uint32_t lds_bytes) { return (lds_bytes + 1279) / 1280; }
+
+// Wavefronts of the stitching kernel that share a compute unit: by their LDS, and at most four per SIMD,
+// which is what their vector registers allow.
 inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 {
-    const uint64_t granules = ((uint64_t)x.kp[1].lds_bytes + 1279) / 1280;
-    const uint64_t w = granules ? plan_detail::LDS_PER_CU / 1280 / granules : 32;
-    return (uint32_t)(w < 32 ? w : 32);                     // a compute unit holds 32 wavefronts at most
+    const uint32_t g = plan_granules(x.kp[1].lds_bytes), w = g ? PLAN_GRANULES / g : 16;
+    return w < 16 ? w : 16;
 }
 
-// The plan for cfg.  With variant 0 the library chooses: a trace replays 1.3 to 2.5 times as fast on the
-// flat variant (its lists are in LDS; the stitching kernel alone, both with all tables in LDS: fragmentation
-// limit study 64x20000 8.8 against 11.8 ms, scale-out 320x20000 9.0 against 13.7, recomputation 1024x20000
-// 8.4 against 21.0), but when the batch does not fit the compute units at once and
-// the fine-grained variant holds at least 2.5 times as many traces per compute unit, the latter
-// finishes the batch sooner.  With table_place 0 it chooses where the fine-grained variant keeps the
-// tables of the sBlocks: throughput grows almost in proportion to the wavefronts per compute unit
-// (measured from 4 to 9) while a wavefront with tables in the workspace is slower, so the workspace it
-// is when the LDS layout leaves fewer than two wavefronts per SIMD and the batch then takes fewer
-// rounds of wavefronts by more than the wavefronts lose.
+// What a batch costs under plan x, in tenths of what one round of wavefronts of the flat variant takes.
+// A round of the fine-grained variant takes 1.25 to 1.6 of that on streams of many small requests (LoRA, ZeRO-3;
+// 64 to 1,280 traces x 20,000: 8.8 to 12.2 ms against 7.1 to 7.7) and 2.3 to 2.9 where every request stitches
+// (recomputation, 64 to 4,096 traces: 17.1 to 23.6 against 7.3 to 8.2); what is known beforehand of the two is
+// that the former hold more than 64 blocks at once.  Sblock tables in the workspace: 5 to 10 % more (offloading
+// 1024x20000 58.6 -> 64.7 ms, ZeRO-3 11.8 -> 12.4); with two tables there instead of three it is not less
+// (offloading 4096x50000 391 against 366 ms), so that place is taken on request only.
+// The splitting kernel beside it takes 0.65 of a round (5 of 7.5 ms) and runs in the LDS that the stitching
+// wavefronts leave, or behind them; a batch of several rounds costs its wavefronts' share of the LDS times how
+// long they hold it, and half a round for the tail.
+inline uint64_t plan_cost(const ReplayPlan &x, const vms_config &c)
+{
+    const uint64_t round = !x.fine ? 100 : (x.slot_regs ? 260 : 160) * (x.tbl_ws ? 106 : 100) / 100;
+    const uint64_t n = c.n_traces, w = plan_waves_per_cu(x), all = (uint64_t)PLAN_CUS * PLAN_GRANULES;
+    if (!w) return ~0ull;
+    const uint64_t lds = plan_granules(x.kp[1].lds_bytes), g = lds > PLAN_GRANULES / 16 ? lds : PLAN_GRANULES / 16;
+    const uint64_t g_split = c.policy_mask & VMS_POLICY_SPLIT ? plan_granules(x.kp[0].lds_bytes) : 0;
+    if (n > PLAN_CUS * w) return n * (g * round + g_split * 65) / all + round / 2;
+    if (!g_split) return round;
+    const uint64_t room = n * lds < all ? (all - n * lds) / g_split : 0;
+    const uint64_t behind = round + (n * g_split + all - 1) / all * 65, beside = room ? (n + room - 1) / room * 65 : behind;
+    const uint64_t split = beside < behind ? beside : behind;
+    return split > round ? split : round;
+}
+
+// The plan for cfg.  With variant 0 and tables that both variants serve the library chooses between them, and
+// with table_place 0 whether the fine-grained variant keeps the tables of the sBlocks in LDS or, where that leaves
+// fewer than two wavefronts per SIMD, in the workspace: whichever plan the batch costs least under.  (Scale-out
+// 320x20000 11.0 -> 7.5 ms, fragmentation limit study 64x20000 9.2 -> 7.1, both fine-grained before because their
+// presets said so; recomputation 2048x20000 22.9 -> 15.8, fine-grained before because the batch did not fit at once.)
 inline int replay_plan_make(const vms_config *cfg, ReplayPlan &p)
 {
     int rc = replay_plan_for(cfg, p);
     if (rc != VMS_OK || !cfg || !(cfg->policy_mask & VMS_POLICY_VMS)) return rc;
-    const uint32_t CUS = 256;
-    if (cfg->variant == VMS_VARIANT_AUTO && !p.fine) {
+    const bool other = cfg->variant == VMS_VARIANT_AUTO && !p.fine;
+    uint64_t best = plan_cost(p, *cfg);
+    auto consider = [&](uint32_t place) {
         vms_config alt = *cfg;
         alt.variant = VMS_VARIANT_FINE;
+        alt.table_place = place;
         ReplayPlan q;
-        if (replay_plan_for(&alt, q) == VMS_OK) {
-            const uint32_t flat = plan_waves_per_cu(p), fine = plan_waves_per_cu(q);
-            if ((uint64_t)cfg->n_traces > (uint64_t)CUS * flat && 2 * fine >= 5 * flat) p = q;
+        if (replay_plan_for(&alt, q) != VMS_OK) return false;
+        const uint64_t c = plan_cost(q, *cfg);
+        if (c < best) {
+            best = c;
+            p = q;
         }
-    }
-    if (p.fine && !p.wide && cfg->table_place == VMS_TABLES_AUTO) {
-        // rounds of wavefronts the batch takes, times what a wavefront pays for tables in the workspace
-        // (1.2 with two tables there, 1.45 with all three: measured on offloading traces when these tables were
-        // read past the vector cache and moved in two groups.  Now, on scale-out 320x20000 with every trace
-        // resident, 1.11 and 1.06; offloading 4096x50000 takes 534 ms with the tables in LDS, 385 with two and
-        // 380 with all three in the workspace, where this rule chooses two.)
-        auto cost = [&](const ReplayPlan &x, uint32_t tenths) {
-            const uint64_t slots = (uint64_t)CUS * plan_waves_per_cu(x);
-            return ((cfg->n_traces + slots - 1) / slots) * tenths;
-        };
-        uint64_t best = cost(p, 100);
-        if (plan_waves_per_cu(p) < 8)
-            for (uint32_t place = VMS_TABLES_WORKSPACE; place <= VMS_TABLES_WORKSPACE_ALL; place++) {
-                vms_config alt = *cfg;
-                alt.variant = VMS_VARIANT_FINE;
-                alt.table_place = place;
-                ReplayPlan q;
-                if (replay_plan_for(&alt, q) != VMS_OK) continue;
-                const uint64_t c = cost(q, place == VMS_TABLES_WORKSPACE ? 120 : 145);
-                if (c < best) {
-                    best = c;
-                    p = q;
-                }
-            }
+        return plan_waves_per_cu(q) < 8 && !q.wide;
+    };
+    if (!other && !p.fine) return VMS_OK;
+    if (cfg->table_place != VMS_TABLES_AUTO) {
+        if (other) consider(cfg->table_place);
+    } else if (consider(VMS_TABLES_LDS)) {
+        consider(VMS_TABLES_WORKSPACE_ALL);
     }
     return VMS_OK;
 }

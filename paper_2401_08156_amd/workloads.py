@@ -19,22 +19,19 @@ TABLES = {
     2: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3840, max_chunks=4096),
     # offloading grinds pBlocks down to single chunks: thousands of pBlocks and sBlocks (the fine-grained kernel
     # variant: single chunks in bitmaps, a table for the pBlocks of two or more chunks, lists in the workspace)
-    # (LDS is handed out in 1,280-byte granules, 128 per compute unit.  With all tables in LDS 30,960 B per wavefront,
-    # five per compute unit; with two tables in the workspace, as the library places them for this batch, 20,400 B,
-    # eight.  Multi-chunk pBlocks: 2,421 to 2,824 at most over 13 seeds; seven of them send one or two traces through
-    # the second pass.  Places for all would take a seventeenth granule: seven wavefronts per compute unit)
-    3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2592, max_sblocks=2560, max_runs=1 << 18, max_chunks=10240),
-    # (the fine-grained kernel with its sBlock tables in the workspace, chunk tables for the 17,699 chunks the
-    # largest trace reserves: 19.5 KB of LDS per wavefront, eight per compute unit instead of the flat kernel's
-    # three; the stitching kernel alone 79 ms, 97 with the tables in LDS, 125 on the flat kernel)
-    4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432,
-            variant=2, table_place=3),
-    # (the same for the 1,280 traces of the scale-out regime, 9,408 chunks at most: 23,040 B, which is 18 LDS granules
-    # exactly, all traces resident at once; the stitching kernel alone 16.1 ms, 18.4 on the flat kernel, and 15.2 with
-    # the tables in LDS, 26,976 B, which leave the splitting kernel beside it half the room.  pBlocks: 497 to 534 at
-    # most over 12 seeds; with 512 places, in the same 18 granules, four of those seeds sent a trace through the
-    # second pass, alone and from its first event)
-    6: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3072, max_chunks=9728, variant=2, table_place=3),
+    # (LDS is handed out in 1,280-byte granules, 128 per compute unit.  Multi-chunk pBlocks: 2,421 to 2,824 at most over
+    # 13 seeds.  2,848 places are what five wavefronts per compute unit have room for with all tables in LDS, 31,984 B,
+    # where the library puts them for up to 1,280 traces; beyond that the tables of the sBlocks are in the workspace and
+    # a wavefront takes 16,144 B.  With 2,592 places seven of the 13 seeds sent one or two traces through the second
+    # pass, 140 ms on 388)
+    3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2848, max_sblocks=2560, max_runs=1 << 18, max_chunks=10240),
+    # (up to 512 traces on the flat kernel, 49,616 B; the fine-grained one beyond that, and with its sBlock tables in the
+    # workspace and 19,520 B, eight wavefronts per compute unit, where that saves a round; chunk tables for the 17,699
+    # chunks the largest trace reserves)
+    4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432),
+    # (the same for the scale-out regime, 9,408 chunks at most; 51,792 / 26,976 / 23,040 B.  pBlocks: 497 to 534 at most
+    # over 12 seeds; with 512 places, in as many granules, four of those seeds sent a trace through the second pass)
+    6: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3072, max_chunks=9728),
 }
 # config 5 mixes the generators of configs 2, 3 and 4 (trace i uses kind 2 + i mod 3) with twice the
 # events; replayed as three batches, one per kind, each with tables of its own
@@ -42,13 +39,11 @@ TABLES_5 = {
     2: dict(max_free_blocks=192, max_pblocks=640, max_sblocks=640, max_runs=5120, max_chunks=4096),
     # (the margins over the high-water marks are one to two per cent; a trace that outgrows a table is replayed
     # again by the second pass.  40,208 B of LDS per wavefront with every table in LDS, four wavefronts per compute
-    # unit; the library moves the sBlock tables to the workspace: 14,960 B, ten)
+    # unit; for more traces than that the library moves the sBlock tables to the workspace: 14,960 B, ten)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2720, max_sblocks=4128, max_runs=1 << 18, max_chunks=8480),
-    # (beside the other two batches the fine-grained kernel with its sBlock tables in the workspace, 19.9 KB of LDS
-    # per wavefront, finishes the step sooner than the flat one with 50.8 KB: 1,339 against 1,456 ms; 18,055
-    # chunks is the most a trace of this kind reserves)
-    4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=736, max_sblocks=576, max_runs=4224, max_chunks=18432,
-            variant=2, table_place=3),
+    # (18,055 chunks is the most a trace of this kind reserves; 19.9 KB of LDS per wavefront with the sBlock tables in the
+    # workspace, where the library puts them for the 5,461 traces of the workload)
+    4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=736, max_sblocks=576, max_runs=4224, max_chunks=18432),
 }
 
 
@@ -64,6 +59,10 @@ def make_config(binding, config, n_traces, n_events, max_slots, kind=None, **ove
     tables = TABLES_5[kind] if config == 5 else TABLES[config % 10]
     for k, v in tables.items():
         setattr(cfg, k, v)
+    if tables is TABLES[3] and 2304 < n_traces <= 2560:
+        # with 2,592 places a wavefront takes 15,120 B, ten per compute unit instead of nine: the batch in one round
+        # (2500x20000 85 ms instead of 127; a trace that needs more places goes through the second pass)
+        cfg.max_multi_pblocks = 2592
     # the tables hold the high-water marks of the seeded workloads with little headroom; a trace of
     # another seed that outgrows one is replayed a second time with doubled tables
     cfg.retry_traces = min(32, n_traces)

@@ -34,7 +34,14 @@ def lib():
         _lib.emu_replay.restype = ctypes.c_int
         _lib.emu_replay.argtypes = [vp, vp, vp, vp, vp, vp]
         _lib.emu_selftest.restype = ctypes.c_uint
+        _lib.emu_plan_lds.restype = ctypes.c_int
+        _lib.emu_plan_lds.argtypes = [vp]
     return _lib
+
+
+def plan(cfg):
+    """LDS bytes of a wavefront of the stitching kernel under the plan the library makes for cfg."""
+    return lib().emu_plan_lds(ctypes.byref(cfg))
 
 
 def replay(events, cfg, stats_dtype, n_events=None):

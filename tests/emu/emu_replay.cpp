@@ -189,6 +189,14 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
     return 0;
 }
 
+// LDS bytes of a wavefront of the stitching kernel under the plan the library makes for cfg, or a VMS_E* code
+int emu_plan_lds(const vms_config *cfg)
+{
+    ReplayPlan plan;
+    const int rc = replay_plan_make(cfg, plan);
+    return rc == VMS_OK ? (int)plan.kp[1].lds_bytes : rc;
+}
+
 // the wave primitives' self-test kernel on the host lanes: 0, its failure bits, or 0xFFFFFFFF if a guard band was written
 unsigned emu_selftest(void)
 {

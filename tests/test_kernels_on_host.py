@@ -154,9 +154,35 @@ def test_fine_grained_variant(kind, nt, ne, tables):
         check(ev, cfg, label="generator %d %s tables %d" % (kind, tables, place))
 
 
+@pytest.mark.parametrize("kind,nt,ne,kw", [
+    (1, 1, 2000, dict(spool_threshold=8)),
+    (1, 2, 1200, dict(frag_limit_bytes=8 * MiB, small_limit_bytes=512)),
+    (1, 2, 1200, dict(capacity_bytes=256 * MiB)),
+    (2, 1, 3000, dict(max_runs=700, spool_threshold=40, max_sblocks=128)),             # small arena: lists are squeezed
+    (4, 1, 14000, dict(max_runs=700, spool_threshold=16, max_sblocks=92)),             # the same under a slot table in LDS
+])
+def test_flat_variant(kind, nt, ne, kw):
+    ev, ms = tg.generate(kind, n_traces=nt, n_events=ne, seed=7 + kind)
+    check(ev, gpu_util.make_cfg(nt, ne, ms, policy_mask=2, variant=binding.VMS_VARIANT_FLAT, **kw), label="generator %d" % kind)
+
+
+# The library's choices cost no more than the others they were made among: flat while a batch fits the compute units
+# at once beside its splitting kernel, then the fine-grained variant, then its tables in the workspace
+@pytest.mark.parametrize("config,slots,sizes", [
+    (2, 64, [(1024, 34832), (2048, 34832), (3072, 8560), (4096, 8560)]),
+    (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2560, 15120), (4096, 16144)]),
+    (4, 650, [(64, 49616), (512, 49616), (1024, 23456), (1280, 23456), (4096, 19520)]),
+    (6, 1163, [(64, 51792), (512, 51792), (1024, 26976), (1280, 23040), (4096, 23040)])])
+def test_plan_of_a_batch_by_its_size(config, slots, sizes):
+    for n, lds in sizes:
+        out = emu.plan(workloads.make_config(binding, config, n, 20000, slots))
+        assert out == lds, (config, n, out)
+
+
 # slot tables in registers (up to 64 slots) and in LDS; a capacity that is reached, and an arena that is squeezed often
 @pytest.mark.parametrize("slots", [3, 64, 65, 300])
-@pytest.mark.parametrize("kw", [dict(policy_mask=1), dict(variant=2, capacity_bytes=192 * MiB),
+@pytest.mark.parametrize("kw", [dict(policy_mask=1), dict(variant=1), dict(variant=2, capacity_bytes=192 * MiB),
+                                dict(variant=1, spool_threshold=4, max_sblocks=128, max_runs=900),
                                 dict(variant=2, table_place=binding.VMS_TABLES_WORKSPACE_ALL, spool_threshold=4, max_sblocks=128, max_runs=160)])
 def test_events_that_follow_each_other_on_a_slot(slots, kw):
     ev, n = gpu_util.slot_reuse_traces(slots, 64 * 9, seed=slots)
