@@ -396,10 +396,13 @@ DI void blk_shift_down(T *a, u32 pos, u32 n)
 
 // The same moves for N arrays of 16-bit elements kept in GLOBAL memory (tables of the fine-grained
 // stitching kernel that do not fit the LDS budget).  Blocks are read with workgroup-scope loads (other
-// lanes of this wavefront wrote them; tbl_fence() first, so that their stores have arrived), G steps of
+// lanes of this wavefront wrote them; tbl_fence() first), G steps of
 // 64 blocks are on their way before the first store.  A step never reads a block that an earlier step
 // of the same call has written.
-DI void tbl_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); }
+// Stores of one wavefront and its later loads of the same places pass the vector cache in order, so a fence among
+// its own lanes asks for no wait (a workgroup-wide one, used before, waited for every store on its way to L2: the
+// stitching kernel alone on ZeRO-3 1280x20000 12.45 -> 11.9 ms, offloading and LoRA 4096x50000 no change).
+DI void tbl_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 DI Blk16 gblk_load(const uint16_t *a, u32 B)
 {
     const u64 *p = (const u64 *)a + 2 * (size_t)B;
