@@ -1399,12 +1399,9 @@ struct SecondPass {
 // side by side (tile_emit).
 // ---------------------------------------------------------------------------
 template <bool SLOT_REGS>
-__global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__restrict__ events,
-                                                        const u32 *__restrict__ n_events,
-                                                        u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats,
-                                                        char *__restrict__ workspace)
+DI void replay_vms_flat(char *lds, const KParams &P, const u64 *__restrict__ events, const u32 *__restrict__ n_events,
+                        u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats, char *__restrict__ workspace)
 {
-    WAVE_DYNAMIC_LDS(lds);
     const u32 lane = lane_id();
     const u32 trace = blockIdx.x;
     char *ws_slice = workspace + (size_t)trace * P.ws_stride;
@@ -1693,16 +1690,24 @@ __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__
     }
 }
 
+template <bool SLOT_REGS>
+__global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__restrict__ events,
+                                                        const u32 *__restrict__ n_events,
+                                                        u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats,
+                                                        char *__restrict__ workspace)
+{
+    WAVE_DYNAMIC_LDS(lds);
+    replay_vms_flat<SLOT_REGS>(lds, P, events, n_events, decisions, stats, workspace);
+}
+
 // ---------------------------------------------------------------------------
 // Replay under the splitting policy (Sec. 2.2), one wavefront per trace.  Both of its paths are
 // hot, so everything is inline and its few scalars stay in registers.
 // ---------------------------------------------------------------------------
 template <bool SLOT_REGS, u32 TILES, bool TAIL>
-__global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *__restrict__ events,
-                                                          const u32 *__restrict__ n_events, u64 *__restrict__ decisions,
-                                                          vms_trace_stats *__restrict__ stats)
+DI void replay_split(char *lds, const KParams &P, const u64 *__restrict__ events, const u32 *__restrict__ n_events,
+                     u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats)
 {
-    WAVE_DYNAMIC_LDS(lds);
     const u32 lane = lane_id();
     u32 trace = blockIdx.x;
     u32 *taken = (u32 *)&stats[2 * (size_t)P.n_traces];     // [0]: trace numbers the second pass has handed out
@@ -1825,4 +1830,36 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
     }
     wave_sync();
     } while (P.retry);
+}
+
+template <bool SLOT_REGS, u32 TILES, bool TAIL>
+__global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *__restrict__ events,
+                                                          const u32 *__restrict__ n_events, u64 *__restrict__ decisions,
+                                                          vms_trace_stats *__restrict__ stats)
+{
+    WAVE_DYNAMIC_LDS(lds);
+    replay_split<SLOT_REGS, TILES, TAIL>(lds, P, events, n_events, decisions, stats);
+}
+
+// Both policies in one launch: a workgroup replays one trace, its first wavefront under the stitching policy (flat
+// variant), its second under the splitting policy, each in a part of the LDS of its own.  Nothing passes between
+// them.  Two launches need a second stream, which costs a fork and a join (3 traces x 61 events: 76 -> 53 us on the
+// device, 110 -> 78 for the caller) and which HIP may put on the hardware queue of the first, where the two kernels
+// then run in turn (one handle in three or four of a process that holds more than four streams: recomputation
+// 1024x20000 13.2 instead of 8.1 ms).
+template <bool SLOT_REGS, u32 TILES, bool TAIL>
+__global__ __launch_bounds__(128) void replay_both_kernel(KParams P, KParams P_split, const u64 *__restrict__ events,
+                                                          const u32 *__restrict__ n_events, u64 *__restrict__ dec_vms,
+                                                          u64 *__restrict__ dec_split, vms_trace_stats *__restrict__ stats,
+                                                          char *__restrict__ workspace)
+{
+    WAVE_DYNAMIC_LDS(lds);
+    if (wave_of_group() == 0) {
+        // (where four workgroups share a compute unit their first wavefronts share two of its SIMDs: ahead of the
+        // short wavefronts beside them, recomputation 1024x20000 8.68 -> 8.02 ms)
+        wave_priority<2>();
+        replay_vms_flat<SLOT_REGS>(lds, P, events, n_events, dec_vms, stats, workspace);
+    } else {
+        replay_split<SLOT_REGS, TILES, TAIL>(lds + P.lds_bytes, P_split, events, n_events, dec_split, stats);
+    }
 }

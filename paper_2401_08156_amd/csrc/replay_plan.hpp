@@ -51,6 +51,7 @@ struct ReplayPlan {
     bool fl_tail;                    // ... and the rest of them in LDS
     size_t ws_bytes;
     bool has_retry;                  // a second pass with the plan below follows the first
+    bool together;                   // both policies in one launch, a workgroup of two wavefronts per trace
 };
 
 namespace plan_detail {
@@ -258,12 +259,22 @@ inline uint64_t plan_cost(const ReplayPlan &x, const vms_config &c)
     return split > round ? split : round;
 }
 
+// Both policies in one launch where all its workgroups are resident at once: each holds the LDS of both its
+// wavefronts until the longer one, the stitching one, is done, so a batch of several rounds goes in two launches.
+inline bool plan_together(const ReplayPlan &x, const vms_config &c)
+{
+    const uint64_t lds = (uint64_t)x.kp[0].lds_bytes + x.kp[1].lds_bytes;
+    if (c.policy_mask != (VMS_POLICY_SPLIT | VMS_POLICY_VMS) || x.fine || lds > plan_detail::LDS_PER_CU) return false;
+    const uint32_t g = plan_granules((uint32_t)lds), w = PLAN_GRANULES / g;
+    return c.n_traces <= PLAN_CUS * (w < 8 ? w : 8);
+}
+
 // The plan for cfg.  With variant 0 and tables that both variants serve the library chooses between them, and
 // with table_place 0 whether the fine-grained variant keeps the tables of the sBlocks in LDS or, where that leaves
 // fewer than two wavefronts per SIMD, in the workspace: whichever plan the batch costs least under.  (Scale-out
 // 320x20000 11.0 -> 7.5 ms, fragmentation limit study 64x20000 9.2 -> 7.1, both fine-grained before because their
 // presets said so; recomputation 2048x20000 22.9 -> 15.8, fine-grained before because the batch did not fit at once.)
-inline int replay_plan_make(const vms_config *cfg, ReplayPlan &p)
+inline int replay_plan_choose(const vms_config *cfg, ReplayPlan &p)
 {
     int rc = replay_plan_for(cfg, p);
     if (rc != VMS_OK || !cfg || !(cfg->policy_mask & VMS_POLICY_VMS)) return rc;
@@ -289,6 +300,13 @@ inline int replay_plan_make(const vms_config *cfg, ReplayPlan &p)
         consider(VMS_TABLES_WORKSPACE_ALL);
     }
     return VMS_OK;
+}
+
+inline int replay_plan_make(const vms_config *cfg, ReplayPlan &p)
+{
+    const int rc = replay_plan_choose(cfg, p);
+    if (rc == VMS_OK) p.together = plan_together(p, *cfg);
+    return rc;
 }
 
 // The plan of the second pass for cfg: every table doubled, as far as the fine-grained variant and a

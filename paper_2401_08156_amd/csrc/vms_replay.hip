@@ -122,6 +122,7 @@ static int selftest_run()
 
 typedef void (*vms_fn)(KParams, const u64 *, const u32 *, u64 *, vms_trace_stats *, char *);
 typedef void (*split_fn)(KParams, const u64 *, const u32 *, u64 *, vms_trace_stats *);
+typedef void (*both_fn)(KParams, KParams, const u64 *, const u32 *, u64 *, u64 *, vms_trace_stats *, char *);
 
 // the kernel variants: flat sorted tables in LDS or the fine-grained layout (16- or 32-bit chunk
 // numbers; witness and list-place tables in LDS or in the workspace), slot table in LDS or registers
@@ -142,6 +143,13 @@ split_fn pick_split(const ReplayPlan &p)
     if (p.fl_tiles == 3) return p.slot_regs ? replay_split_kernel<true, 3, false> : replay_split_kernel<false, 3, false>;
     if (!p.fl_tail) return p.slot_regs ? replay_split_kernel<true, 5, false> : replay_split_kernel<false, 5, false>;
     return p.slot_regs ? replay_split_kernel<true, 5, true> : replay_split_kernel<false, 5, true>;
+}
+
+both_fn pick_both(const ReplayPlan &p)
+{
+    if (p.fl_tiles == 3) return p.slot_regs ? replay_both_kernel<true, 3, false> : replay_both_kernel<false, 3, false>;
+    if (!p.fl_tail) return p.slot_regs ? replay_both_kernel<true, 5, false> : replay_both_kernel<false, 5, false>;
+    return p.slot_regs ? replay_both_kernel<true, 5, true> : replay_both_kernel<false, 5, true>;
 }
 
 }  // namespace
@@ -210,6 +218,8 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)pick_vms(h->plan), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)LDS_PER_CU);
+    if (e == hipSuccess && h->plan.together)
+        e = hipFuncSetAttribute((const void *)pick_both(h->plan), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
     if (e == hipSuccess && h->retry.has_retry)
         e = hipFuncSetAttribute((const void *)pick_split(h->retry),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
@@ -245,13 +255,17 @@ int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_
     if ((c.policy_mask & VMS_POLICY_VMS) && h->ws_bytes && (!d_workspace || ((uintptr_t)d_workspace & 255)))
         return VMS_EWORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
-    // Fork: the two policies are independent, so the short splitting kernel runs on a second
-    // stream beside the long stitching kernel and the caller's stream joins it at the end.
+    // The two policies are independent: in one launch where that is planned, else the short splitting kernel
+    // runs on a second stream beside the long stitching kernel and the caller's stream joins it at the end.
     HIP_TRY(h, hipEventRecord(h->ev[0], st));
-    const bool both = c.policy_mask == (VMS_POLICY_SPLIT | VMS_POLICY_VMS);
+    const bool both = c.policy_mask == (VMS_POLICY_SPLIT | VMS_POLICY_VMS) && !h->plan.together;
     hipStream_t sst = both ? h->side : st;
     if (both) HIP_TRY(h, hipStreamWaitEvent(sst, h->ev[0], 0));
-    if (c.policy_mask & VMS_POLICY_VMS) {
+    if (h->plan.together) {
+        hipLaunchKernelGGL(pick_both(h->plan), dim3(c.n_traces), dim3(128), h->plan.kp[0].lds_bytes + h->plan.kp[1].lds_bytes, st,
+                           h->plan.kp[1], h->plan.kp[0], d_events, d_n_events, d_dec_vms, d_dec_split, h->d_stats, (char *)d_workspace);
+        HIP_TRY(h, hipGetLastError());
+    } else if (c.policy_mask & VMS_POLICY_VMS) {
         hipLaunchKernelGGL(pick_vms(h->plan), dim3(c.n_traces), dim3(64), h->plan.kp[1].lds_bytes, st, h->plan.kp[1],
                            d_events, d_n_events, d_dec_vms, h->d_stats, (char *)d_workspace);
         HIP_TRY(h, hipGetLastError());
@@ -263,20 +277,22 @@ int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_
                            d_events, d_n_events, d_dec_vms, h->d_stats, (char *)d_workspace);
         HIP_TRY(h, hipGetLastError());
     }
-    HIP_TRY(h, hipEventRecord(h->ev[2], sst));
-    if (c.policy_mask & VMS_POLICY_SPLIT) {
+    if (!h->plan.together) HIP_TRY(h, hipEventRecord(h->ev[2], sst));
+    if ((c.policy_mask & VMS_POLICY_SPLIT) && !h->plan.together) {
         hipLaunchKernelGGL(pick_split(h->plan), dim3(c.n_traces), dim3(64), h->plan.kp[0].lds_bytes, sst, h->plan.kp[0],
                            d_events, d_n_events, d_dec_split, h->d_stats);
         HIP_TRY(h, hipGetLastError());
     }
-    HIP_TRY(h, hipEventRecord(h->ev[3], sst));
+    if (!h->plan.together) HIP_TRY(h, hipEventRecord(h->ev[3], sst));
     if ((c.policy_mask & VMS_POLICY_SPLIT) && h->retry.has_retry) {
         hipLaunchKernelGGL(pick_split(h->retry), dim3(second_pass_waves(c)), dim3(64),
                            h->retry.kp[0].lds_bytes, sst, h->retry.kp[0], d_events, d_n_events, d_dec_split, h->d_stats);
         HIP_TRY(h, hipGetLastError());
     }
-    HIP_TRY(h, hipEventRecord(h->ev[5], sst));
-    if (both) HIP_TRY(h, hipStreamWaitEvent(st, h->ev[5], 0));
+    if (both) {
+        HIP_TRY(h, hipEventRecord(h->ev[5], sst));
+        HIP_TRY(h, hipStreamWaitEvent(st, h->ev[5], 0));
+    }
     HIP_TRY(h, hipEventRecord(h->ev[4], st));
     h->last_stream = st;
     h->ran = true;
@@ -333,7 +349,8 @@ int vms_replay_last_kernel_ms(vms_replay *h, float out_ms[3])
     if (!h->ran) return VMS_ESTATE;
     HIP_TRY(h, hipEventSynchronize(h->ev[4]));
     HIP_TRY(h, hipEventElapsedTime(&out_ms[1], h->ev[0], h->ev[1]));
-    HIP_TRY(h, hipEventElapsedTime(&out_ms[0], h->ev[2], h->ev[3]));
+    if (h->plan.together) out_ms[0] = out_ms[1];
+    else HIP_TRY(h, hipEventElapsedTime(&out_ms[0], h->ev[2], h->ev[3]));
     HIP_TRY(h, hipEventElapsedTime(&out_ms[2], h->ev[0], h->ev[4]));
     return VMS_OK;
 }

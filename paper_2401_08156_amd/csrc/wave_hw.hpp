@@ -1,7 +1,7 @@
 // Wavefront-wide primitives for gfx950 (wave64): the ones that name the hardware (lane
-// numbers, ballots, lane reads and writes, DPP reductions, fences).  Every workgroup of the
-// replay kernels is exactly one wavefront, so "the wave" and "the workgroup" coincide and all
-// of these must be called from wave-uniform control flow (EXEC full).
+// numbers, ballots, lane reads and writes, DPP reductions, fences).  A replay is the work of one
+// wavefront; where two share a workgroup they have nothing in common but the launch.  All of these
+// must be called from wave-uniform control flow (EXEC full).
 #ifndef VMS_WAVE_HW_HPP
 #define VMS_WAVE_HW_HPP
 #include <hip/hip_runtime.h>
@@ -12,7 +12,9 @@ typedef uint64_t u64;
 
 #define DI __device__ __forceinline__
 
-DI u32 lane_id() { return threadIdx.x; }
+DI u32 lane_id() { return threadIdx.x & 63; }
+// which wavefront of its workgroup this is, wave-uniform
+DI u32 wave_of_group() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // the wavefront's dynamically sized LDS (a kernel declares it once, at function scope)
 #define WAVE_DYNAMIC_LDS(name) extern __shared__ __attribute__((aligned(16))) char name[]

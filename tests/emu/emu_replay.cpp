@@ -12,6 +12,7 @@
 
 namespace emu {
 int cur;
+u32 wave;
 ucontext_t ctx[LANES], back;
 u64 xchg[2][LANES];
 u64 n_coll;
@@ -89,7 +90,7 @@ struct Guarded {
 };
 
 struct Args {
-    KParams P;
+    KParams P, P_split;
     const u64 *events;
     const u32 *n_events;
     u64 *dec;
@@ -125,6 +126,20 @@ void body_split(void *p)
     case 3: replay_split_kernel<false, 5, true>(a.P, a.events, a.n_events, a.dec, a.stats); break;
     case 4: replay_split_kernel<true, 5, false>(a.P, a.events, a.n_events, a.dec, a.stats); break;
     case 5: replay_split_kernel<false, 5, false>(a.P, a.events, a.n_events, a.dec, a.stats); break;
+    }
+}
+
+// both policies in one launch: only the wavefront emu::wave of the workgroup runs
+void body_both(void *p)
+{
+    Args &a = *(Args *)p;
+    switch (a.variant) {
+    case 0: replay_both_kernel<true, 3, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
+    case 1: replay_both_kernel<false, 3, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
+    case 2: replay_both_kernel<true, 5, true>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
+    case 3: replay_both_kernel<false, 5, true>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
+    case 4: replay_both_kernel<true, 5, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
+    case 5: replay_both_kernel<false, 5, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
     }
 }
 
@@ -171,13 +186,22 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
             a.P = pl.kp[pol];
             if (pol) a.variant = pl.fine ? (pl.wide ? 4 : pl.tbl_ws == 3 ? 8 : pl.tbl_ws ? 6 : 2) + (pl.slot_regs ? 0 : 1) : (pl.slot_regs ? 0 : 1);
             else a.variant = (pl.fl_tiles == 3 ? 0 : pl.fl_tail ? 2 : 4) + (pl.slot_regs ? 0 : 1);
+            const bool together = plan.together && !pass;
+            if (together) {
+                a.P = plan.kp[1];
+                a.P_split = plan.kp[0];
+                a.variant = (plan.fl_tiles == 3 ? 0 : plan.fl_tail ? 2 : 4) + (plan.slot_regs ? 0 : 1);
+                emu::wave = pol ? 0 : 1;
+            }
+            // this wavefront's part of the LDS
+            const size_t lds_from = together && !pol ? plan.kp[1].lds_bytes : 0, lds_to = lds_from + pl.kp[pol].lds_bytes;
             // the second pass is a launch of retry_traces wavefronts that share out the flagged traces
             const u32 waves = pass ? std::min(cfg->retry_traces, cfg->n_traces) : cfg->n_traces;
             for (u32 t = 0; t < waves; t++) {
                 memset(lds, CANARY, sizeof lds);
-                emu::launch(pol ? body_vms : body_split, &a, t);
-                for (size_t i = a.P.lds_bytes; i < sizeof lds; i++)
-                    if ((unsigned char)lds[i] != CANARY) return -101;
+                emu::launch(together ? body_both : pol ? body_vms : body_split, &a, t);
+                for (size_t i = 0; i < sizeof lds; i++)
+                    if ((i < lds_from || i >= lds_to) && (unsigned char)lds[i] != CANARY) return -101;
             }
         }
         if (!g_dec.intact()) return -102;

@@ -31,6 +31,7 @@ namespace emu {
 struct Dim { u32 x; };
 const int LANES = 64;
 extern int cur;                     // the lane that is running
+extern u32 wave;                    // which wavefront of its workgroup is running (they run one after the other)
 extern ucontext_t ctx[LANES], back;
 extern u64 xchg[2][LANES];
 extern u64 n_coll;                  // collectives passed so far (the same in every lane when it matters)
@@ -61,6 +62,7 @@ extern emu::Dim blockIdx;
 extern char lds[];
 
 DI u32 lane_id() { return (u32)emu::cur; }
+DI u32 wave_of_group() { return emu::wave; }
 DI void wave_sync() { emu::coll_of[emu::cur]++; emu::switch_lane(); }
 DI void wave_lockstep() { emu::coll_of[emu::cur]++; emu::switch_lane(); }
 #define __builtin_amdgcn_fence(order, scope) wave_sync()

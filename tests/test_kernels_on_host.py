@@ -166,6 +166,16 @@ def test_flat_variant(kind, nt, ne, kw):
     check(ev, gpu_util.make_cfg(nt, ne, ms, policy_mask=2, variant=binding.VMS_VARIANT_FLAT, **kw), label="generator %d" % kind)
 
 
+# both policies in one launch: slot table in registers and in LDS, the splitting pool in three and five registers per
+# lane and beyond; the wavefronts' parts of the LDS are told apart by guard bytes
+@pytest.mark.parametrize("kind,free", [(2, 192), (2, 320), (2, 512), (4, 192), (4, 320), (1, 512)])
+def test_both_policies_in_one_launch(kind, free):
+    ev, ms = tg.generate(kind, n_traces=2, n_events=1000, seed=3)
+    ev = ev[:, :1000]
+    check(ev, gpu_util.make_cfg(2, 1000, ms, variant=binding.VMS_VARIANT_FLAT, max_free_blocks=free, retry_traces=1),
+          n_events=np.array([1000, 937], dtype=np.uint32), label="generator %d, %d free blocks" % (kind, free))
+
+
 # The library's choices cost no more than the others they were made among: flat while a batch fits the compute units
 # at once beside its splitting kernel, then the fine-grained variant, then its tables in the workspace
 @pytest.mark.parametrize("config,slots,sizes", [
