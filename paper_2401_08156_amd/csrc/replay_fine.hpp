@@ -1067,7 +1067,7 @@ DI bool fine_alloc_cold(char *lds, FineT<IDX, TH> &V, const KParams &P, u32 bsiz
 // The kernel: same event loop, slot table, small-request pool and per-tile accounting as
 // replay_vms_kernel; the pools are the ones above.  IDX: the type of a chunk number.
 // ---------------------------------------------------------------------------
-template <bool SLOT_REGS, class IDX, int TH>
+template <int SLOTS, class IDX, int TH>
 __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u64 *__restrict__ events,
                                                              const u32 *__restrict__ n_events,
                                                              u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats,
@@ -1089,8 +1089,8 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
         ws_slice = workspace + P.retry_ws_off + (size_t)blockIdx.x * P.ws_stride;
     }
 
-    SlotsT<SLOT_REGS, true, u16> S;
-    S.init(lds, P);
+    SlotsT<SLOTS, true, u16> S;
+    S.init(lds, P, blockIdx.x);
     ((u32 *)(lds + LDS_SCALARS))[lane] = lane == SC_FIRST_OOM || lane == SC_OVF_EVENT ? NONE32 : 0u;     // LDS header
     FineT<IDX, TH> V;
     V.pool = (pkey_t *)(lds + P.off_pool);

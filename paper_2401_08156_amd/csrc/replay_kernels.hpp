@@ -87,28 +87,43 @@ struct AcctLds {
 // An event asks at() where its slot's record is (readable with get_*() until the event ends) and ends in one
 // of free_done(), alloc_done(), failed() and not_done(), which also note what the decision word and the totals
 // of the event are made of; tile_end() hands these over once per 64 events.
-// With at most 64 slots (REGS) the table is four registers, slot s in lane s.  Else it is in LDS, and a
-// tile of events works on records in registers: lane j takes a copy of its event's record when the tile
-// begins, keeps what the event makes of it, and knows the last lane before it with the same slot (`prev`),
-// whose record is the current one then; the last event of each slot puts its record back when the tile ends.
-// So an event never waits for the table, and stores nothing; per event the look-ups cost three dependent
-// LDS round trips and up to seven stores before (alone: the splitting kernel on LoRA 2048x20000 7.25 -> 6.18 ms,
-// on one random trace 0.637 -> 0.529; the stitching kernel on ZeRO-3 1280x20000 13.4 -> 12.5, on LoRA
-// 4096x50000 62 -> 58).
+// With at most 64 slots (SLOTS_IN_REGS) the table is four registers, slot s in lane s.  Else a tile of events
+// works on records in registers: lane j takes a copy of its event's record when the tile begins, keeps what the
+// event makes of it, and knows the last lane before it with the same slot (`prev`), whose record is the current
+// one then; the last event of each slot puts its record back when the tile ends.  So an event never waits for
+// the table, and stores nothing; per event the look-ups cost three dependent LDS round trips and up to seven
+// stores before (alone: the splitting kernel on LoRA 2048x20000 7.25 -> 6.18 ms, on one random trace 0.637 ->
+// 0.529; the stitching kernel on ZeRO-3 1280x20000 13.4 -> 12.5, on LoRA 4096x50000 62 -> 58).
+// The table itself is asked once per 64 events, so it need not be near: it is in global memory (SLOTS_IN_MEM),
+// one record of 16 bytes (splitting policy: 8) per slot, read with one load per lane that is on its way while
+// the lanes find their `prev`.  The 10 to 20 KB of LDS it took per wavefront leave room for others (whole pass:
+// LoRA 4096x50000 75 -> 55 ms, 1024x20000 12.5 -> 7.8, ZeRO-3 1280x20000 12.6 -> 12.2, the splitting policy alone on
+// LoRA 2048x20000 6.69 -> 6.50).  Where that room is not needed it stays in LDS (SLOTS_IN_LDS): the flat variant is 1 to
+// 2 % faster so.
 // ---------------------------------------------------------------------------
-template <bool REGS, bool VMS, class LIST>
+template <int WHERE, bool VMS, class LIST>
 struct SlotsT {
+    static constexpr bool REGS = WHERE == SLOTS_IN_REGS, MEM = WHERE == SLOTS_IN_MEM;
+    struct alignas(VMS ? 16 : 8) Rec {
+        u32 w[VMS ? 4 : 2];
+    };
     u32 req, a, b, c;           // the table (REGS), or the records of the tile's events
     u32 v_dlo, v_dhi, v_req, v_act;         // the events' decision words and what they added to the totals
     u32 *t_req, *t_a, *t_b;     // the table in LDS
     LIST *t_c;
+    Rec *tab;                   // the table in global memory
     u32 n_slots;
     u32 prev, slot, old_req;    // per lane: see above; the slot; what req was when the tile began
-    DI void init(char *lds, const KParams &P)
+    // slice: which slice of the launch's tables in global memory is this wavefront's
+    DI void init(char *lds, const KParams &P, u32 slice)
     {
         req = a = b = c = 0;
         n_slots = P.max_slots;
-        if constexpr (!REGS) {
+        if constexpr (MEM) {
+            tab = (Rec *)(P.mem + (size_t)slice * P.mem_stride);
+            for (u32 i = lane_id(); i < n_slots; i += 64) tab[i] = Rec{};
+            wave_sync();
+        } else if constexpr (!REGS) {
             t_req = (u32 *)(lds + P.off_slot_req);
             t_a = (u32 *)(lds + P.off_slot_a);
             t_b = (u32 *)(lds + P.off_slot_b);
@@ -135,6 +150,9 @@ struct SlotsT {
         v_dlo = v_dhi = v_req = v_act = 0;
         if constexpr (!REGS) {
             slot = lane < n && exists ? ev_hi : n_slots;
+            const u32 i = min(slot, n_slots - 1);
+            Rec r;
+            if constexpr (MEM) r = tab[i];      // (on its way while `prev` is found)
             // the last lane before this one with the same slot: key is slot * 128 + lane, so key - key' - 1 is
             // below 63 exactly for the same slot in an earlier lane, and smallest for the last of those
             const u32 key = (slot << 7) | lane;
@@ -145,12 +163,20 @@ struct SlotsT {
 #pragma unroll STEP
             for (u32 i = 0; i < 63; i++) d = min(d, key - 1 - from_lane(key, i));
             prev = d < 63 ? lane - 1 - d : lane;
-            const u32 i = min(slot, n_slots - 1);
-            req = t_req[i];
-            a = t_a[i];
-            if constexpr (VMS) {
-                b = t_b[i];
-                c = t_c[i];
+            if constexpr (MEM) {
+                req = r.w[0];
+                a = r.w[1];
+                if constexpr (VMS) {
+                    b = r.w[2];
+                    c = r.w[3];
+                }
+            } else {
+                req = t_req[i];
+                a = t_a[i];
+                if constexpr (VMS) {
+                    b = t_b[i];
+                    c = t_c[i];
+                }
             }
             old_req = req;
         }
@@ -235,11 +261,22 @@ struct SlotsT {
             // arrives there is from the lanes that name none)
             const u32 later = to_lane(prev != lane ? 1u : 0u, prev != lane ? prev : 63u);
             if (slot < n_slots && (lane == 63 || later == 0)) {
-                t_req[slot] = req;
-                t_a[slot] = a;
-                if constexpr (VMS) {
-                    t_b[slot] = b;
-                    t_c[slot] = (LIST)c;
+                if constexpr (MEM) {
+                    Rec r;
+                    r.w[0] = req;
+                    r.w[1] = a;
+                    if constexpr (VMS) {
+                        r.w[2] = b;
+                        r.w[3] = c;
+                    }
+                    tab[slot] = r;
+                } else {
+                    t_req[slot] = req;
+                    t_a[slot] = a;
+                    if constexpr (VMS) {
+                        t_b[slot] = b;
+                        t_c[slot] = (LIST)c;
+                    }
                 }
             }
             wave_sync();
@@ -256,9 +293,24 @@ struct SlotsT {
         if constexpr (!REGS) {
             for (u32 base = 0; base < n_slots; base += 64) {
                 const u32 i = min(base + lane_id(), n_slots - 1);
-                const u32 r = t_req[i], tb = t_b[i], tc = t_c[i], now = moved_to(t_a[i], tb, tc);
+                u32 r, ta, tb, tc;
+                if constexpr (MEM) {
+                    const Rec x = tab[i];
+                    r = x.w[0];
+                    ta = x.w[1];
+                    tb = x.w[2];
+                    tc = x.w[3];
+                } else {
+                    r = t_req[i];
+                    ta = t_a[i];
+                    tb = t_b[i];
+                    tc = t_c[i];
+                }
+                const u32 now = moved_to(ta, tb, tc);
                 wave_lockstep();
-                t_c[i] = (LIST)(r + 1u > 1u && (tb & 3) == KIND_SBLOCK ? now : tc);
+                const u32 place = r + 1u > 1u && (tb & 3) == KIND_SBLOCK ? now : tc;
+                if constexpr (MEM) tab[i].w[3] = place;
+                else t_c[i] = (LIST)place;
             }
             wave_sync();
         }
@@ -1389,7 +1441,7 @@ struct SecondPass {
 
 // ---------------------------------------------------------------------------
 // Replay under the stitching policy (Sec. 3, Sec. 4.1), one wavefront per trace.
-// SLOT_REGS: slot table in registers (max_slots <= 64).
+// SLOTS: where the slot table is (SLOTS_IN_REGS: max_slots <= 64).
 //
 // Per event only the allocator runs; the decision word and what the event added to the requested
 // and active units are parked in lane j of four registers, and where memory was reserved the lanes
@@ -1398,7 +1450,7 @@ struct SecondPass {
 // sums and maxima, count the decision codes and fold their event into the digest, all 64 events
 // side by side (tile_emit).
 // ---------------------------------------------------------------------------
-template <bool SLOT_REGS>
+template <int SLOTS>
 DI void replay_vms_flat(char *lds, const KParams &P, const u64 *__restrict__ events, const u32 *__restrict__ n_events,
                         u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats, char *__restrict__ workspace)
 {
@@ -1408,8 +1460,8 @@ DI void replay_vms_flat(char *lds, const KParams &P, const u64 *__restrict__ eve
     // a second pass follows for traces that outgrow these tables: it counts the traces it takes on
     if (P.retry_slots && trace == 0) ((u32 *)&stats[2 * (size_t)P.n_traces])[1] = 0;     // the second pass counts from 0
 
-    SlotsT<SLOT_REGS, true, u32> S;
-    S.init(lds, P);
+    SlotsT<SLOTS, true, u32> S;
+    S.init(lds, P, trace);
     ((u32 *)(lds + LDS_SCALARS))[lane] = lane == SC_FIRST_OOM || lane == SC_OVF_EVENT ? NONE32 : 0u;     // LDS header
     VmsT V;
     vms_bind(V, lds, ws_slice, P);
@@ -1690,21 +1742,21 @@ DI void replay_vms_flat(char *lds, const KParams &P, const u64 *__restrict__ eve
     }
 }
 
-template <bool SLOT_REGS>
+template <int SLOTS>
 __global__ __launch_bounds__(64) void replay_vms_kernel(KParams P, const u64 *__restrict__ events,
                                                         const u32 *__restrict__ n_events,
                                                         u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats,
                                                         char *__restrict__ workspace)
 {
     WAVE_DYNAMIC_LDS(lds);
-    replay_vms_flat<SLOT_REGS>(lds, P, events, n_events, decisions, stats, workspace);
+    replay_vms_flat<SLOTS>(lds, P, events, n_events, decisions, stats, workspace);
 }
 
 // ---------------------------------------------------------------------------
 // Replay under the splitting policy (Sec. 2.2), one wavefront per trace.  Both of its paths are
 // hot, so everything is inline and its few scalars stay in registers.
 // ---------------------------------------------------------------------------
-template <bool SLOT_REGS, u32 TILES, bool TAIL>
+template <int SLOTS, u32 TILES, bool TAIL>
 DI void replay_split(char *lds, const KParams &P, const u64 *__restrict__ events, const u32 *__restrict__ n_events,
                      u64 *__restrict__ decisions, vms_trace_stats *__restrict__ stats)
 {
@@ -1716,8 +1768,8 @@ DI void replay_split(char *lds, const KParams &P, const u64 *__restrict__ events
     do {        // once; the second pass: once per flagged trace this wavefront takes on
     if (P.retry && !W.next(P, stats, &taken[0], trace)) return;
 
-    SlotsT<SLOT_REGS, false, u32> S;
-    S.init(lds, P);
+    SlotsT<SLOTS, false, u32> S;
+    S.init(lds, P, blockIdx.x);
     SplitPool<TILES, TAIL> sp;
     sp.init(lds, P);
 
@@ -1832,13 +1884,13 @@ DI void replay_split(char *lds, const KParams &P, const u64 *__restrict__ events
     } while (P.retry);
 }
 
-template <bool SLOT_REGS, u32 TILES, bool TAIL>
+template <int SLOTS, u32 TILES, bool TAIL>
 __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *__restrict__ events,
                                                           const u32 *__restrict__ n_events, u64 *__restrict__ decisions,
                                                           vms_trace_stats *__restrict__ stats)
 {
     WAVE_DYNAMIC_LDS(lds);
-    replay_split<SLOT_REGS, TILES, TAIL>(lds, P, events, n_events, decisions, stats);
+    replay_split<SLOTS, TILES, TAIL>(lds, P, events, n_events, decisions, stats);
 }
 
 // Both policies in one launch: a workgroup replays one trace, its first wavefront under the stitching policy (flat
@@ -1847,7 +1899,7 @@ __global__ __launch_bounds__(64) void replay_split_kernel(KParams P, const u64 *
 // device, 110 -> 78 for the caller) and which HIP may put on the hardware queue of the first, where the two kernels
 // then run in turn (one handle in three or four of a process that holds more than four streams: recomputation
 // 1024x20000 13.2 instead of 8.1 ms).
-template <bool SLOT_REGS, u32 TILES, bool TAIL>
+template <int SLOTS, u32 TILES, bool TAIL>
 __global__ __launch_bounds__(128) void replay_both_kernel(KParams P, KParams P_split, const u64 *__restrict__ events,
                                                           const u32 *__restrict__ n_events, u64 *__restrict__ dec_vms,
                                                           u64 *__restrict__ dec_split, vms_trace_stats *__restrict__ stats,
@@ -1858,8 +1910,8 @@ __global__ __launch_bounds__(128) void replay_both_kernel(KParams P, KParams P_s
         // (where four workgroups share a compute unit their first wavefronts share two of its SIMDs: ahead of the
         // short wavefronts beside them, recomputation 1024x20000 8.68 -> 8.02 ms)
         wave_priority<2>();
-        replay_vms_flat<SLOT_REGS>(lds, P, events, n_events, dec_vms, stats, workspace);
+        replay_vms_flat<SLOTS>(lds, P, events, n_events, dec_vms, stats, workspace);
     } else {
-        replay_split<SLOT_REGS, TILES, TAIL>(lds + P.lds_bytes, P_split, events, n_events, dec_split, stats);
+        replay_split<SLOTS, TILES, TAIL>(lds + P.lds_bytes, P_split, events, n_events, dec_split, stats);
     }
 }

@@ -39,14 +39,21 @@ struct KParams {
     uint32_t retry;                  // this launch is that pass: traces without an overflow flag are left alone
     uint32_t retry_slots;            // traces it has workspace for
     uint64_t retry_ws_off;           // where that workspace starts (bytes from the start of the caller's workspace)
+    // tables in global memory of the handle: a slice of mem_stride bytes per wavefront of the launch: its slot table
+    char *mem;
+    uint64_t mem_stride;
 };
+
+// Where the slot table of a trace is: in LDS, in registers (at most 64 slots), in global memory of the handle
+enum { SLOTS_IN_LDS, SLOTS_IN_REGS, SLOTS_IN_MEM };
 
 struct ReplayPlan {
     KParams kp[2];                   // [0] splitting kernel, [1] stitching kernel
     bool fine;                       // stitching kernel: the fine-grained variant (lists in the workspace)
     bool wide;                       // fine-grained variant with 32-bit chunk numbers (more than 65,000 chunks)
     int tbl_ws;                      // fine-grained variant: 0 the sBlock tables in LDS; 2 witnesses and list places in the workspace; 3 sizes too
-    bool slot_regs;                  // slot table in registers (at most 64 slots)
+    bool slot_regs;                  // at most 64 slots
+    int slots;                       // SLOTS_IN_*
     uint32_t fl_tiles;               // splitting policy: places for inactive blocks in registers, per lane: 3 or 5 (see SplitPool)
     bool fl_tail;                    // ... and the rest of them in LDS
     size_t ws_bytes;
@@ -61,6 +68,9 @@ const uint64_t ENGINE_MAX_BYTES = 1ull << 39;       // 30-bit block addresses in
 const uint64_t LDS_PER_CU = 160 * 1024;
 const uint32_t TABLE_MAX = 1u << 24;                // upper bound of every per-trace table size
 
+inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
+inline bool is_pow2(uint64_t x) { return x && !(x & (x - 1)); }
+
 // what a pool whose blocks are not all in registers would take with all of them in LDS, beyond what it takes
 // there: counted against the compute unit's LDS, so that no table size is refused or accepted for where it lives
 inline uint64_t pool_bytes_saved(const KParams &k, int policy, const ReplayPlan &p)
@@ -68,9 +78,16 @@ inline uint64_t pool_bytes_saved(const KParams &k, int policy, const ReplayPlan 
     const uint32_t in_regs = 64 * (policy ? SMALL_TILES : p.fl_tiles);
     return k.cap_free <= in_regs ? 0 : (128ull + in_regs) * 8;
 }
-
-inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
-inline bool is_pow2(uint64_t x) { return x && !(x & (x - 1)); }
+// ... and what a slot table outside it would take there
+inline uint64_t slot_bytes_saved(uint32_t max_slots, int policy, const ReplayPlan &p)
+{
+    if (p.slots != SLOTS_IN_MEM) return 0;
+    const uint64_t words = align_up(4ull * max_slots, 16);
+    return policy ? 3 * words + align_up((p.fine ? 2ull : 4ull) * max_slots, 16) : 2 * words;
+}
+// bytes of a slot table in global memory
+inline uint64_t slot_table_bytes(uint32_t max_slots, int policy) { return align_up((uint64_t)max_slots * (policy ? 16 : 8), 16); }
+const uint64_t MEM_TABLES_MAX = 1ull << 30;         // bytes of global memory that the slot tables of a launch may take
 
 // Per-wave LDS layout, in 64-bit arithmetic (a table size that would wrap a 32-bit offset must end
 // as "too big", not as a small layout).  Returns the bytes needed.
@@ -86,7 +103,7 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
     k.off_pool = k.off_bmp = k.off_skey = k.off_smeta = k.off_sstamp = k.off_swit = k.off_tmp = k.off_arena = 0;
     k.off_bnd = k.off_soff = 0;
     if (policy) take(256);      // scalars of the trace (see replay_kernels.hpp)
-    if (!p.slot_regs) {
+    if (p.slots == SLOTS_IN_LDS) {
         k.off_slot_req = take((uint64_t)c.max_slots * 4);
         k.off_slot_a = take((uint64_t)c.max_slots * 4);
         k.off_slot_b = policy ? take((uint64_t)c.max_slots * 4) : 0;
@@ -101,7 +118,7 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
         k.off_bmp = take(((uint64_t)k.bmp_words + 1) * 4);      // and one spare word
         k.off_bnd = take(((uint64_t)k.bmp_words + 1) * 4);      // scans read one word ahead
         k.off_tmp = take(((uint64_t)k.bmp_words + 64) * 4);     // and 64 spare words
-        if (p.tbl_ws != 3) k.off_skey = take(((uint64_t)c.max_sblocks + 80) * idx);    // 64 spare places, and shifts move whole 16-byte blocks
+        if (p.tbl_ws < 3) k.off_skey = take(((uint64_t)c.max_sblocks + 80) * idx);    // 64 spare places, and shifts move whole 16-byte blocks
         if (!p.tbl_ws) {
             k.off_swit = take(((uint64_t)c.max_sblocks + 80) * idx);
             k.off_soff = take(((uint64_t)c.max_sblocks + 80) * 2);
@@ -126,7 +143,8 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
 // The plan for cfg with the variant it names (0: flat unless the tables are too large for it).
 // VMS_OK, VMS_EINVAL / VMS_ESTRUCT for a configuration that makes no sense, VMS_ETOOBIG for tables
 // that do not fit a compute unit's LDS.  Touches no device.
-inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
+// slots_in_mem: slot tables of more than 64 slots in global memory, unless they take too much of it.
+inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_mem)
 {
     using namespace plan_detail;
     if (!cfg) return VMS_EINVAL;
@@ -160,6 +178,8 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
     p.tbl_ws = p.fine && !p.wide && c.table_place >= VMS_TABLES_WORKSPACE ? (int)c.table_place : 0;
     if (c.table_place >= VMS_TABLES_WORKSPACE && p.fine && p.wide) return VMS_EINVAL;
     p.slot_regs = c.max_slots <= 64;
+    slots_in_mem = slots_in_mem && c.n_traces * slot_table_bytes(c.max_slots, 1) <= MEM_TABLES_MAX;
+    p.slots = p.slot_regs ? SLOTS_IN_REGS : slots_in_mem ? SLOTS_IN_MEM : SLOTS_IN_LDS;
     p.fl_tiles = c.max_free_blocks <= 192 ? 3u : 5u;
     p.fl_tail = c.max_free_blocks > 320;
     uint32_t shift = 0;
@@ -201,11 +221,12 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
             // behind them the two 16-bit tables, if they are kept here
             k.ws_half = align_up((((uint64_t)k.cap_grans << k.gran_shift) + 64) * 8, 256);
             k.ws_tbl_bytes = p.tbl_ws ? (uint32_t)align_up(((uint64_t)c.max_sblocks + 80) * 2, 256) : 0u;
-            k.ws_stride = 2 * k.ws_half + (uint64_t)p.tbl_ws * k.ws_tbl_bytes;          // (2 or 3 tables)
+            k.ws_stride = 2 * k.ws_half + (p.tbl_ws < 3 ? 2ull : 3ull) * k.ws_tbl_bytes;
         } else if (pol) {
             k.ws_stride = align_up(((uint64_t)c.max_runs + 64) * 4, 256);     // where compaction copies the lists
         }
-        const uint64_t need = layout(k, pol, c, p) + plan_detail::pool_bytes_saved(k, pol, p);
+        k.mem_stride = p.slots == SLOTS_IN_MEM ? slot_table_bytes(c.max_slots, pol) : 0;
+        const uint64_t need = layout(k, pol, c, p) + pool_bytes_saved(k, pol, p) + slot_bytes_saved(c.max_slots, pol, p);
         if ((c.policy_mask & (1u << pol)) && need > LDS_PER_CU) {
             // flat variant: the lists' places in a slot table in LDS are there for speed only; tables that fit
             // without them are served by the fine-grained variant
@@ -214,7 +235,7 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p)
             vms_config alt = c;
             alt.variant = VMS_VARIANT_FINE;
             alt.table_place = VMS_TABLES_AUTO;
-            return replay_plan_for(&alt, p);
+            return replay_plan_for(&alt, p, slots_in_mem);
         }
     }
     p.ws_bytes = (c.policy_mask & VMS_POLICY_VMS) ? (size_t)p.kp[1].ws_stride * c.n_traces : 0;
@@ -243,15 +264,23 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 // (offloading 4096x50000 391 against 366 ms), so that place is taken on request only.
 // The splitting kernel beside it takes 0.65 of a round (5 of 7.5 ms) and runs in the LDS that the stitching
 // wavefronts leave, or behind them; a batch of several rounds costs its wavefronts' share of the LDS times how
-// long they hold it, and half a round for the tail.
+// long they hold it, and half a round for the tail, but two rounds at least where each has a SIMD to itself and so
+// gains nothing from a round that is not full (ZeRO-3 1280x20000 on the flat variant, 1,024 of them at a time: 14.8 ms,
+// fine-grained 12.0).
+// A slot table in global memory costs the flat variant 1 to 2 % (one random trace 1.057 -> 1.069 ms, scale-out
+// 320x20000 7.58 -> 7.75).
 inline uint64_t plan_cost(const ReplayPlan &x, const vms_config &c)
 {
-    const uint64_t round = !x.fine ? 100 : (x.slot_regs ? 260 : 160) * (x.tbl_ws ? 106 : 100) / 100;
+    const uint64_t round = !x.fine ? 100 + (x.slots == SLOTS_IN_MEM ? 2 : 0)
+                                   : (x.slot_regs ? 260 : 160) * (x.tbl_ws ? 106 : 100) / 100;
     const uint64_t n = c.n_traces, w = plan_waves_per_cu(x), all = (uint64_t)PLAN_CUS * PLAN_GRANULES;
     if (!w) return ~0ull;
     const uint64_t lds = plan_granules(x.kp[1].lds_bytes), g = lds > PLAN_GRANULES / 16 ? lds : PLAN_GRANULES / 16;
     const uint64_t g_split = c.policy_mask & VMS_POLICY_SPLIT ? plan_granules(x.kp[0].lds_bytes) : 0;
-    if (n > PLAN_CUS * w) return n * (g * round + g_split * 65) / all + round / 2;
+    if (n > PLAN_CUS * w) {
+        const uint64_t shares = n * (g * round + g_split * 65) / all + round / 2;
+        return w > 4 || shares > 2 * round ? shares : 2 * round;
+    }
     if (!g_split) return round;
     const uint64_t room = n * lds < all ? (all - n * lds) / g_split : 0;
     const uint64_t behind = round + (n * g_split + all - 1) / all * 65, beside = room ? (n + room - 1) / room * 65 : behind;
@@ -269,6 +298,10 @@ inline bool plan_together(const ReplayPlan &x, const vms_config &c)
     return c.n_traces <= PLAN_CUS * (w < 8 ? w : 8);
 }
 
+// Up to this many traces of the splitting policy alone keep their slot tables in LDS (LoRA 64 and 512 x 20,000: no
+// difference; 1024: 5.84 ms there, 5.59 in global memory; 2048: 6.69 and 6.50)
+const uint32_t SPLIT_SLOTS_IN_LDS = 512;
+
 // The plan for cfg.  With variant 0 and tables that both variants serve the library chooses between them, and
 // with table_place 0 whether the fine-grained variant keeps the tables of the sBlocks in LDS or, where that leaves
 // fewer than two wavefronts per SIMD, in the workspace: whichever plan the batch costs least under.  (Scale-out
@@ -276,28 +309,33 @@ inline bool plan_together(const ReplayPlan &x, const vms_config &c)
 // presets said so; recomputation 2048x20000 22.9 -> 15.8, fine-grained before because the batch did not fit at once.)
 inline int replay_plan_choose(const vms_config *cfg, ReplayPlan &p)
 {
-    int rc = replay_plan_for(cfg, p);
-    if (rc != VMS_OK || !cfg || !(cfg->policy_mask & VMS_POLICY_VMS)) return rc;
+    int rc = replay_plan_for(cfg, p, false);
+    if (rc != VMS_OK || !cfg) return rc;
+    const bool stitch = cfg->policy_mask & VMS_POLICY_VMS;
+    if (!stitch) return cfg->n_traces > SPLIT_SLOTS_IN_LDS ? replay_plan_for(cfg, p, true) : rc;
     const bool other = cfg->variant == VMS_VARIANT_AUTO && !p.fine;
-    uint64_t best = plan_cost(p, *cfg);
-    auto consider = [&](uint32_t place) {
+    uint64_t best = ~0ull;
+    // takes the plan if it costs less
+    auto consider = [&](uint32_t variant, uint32_t place, bool slots_in_mem) {
         vms_config alt = *cfg;
-        alt.variant = VMS_VARIANT_FINE;
+        alt.variant = variant;
         alt.table_place = place;
         ReplayPlan q;
-        if (replay_plan_for(&alt, q) != VMS_OK) return false;
+        if (replay_plan_for(&alt, q, slots_in_mem) != VMS_OK) return;
         const uint64_t c = plan_cost(q, *cfg);
         if (c < best) {
             best = c;
             p = q;
         }
-        return plan_waves_per_cu(q) < 8 && !q.wide;
     };
+    if (!p.fine) consider(cfg->variant, cfg->table_place, false);
+    consider(cfg->variant, cfg->table_place, true);
     if (!other && !p.fine) return VMS_OK;
     if (cfg->table_place != VMS_TABLES_AUTO) {
-        if (other) consider(cfg->table_place);
-    } else if (consider(VMS_TABLES_LDS)) {
-        consider(VMS_TABLES_WORKSPACE_ALL);
+        if (other) consider(VMS_VARIANT_FINE, cfg->table_place, true);
+    } else {
+        consider(VMS_VARIANT_FINE, VMS_TABLES_LDS, true);
+        consider(VMS_VARIANT_FINE, VMS_TABLES_WORKSPACE_ALL, true);
     }
     return VMS_OK;
 }
@@ -328,7 +366,7 @@ inline int replay_plan_retry(const vms_config *cfg, const ReplayPlan &first, Rep
     while ((uint64_t)big.max_chunks * big.chunk_bytes > plan_detail::ENGINE_MAX_BYTES) big.max_chunks /= 2;
     // shrink towards the first pass's sizes until the tables fit
     for (int tries = 0; tries < 8; tries++) {
-        const int rc = replay_plan_for(&big, q);
+        const int rc = replay_plan_for(&big, q, first.slots == SLOTS_IN_MEM);
         if (rc == VMS_OK) {
             q.has_retry = true;
             for (int pol = 0; pol < 2; pol++) {

@@ -29,6 +29,7 @@ struct vms_replay {
     ReplayPlan retry;           // the same for the second pass over traces that outgrew the tables (has_retry)
     vms_trace_stats *d_stats;
     vms_summary *d_summary;
+    char *d_mem;                // tables in global memory: per policy those of the first pass, then those of the second
     hipEvent_t ev[6];           // run start, stitching kernel end, splitting kernel start / end, run end, side stream done
     hipStream_t side;           // the splitting kernel runs here, beside the stitching kernel
     hipStream_t last_stream;
@@ -125,32 +126,35 @@ typedef void (*split_fn)(KParams, const u64 *, const u32 *, u64 *, vms_trace_sta
 typedef void (*both_fn)(KParams, KParams, const u64 *, const u32 *, u64 *, u64 *, vms_trace_stats *, char *);
 
 // the kernel variants: flat sorted tables in LDS or the fine-grained layout (16- or 32-bit chunk
-// numbers; witness and list-place tables in LDS or in the workspace), slot table in LDS or registers
-vms_fn pick_vms(const ReplayPlan &p)
+// numbers; witness and list-place tables in LDS or in the workspace), each for every place of the slot table
+template <int SLOTS>
+vms_fn pick_vms_with(const ReplayPlan &p)
 {
-    if (p.fine) {
-        if (p.wide) return p.slot_regs ? replay_vms_fine_kernel<true, u32, 0> : replay_vms_fine_kernel<false, u32, 0>;
-        if (p.tbl_ws == 3) return p.slot_regs ? replay_vms_fine_kernel<true, u16, 3> : replay_vms_fine_kernel<false, u16, 3>;
-        if (p.tbl_ws) return p.slot_regs ? replay_vms_fine_kernel<true, u16, 2> : replay_vms_fine_kernel<false, u16, 2>;
-        return p.slot_regs ? replay_vms_fine_kernel<true, u16, 0> : replay_vms_fine_kernel<false, u16, 0>;
-    }
-    return p.slot_regs ? replay_vms_kernel<true> : replay_vms_kernel<false>;
+    if (!p.fine) return replay_vms_kernel<SLOTS>;
+    if (p.wide) return replay_vms_fine_kernel<SLOTS, u32, 0>;
+    if (p.tbl_ws == 3) return replay_vms_fine_kernel<SLOTS, u16, 3>;
+    return p.tbl_ws ? replay_vms_fine_kernel<SLOTS, u16, 2> : replay_vms_fine_kernel<SLOTS, u16, 0>;
 }
 // the splitting pool's inactive blocks: three or five register pairs per lane (tables of at most 192 or 320
 // blocks), or five and the rest in LDS
-split_fn pick_split(const ReplayPlan &p)
+template <int SLOTS>
+split_fn pick_split_with(const ReplayPlan &p)
 {
-    if (p.fl_tiles == 3) return p.slot_regs ? replay_split_kernel<true, 3, false> : replay_split_kernel<false, 3, false>;
-    if (!p.fl_tail) return p.slot_regs ? replay_split_kernel<true, 5, false> : replay_split_kernel<false, 5, false>;
-    return p.slot_regs ? replay_split_kernel<true, 5, true> : replay_split_kernel<false, 5, true>;
+    if (p.fl_tiles == 3) return replay_split_kernel<SLOTS, 3, false>;
+    return p.fl_tail ? replay_split_kernel<SLOTS, 5, true> : replay_split_kernel<SLOTS, 5, false>;
 }
-
-both_fn pick_both(const ReplayPlan &p)
+template <int SLOTS>
+both_fn pick_both_with(const ReplayPlan &p)
 {
-    if (p.fl_tiles == 3) return p.slot_regs ? replay_both_kernel<true, 3, false> : replay_both_kernel<false, 3, false>;
-    if (!p.fl_tail) return p.slot_regs ? replay_both_kernel<true, 5, false> : replay_both_kernel<false, 5, false>;
-    return p.slot_regs ? replay_both_kernel<true, 5, true> : replay_both_kernel<false, 5, true>;
+    if (p.fl_tiles == 3) return replay_both_kernel<SLOTS, 3, false>;
+    return p.fl_tail ? replay_both_kernel<SLOTS, 5, true> : replay_both_kernel<SLOTS, 5, false>;
 }
+#define PICK_BY_SLOTS(pick, p) \
+    ((p).slots == SLOTS_IN_REGS ? pick<SLOTS_IN_REGS>(p) : (p).slots == SLOTS_IN_MEM ? pick<SLOTS_IN_MEM>(p) : pick<SLOTS_IN_LDS>(p))
+vms_fn pick_vms(const ReplayPlan &p) { return PICK_BY_SLOTS(pick_vms_with, p); }
+split_fn pick_split(const ReplayPlan &p) { return PICK_BY_SLOTS(pick_split_with, p); }
+both_fn pick_both(const ReplayPlan &p) { return PICK_BY_SLOTS(pick_both_with, p); }
+#undef PICK_BY_SLOTS
 
 }  // namespace
 
@@ -175,6 +179,31 @@ void vms_config_default(vms_config *cfg, uint32_t n_traces, uint32_t max_events,
     cfg->max_sblocks = 640;
     cfg->max_runs = 4096;
     cfg->max_chunks = 32768;    // 64 GiB of 2 MiB chunks
+}
+
+static inline uint32_t second_pass_waves(const vms_config &c) { return c.retry_traces < c.n_traces ? c.retry_traces : c.n_traces; }
+
+// One allocation for the tables of all launches of a run that are in global memory: a wavefront writes its slice
+// before it reads it.
+static hipError_t alloc_tables(vms_replay *h)
+{
+    const vms_config &c = h->cfg;
+    size_t bytes = 0;
+    for (int set = 0; set < 2; set++) {
+        KParams *kp[2] = { h->plan.kp, h->retry.kp };
+        for (int pass = 0; pass < (h->retry.has_retry ? 2 : 1); pass++)
+            for (int pol = 0; pol < 2; pol++) {
+                if (!(c.policy_mask & (1u << pol))) continue;
+                KParams &k = kp[pass][pol];
+                if (set) k.mem = h->d_mem + bytes;
+                bytes += (k.mem_stride * (pass ? second_pass_waves(c) : c.n_traces) + 255) / 256 * 256;
+            }
+        if (set || !bytes) break;
+        const hipError_t e = hipMalloc((void **)&h->d_mem, bytes);
+        if (e != hipSuccess) return e;
+        bytes = 0;
+    }
+    return hipSuccess;
 }
 
 int vms_replay_create(const vms_config *cfg, vms_replay **out)
@@ -209,6 +238,7 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
     // records of a policy that never runs stay zero; a run rewrites every record of its policies
     if (e == hipSuccess) e = hipMemset(h->d_stats, 0, sizeof(vms_trace_stats) * (2 * (size_t)c.n_traces + 1));
     if (e == hipSuccess) e = hipMalloc((void **)&h->d_summary, sizeof(vms_summary));
+    if (e == hipSuccess) e = alloc_tables(h);
     for (int i = 0; i < 6 && e == hipSuccess; i++) e = hipEventCreate(&h->ev[i]);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     // LDS above 64 KB per workgroup has to be requested explicitly
@@ -244,8 +274,6 @@ int vms_replay_lds_bytes(const vms_replay *h, uint32_t out[2])
     out[1] = h->plan.kp[1].lds_bytes;
     return VMS_OK;
 }
-
-static inline uint32_t second_pass_waves(const vms_config &c) { return c.retry_traces < c.n_traces ? c.retry_traces : c.n_traces; }
 
 int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_events, uint64_t *d_dec_split,
                    uint64_t *d_dec_vms, void *d_workspace, void *hip_stream)
@@ -360,6 +388,7 @@ void vms_replay_destroy(vms_replay *h)
     if (!h) return;
     if (h->d_stats) (void)hipFree(h->d_stats);
     if (h->d_summary) (void)hipFree(h->d_summary);
+    if (h->d_mem) (void)hipFree(h->d_mem);
     for (int i = 0; i < 6; i++)
         if (h->ev[i]) (void)hipEventDestroy(h->ev[i]);
     if (h->side) (void)hipStreamDestroy(h->side);

@@ -18,7 +18,7 @@ _DEPS = [_SRC, os.path.join(_HERE, "wave_hw_emu.hpp")] + [
 def build(force=False):
     if not force and os.path.exists(_LIB) and all(os.path.getmtime(_LIB) >= os.path.getmtime(d) for d in _DEPS):
         return _LIB
-    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-unused", "-Wno-unknown-pragmas",
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-unused", "-Wno-unknown-pragmas", "-Wno-restrict",
                     "-o", _LIB, _SRC], check=True)
     return _LIB
 

@@ -96,52 +96,45 @@ struct Args {
     u64 *dec;
     vms_trace_stats *stats;
     char *ws;
-    int variant;
+    const ReplayPlan *plan;
 };
 
-void body_vms(void *p)
+// the kernel of a plan, as the library picks it
+template <int SLOTS>
+void vms_with(const ReplayPlan &p, Args &a)
 {
-    Args &a = *(Args *)p;
-    switch (a.variant) {
-    case 0: replay_vms_kernel<true>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 1: replay_vms_kernel<false>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 2: replay_vms_fine_kernel<true, uint16_t, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 3: replay_vms_fine_kernel<false, uint16_t, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 4: replay_vms_fine_kernel<true, u32, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 5: replay_vms_fine_kernel<false, u32, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 6: replay_vms_fine_kernel<true, uint16_t, 2>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 7: replay_vms_fine_kernel<false, uint16_t, 2>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 8: replay_vms_fine_kernel<true, uint16_t, 3>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    case 9: replay_vms_fine_kernel<false, uint16_t, 3>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws); break;
-    }
+    if (!p.fine) return replay_vms_kernel<SLOTS>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
+    if (p.wide) return replay_vms_fine_kernel<SLOTS, u32, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
+    if (p.tbl_ws == 3) return replay_vms_fine_kernel<SLOTS, uint16_t, 3>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
+    if (p.tbl_ws) return replay_vms_fine_kernel<SLOTS, uint16_t, 2>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
+    replay_vms_fine_kernel<SLOTS, uint16_t, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
 }
-
-void body_split(void *p)
+template <int SLOTS>
+void split_with(const ReplayPlan &p, Args &a)
 {
-    Args &a = *(Args *)p;
-    switch (a.variant) {
-    case 0: replay_split_kernel<true, 3, false>(a.P, a.events, a.n_events, a.dec, a.stats); break;
-    case 1: replay_split_kernel<false, 3, false>(a.P, a.events, a.n_events, a.dec, a.stats); break;
-    case 2: replay_split_kernel<true, 5, true>(a.P, a.events, a.n_events, a.dec, a.stats); break;
-    case 3: replay_split_kernel<false, 5, true>(a.P, a.events, a.n_events, a.dec, a.stats); break;
-    case 4: replay_split_kernel<true, 5, false>(a.P, a.events, a.n_events, a.dec, a.stats); break;
-    case 5: replay_split_kernel<false, 5, false>(a.P, a.events, a.n_events, a.dec, a.stats); break;
-    }
+    if (p.fl_tiles == 3) return replay_split_kernel<SLOTS, 3, false>(a.P, a.events, a.n_events, a.dec, a.stats);
+    if (p.fl_tail) return replay_split_kernel<SLOTS, 5, true>(a.P, a.events, a.n_events, a.dec, a.stats);
+    replay_split_kernel<SLOTS, 5, false>(a.P, a.events, a.n_events, a.dec, a.stats);
 }
-
 // both policies in one launch: only the wavefront emu::wave of the workgroup runs
-void body_both(void *p)
+template <int SLOTS>
+void both_with(const ReplayPlan &p, Args &a)
 {
-    Args &a = *(Args *)p;
-    switch (a.variant) {
-    case 0: replay_both_kernel<true, 3, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
-    case 1: replay_both_kernel<false, 3, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
-    case 2: replay_both_kernel<true, 5, true>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
-    case 3: replay_both_kernel<false, 5, true>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
-    case 4: replay_both_kernel<true, 5, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
-    case 5: replay_both_kernel<false, 5, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws); break;
-    }
+    if (p.fl_tiles == 3) return replay_both_kernel<SLOTS, 3, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws);
+    if (p.fl_tail) return replay_both_kernel<SLOTS, 5, true>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws);
+    replay_both_kernel<SLOTS, 5, false>(a.P, a.P_split, a.events, a.n_events, a.dec, a.dec, a.stats, a.ws);
 }
+#define BY_SLOTS(f)                                                        \
+    {                                                                      \
+        Args &a = *(Args *)x;                                              \
+        const ReplayPlan &p = *a.plan;                                     \
+        if (p.slots == SLOTS_IN_REGS) f<SLOTS_IN_REGS>(p, a);              \
+        else if (p.slots == SLOTS_IN_MEM) f<SLOTS_IN_MEM>(p, a);           \
+        else f<SLOTS_IN_LDS>(p, a);                                        \
+    }
+void body_vms(void *x) BY_SLOTS(vms_with)
+void body_split(void *x) BY_SLOTS(split_with)
+void body_both(void *x) BY_SLOTS(both_with)
 
 u32 g_selftest_fail;
 void body_selftest(void *tab) { selftest_kernel(&g_selftest_fail, (uint16_t *)tab); }
@@ -153,7 +146,7 @@ extern "C" {
 // Replays every trace under the policies of cfg->policy_mask with the kernels the library would
 // launch.  dec_split / dec_vms: [n_traces][max_events] or NULL; stats: [2][n_traces].
 // Returns 0, a VMS_E* code from planning, or -100 - k if guard band k was written
-// (1 LDS, 2 decisions, 3 statistics, 4 workspace).
+// (1 LDS, 2 decisions, 3 statistics, 4 workspace, 5 tables in global memory).
 int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_events, uint64_t *dec_split,
                uint64_t *dec_vms, vms_trace_stats *stats)
 {
@@ -168,6 +161,12 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
     const size_t n = (size_t)cfg->n_traces * cfg->max_events, ws_bytes = plan.ws_bytes + again.ws_bytes;
     Guarded g_dec(n * 8), g_stats(sizeof(vms_trace_stats) * (2 * cfg->n_traces + 1)), g_ws(ws_bytes ? ws_bytes : 256);
     memset(g_stats.ptr(), 0, g_stats.bytes);
+    // tables in global memory: of both passes, each policy's in turn
+    Guarded g_mem[2] = { Guarded(plan.kp[1].mem_stride * cfg->n_traces), Guarded(again.kp[1].mem_stride * cfg->retry_traces) };
+    for (int pol = 0; pol < 2; pol++) {
+        plan.kp[pol].mem = g_mem[0].ptr();
+        again.kp[pol].mem = g_mem[1].ptr();
+    }
     for (int pol = 0; pol < 2; pol++) {
         if (!(cfg->policy_mask & (1u << pol))) continue;
         Args a;
@@ -178,19 +177,15 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
         a.dec = out ? (u64 *)g_dec.ptr() : nullptr;
         a.stats = (vms_trace_stats *)g_stats.ptr();
         a.ws = g_ws.ptr();
-        if (pol) a.variant = plan.fine ? (plan.wide ? 4 : plan.tbl_ws == 3 ? 8 : plan.tbl_ws ? 6 : 2) + (plan.slot_regs ? 0 : 1) : (plan.slot_regs ? 0 : 1);
-        else a.variant = (plan.fl_tiles == 3 ? 0 : plan.fl_tail ? 2 : 4) + (plan.slot_regs ? 0 : 1);
         if (out) memset(g_dec.ptr(), 0xFF, n * 8);
         for (int pass = 0; pass < (again.has_retry ? 2 : 1); pass++) {
             const ReplayPlan &pl = pass ? again : plan;
             a.P = pl.kp[pol];
-            if (pol) a.variant = pl.fine ? (pl.wide ? 4 : pl.tbl_ws == 3 ? 8 : pl.tbl_ws ? 6 : 2) + (pl.slot_regs ? 0 : 1) : (pl.slot_regs ? 0 : 1);
-            else a.variant = (pl.fl_tiles == 3 ? 0 : pl.fl_tail ? 2 : 4) + (pl.slot_regs ? 0 : 1);
+            a.plan = &pl;
             const bool together = plan.together && !pass;
             if (together) {
                 a.P = plan.kp[1];
                 a.P_split = plan.kp[0];
-                a.variant = (plan.fl_tiles == 3 ? 0 : plan.fl_tail ? 2 : 4) + (plan.slot_regs ? 0 : 1);
                 emu::wave = pol ? 0 : 1;
             }
             // this wavefront's part of the LDS
@@ -207,6 +202,7 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
         if (!g_dec.intact()) return -102;
         if (!g_stats.intact()) return -103;
         if (!g_ws.intact()) return -104;
+        if (!g_mem[0].intact() || !g_mem[1].intact()) return -105;
         if (out) memcpy(out, g_dec.ptr(), n * 8);
     }
     memcpy(stats, g_stats.ptr(), sizeof(vms_trace_stats) * 2 * cfg->n_traces);

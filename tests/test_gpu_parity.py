@@ -111,6 +111,15 @@ def test_invalid_events_and_oom():
     assert st["status"][0, 0] == 1 and st["n_code"][1, 0, 5] == 1
 
 
+def test_slot_tables_too_large_for_global_memory_are_in_lds():
+    # 17,000 traces of 4,000 slots: more than 1 GiB of records, both variants
+    n, slots = 17000, 4000
+    ev, _ = gpu_util.slot_reuse_traces(slots, 64 * 3, seed=4, traces=8)
+    ev = np.ascontiguousarray(np.tile(ev, (n // 8, 1)))
+    for variant in (1, 2):
+        gpu_util.assert_parity(ev, gpu_util.make_cfg(n, ev.shape[1], slots, variant=variant, max_runs=900), label="variant %d" % variant)
+
+
 @pytest.mark.parametrize("slots", [3, 64, 65, 300])
 @pytest.mark.parametrize("kw", [dict(variant=1), dict(variant=1, spool_threshold=4, max_sblocks=128, max_runs=900), dict(variant=2),
                                 dict(variant=2, table_place=binding.VMS_TABLES_WORKSPACE_ALL, spool_threshold=4, max_sblocks=128, max_runs=160)])

@@ -181,15 +181,15 @@ def test_both_policies_in_one_launch(kind, free):
 @pytest.mark.parametrize("config,slots,sizes", [
     (2, 64, [(1024, 34832), (2048, 34832), (3072, 8560), (4096, 8560)]),
     (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2560, 15120), (4096, 16144)]),
-    (4, 650, [(64, 49616), (512, 49616), (1024, 23456), (1280, 23456), (4096, 19520)]),
-    (6, 1163, [(64, 51792), (512, 51792), (1024, 26976), (1280, 23040), (4096, 23040)])])
+    (4, 650, [(64, 49616), (512, 49616), (1024, 39184), (1280, 14320), (4096, 10384)]),
+    (6, 1163, [(64, 51792), (512, 51792), (1024, 33168), (1280, 10672), (4096, 6736)])])
 def test_plan_of_a_batch_by_its_size(config, slots, sizes):
     for n, lds in sizes:
         out = emu.plan(workloads.make_config(binding, config, n, 20000, slots))
         assert out == lds, (config, n, out)
 
 
-# slot tables in registers (up to 64 slots) and in LDS; a capacity that is reached, and an arena that is squeezed often
+# slot tables in registers (up to 64 slots), in LDS (flat variant) and in global memory; a capacity that is reached, and an arena that is squeezed often
 @pytest.mark.parametrize("slots", [3, 64, 65, 300])
 @pytest.mark.parametrize("kw", [dict(policy_mask=1), dict(variant=1), dict(variant=2, capacity_bytes=192 * MiB),
                                 dict(variant=1, spool_threshold=4, max_sblocks=128, max_runs=900),
@@ -262,3 +262,4 @@ def test_table_overflow_is_flagged_not_fatal():
     cfg = gpu_util.make_cfg(1, 2500, ms, policy_mask=2, variant=2, max_pblocks=64, max_sblocks=520, max_chunks=4096)
     _, _, st = emu.replay(ev, cfg, binding.STATS_DTYPE)
     assert st["status"][1, 0] & binding.VMS_ST_TABLE_OVERFLOW and st["overflow_event"][1, 0] < 2500
+
