@@ -55,13 +55,16 @@ struct FineT {
     u32 w_spare;                // a bitmap word no chunk lives in
     u32 gs, cap_grans;
     Probe2<IDX> sp;             // first level of the rank search over ssz[]
+    Probe2<pkey_t> pp;          // and over pool[], as it was when the event began
     static DI pkey_t key(u32 size, u32 start) { return ((pkey_t)size << W) | (pkey_t)(IDX)~start; }
     static DI u32 ksize(pkey_t k) { return (u32)(k >> W); }
     static DI u32 kstart(pkey_t k) { return (u32)(IDX) ~(IDX)k; }
     DI u64 *list_at(u32 place) const { return arena + ((size_t)place << gs); }
     // TH 0: ssz[] / swit[] / soff[] live in LDS.  TH 2: swit[] and soff[], TH 3: all three live in the
     // trace's workspace slice: then they are read with workgroup-scope loads and moved by gblk_shift_*;
-    // IDX is 16 bits wide there
+    // IDX is 16 bits wide there.  TH 4: pool[] is in global memory as well, which leaves 4 KB of LDS per trace, so that
+    // the vector registers alone limit the wavefronts per compute unit (16; offloading 4096x50000, nine before, 371 ->
+    // 254 ms); its steps are longer, so scans have the next step's keys on their way and moves two steps
     // before the first read of these tables after they were written (the stores must have arrived)
     DI void tables_written() const
     {
@@ -69,7 +72,7 @@ struct FineT {
     }
     DI u32 sz_at(u32 i) const
     {
-        if constexpr (TH == 3) return ld_tab((const u16 *)ssz + i);
+        if constexpr (TH >= 3) return ld_tab((const u16 *)ssz + i);
         else return ssz[i];
     }
     DI u32 wit_at(u32 i) const
@@ -166,45 +169,65 @@ DI bool s1_single(const FineT<IDX, TH> &V, u32 &start)
 
 // ---- pool[] of multi-chunk pBlocks --------------------------------------------------------------
 // (4-byte keys move sixteen bytes per lane and step; the 8-byte keys of the variant with 32-bit chunk
-// numbers one key per lane)
+// numbers one key per lane.)  An event changes pool[] at most once, after all its searches: pp is valid until then.
+// pool[pos..np) one place up
+template <class IDX, int TH>
+DI void fine_pool_up(FineT<IDX, TH> &V, u32 pos)
+{
+    if constexpr (sizeof(IDX) == 2) key_shift_up<TH == 4 ? 2 : 1>(V.pool, pos, V.np);
+    else shift_up(V.pool, pos, V.np);
+}
+// pool[pos+1..end) one place down; pool[end-1] is left as it was
+template <class IDX, int TH>
+DI void fine_pool_down(FineT<IDX, TH> &V, u32 pos, u32 end)
+{
+    if constexpr (sizeof(IDX) == 2) key_shift_down<TH == 4 ? 2 : 1>(V.pool, pos, end);
+    else shift_down(V.pool, pos, end);
+}
+
 template <class IDX, int TH, class AcctT>
 DI void fine_pool_insert(FineT<IDX, TH> &V, u32 size, u32 start, AcctT &A)
 {
     const auto k = V.key(size, start);
-    const u32 pos = rank_desc_k(V.pool, V.np, k);
-    if constexpr (sizeof(IDX) == 2) blk_shift_up(V.pool, pos, V.np);
-    else shift_up(V.pool, pos, V.np);
+    const u32 pos = V.pp.rank(V.pool, k);
+    fine_pool_up(V, pos);
     st_one(V.pool, pos, k);
     V.np++;
     A.peak(SC_HW_MULTI, V.np);
     wave_sync();
 }
 
-template <class IDX, int TH>
-DI void fine_pool_remove(FineT<IDX, TH> &V, u32 idx)
-{
-    if constexpr (sizeof(IDX) == 2) {
-        blk_shift_down(V.pool, idx, V.np);                      // (leaves a zero key in the last place)
-        V.np--;
-    } else {
-        shift_down(V.pool, idx, V.np);
-        V.np--;
-        st_one(V.pool, V.np, (typename FineT<IDX, TH>::pkey_t)0);
-    }
-    wave_sync();
-}
-
 // Split (Sec. 3.3.1): the pBlock at pool[idx] = [start, start + size) becomes [start, start + keep)
-// and the rest.  A piece of one chunk leaves the array: its boundary bits say all there is to say.
+// and the rest.  Both are smaller and so further down; only the keys between the old place and the new ones
+// move.  (Taken out and put in again one by one, the keys behind a new place moved down and up.)  A piece of one
+// chunk leaves the array: its boundary bits say all there is to say.
 template <class IDX, int TH, class AcctT>
 DI void fine_cut(FineT<IDX, TH> &V, u32 idx, u32 start, u32 size, u32 keep, AcctT &A)
 {
-    fine_pool_remove(V, idx);
-    const u32 cut = start + keep;
+    const u32 cut = start + keep, rest = size - keep;
     atomicOr(lane_id() == 0 ? &V.bnd[cut >> 5] : &V.idle[lane_id()], lane_id() == 0 ? 1u << (cut & 31) : 0u);
+    const u32 big = max(keep, rest), small = min(keep, rest);
+    const auto k1 = V.key(big, keep >= rest ? start : cut), k2 = V.key(small, keep >= rest ? cut : start);
+    if (big > 1) {
+        // ranks among the old keys, the cut block (greater than both) among them
+        const u32 b1 = V.pp.block(k1), b2 = V.pp.block(k2);
+        const auto v1 = V.pool[b1 + lane_id()], v2 = V.pool[b2 + lane_id()];
+        const u32 r1 = b1 + popc64(ballot(v1 > k1)), r2 = b2 + popc64(ballot(v2 > k2));
+        fine_pool_down(V, idx, r1);
+        if (small > 1) fine_pool_up(V, r2);
+        st_one(V.pool, r1 - 1, k1);
+        if (small > 1) {
+            wave_sync();
+            st_one(V.pool, r2, k2);
+            V.np++;
+        }
+    } else {
+        fine_pool_down(V, idx, V.np);
+        V.np--;
+        st_one(V.pool, V.np, (typename FineT<IDX, TH>::pkey_t)0);
+    }
+    A.peak(SC_HW_MULTI, V.np);
     wave_sync();
-    if (keep > 1) fine_pool_insert(V, keep, start, A);
-    if (size - keep > 1) fine_pool_insert(V, size - keep, cut, A);
     V.np_all++;
     A.add(SC_N_SPLIT, 1);
     A.peak(SC_HW_PBLOCKS, V.np_all);
@@ -301,7 +324,7 @@ DI void fine_spool_shift(FineT<IDX, TH> &V, u32 pos, bool up)
 {
     if constexpr (TH) {
         static_assert(sizeof(IDX) == 2, "tables in the workspace: 16-bit chunk numbers only");
-        if constexpr (TH == 3) {
+        if constexpr (TH >= 3) {
             u16 *const g[3] = { (u16 *)V.ssz, (u16 *)V.swit, V.soff };
             if (up) gblk_shift_up<3>(g, pos, V.ns);
             else gblk_shift_down<3>(g, pos, V.ns);
@@ -336,8 +359,8 @@ template <class IDX, int TH, class AcctT>
 DI void fine_spool_insert(FineT<IDX, TH> &V, u32 size, u32 place, u32 witness, AcctT &A)
 {
     V.tables_written();
-    V.sp.template refresh<TH == 3>(V.ssz, V.ns);
-    const u32 pos = V.sp.template rank<TH == 3>(V.ssz, (IDX)(size - 1));    // sizes >= size come before it
+    V.sp.template refresh<TH >= 3>(V.ssz, V.ns);
+    const u32 pos = V.sp.template rank<TH >= 3>(V.ssz, (IDX)(size - 1));    // sizes >= size come before it
     fine_spool_shift(V, pos, true);
     st_one(V.ssz, pos, (IDX)size);
     st_one(V.swit, pos, (IDX)witness);
@@ -699,18 +722,32 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, u32 bsize, u32 lo_p, u32 hi_p, u32 re
     R.list = 0;
     // pool[lo_p, hi_p) are the multi-chunk pBlocks of exactly bsize chunks (all active, or S1 had taken one)
 
+    constexpr u32 KE = 16 / sizeof(pkey_t);
+    struct alignas(16) Keys {
+        pkey_t k[KE];
+    };
+
     // ---- Algorithm 1, second loop.  Larger blocks are pool[0, lo_p): the last inactive one in
     // pool order is the single-block candidate (state 2).
     for (u32 hi = lo_p; hi > 0;) {
-        const u32 lo = hi > 64 ? hi - 64 : 0;
-        const bool v = lane < hi - lo;
-        const pkey_t k = V.pool[v ? hi - 1 - lane : 0u];
-        const u32 fc = V.kstart(k);
-        const u32 kw = V.bmp[v ? fc >> 5 : V.w_spare];
-        const u64 m = ballot(v && !((kw >> (fc & 31)) & 1u));
+        // from the last key on, sixteen bytes of keys per lane
+        const u32 last = (hi - 1) / KE, blk = last - min(lane, last);
+        const Keys K = ((const Keys *)V.pool)[blk];
+        u32 kw[KE];
+        pkey_t found = 0;                                       // this lane's last inactive one, and where it is
+        u32 at = 0;
+#pragma unroll
+        for (u32 e = 0; e < KE; e++) kw[e] = V.bmp[blk * KE + e < hi ? V.kstart(K.k[e]) >> 5 : V.w_spare];
+#pragma unroll
+        for (u32 e = 0; e < KE; e++) {
+            const bool ok = lane <= last && blk * KE + e < hi && !((kw[e] >> (V.kstart(K.k[e]) & 31)) & 1u);
+            found = ok ? K.k[e] : found;
+            at = ok ? blk * KE + e : at;
+        }
+        const u64 m = ballot(found != 0);
         if (m) {
-            const u32 l = first_lane(m), idx = hi - 1 - l;
-            const pkey_t pk = from_lane_k(k, l);
+            const u32 l = first_lane(m), idx = from_lane(at, l);
+            const pkey_t pk = from_lane_k(found, l);
             const u32 psize = V.ksize(pk), pstart = V.kstart(pk);
             if (UNLIKELY(psize < P.frag_limit_chunks)) {
                 // below the fragmentation limit: not worth cutting, hand it out whole (Sec. 4.2.3)
@@ -739,7 +776,7 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, u32 bsize, u32 lo_p, u32 hi_p, u32 re
             if (fine_stitch_free(V, P, A)) R.dec_lo |= B_7;
             return;
         }
-        hi = lo;
+        hi = last >= 64 ? (last - 63) * KE : 0;
     }
 
     // Smaller blocks, largest first, until the request is covered (states 3 and 4): first the
@@ -747,7 +784,7 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, u32 bsize, u32 lo_p, u32 hi_p, u32 re
     // fragmentation limit sit at the tail of the pool and are never stitched.
     u32 lim = V.np;
     const bool singles_ok = P.frag_limit_chunks <= 1;
-    if (UNLIKELY(!singles_ok)) lim = rank_desc_k(V.pool, V.np, (pkey_t)(((pkey_t)P.frag_limit_chunks << V.W) - 1));
+    if (UNLIKELY(!singles_ok)) lim = V.pp.rank(V.pool, (pkey_t)(((pkey_t)P.frag_limit_chunks << V.W) - 1));
     u32 sum = 0, k = 0, pos = NONE32;
     // No inactive pBlock of bsize chunks or more exists at this point, so every inactive chunk that is
     // not a single-chunk pBlock belongs to a candidate.  If all of those together do not cover the
@@ -780,16 +817,15 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, u32 bsize, u32 lo_p, u32 hi_p, u32 re
     // bit of its first chunk and the bit behind its last one.  A chunk then belongs to a candidate iff
     // an odd number of flipped bits lies at or below it (runs do not overlap; where two touch, the two
     // flips of the shared place cancel): the list is read off tmp[] afterwards whatever the runs' lengths.
-    constexpr u32 KE = 16 / sizeof(pkey_t);
-    struct alignas(16) Keys {
-        pkey_t k[KE];
-    };
-    u64 qk = 0;                                                 // the key of a candidate that is cut
+    u64 qk = 0;                                                 // the key of the last candidate: the one that is cut
     bool flipped = false;
     if (!all_multi) {
+        auto keys_at = [&](u32 base) { return ((const Keys *)V.pool)[base + lane * KE < lim ? (base + lane * KE) / KE : 0u]; };
+        Keys K_next = keys_at(hi_p & ~(KE - 1));
         for (u32 base = hi_p & ~(KE - 1); base < lim && pos == NONE32; base += 64 * KE) {
             const u32 i0 = base + lane * KE;
-            const Keys K = ((const Keys *)V.pool)[i0 < lim ? i0 / KE : 0u];
+            const Keys K = K_next;
+            if (base + 64 * KE < lim) K_next = keys_at(base + 64 * KE);         // on their way while these are looked at
             u32 kw[KE], sz[KE], mine = 0;
             bool in[KE];
 #pragma unroll
@@ -821,11 +857,11 @@ DI void fine_alloc_rest(FineT<IDX, TH> &V, u32 bsize, u32 lo_p, u32 hi_p, u32 re
                         if (sum >= bsize) {
                             pos = base + l_end * KE + e;
                             e_end = e;
+                            qk = (u64)from_lane_k(K.k[e], l_end);
                         }
                     }
                 }
                 cut_by = sum - bsize;
-                if (cut_by) qk = (u64)ld_uni(V.pool, pos);
             } else {
 #pragma unroll
                 for (u32 e = 0; e < KE; e++) k += popc64(ballot(in[e]));
@@ -1093,12 +1129,12 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
     S.init(lds, P, blockIdx.x);
     ((u32 *)(lds + LDS_SCALARS))[lane] = lane == SC_FIRST_OOM || lane == SC_OVF_EVENT ? NONE32 : 0u;     // LDS header
     FineT<IDX, TH> V;
-    V.pool = (pkey_t *)(lds + P.off_pool);
+    V.pool = TH == 4 ? (pkey_t *)(P.mem + (size_t)blockIdx.x * P.mem_stride + P.mem_pool) : (pkey_t *)(lds + P.off_pool);
     V.bmp = (u32 *)(lds + P.off_bmp);
     V.bnd = (u32 *)(lds + P.off_bnd);
     V.tmp = (u32 *)(lds + P.off_tmp);
     V.idle = V.tmp + P.bmp_words;
-    V.ssz = TH == 3 ? (IDX *)(ws_slice + 2 * P.ws_half + 2 * (size_t)P.ws_tbl_bytes) : (IDX *)(lds + P.off_skey);
+    V.ssz = TH >= 3 ? (IDX *)(ws_slice + 2 * P.ws_half + 2 * (size_t)P.ws_tbl_bytes) : (IDX *)(lds + P.off_skey);
     if constexpr (TH) {
         V.swit = (IDX *)(ws_slice + 2 * P.ws_half);
         V.soff = (u16 *)(ws_slice + 2 * P.ws_half + P.ws_tbl_bytes);
@@ -1127,7 +1163,8 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
     wave_sync();
     st_one(V.bnd, 0u, 1u);                                  // no chunk yet: the end of the last pBlock is chunk 0
     V.tables_written();
-    V.sp.template refresh<TH == 3>(V.ssz, 0u);
+    V.sp.template refresh<TH >= 3>(V.ssz, 0u);
+    V.pp.refresh(V.pool, 0u);
     wave_sync();
 
     u32 lost = 0;               // request of a FREE that outgrew a table: the trace ends there, the request counts as gone
@@ -1234,7 +1271,13 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
             }
             // pool[lo_p, hi_p): the multi-chunk pBlocks of exactly bsize chunks
             u32 lo_p, hi_p;
-            rank_desc2_k(V.pool, V.np, V.key(bsize, 0), (pkey_t)(((pkey_t)bsize << V.W) - 1), &lo_p, &hi_p);
+            {
+                const pkey_t k1 = V.key(bsize, 0), k2 = (pkey_t)(((pkey_t)bsize << V.W) - 1);
+                const u32 b1 = V.pp.block(k1), b2 = V.pp.block(k2);
+                const pkey_t v1 = V.pool[b1 + lane], v2 = V.pool[b2 + lane];
+                lo_p = b1 + popc64(ballot(v1 > k1));
+                hi_p = b2 + popc64(ballot(v2 > k2));
+            }
             if (bsize > 1 ? fine_s1_pblock(V, lo_p, hi_p, ref) : s1_single(V, ref)) {
                 bmp_fill(V.bmp, V.w_spare, ref, bsize, true);
                 S.alloc_done(j, at, C_EXACT | (1u << 8), ref, size, bsize << P.chunk_shift, ref, KIND_PBLOCK | (bsize << 2), 0u);
@@ -1245,7 +1288,8 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
             const u64 *const before = V.arena;
             const bool went = fine_alloc_cold(lds, V, P, bsize, lo_p, hi_p, sp_reserved + (V.n_chunks << P.chunk_shift), base + j, R);
             V.tables_written();
-            V.sp.template refresh<TH == 3>(V.ssz, V.ns);        // the sBlock table may have changed
+            V.sp.template refresh<TH >= 3>(V.ssz, V.ns);        // the tables may have changed
+            V.pp.refresh(V.pool, V.np);
             if (UNLIKELY(V.arena != before))
                 S.relist([&](u32, u32, u32 place) { return (u32)ld_list(before + ((size_t)min(place, V.cap_grans - 1) << V.gs)); });
             if (UNLIKELY(!went)) {                      // an engine table overflowed: the trace ends here

@@ -39,9 +39,10 @@ struct KParams {
     uint32_t retry;                  // this launch is that pass: traces without an overflow flag are left alone
     uint32_t retry_slots;            // traces it has workspace for
     uint64_t retry_ws_off;           // where that workspace starts (bytes from the start of the caller's workspace)
-    // tables in global memory of the handle: a slice of mem_stride bytes per wavefront of the launch: its slot table
+    // tables in global memory of the handle: a slice of mem_stride bytes per wavefront of the launch, the slot table
+    // at its start, pool[] of the fine-grained variant mem_pool bytes behind
     char *mem;
-    uint64_t mem_stride;
+    uint64_t mem_stride, mem_pool;
 };
 
 // Where the slot table of a trace is: in LDS, in registers (at most 64 slots), in global memory of the handle
@@ -51,7 +52,8 @@ struct ReplayPlan {
     KParams kp[2];                   // [0] splitting kernel, [1] stitching kernel
     bool fine;                       // stitching kernel: the fine-grained variant (lists in the workspace)
     bool wide;                       // fine-grained variant with 32-bit chunk numbers (more than 65,000 chunks)
-    int tbl_ws;                      // fine-grained variant: 0 the sBlock tables in LDS; 2 witnesses and list places in the workspace; 3 sizes too
+    int tbl_ws;                      // fine-grained variant: 0 the sBlock tables in LDS; 2 witnesses and list places in the workspace;
+                                     // 3 sizes too; 4 and pool[] in global memory of the handle
     bool slot_regs;                  // at most 64 slots
     int slots;                       // SLOTS_IN_*
     uint32_t fl_tiles;               // splitting policy: places for inactive blocks in registers, per lane: 3 or 5 (see SplitPool)
@@ -85,9 +87,10 @@ inline uint64_t slot_bytes_saved(uint32_t max_slots, int policy, const ReplayPla
     const uint64_t words = align_up(4ull * max_slots, 16);
     return policy ? 3 * words + align_up((p.fine ? 2ull : 4ull) * max_slots, 16) : 2 * words;
 }
-// bytes of a slot table in global memory
+// bytes of a slot table in global memory, and of pool[] of the fine-grained variant
 inline uint64_t slot_table_bytes(uint32_t max_slots, int policy) { return align_up((uint64_t)max_slots * (policy ? 16 : 8), 16); }
-const uint64_t MEM_TABLES_MAX = 1ull << 30;         // bytes of global memory that the slot tables of a launch may take
+inline uint64_t pool_bytes(const KParams &k, const ReplayPlan &p) { return ((uint64_t)k.cap_pblocks + 80) * (p.wide ? 8 : 4); }
+const uint64_t MEM_TABLES_MAX = 1ull << 30;         // bytes of global memory that the slot tables of a launch, or its pools, may take
 
 // Per-wave LDS layout, in 64-bit arithmetic (a table size that would wrap a 32-bit offset must end
 // as "too big", not as a small layout).  Returns the bytes needed.
@@ -114,7 +117,7 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
     k.off_fl = k.cap_free <= in_regs ? 0 : take(((uint64_t)k.cap_free - in_regs) * 8);
     if (policy && p.fine) {
         const uint64_t idx = p.wide ? 4 : 2;                    // bytes of a chunk number
-        k.off_pool = take(((uint64_t)k.cap_pblocks + 80) * 2 * idx);      // 64 spare places, and moves of whole 16-byte blocks
+        if (p.tbl_ws != 4) k.off_pool = take(pool_bytes(k, p));      // 64 spare places, and moves of whole 16-byte blocks
         k.off_bmp = take(((uint64_t)k.bmp_words + 1) * 4);      // and one spare word
         k.off_bnd = take(((uint64_t)k.bmp_words + 1) * 4);      // scans read one word ahead
         k.off_tmp = take(((uint64_t)k.bmp_words + 64) * 4);     // and 64 spare words
@@ -143,8 +146,9 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
 // The plan for cfg with the variant it names (0: flat unless the tables are too large for it).
 // VMS_OK, VMS_EINVAL / VMS_ESTRUCT for a configuration that makes no sense, VMS_ETOOBIG for tables
 // that do not fit a compute unit's LDS.  Touches no device.
-// slots_in_mem: slot tables of more than 64 slots in global memory, unless they take too much of it.
-inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_mem)
+// slots_in_mem: slot tables of more than 64 slots in global memory, unless they take too much of it; pool_in_mem: with
+// all sBlock tables in the workspace pool[] goes there too, likewise.
+inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_mem, bool pool_in_mem = false)
 {
     using namespace plan_detail;
     if (!cfg) return VMS_EINVAL;
@@ -222,10 +226,12 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_m
             k.ws_half = align_up((((uint64_t)k.cap_grans << k.gran_shift) + 64) * 8, 256);
             k.ws_tbl_bytes = p.tbl_ws ? (uint32_t)align_up(((uint64_t)c.max_sblocks + 80) * 2, 256) : 0u;
             k.ws_stride = 2 * k.ws_half + (p.tbl_ws < 3 ? 2ull : 3ull) * k.ws_tbl_bytes;
+            if (pool_in_mem && p.tbl_ws == 3 && c.n_traces * pool_bytes(k, p) <= MEM_TABLES_MAX) p.tbl_ws = 4;
         } else if (pol) {
             k.ws_stride = align_up(((uint64_t)c.max_runs + 64) * 4, 256);     // where compaction copies the lists
         }
-        k.mem_stride = p.slots == SLOTS_IN_MEM ? slot_table_bytes(c.max_slots, pol) : 0;
+        k.mem_pool = p.slots == SLOTS_IN_MEM ? slot_table_bytes(c.max_slots, pol) : 0;
+        k.mem_stride = k.mem_pool + (pol && p.tbl_ws == 4 ? align_up(pool_bytes(k, p), 16) : 0);
         const uint64_t need = layout(k, pol, c, p) + pool_bytes_saved(k, pol, p) + slot_bytes_saved(c.max_slots, pol, p);
         if ((c.policy_mask & (1u << pol)) && need > LDS_PER_CU) {
             // flat variant: the lists' places in a slot table in LDS are there for speed only; tables that fit
@@ -261,7 +267,8 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 // (recomputation, 64 to 4,096 traces: 17.1 to 23.6 against 7.3 to 8.2); what is known beforehand of the two is
 // that the former hold more than 64 blocks at once.  Sblock tables in the workspace: 5 to 10 % more (offloading
 // 1024x20000 58.6 -> 64.7 ms, ZeRO-3 11.8 -> 12.4); with two tables there instead of three it is not less
-// (offloading 4096x50000 391 against 366 ms), so that place is taken on request only.
+// (offloading 4096x50000 391 against 366 ms), so that place is taken on request only; with pool[] in global memory too
+// another 5 % (offloading 2500x20000, resident at once either way, 85.1 -> 89.7 ms).
 // The splitting kernel beside it takes 0.65 of a round (5 of 7.5 ms) and runs in the LDS that the stitching
 // wavefronts leave, or behind them; a batch of several rounds costs its wavefronts' share of the LDS times how
 // long they hold it, and half a round for the tail, but two rounds at least where each has a SIMD to itself and so
@@ -272,7 +279,7 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 inline uint64_t plan_cost(const ReplayPlan &x, const vms_config &c)
 {
     const uint64_t round = !x.fine ? 100 + (x.slots == SLOTS_IN_MEM ? 2 : 0)
-                                   : (x.slot_regs ? 260 : 160) * (x.tbl_ws ? 106 : 100) / 100;
+                                   : (x.slot_regs ? 260 : 160) * (x.tbl_ws == 4 ? 112 : x.tbl_ws ? 106 : 100) / 100;
     const uint64_t n = c.n_traces, w = plan_waves_per_cu(x), all = (uint64_t)PLAN_CUS * PLAN_GRANULES;
     if (!w) return ~0ull;
     const uint64_t lds = plan_granules(x.kp[1].lds_bytes), g = lds > PLAN_GRANULES / 16 ? lds : PLAN_GRANULES / 16;
@@ -303,8 +310,8 @@ inline bool plan_together(const ReplayPlan &x, const vms_config &c)
 const uint32_t SPLIT_SLOTS_IN_LDS = 512;
 
 // The plan for cfg.  With variant 0 and tables that both variants serve the library chooses between them, and
-// with table_place 0 whether the fine-grained variant keeps the tables of the sBlocks in LDS or, where that leaves
-// fewer than two wavefronts per SIMD, in the workspace: whichever plan the batch costs least under.  (Scale-out
+// with table_place 0 whether the fine-grained variant keeps the tables of the sBlocks in LDS, in the workspace, or there
+// with pool[] in global memory too: whichever plan the batch costs least under.  (Scale-out
 // 320x20000 11.0 -> 7.5 ms, fragmentation limit study 64x20000 9.2 -> 7.1, both fine-grained before because their
 // presets said so; recomputation 2048x20000 22.9 -> 15.8, fine-grained before because the batch did not fit at once.)
 inline int replay_plan_choose(const vms_config *cfg, ReplayPlan &p)
@@ -316,12 +323,12 @@ inline int replay_plan_choose(const vms_config *cfg, ReplayPlan &p)
     const bool other = cfg->variant == VMS_VARIANT_AUTO && !p.fine;
     uint64_t best = ~0ull;
     // takes the plan if it costs less
-    auto consider = [&](uint32_t variant, uint32_t place, bool slots_in_mem) {
+    auto consider = [&](uint32_t variant, uint32_t place, bool slots_in_mem, bool pool_in_mem = false) {
         vms_config alt = *cfg;
         alt.variant = variant;
         alt.table_place = place;
         ReplayPlan q;
-        if (replay_plan_for(&alt, q, slots_in_mem) != VMS_OK) return;
+        if (replay_plan_for(&alt, q, slots_in_mem, pool_in_mem) != VMS_OK) return;
         const uint64_t c = plan_cost(q, *cfg);
         if (c < best) {
             best = c;
@@ -336,6 +343,7 @@ inline int replay_plan_choose(const vms_config *cfg, ReplayPlan &p)
     } else {
         consider(VMS_VARIANT_FINE, VMS_TABLES_LDS, true);
         consider(VMS_VARIANT_FINE, VMS_TABLES_WORKSPACE_ALL, true);
+        consider(VMS_VARIANT_FINE, VMS_TABLES_WORKSPACE_ALL, true, true);
     }
     return VMS_OK;
 }

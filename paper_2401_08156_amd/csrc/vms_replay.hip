@@ -132,6 +132,7 @@ vms_fn pick_vms_with(const ReplayPlan &p)
 {
     if (!p.fine) return replay_vms_kernel<SLOTS>;
     if (p.wide) return replay_vms_fine_kernel<SLOTS, u32, 0>;
+    if (p.tbl_ws == 4) return replay_vms_fine_kernel<SLOTS, u16, 4>;
     if (p.tbl_ws == 3) return replay_vms_fine_kernel<SLOTS, u16, 3>;
     return p.tbl_ws ? replay_vms_fine_kernel<SLOTS, u16, 2> : replay_vms_fine_kernel<SLOTS, u16, 0>;
 }

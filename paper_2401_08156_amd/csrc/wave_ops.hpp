@@ -219,27 +219,6 @@ DI u32 rank_desc_k(const K *a, u32 n, K key)
     return b0 + popc64(ballot(a[b0 + lane] > key));
 }
 
-// the same for two keys (k1 >= k2, hence r1 <= r2) sharing the probe pass
-template <class K>
-DI void rank_desc2_k(const K *a, u32 n, K k1, K k2, u32 *r1, u32 *r2)
-{
-    const u32 lane = lane_id();
-    if (n <= 64) {
-        const K v = a[lane];
-        *r1 = popc64(ballot(v > k1));
-        *r2 = popc64(ballot(v > k2));
-        return;
-    }
-    const u32 stride = (n + 63) >> 6;
-    const u32 pi = lane * stride;
-    const K pv = a[pi < n ? pi : n];
-    const u32 c1 = popc64(ballot(pv > k1)), c2 = popc64(ballot(pv > k2));
-    const u32 b1 = dec_sat(c1) * stride, b2 = dec_sat(c2) * stride;
-    const K v1 = a[b1 + lane], v2 = a[b2 + lane];
-    *r1 = b1 + popc64(ballot(v1 > k1));
-    *r2 = b2 + popc64(ballot(v2 > k2));
-}
-
 // 128 probes held in registers: lane l holds a[l * stride] and a[(64 + l) * stride] (0 past the
 // end).  With stride < 64 (n <= 8064) the block of 64 keys from block() on holds every key greater
 // than `key` that lies behind its start, and the first key not greater than `key`.
@@ -498,6 +477,68 @@ DI void gblk_shift_down(uint16_t *const (&a)[N], u32 pos, u32 n)
                 const Blk16 out = blk_select<uint16_t>(old[g][f], mv, B[g] * E, pos);
                 if (mine[g]) gblk_store(a[f], B[g], out);
             }
+        wave_lockstep();
+    }
+    wave_sync();
+}
+
+// Moves inside arrays of 32-bit keys, sixteen bytes per lane: G steps of 64 blocks are on their way before the first
+// store (2 for arrays in global memory).  The same conventions as above.
+// a[pos..n) -> a[pos+1..n+1), highest blocks first; a[pos] keeps its old value
+template <int G>
+DI void key_shift_up(u32 *a, u32 pos, u32 n)
+{
+    const u32 bf = (pos + 1) / 4, bl = n / 4;
+    for (u32 hi = bl + 1; hi > bf;) {
+        Blk16 old[G];
+        u32 prev[G], B[G];
+        bool mine[G];
+        u32 h = hi;
+#pragma unroll
+        for (u32 g = 0; g < G; g++) {
+            const u32 lo = h - bf > 64 ? h - 64 : bf;
+            B[g] = lo + lane_id();
+            mine[g] = B[g] < h;
+            old[g] = ((const Blk16 *)a)[mine[g] ? B[g] : bf];
+            prev[g] = a[(mine[g] && B[g] ? B[g] : 1u) * 4 - 1];
+            h = lo;
+        }
+        wave_lockstep();
+#pragma unroll
+        for (u32 g = 0; g < G; g++) {
+            const Blk16 mv = { { prev[g], old[g].w[0], old[g].w[1], old[g].w[2] } };
+            const Blk16 out = blk_select<u32>(old[g], mv, B[g] * 4, pos + 1);
+            if (mine[g]) ((Blk16 *)a)[B[g]] = out;
+        }
+        wave_lockstep();
+        hi = h;
+    }
+    wave_sync();
+}
+
+// a[pos+1..end) -> a[pos..end-1), lowest blocks first; a[end-1] keeps its old value (pos < end)
+template <int G>
+DI void key_shift_down(u32 *a, u32 pos, u32 end)
+{
+    const u32 bf = pos / 4, bl = (end - 1) / 4;
+    for (u32 lo = bf; lo <= bl; lo += 64 * G) {
+        Blk16 old[G];
+        u32 next[G], B[G];
+        bool mine[G];
+#pragma unroll
+        for (u32 g = 0; g < G; g++) {
+            B[g] = lo + 64 * g + lane_id();
+            mine[g] = B[g] <= bl;
+            old[g] = ((const Blk16 *)a)[mine[g] ? B[g] : bl];
+            next[g] = a[(mine[g] ? B[g] : bl) * 4 + 4];
+        }
+        wave_lockstep();
+#pragma unroll
+        for (u32 g = 0; g < G; g++) {
+            const Blk16 mv = { { old[g].w[1], old[g].w[2], old[g].w[3], next[g] } };
+            const Blk16 out = blk_select<u32>(blk_select<u32>(old[g], mv, B[g] * 4, pos), old[g], B[g] * 4, end - 1);
+            if (mine[g]) ((Blk16 *)a)[B[g]] = out;
+        }
         wave_lockstep();
     }
     wave_sync();

@@ -44,14 +44,16 @@ def plan(cfg):
     return lib().emu_plan_lds(ctypes.byref(cfg))
 
 
-def replay(events, cfg, stats_dtype, n_events=None):
-    """events: uint64[n_traces, max_events]; cfg: the binding's vms_config.
+def replay(events, cfg, stats_dtype, n_events=None, pool_in_mem=False):
+    """events: uint64[n_traces, max_events]; cfg: the binding's vms_config; pool_in_mem: the plan of a large batch with
+    all tables in the workspace (cfg names VMS_TABLES_WORKSPACE_ALL).
     Returns (dec_split, dec_vms, stats[2, n_traces])."""
     ev = np.ascontiguousarray(events, dtype=np.uint64)
     assert ev.shape == (cfg.n_traces, cfg.max_events)
     ds, dv = np.zeros_like(ev), np.zeros_like(ev)
     st = np.zeros((2, cfg.n_traces), dtype=stats_dtype)
     ne = None if n_events is None else np.ascontiguousarray(n_events, dtype=np.uint32)
+    lib().emu_pool_in_mem(1 if pool_in_mem else 0)
     rc = lib().emu_replay(ctypes.byref(cfg), ev.ctypes.data, None if ne is None else ne.ctypes.data,
                           ds.ctypes.data, dv.ctypes.data, st.ctypes.data)
     if rc != 0:

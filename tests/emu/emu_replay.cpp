@@ -105,6 +105,7 @@ void vms_with(const ReplayPlan &p, Args &a)
 {
     if (!p.fine) return replay_vms_kernel<SLOTS>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
     if (p.wide) return replay_vms_fine_kernel<SLOTS, u32, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
+    if (p.tbl_ws == 4) return replay_vms_fine_kernel<SLOTS, uint16_t, 4>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
     if (p.tbl_ws == 3) return replay_vms_fine_kernel<SLOTS, uint16_t, 3>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
     if (p.tbl_ws) return replay_vms_fine_kernel<SLOTS, uint16_t, 2>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
     replay_vms_fine_kernel<SLOTS, uint16_t, 0>(a.P, a.events, a.n_events, a.dec, a.stats, a.ws);
@@ -141,7 +142,12 @@ void body_selftest(void *tab) { selftest_kernel(&g_selftest_fail, (uint16_t *)ta
 
 }  // namespace
 
+static bool g_pool_in_mem;
+
 extern "C" {
+
+// the fine-grained variant with all its tables out of the LDS, which the library plans for large batches only
+void emu_pool_in_mem(int on) { g_pool_in_mem = on != 0; }
 
 // Replays every trace under the policies of cfg->policy_mask with the kernels the library would
 // launch.  dec_split / dec_vms: [n_traces][max_events] or NULL; stats: [2][n_traces].
@@ -152,6 +158,7 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
 {
     ReplayPlan plan;
     int rc = replay_plan_make(cfg, plan);
+    if (rc == VMS_OK && g_pool_in_mem) rc = replay_plan_for(cfg, plan, true, true);
     if (rc != VMS_OK) return rc;
     ReplayPlan again;
     rc = replay_plan_retry(cfg, plan, again);

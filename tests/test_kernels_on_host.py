@@ -19,8 +19,8 @@ from test_oracle_examples import GOLDEN, load_fixture
 MiB = 1 << 20
 
 
-def check(ev, cfg, n_events=None, label=""):
-    ds, dv, st = emu.replay(ev, cfg, binding.STATS_DTYPE, n_events)
+def check(ev, cfg, n_events=None, label="", **kw):
+    ds, dv, st = emu.replay(ev, cfg, binding.STATS_DTYPE, n_events, **kw)
     P = gpu_util.oracle_params(cfg)
     for pol, gdec in ((0, ds), (1, dv)):
         if not (cfg.policy_mask & (1 << pol)):
@@ -180,8 +180,8 @@ def test_both_policies_in_one_launch(kind, free):
 # at once beside its splitting kernel, then the fine-grained variant, then its tables in the workspace
 @pytest.mark.parametrize("config,slots,sizes", [
     (2, 64, [(1024, 34832), (2048, 34832), (3072, 8560), (4096, 8560)]),
-    (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2560, 15120), (4096, 16144)]),
-    (4, 650, [(64, 49616), (512, 49616), (1024, 39184), (1280, 14320), (4096, 10384)]),
+    (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2560, 15120), (4096, 4432)]),
+    (4, 650, [(64, 49616), (512, 49616), (1024, 39184), (1280, 14320), (4096, 7504)]),
     (6, 1163, [(64, 51792), (512, 51792), (1024, 33168), (1280, 10672), (4096, 6736)])])
 def test_plan_of_a_batch_by_its_size(config, slots, sizes):
     for n, lds in sizes:
@@ -263,3 +263,17 @@ def test_table_overflow_is_flagged_not_fatal():
     _, _, st = emu.replay(ev, cfg, binding.STATS_DTYPE)
     assert st["status"][1, 0] & binding.VMS_ST_TABLE_OVERFLOW and st["overflow_event"][1, 0] < 2500
 
+
+# pool[] of the fine-grained variant in global memory, all other tables in the workspace: one to several steps of its
+# moves and scans (256 blocks each), cuts into pieces of one chunk and more, the fragmentation limit, an arena that is
+# squeezed, a pool that is outgrown
+@pytest.mark.parametrize("kind,events,kw", [
+    (3, 2500, dict(max_runs=1 << 16, max_sblocks=2560, max_pblocks=8192, max_multi_pblocks=2848, max_chunks=10240)),
+    (3, 1500, dict(max_runs=1 << 15, max_sblocks=1024, max_pblocks=8192, max_multi_pblocks=1030, max_chunks=10240, frag_limit_bytes=6 * MiB)),
+    (1, 1500, dict(spool_threshold=8, max_sblocks=256, max_runs=700, max_chunks=8192)),
+    (4, 3000, dict(max_pblocks=700, spool_threshold=16, max_sblocks=92, max_runs=700, max_chunks=20480)),
+    (2, 2000, dict(max_pblocks=100, max_runs=4000, max_chunks=8192, retry_traces=1))])
+def test_pool_in_global_memory(kind, events, kw):
+    ev, ms = tg.generate(kind, n_traces=2, n_events=events, seed=11)
+    cfg = gpu_util.make_cfg(2, events, ms, policy_mask=2, variant=2, table_place=binding.VMS_TABLES_WORKSPACE_ALL, **kw)
+    check(ev, cfg, n_events=np.array([events, events - 37], dtype=np.uint32), label="generator %d" % kind, pool_in_mem=True)
