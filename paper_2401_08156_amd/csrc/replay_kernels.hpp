@@ -922,68 +922,66 @@ DI bool list_busy(const VmsT &V, u32 off, u32 cnt, u32 *witness)
 // sBlock whose witness is still active (three tiles at a time: all stamps and witnesses are loaded,
 // then all witness words, two LDS round trips per 192 sBlocks) and leaves in every lane the two
 // least recently used of the sBlocks it saw.  The oldest of all is tested with all lanes on its
-// list; if it is active after all, its lane falls back on its second and the search goes on
-// without a new scan (a lane that runs out of its two forces one).
+// list and released if it is inactive; its lane falls back on its second and the search goes on
+// without a new scan (a lane that runs out of its two forces one).  With a scan for each of the three sBlocks that
+// a call of the threshold study releases, 64x20000 took 10.7 instead of 10.4 ms.
 template <class AcctT>
 DI bool stitch_free(VmsT &V, const KParams &P, AcctT &A)
 {
     const u32 lane = lane_id();
-    bool any = false;
+    bool any = false, rescan = true;
+    u32 b1 = NONE32, i1 = 0, b2 = NONE32, i2 = 0;
+    bool spent = false;                         // this lane has given up its best once since the scan
     while (V.ns > P.spool_threshold) {
-        u32 victim = NONE32;
-        bool rescan = true;
-        u32 b1 = NONE32, i1 = 0, b2 = NONE32, i2 = 0;
-        bool spent = false;                     // this lane has given up its best once since the scan
-        for (;;) {
-            if (rescan) {
-                b1 = b2 = NONE32;
-                i1 = i2 = 0;
-                spent = false;
-                for (u32 g = 0; g < V.ns; g += 192) {
-                    u32 st[3], wit[3], ww[3];
+        if (rescan) {
+            b1 = b2 = NONE32;
+            i1 = i2 = 0;
+            spent = false;
+            for (u32 g = 0; g < V.ns; g += 192) {
+                u32 st[3], wit[3], ww[3];
 #pragma unroll
-                    for (u32 t = 0; t < 3; t++) {
-                        const u32 i = g + t * 64 + lane, ic = i < V.ns ? i : 0u;
-                        st[t] = V.sstamp[ic];
-                        wit[t] = V.swit[ic];
-                    }
-#pragma unroll
-                    for (u32 t = 0; t < 3; t++) ww[t] = pin(V.bmp[ENT_WORD(wit[t])]);
-#pragma unroll
-                    for (u32 t = 0; t < 3; t++) {
-                        const u32 i = g + t * 64 + lane;
-                        const bool ok = (i < V.ns) & ((ww[t] & emask(wit[t])) == 0);
-                        const u32 sv = ok ? st[t] : NONE32;
-                        const bool lt1 = sv < b1, lt2 = sv < b2;
-                        b2 = lt1 ? b1 : (lt2 ? sv : b2);
-                        i2 = lt1 ? i1 : (lt2 ? i : i2);
-                        b1 = lt1 ? sv : b1;
-                        i1 = lt1 ? i : i1;
-                    }
+                for (u32 t = 0; t < 3; t++) {
+                    const u32 i = g + t * 64 + lane, ic = i < V.ns ? i : 0u;
+                    st[t] = V.sstamp[ic];
+                    wit[t] = V.swit[ic];
                 }
-                rescan = false;
+#pragma unroll
+                for (u32 t = 0; t < 3; t++) ww[t] = pin(V.bmp[ENT_WORD(wit[t])]);
+#pragma unroll
+                for (u32 t = 0; t < 3; t++) {
+                    const u32 i = g + t * 64 + lane;
+                    const bool ok = (i < V.ns) & ((ww[t] & emask(wit[t])) == 0);
+                    const u32 sv = ok ? st[t] : NONE32;
+                    const bool lt1 = sv < b1, lt2 = sv < b2;
+                    b2 = lt1 ? b1 : (lt2 ? sv : b2);
+                    i2 = lt1 ? i1 : (lt2 ? i : i2);
+                    b1 = lt1 ? sv : b1;
+                    i1 = lt1 ? i : i1;
+                }
             }
-            const u32 m = wave_min_u32(b1);
-            if (m == NONE32) break;             // everything cached is in use: the threshold stays exceeded
-            const u32 owner = first_lane(ballot(b1 == m));
-            const u32 c = from_lane(i1, owner);
-            const auto meta = ld_uni(V.smeta, c);
-            u32 witness;
-            if (!list_busy(V, V.off(meta), V.cnt(meta), &witness)) {
-                victim = c;
-                break;
-            }
+        }
+        const u32 m = wave_min_u32(b1);
+        if (m == NONE32) break;                 // everything cached is in use: the threshold stays exceeded
+        const u32 owner = first_lane(ballot(b1 == m));
+        const u32 c = from_lane(i1, owner);
+        const auto meta = ld_uni(V.smeta, c);
+        u32 witness;
+        const bool busy = list_busy(V, V.off(meta), V.cnt(meta), &witness);
+        // either way the lane falls back on its second
+        rescan = from_lane(spent ? 1u : 0u, owner) != 0;
+        const bool mine = lane == owner;
+        b1 = mine ? b2 : b1;
+        i1 = mine ? i2 : i1;
+        b2 = mine ? NONE32 : b2;
+        spent = spent || mine;
+        if (busy) {
             st_one(V.swit, c, witness);         // active after all: remember where, look further
             wave_sync();
-            rescan = from_lane(spent ? 1u : 0u, owner) != 0;
-            const bool mine = lane == owner;
-            b1 = mine ? b2 : b1;
-            i1 = mine ? i2 : i1;
-            b2 = mine ? NONE32 : b2;
-            spent = spent || mine;
+            continue;
         }
-        if (victim == NONE32) break;
-        spool_remove(V, victim);
+        spool_remove(V, c);
+        i1 -= i1 > c ? 1u : 0u;                 // (the sBlocks behind it have moved down one place)
+        i2 -= i2 > c ? 1u : 0u;
         A.add(SC_N_EVICTED, 1);
         any = true;
     }
