@@ -271,8 +271,8 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 // another 5 % (offloading 2500x20000, resident at once either way, 85.1 -> 89.7 ms).
 // The splitting kernel beside it takes 0.65 of a round (5 of 7.5 ms) and runs in the LDS that the stitching
 // wavefronts leave, or behind them; a batch of several rounds costs its wavefronts' share of the LDS times how
-// long they hold it, and half a round for the tail, but two rounds at least where each has a SIMD to itself and so
-// gains nothing from a round that is not full (ZeRO-3 1280x20000 on the flat variant, 1,024 of them at a time: 14.8 ms,
+// long they hold it, and half a round for the tail, but whole rounds where at most two share a SIMD and so gain
+// little from a round that is not full (ZeRO-3 1280x20000 on the flat variant, 1,024 of them at a time: 14.8 ms,
 // fine-grained 12.0).
 // A slot table in global memory costs the flat variant 1 to 2 % (one random trace 1.057 -> 1.069 ms, scale-out
 // 320x20000 7.58 -> 7.75).
@@ -285,8 +285,8 @@ inline uint64_t plan_cost(const ReplayPlan &x, const vms_config &c)
     const uint64_t lds = plan_granules(x.kp[1].lds_bytes), g = lds > PLAN_GRANULES / 16 ? lds : PLAN_GRANULES / 16;
     const uint64_t g_split = c.policy_mask & VMS_POLICY_SPLIT ? plan_granules(x.kp[0].lds_bytes) : 0;
     if (n > PLAN_CUS * w) {
-        const uint64_t shares = n * (g * round + g_split * 65) / all + round / 2;
-        return w > 4 || shares > 2 * round ? shares : 2 * round;
+        const uint64_t shares = n * (g * round + g_split * 65) / all + round / 2, rounds = (n + PLAN_CUS * w - 1) / (PLAN_CUS * w);
+        return w > 8 || shares > rounds * round ? shares : rounds * round;
     }
     if (!g_split) return round;
     const uint64_t room = n * lds < all ? (all - n * lds) / g_split : 0;

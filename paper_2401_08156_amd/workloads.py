@@ -25,13 +25,16 @@ TABLES = {
     # a wavefront takes 16,144 B.  With 2,592 places seven of the 13 seeds sent one or two traces through the second
     # pass, 140 ms on 388)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2848, max_sblocks=2560, max_runs=1 << 18, max_chunks=10240),
-    # (up to 512 traces on the flat kernel, 49,616 B; the fine-grained one beyond that, and with its sBlock tables in the
-    # workspace and 19,520 B, eight wavefronts per compute unit, where that saves a round; chunk tables for the 17,699
-    # chunks the largest trace reserves)
+    # (up to 512 traces on the flat kernel with the slot table in LDS, 49,616 B, up to 1,024 with it in global memory,
+    # 39,184; the fine-grained one beyond that, 14,320 B, and with all its tables in the workspace and global memory 7,504,
+    # sixteen wavefronts per compute unit, where that saves a round; chunk tables for the 17,699 chunks the largest trace
+    # reserves)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432),
-    # (the same for the scale-out regime, 9,408 chunks at most; 51,792 / 26,976 / 23,040 B.  pBlocks: 497 to 534 at most
-    # over 12 seeds; with 512 places, in as many granules, four of those seeds sent a trace through the second pass)
-    6: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3072, max_chunks=9728),
+    # (the same for the scale-out regime, 9,408 chunks at most; 50,576 / 31,952 / 10,480 / 6,640 B.  pBlocks: 497 to 534 at
+    # most over 12 seeds.  31,952 B are what five wavefronts per compute unit have room for, so that the 1,280 traces of
+    # the workload are on the flat kernel at once: 8.4 ms, 12.0 on the fine-grained one, which 3,072 list entries, 576
+    # sBlocks and 9,728 chunks made them take)
+    6: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=560, max_runs=2864, max_chunks=9472),
 }
 # config 5 mixes the generators of configs 2, 3 and 4 (trace i uses kind 2 + i mod 3) with twice the
 # events; replayed as three batches, one per kind, each with tables of its own
