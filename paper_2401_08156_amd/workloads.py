@@ -21,20 +21,21 @@ TABLES = {
     # variant: single chunks in bitmaps, a table for the pBlocks of two or more chunks, lists in the workspace)
     # (LDS is handed out in 1,280-byte granules, 128 per compute unit.  Multi-chunk pBlocks: 2,421 to 2,824 at most over
     # 13 seeds.  2,848 places are what five wavefronts per compute unit have room for with all tables in LDS, 31,984 B,
-    # where the library puts them for up to 1,280 traces; beyond that the tables of the sBlocks are in the workspace and
-    # a wavefront takes 16,144 B.  With 2,592 places seven of the 13 seeds sent one or two traces through the second
-    # pass, 140 ms on 388)
+    # where the library puts them for up to 1,280 traces; up to 2,560 the tables of the sBlocks are in the workspace and
+    # a wavefront takes 16,144 B; for more traces than that the table of the multi-chunk pBlocks is in global memory too,
+    # 4,432 B, sixteen wavefronts.  With 2,592 places seven of the 13 seeds sent one or two traces through the second pass)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2848, max_sblocks=2560, max_runs=1 << 18, max_chunks=10240),
     # (up to 512 traces on the flat kernel with the slot table in LDS, 49,616 B, up to 1,024 with it in global memory,
     # 39,184; the fine-grained one beyond that, 14,320 B, and with all its tables in the workspace and global memory 7,504,
     # sixteen wavefronts per compute unit, where that saves a round; chunk tables for the 17,699 chunks the largest trace
     # reserves)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432),
-    # (the same for the scale-out regime, 9,408 chunks at most; 50,576 / 31,952 / 10,480 / 6,640 B.  pBlocks: 497 to 534 at
-    # most over 12 seeds.  31,952 B are what five wavefronts per compute unit have room for, so that the 1,280 traces of
-    # the workload are on the flat kernel at once: 8.4 ms, 12.0 on the fine-grained one, which 3,072 list entries, 576
-    # sBlocks and 9,728 chunks made them take)
-    6: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=560, max_runs=2864, max_chunks=9472),
+    # (the same for the scale-out regime, 9,408 chunks at most; 50,560 / 31,936 / 10,304 / 6,560 B.  31,936 B are what five
+    # wavefronts per compute unit have room for, so that the 1,280 traces of the workload are on the flat kernel at once:
+    # 8.4 ms, 12.0 on the fine-grained one, which 3,072 list entries, 576 sBlocks, 9,728 chunks and 544 pBlocks made them
+    # take.  No trace of 19 seeds outgrows these sizes; with 2,864 list entries one of them sent a trace through the
+    # second pass)
+    6: dict(max_free_blocks=192, max_pblocks=536, max_sblocks=544, max_runs=2960, max_chunks=9408),
 }
 # config 5 mixes the generators of configs 2, 3 and 4 (trace i uses kind 2 + i mod 3) with twice the
 # events; replayed as three batches, one per kind, each with tables of its own
@@ -42,10 +43,11 @@ TABLES_5 = {
     2: dict(max_free_blocks=192, max_pblocks=640, max_sblocks=640, max_runs=5120, max_chunks=4096),
     # (the margins over the high-water marks are one to two per cent; a trace that outgrows a table is replayed
     # again by the second pass.  40,208 B of LDS per wavefront with every table in LDS, four wavefronts per compute
-    # unit; for more traces than that the library moves the sBlock tables to the workspace: 14,960 B, ten)
+    # unit; for more traces than that the library moves the sBlock tables to the workspace, 14,960 B, ten, and beyond
+    # 2,560 the table of the multi-chunk pBlocks too, 3,760 B, sixteen)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2720, max_sblocks=4128, max_runs=1 << 18, max_chunks=8480),
-    # (18,055 chunks is the most a trace of this kind reserves; 19.9 KB of LDS per wavefront with the sBlock tables in the
-    # workspace, where the library puts them for the 5,461 traces of the workload)
+    # (18,055 chunks is the most a trace of this kind reserves; 7,504 B of LDS per wavefront for the 5,461 traces of the
+    # workload)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=736, max_sblocks=576, max_runs=4224, max_chunks=18432),
 }
 
