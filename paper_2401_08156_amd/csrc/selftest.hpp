@@ -53,6 +53,39 @@ DI u32 selftest_gblk(uint16_t *tab)
     return bad;
 }
 
+// Moves inside an array of 32-bit keys (2048 places): up to its end, and down inside [pos, end), around blocks of 4
+// keys, groups of 64 blocks and two groups.
+template <int G>
+DI u32 selftest_keys(u32 *a)
+{
+    const u32 lane = lane_id();
+    const u32 lengths[] = { 1, 3, 4, 5, 255, 256, 257, 511, 512, 513, 1030, 1900 };
+    u32 bad = 0;
+    for (u32 n : lengths) {
+        const u32 places[] = { 0, 3, 4, n / 2, n - 1 };
+        for (u32 pos : places) {
+            if (pos >= n) continue;
+            const u32 ends[] = { pos + 1, pos + 2, (pos + n) / 2 + 1, n - 1, n };
+            for (u32 i = lane; i < 2048; i += 64) a[i] = i < n ? 4000 - 2 * i : 0;
+            wave_sync();
+            key_shift_up<G>(a, pos, n);
+            for (u32 i = lane; i < 2048; i += 64)
+                if (a[i] != (i <= pos ? 4000 - 2 * i : i <= n ? 4000 - 2 * (i - 1) : 0)) bad |= 1u << 20;
+            wave_sync();
+            for (u32 end : ends) {
+                if (end <= pos || end > n) continue;
+                for (u32 i = lane; i < 2048; i += 64) a[i] = i < n ? 4000 - 2 * i : 0;
+                wave_sync();
+                key_shift_down<G>(a, pos, end);
+                for (u32 i = lane; i < 2048; i += 64)
+                    if (a[i] != (i >= n ? 0 : i < pos || i >= end - 1 ? 4000 - 2 * i : 4000 - 2 * (i + 1))) bad |= 1u << 21;
+                wave_sync();
+            }
+        }
+    }
+    return bad;
+}
+
 __global__ __launch_bounds__(64) void selftest_kernel(u32 *fail, uint16_t *tab)
 {
     __shared__ u32 in[64], out[64];
@@ -220,16 +253,18 @@ __global__ __launch_bounds__(64) void selftest_kernel(u32 *fail, uint16_t *tab)
         }
         Probe2<uint16_t> pr;
         pr.refresh(nar, n);
+        Probe2<u32> pr32;
+        pr32.refresh(nar32, n);
         for (u32 key = 150; key <= 4003; key += 7) {
             u32 ref = 0;
             for (u32 i = 0; i < n; i++) ref += nar[i] > key ? 1u : 0u;
-            if (pr.rank(nar, (uint16_t)key) != ref || rank_desc_k(nar, n, (uint16_t)key) != ref ||
-                rank_desc_k(nar32, n, key) != ref)
-                bad |= 16384;
+            if (pr.rank(nar, (uint16_t)key) != ref || pr32.rank(nar32, key) != ref) bad |= 16384;
             const u32 b0 = pr.block((uint16_t)key);
             if (b0 > ref || ref - b0 >= 64) bad |= 32768;
         }
     }
+    bad |= selftest_keys<1>(nar32);
+    bad |= selftest_keys<2>(nar32);
     bad |= selftest_gblk<2>(tab);
     bad |= selftest_gblk<3>(tab);
     u64 any = ballot(bad != 0);

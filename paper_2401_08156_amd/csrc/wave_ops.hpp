@@ -204,21 +204,6 @@ DI u32 rank_fast(const Probe &p, const u64 *a, u32 n, u64 key)
 // ---- sorted arrays of narrow keys (K = uint16_t, u32 or u64) ------------------------------------
 // Same conventions: descending order, at least 64 zero keys behind the live ones, live keys never 0.
 
-// number of elements of a[0..n) that are greater than key, by a two-level search whose first level
-// is read on the spot (two dependent LDS reads; every n up to 64 * 64)
-template <class K>
-DI u32 rank_desc_k(const K *a, u32 n, K key)
-{
-    const u32 lane = lane_id();
-    if (n <= 64) return popc64(ballot(a[lane] > key));
-    const u32 stride = (n + 63) >> 6;               // at most 64 for n <= 4096
-    const u32 pi = lane * stride;
-    const K pv = a[pi < n ? pi : n];                // a[n] is a spare zero key
-    const u32 c = popc64(ballot(pv > key));
-    const u32 b0 = dec_sat(c) * stride;             // a[b0] > key >= a[b0 + stride] (if c)
-    return b0 + popc64(ballot(a[b0 + lane] > key));
-}
-
 // 128 probes held in registers: lane l holds a[l * stride] and a[(64 + l) * stride] (0 past the
 // end).  With stride < 64 (n <= 8064) the block of 64 keys from block() on holds every key greater
 // than `key` that lies behind its start, and the first key not greater than `key`.
