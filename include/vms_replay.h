@@ -213,8 +213,9 @@ int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_
  * loops, harnesses that forbid hipMalloc): vms_replay_run with the workspace taken from an array
  * that is part of the library's device code (vms_replay_static_workspace_bytes() = 32 MiB per
  * device, held from the first use on that device until the process ends) instead of from the
- * caller.  Allocates nothing and calls no allocating routine.  VMS_EWORKSPACE if the handle needs
- * more workspace than the array holds (vms_replay_workspace_bytes), VMS_EINVAL if the current
+ * caller.  Allocates nothing and calls no allocating routine.  A handle that needs more workspace
+ * than the array holds (vms_replay_workspace_bytes) is replayed under the plan that needs least;
+ * VMS_EWORKSPACE if that does not fit either, VMS_EINVAL if the current
  * device is not the one the handle was created on.  All calls on one device share the one array:
  * runs that overlap on a device race (also across handles); the array keeps the last run's lists,
  * which the next run overwrites before reading.  Everything else as vms_replay_run.            */

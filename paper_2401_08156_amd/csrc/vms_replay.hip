@@ -27,6 +27,10 @@ struct vms_replay {
     vms_config cfg;
     ReplayPlan plan;            // kernel variants, LDS layouts, workspace slice (replay_plan.hpp)
     ReplayPlan retry;           // the same for the second pass over traces that outgrew the tables (has_retry)
+    // Where those need more workspace than the built-in one has: the plan with the smallest workspace, if that fits
+    // (small.ws_bytes; else 0).  A batch that the library replays on the fine-grained variant for its speed is so no
+    // less accepted by vms_replay_run_static than one it replays on the flat variant.
+    ReplayPlan small, small_retry;
     vms_trace_stats *d_stats;
     vms_summary *d_summary;
     char *d_mem;                // tables in global memory: per policy those of the first pass, then those of the second
@@ -35,7 +39,7 @@ struct vms_replay {
     hipStream_t last_stream;
     int device;
     int last_hip;
-    bool ran;
+    bool ran, last_together;    // last_together: both policies went in one launch
     size_t ws_bytes;
 };
 
@@ -229,6 +233,13 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
     if (h->retry.has_retry)
         for (int pol = 0; pol < 2; pol++) h->plan.kp[pol].retry_slots = c.retry_traces;    // the first pass resets the count
     h->ws_bytes = plan.ws_bytes + h->retry.ws_bytes;
+    if (h->ws_bytes > STATIC_WS_BYTES) {
+        if (replay_plan_for(cfg, h->small, false) != VMS_OK || replay_plan_retry(cfg, h->small, h->small_retry) != VMS_OK ||
+            h->small.ws_bytes + h->small_retry.ws_bytes > STATIC_WS_BYTES)
+            h->small.ws_bytes = 0;
+        if (h->small_retry.has_retry)
+            for (int pol = 0; pol < 2; pol++) h->small.kp[pol].retry_slots = c.retry_traces;
+    }
 
     if (hipGetDevice(&h->device) != hipSuccess) {
         delete h;
@@ -243,20 +254,20 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
     for (int i = 0; i < 6 && e == hipSuccess; i++) e = hipEventCreate(&h->ev[i]);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     // LDS above 64 KB per workgroup has to be requested explicitly
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)pick_split(h->plan), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)LDS_PER_CU);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)pick_vms(h->plan), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)LDS_PER_CU);
-    if (e == hipSuccess && h->plan.together)
-        e = hipFuncSetAttribute((const void *)pick_both(h->plan), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
-    if (e == hipSuccess && h->retry.has_retry)
-        e = hipFuncSetAttribute((const void *)pick_split(h->retry),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
-    if (e == hipSuccess && h->retry.has_retry)
-        e = hipFuncSetAttribute((const void *)pick_vms(h->retry), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)LDS_PER_CU);
+    auto all_lds = [&](const void *kernel) {
+        if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
+    };
+    auto all_lds_of = [&](const ReplayPlan &p) {
+        all_lds((const void *)pick_split(p));
+        all_lds((const void *)pick_vms(p));
+        if (p.together) all_lds((const void *)pick_both(p));
+    };
+    all_lds_of(h->plan);
+    if (h->retry.has_retry) all_lds_of(h->retry);
+    if (h->small.ws_bytes) {
+        all_lds_of(h->small);
+        if (h->small_retry.has_retry) all_lds_of(h->small_retry);
+    }
     if (e != hipSuccess) {
         int rc = e == hipErrorOutOfMemory ? VMS_ENOMEM : VMS_EHIP;
         vms_replay_destroy(h);
@@ -276,46 +287,43 @@ int vms_replay_lds_bytes(const vms_replay *h, uint32_t out[2])
     return VMS_OK;
 }
 
-int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_events, uint64_t *d_dec_split,
-                   uint64_t *d_dec_vms, void *d_workspace, void *hip_stream)
+static int run_plan(vms_replay *h, const ReplayPlan &plan, const ReplayPlan &retry, const uint64_t *d_events, const uint32_t *d_n_events,
+                    uint64_t *d_dec_split, uint64_t *d_dec_vms, void *d_workspace, void *hip_stream)
 {
-    if (!h || !d_events) return VMS_EINVAL;
     const vms_config &c = h->cfg;
-    if ((c.policy_mask & VMS_POLICY_VMS) && h->ws_bytes && (!d_workspace || ((uintptr_t)d_workspace & 255)))
-        return VMS_EWORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
     // The two policies are independent: in one launch where that is planned, else the short splitting kernel
     // runs on a second stream beside the long stitching kernel and the caller's stream joins it at the end.
     HIP_TRY(h, hipEventRecord(h->ev[0], st));
-    const bool both = c.policy_mask == (VMS_POLICY_SPLIT | VMS_POLICY_VMS) && !h->plan.together;
+    const bool both = c.policy_mask == (VMS_POLICY_SPLIT | VMS_POLICY_VMS) && !plan.together;
     hipStream_t sst = both ? h->side : st;
     if (both) HIP_TRY(h, hipStreamWaitEvent(sst, h->ev[0], 0));
-    if (h->plan.together) {
-        hipLaunchKernelGGL(pick_both(h->plan), dim3(c.n_traces), dim3(128), h->plan.kp[0].lds_bytes + h->plan.kp[1].lds_bytes, st,
-                           h->plan.kp[1], h->plan.kp[0], d_events, d_n_events, d_dec_vms, d_dec_split, h->d_stats, (char *)d_workspace);
+    if (plan.together) {
+        hipLaunchKernelGGL(pick_both(plan), dim3(c.n_traces), dim3(128), plan.kp[0].lds_bytes + plan.kp[1].lds_bytes, st,
+                           plan.kp[1], plan.kp[0], d_events, d_n_events, d_dec_vms, d_dec_split, h->d_stats, (char *)d_workspace);
         HIP_TRY(h, hipGetLastError());
     } else if (c.policy_mask & VMS_POLICY_VMS) {
-        hipLaunchKernelGGL(pick_vms(h->plan), dim3(c.n_traces), dim3(64), h->plan.kp[1].lds_bytes, st, h->plan.kp[1],
+        hipLaunchKernelGGL(pick_vms(plan), dim3(c.n_traces), dim3(64), plan.kp[1].lds_bytes, st, plan.kp[1],
                            d_events, d_n_events, d_dec_vms, h->d_stats, (char *)d_workspace);
         HIP_TRY(h, hipGetLastError());
     }
     HIP_TRY(h, hipEventRecord(h->ev[1], st));       // the kernel times are those of the first pass
-    if ((c.policy_mask & VMS_POLICY_VMS) && h->retry.has_retry) {
+    if ((c.policy_mask & VMS_POLICY_VMS) && retry.has_retry) {
         // second pass: retry_traces wavefronts with larger tables replay the traces whose tables overflowed
-        hipLaunchKernelGGL(pick_vms(h->retry), dim3(second_pass_waves(c)), dim3(64), h->retry.kp[1].lds_bytes, st, h->retry.kp[1],
+        hipLaunchKernelGGL(pick_vms(retry), dim3(second_pass_waves(c)), dim3(64), retry.kp[1].lds_bytes, st, retry.kp[1],
                            d_events, d_n_events, d_dec_vms, h->d_stats, (char *)d_workspace);
         HIP_TRY(h, hipGetLastError());
     }
-    if (!h->plan.together) HIP_TRY(h, hipEventRecord(h->ev[2], sst));
-    if ((c.policy_mask & VMS_POLICY_SPLIT) && !h->plan.together) {
-        hipLaunchKernelGGL(pick_split(h->plan), dim3(c.n_traces), dim3(64), h->plan.kp[0].lds_bytes, sst, h->plan.kp[0],
+    if (!plan.together) HIP_TRY(h, hipEventRecord(h->ev[2], sst));
+    if ((c.policy_mask & VMS_POLICY_SPLIT) && !plan.together) {
+        hipLaunchKernelGGL(pick_split(plan), dim3(c.n_traces), dim3(64), plan.kp[0].lds_bytes, sst, plan.kp[0],
                            d_events, d_n_events, d_dec_split, h->d_stats);
         HIP_TRY(h, hipGetLastError());
     }
-    if (!h->plan.together) HIP_TRY(h, hipEventRecord(h->ev[3], sst));
-    if ((c.policy_mask & VMS_POLICY_SPLIT) && h->retry.has_retry) {
-        hipLaunchKernelGGL(pick_split(h->retry), dim3(second_pass_waves(c)), dim3(64),
-                           h->retry.kp[0].lds_bytes, sst, h->retry.kp[0], d_events, d_n_events, d_dec_split, h->d_stats);
+    if (!plan.together) HIP_TRY(h, hipEventRecord(h->ev[3], sst));
+    if ((c.policy_mask & VMS_POLICY_SPLIT) && retry.has_retry) {
+        hipLaunchKernelGGL(pick_split(retry), dim3(second_pass_waves(c)), dim3(64),
+                           retry.kp[0].lds_bytes, sst, retry.kp[0], d_events, d_n_events, d_dec_split, h->d_stats);
         HIP_TRY(h, hipGetLastError());
     }
     if (both) {
@@ -324,8 +332,18 @@ int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_
     }
     HIP_TRY(h, hipEventRecord(h->ev[4], st));
     h->last_stream = st;
+    h->last_together = plan.together;
     h->ran = true;
     return VMS_OK;
+}
+
+int vms_replay_run(vms_replay *h, const uint64_t *d_events, const uint32_t *d_n_events, uint64_t *d_dec_split,
+                   uint64_t *d_dec_vms, void *d_workspace, void *hip_stream)
+{
+    if (!h || !d_events) return VMS_EINVAL;
+    if ((h->cfg.policy_mask & VMS_POLICY_VMS) && h->ws_bytes && (!d_workspace || ((uintptr_t)d_workspace & 255)))
+        return VMS_EWORKSPACE;
+    return run_plan(h, h->plan, h->retry, d_events, d_n_events, d_dec_split, d_dec_vms, d_workspace, hip_stream);
 }
 
 size_t vms_replay_static_workspace_bytes(void) { return STATIC_WS_BYTES; }
@@ -334,7 +352,8 @@ int vms_replay_run_static(vms_replay *h, const uint64_t *d_events, const uint32_
                           uint64_t *d_dec_vms, void *hip_stream)
 {
     if (!h || !d_events) return VMS_EINVAL;
-    if (h->ws_bytes > STATIC_WS_BYTES) return VMS_EWORKSPACE;   // this handle needs more than the built-in array holds
+    const bool small = h->ws_bytes > STATIC_WS_BYTES;
+    if (small && !h->small.ws_bytes) return VMS_EWORKSPACE;     // this handle needs more than the built-in array holds
     int dev = -1;
     HIP_TRY(h, hipGetDevice(&dev));
     if (dev < 0 || dev >= STATIC_WS_DEVICES || dev != h->device) return VMS_EINVAL;
@@ -347,8 +366,8 @@ int vms_replay_run_static(vms_replay *h, const uint64_t *d_events, const uint32_
     }
     // Nothing in the array has to start at zero: the kernels write every word of a trace's slice
     // before they read it.  Calls that overlap on one device share the array and race.
-    return vms_replay_run(h, d_events, d_n_events, d_dec_split, d_dec_vms, h->ws_bytes ? g_scratch_ptr[dev] : nullptr,
-                          hip_stream);
+    return run_plan(h, small ? h->small : h->plan, small ? h->small_retry : h->retry, d_events, d_n_events, d_dec_split, d_dec_vms,
+                    h->ws_bytes ? g_scratch_ptr[dev] : nullptr, hip_stream);
 }
 
 int vms_replay_stats(vms_replay *h, vms_trace_stats *h_out, size_t n)
@@ -378,7 +397,7 @@ int vms_replay_last_kernel_ms(vms_replay *h, float out_ms[3])
     if (!h->ran) return VMS_ESTATE;
     HIP_TRY(h, hipEventSynchronize(h->ev[4]));
     HIP_TRY(h, hipEventElapsedTime(&out_ms[1], h->ev[0], h->ev[1]));
-    if (h->plan.together) out_ms[0] = out_ms[1];
+    if (h->last_together) out_ms[0] = out_ms[1];
     else HIP_TRY(h, hipEventElapsedTime(&out_ms[0], h->ev[2], h->ev[3]));
     HIP_TRY(h, hipEventElapsedTime(&out_ms[2], h->ev[0], h->ev[4]));
     return VMS_OK;

@@ -120,6 +120,28 @@ def test_slot_tables_too_large_for_global_memory_are_in_lds():
         gpu_util.assert_parity(ev, gpu_util.make_cfg(n, ev.shape[1], slots, variant=variant, max_runs=900), label="variant %d" % variant)
 
 
+def test_static_run_of_a_batch_whose_own_plan_needs_more_workspace():
+    # the library plans this batch on the fine-grained variant, whose lists do not fit the built-in workspace; the flat
+    # variant's do
+    import torch
+    n, ne = 1500, 200
+    ev, ms = tg.generate(1, n_traces=n, n_events=ne, seed=8)
+    cfg = gpu_util.make_cfg(n, ne, max(ms, 100))
+    rep = binding.Replay(cfg)
+    assert rep.workspace_bytes() > binding.lib().vms_replay_static_workspace_bytes()
+    d = torch.from_numpy(ev.view(np.int64)).cuda()
+    out = [torch.full_like(d, -1), torch.full_like(d, -1)]
+    for _ in range(2):
+        rep.run_static(d, None, *out)
+        st = rep.stats()
+        for pol in (oracle.SPLIT, oracle.VMS):
+            dec, ost = oracle.replay(ev, gpu_util.oracle_params(cfg), pol, threads=8)
+            assert np.array_equal(out[pol].cpu().numpy().view(np.uint64), dec)
+            assert np.array_equal(st[pol]["digest"], ost["digest"])
+        rep.run(d, None, *out)          # its own plan in between
+    rep.close()
+
+
 @pytest.mark.parametrize("slots", [3, 64, 65, 300])
 @pytest.mark.parametrize("kw", [dict(variant=1), dict(variant=1, spool_threshold=4, max_sblocks=128, max_runs=900), dict(variant=2),
                                 dict(variant=2, table_place=binding.VMS_TABLES_WORKSPACE_ALL, spool_threshold=4, max_sblocks=128, max_runs=160)])
