@@ -1264,15 +1264,18 @@ __global__ __launch_bounds__(64) void replay_vms_fine_kernel(KParams P, const u6
             }
             const u32 bsize = (size + chunk_units - 1) >> P.chunk_shift;
             u32 ref, place;
+            // What is searched for: with 16-bit chunk numbers there are at most 63,000 chunks, so a request for more than
+            // 65,534 looks for a size that no block has.  Cut to 16 bits it would meet the blocks of another size.
+            const u32 sought = sizeof(IDX) == 2 ? min(bsize, 0xFFFFu) : bsize;
             // S1: stitched blocks first, then primitive blocks (Algorithm 1, first loop)
-            if (fine_s1_sblock(V, bsize, ref, place)) {
+            if (fine_s1_sblock(V, sought, ref, place)) {
                 S.alloc_done(j, at, C_EXACT | B_SBLOCK | (1u << 8), ref, size, bsize << P.chunk_shift, ref, KIND_SBLOCK | (bsize << 2), place);
                 continue;
             }
             // pool[lo_p, hi_p): the multi-chunk pBlocks of exactly bsize chunks
             u32 lo_p, hi_p;
             {
-                const pkey_t k1 = V.key(bsize, 0), k2 = (pkey_t)(((pkey_t)bsize << V.W) - 1);
+                const pkey_t k1 = V.key(sought, 0), k2 = (pkey_t)(((pkey_t)sought << V.W) - 1);
                 const u32 b1 = V.pp.block(k1), b2 = V.pp.block(k2);
                 const pkey_t v1 = V.pool[b1 + lane], v2 = V.pool[b2 + lane];
                 lo_p = b1 + popc64(ballot(v1 > k1));

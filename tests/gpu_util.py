@@ -130,6 +130,16 @@ def slot_reuse_traces(slots, events, seed, traces=4):
     return out, np.array([events, events - 1, events - 63, events - 64][:traces], dtype=np.uint32)
 
 
+def huge_request_ops(chunks):
+    """Cached blocks of as many chunks as the low 16 bits of `chunks` say (at least two), then three requests for about
+    `chunks` chunks beside ordinary ones."""
+    mib = 1 << 20
+    low = max(chunks & 0xFFFF, 2) if chunks & 0xFFFF < 64 else 5
+    return [("A", 0, low * 2 * mib), ("A", 1, 2 * mib), ("A", 2, 3 * 2 * mib), ("F", 0), ("F", 2),
+            ("A", 3, (low + 2) * 2 * mib), ("F", 3), ("A", 4, chunks * 2 * mib), ("A", 0, low * 2 * mib), ("F", 0),
+            ("A", 5, (chunks - 1) * 2 * mib + 512), ("F", 5), ("A", 2, 2 * mib), ("A", 6, chunks * 2 * mib), ("F", 1), ("F", 4)]
+
+
 def alternate_frees_trace(n):
     """2 n requests of 1 KiB out of one chunk, then every second one back: each FREE adds a block to the splitting
     pool that merges with nothing, beside the rest of the chunk.  Returns (events, slots)."""

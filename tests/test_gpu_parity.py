@@ -304,6 +304,15 @@ def test_largest_requests_and_full_capacity():
         assert (st["peak_reserved"] == 512 * GiB).all()
 
 
+@pytest.mark.parametrize("chunks", [65535, 65536, 65541])
+def test_request_of_more_chunks_than_16_bits_count(chunks):
+    # fails for want of capacity, and does not meet a cached block of the same size modulo 65,536
+    ev = tg.make_events(gpu_util.huge_request_ops(chunks))[None, :]
+    for kw in [dict(variant=2, table_place=p) for p in (1, 2, 3)] + [dict(variant=1), dict(variant=1, max_pblocks=4, max_chunks=10, retry_traces=1)]:
+        st = gpu_util.assert_parity(ev, gpu_util.make_cfg(1, ev.shape[1], 16, capacity_bytes=4 << 30, **kw), label="%d chunks %s" % (chunks, kw))
+        assert st["n_code"][1, 0, 5] == 3
+
+
 def test_batch_summary_matches_the_oracle():
     # Sec. 5.1 "Metric": sums of the peaks, mean and maximum fragmentation over the batch, and the
     # memory reduction ratio (sum reserved splitting - sum reserved stitching) / sum reserved splitting,

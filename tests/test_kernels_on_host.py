@@ -277,3 +277,50 @@ def test_pool_in_global_memory(kind, events, kw):
     ev, ms = tg.generate(kind, n_traces=2, n_events=events, seed=11)
     cfg = gpu_util.make_cfg(2, events, ms, policy_mask=2, variant=2, table_place=binding.VMS_TABLES_WORKSPACE_ALL, **kw)
     check(ev, cfg, n_events=np.array([events, events - 37], dtype=np.uint32), label="generator %d" % kind, pool_in_mem=True)
+
+
+# requests of more chunks than 16 bits count: no block of that size can exist, so they fail (a capacity) or outgrow the
+# chunk table, and must not meet the blocks of the same size modulo 65,536
+HUGE = [65534, 65535, 65536, 65537, 65541, 131077, (1 << 19) - 4096]
+
+
+def assert_chunks_overflow(ev, cfg, chunks, n_events=None, **kw):
+    """Up to the engine's own capacity of 512 GiB the first such request outgrows the chunk table: the replay ends before
+    it, flagged."""
+    at = 7
+    if chunks * 2 * MiB > 512 << 30:
+        check(ev, cfg, n_events=n_events, label="%d chunks" % chunks, **kw)
+        return
+    _, dv, st = emu.replay(ev, cfg, binding.STATS_DTYPE, n_events, **kw)
+    P = gpu_util.oracle_params(cfg)
+    odec, ost = oracle.replay(ev[-1:], P, 1, n_events=[at])
+    g = st[1][-1]
+    assert g["status"] == binding.VMS_ST_TABLE_OVERFLOW | binding.VMS_ST_OVF_CHUNKS and g["overflow_event"] == at
+    assert np.array_equal(dv[-1, :at], odec[0, :at]) and (dv[-1, at:] == np.uint64(0xFFFFFFFFFFFFFFFF)).all()
+    for f in ("peak_active", "peak_reserved", "final_active", "final_reserved", "n_code", "digest"):
+        assert np.array_equal(g[f], ost[0][f]), f
+
+
+@pytest.mark.parametrize("chunks", HUGE)
+@pytest.mark.parametrize("place", [binding.VMS_TABLES_LDS, binding.VMS_TABLES_WORKSPACE, binding.VMS_TABLES_WORKSPACE_ALL, 4])
+@pytest.mark.parametrize("frag", [0, 6 * MiB])
+def test_request_of_more_chunks_than_16_bits_count(chunks, place, frag):
+    ev = tg.make_events(gpu_util.huge_request_ops(chunks))[None, :]
+    kw = dict(policy_mask=2, variant=binding.VMS_VARIANT_FINE, table_place=min(place, 3), frag_limit_bytes=frag)
+    in_mem = dict(pool_in_mem=place == 4)
+    st = check(ev, gpu_util.make_cfg(1, ev.shape[1], 16, capacity_bytes=4 << 30, **kw), label="%d chunks" % chunks, **in_mem)
+    assert st["n_code"][1, 0, 5] == 3
+    assert_chunks_overflow(ev, gpu_util.make_cfg(1, ev.shape[1], 16, **kw), chunks, **in_mem)
+
+
+# the same where the library chooses the variant, in the flat variant, and in the second pass behind it
+@pytest.mark.parametrize("chunks", [65536, 65541])
+@pytest.mark.parametrize("traces,slots,kw", [(1, 16, {}), (800, 650, {}), (2, 16, dict(variant=1, retry_traces=1, max_chunks=9000)),
+                                             (2, 16, dict(variant=2, retry_traces=1, max_chunks=9000))])
+def test_request_of_more_chunks_than_16_bits_count_by_default(chunks, traces, slots, kw):
+    one = tg.make_events(gpu_util.huge_request_ops(chunks))
+    ev = np.repeat(one[None, :], traces, axis=0)
+    n = np.full(traces, 0, dtype=np.uint32)
+    n[-1] = ev.shape[1]
+    check(ev, gpu_util.make_cfg(traces, ev.shape[1], slots, policy_mask=2, capacity_bytes=4 << 30, **kw), n_events=n, label="%d chunks" % chunks)
+    assert_chunks_overflow(ev, gpu_util.make_cfg(traces, ev.shape[1], slots, policy_mask=2, **kw), chunks, n_events=n)
