@@ -359,7 +359,7 @@ struct Replay {
     u64 alloc_vms(Slot &s, u64 size, u32 ev)
     {
         const u32 bsize = (u32)((size + chunk_units - 1) / chunk_units);   // chunks (Sec. 3.1: uniform chunks)
-        const u32 frag_limit = (u32)(P.frag_limit_bytes / P.chunk_bytes);
+        const u32 frag_limit = (u32)std::min<u64>(P.frag_limit_bytes / P.chunk_bytes, 0xFFFFFFFFu);
 
         // S1: exact match, stitched blocks first, then primitive blocks, each in pool order
         for (auto it = vp.spool.lower_bound(SKey{ bsize, 0 }); it != vp.spool.end() && it->first.size == bsize; ++it) {

@@ -196,7 +196,9 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_m
         k.max_events = c.max_events;
         k.chunk_shift = shift;
         k.small_limit_units = (uint32_t)(c.small_limit_bytes / UNIT);
-        k.frag_limit_chunks = (uint32_t)(c.frag_limit_bytes / c.chunk_bytes);
+        // (no block has more than max_chunks chunks; the kernels make keys of this limit, in as many bits as a chunk number has)
+        const uint64_t limit = c.frag_limit_bytes / c.chunk_bytes;
+        k.frag_limit_chunks = limit > c.max_chunks ? c.max_chunks + 1 : (uint32_t)limit;
         k.spool_threshold = c.spool_threshold;
         k.capacity_units = (uint32_t)(cap / UNIT);
         k.max_slots = c.max_slots;

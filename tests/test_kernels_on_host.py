@@ -324,3 +324,14 @@ def test_request_of_more_chunks_than_16_bits_count_by_default(chunks, traces, sl
     n[-1] = ev.shape[1]
     check(ev, gpu_util.make_cfg(traces, ev.shape[1], slots, policy_mask=2, capacity_bytes=4 << 30, **kw), n_events=n, label="%d chunks" % chunks)
     assert_chunks_overflow(ev, gpu_util.make_cfg(traces, ev.shape[1], slots, policy_mask=2, **kw), chunks, n_events=n)
+
+
+# limits of more chunks than 16 bits count, and of more than a trace has: no block is split or stitched
+@pytest.mark.parametrize("chunks", [4096, 62999, 65535, 65536, 65537, 65541, 1 << 32])
+@pytest.mark.parametrize("variant,place", [(1, 0), (2, 1), (2, 3), (2, 4)])
+def test_fragmentation_limit_of_more_chunks_than_16_bits_count(chunks, variant, place):
+    ev, ms = tg.generate(1, n_traces=1, n_events=300, seed=3)
+    cfg = gpu_util.make_cfg(1, 300, ms, policy_mask=2, variant=variant, table_place=min(place, 3), max_chunks=4095,
+                            frag_limit_bytes=chunks * 2 * MiB)
+    st = check(ev, cfg, label="limit of %d chunks" % chunks, pool_in_mem=place == 4)
+    assert st["max_members"][1, 0] <= 1
