@@ -146,9 +146,9 @@ inline uint64_t layout(KParams &k, int policy, const vms_config &c, const Replay
 // The plan for cfg with the variant it names (0: flat unless the tables are too large for it).
 // VMS_OK, VMS_EINVAL / VMS_ESTRUCT for a configuration that makes no sense, VMS_ETOOBIG for tables
 // that do not fit a compute unit's LDS.  Touches no device.
-// slots_in_mem: slot tables of more than 64 slots in global memory, unless they take too much of it; pool_in_mem: with
-// all sBlock tables in the workspace pool[] goes there too, likewise.
-inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_mem, bool pool_in_mem = false)
+// slots_in_mem: slot tables of more than 64 slots in global memory, unless they take too much of it (any_size: even
+// then); pool_in_mem: with all sBlock tables in the workspace pool[] goes there too, likewise.
+inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_mem, bool pool_in_mem = false, bool any_size = false)
 {
     using namespace plan_detail;
     if (!cfg) return VMS_EINVAL;
@@ -182,7 +182,7 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_m
     p.tbl_ws = p.fine && !p.wide && c.table_place >= VMS_TABLES_WORKSPACE ? (int)c.table_place : 0;
     if (c.table_place >= VMS_TABLES_WORKSPACE && p.fine && p.wide) return VMS_EINVAL;
     p.slot_regs = c.max_slots <= 64;
-    slots_in_mem = slots_in_mem && c.n_traces * slot_table_bytes(c.max_slots, 1) <= MEM_TABLES_MAX;
+    slots_in_mem = slots_in_mem && (any_size || c.n_traces * slot_table_bytes(c.max_slots, 1) <= MEM_TABLES_MAX);
     p.slots = p.slot_regs ? SLOTS_IN_REGS : slots_in_mem ? SLOTS_IN_MEM : SLOTS_IN_LDS;
     p.fl_tiles = c.max_free_blocks <= 192 ? 3u : 5u;
     p.fl_tail = c.max_free_blocks > 320;
@@ -234,17 +234,12 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_m
         }
         k.mem_pool = p.slots == SLOTS_IN_MEM ? slot_table_bytes(c.max_slots, pol) : 0;
         k.mem_stride = k.mem_pool + (pol && p.tbl_ws == 4 ? align_up(pool_bytes(k, p), 16) : 0);
-        const uint64_t need = layout(k, pol, c, p) + pool_bytes_saved(k, pol, p) + slot_bytes_saved(c.max_slots, pol, p);
-        if ((c.policy_mask & (1u << pol)) && need > LDS_PER_CU) {
-            // flat variant: the lists' places in a slot table in LDS are there for speed only; tables that fit
-            // without them are served by the fine-grained variant
-            const uint64_t lists = pol && !p.fine && !p.slot_regs ? 4ull * c.max_slots + 16 : 0;
-            if (need - lists > LDS_PER_CU) return VMS_ETOOBIG;
-            vms_config alt = c;
-            alt.variant = VMS_VARIANT_FINE;
-            alt.table_place = VMS_TABLES_AUTO;
-            return replay_plan_for(&alt, p, slots_in_mem);
-        }
+        const uint64_t lds = layout(k, pol, c, p), need = lds + pool_bytes_saved(k, pol, p) + slot_bytes_saved(c.max_slots, pol, p);
+        // flat variant: the lists' places in a slot table in LDS are there for speed only and refuse no tables; where
+        // there is no room for them the slot table is in global memory, whatever it takes there
+        const uint64_t lists = pol && !p.fine && !p.slot_regs ? align_up(4ull * c.max_slots, 16) : 0;
+        if ((c.policy_mask & (1u << pol)) && need - lists > LDS_PER_CU) return VMS_ETOOBIG;
+        if ((c.policy_mask & (1u << pol)) && lds > LDS_PER_CU) return replay_plan_for(cfg, p, true, pool_in_mem, true);
     }
     p.ws_bytes = (c.policy_mask & VMS_POLICY_VMS) ? (size_t)p.kp[1].ws_stride * c.n_traces : 0;
     return VMS_OK;
@@ -394,6 +389,33 @@ inline int replay_plan_retry(const vms_config *cfg, const ReplayPlan &first, Rep
     }
     memset(&q, 0, sizeof q);
     return VMS_OK;
+}
+
+// For a handle whose own plans need more than `room` bytes of workspace: those that need least, with first.ws_bytes 0
+// if they need more than that too.
+inline void replay_plan_small(const vms_config *cfg, uint64_t room, ReplayPlan &first, ReplayPlan &second)
+{
+    if (replay_plan_for(cfg, first, false) != VMS_OK || replay_plan_retry(cfg, first, second) != VMS_OK ||
+        first.ws_bytes + second.ws_bytes > room)
+        first.ws_bytes = 0;
+}
+
+// wavefronts of the second pass
+inline uint32_t plan_second_pass_waves(const vms_config &c) { return c.retry_traces < c.n_traces ? c.retry_traces : c.n_traces; }
+
+// The tables of a run that are in global memory, those of each launch behind those of the one before: returns their
+// bytes, and with `mem` says where each launch finds its own.
+inline uint64_t plan_place_tables(const vms_config &c, ReplayPlan &first, ReplayPlan &second, char *mem)
+{
+    uint64_t bytes = 0;
+    for (int pass = 0; pass < (second.has_retry ? 2 : 1); pass++)
+        for (int pol = 0; pol < 2; pol++) {
+            if (!(c.policy_mask & (1u << pol))) continue;
+            KParams &k = (pass ? second : first).kp[pol];
+            if (mem) k.mem = mem + bytes;
+            bytes += plan_detail::align_up(k.mem_stride * (pass ? plan_second_pass_waves(c) : c.n_traces), 256);
+        }
+    return bytes;
 }
 
 #endif

@@ -186,29 +186,22 @@ void vms_config_default(vms_config *cfg, uint32_t n_traces, uint32_t max_events,
     cfg->max_chunks = 32768;    // 64 GiB of 2 MiB chunks
 }
 
-static inline uint32_t second_pass_waves(const vms_config &c) { return c.retry_traces < c.n_traces ? c.retry_traces : c.n_traces; }
-
-// One allocation for the tables of all launches of a run that are in global memory: a wavefront writes its slice
-// before it reads it.
+// One allocation for the tables in global memory of all launches of a run, under whichever plan it goes: a wavefront
+// writes its slice before it reads it, and the runs of a handle do not overlap.
 static hipError_t alloc_tables(vms_replay *h)
 {
-    const vms_config &c = h->cfg;
-    size_t bytes = 0;
-    for (int set = 0; set < 2; set++) {
-        KParams *kp[2] = { h->plan.kp, h->retry.kp };
-        for (int pass = 0; pass < (h->retry.has_retry ? 2 : 1); pass++)
-            for (int pol = 0; pol < 2; pol++) {
-                if (!(c.policy_mask & (1u << pol))) continue;
-                KParams &k = kp[pass][pol];
-                if (set) k.mem = h->d_mem + bytes;
-                bytes += (k.mem_stride * (pass ? second_pass_waves(c) : c.n_traces) + 255) / 256 * 256;
-            }
-        if (set || !bytes) break;
+    char *mem = nullptr;
+    for (;;) {
+        uint64_t bytes = plan_place_tables(h->cfg, h->plan, h->retry, mem);
+        if (h->small.ws_bytes) {
+            const uint64_t b = plan_place_tables(h->cfg, h->small, h->small_retry, mem);
+            bytes = b > bytes ? b : bytes;
+        }
+        if (mem || !bytes) return hipSuccess;
         const hipError_t e = hipMalloc((void **)&h->d_mem, bytes);
         if (e != hipSuccess) return e;
-        bytes = 0;
+        mem = h->d_mem;
     }
-    return hipSuccess;
 }
 
 int vms_replay_create(const vms_config *cfg, vms_replay **out)
@@ -234,9 +227,7 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
         for (int pol = 0; pol < 2; pol++) h->plan.kp[pol].retry_slots = c.retry_traces;    // the first pass resets the count
     h->ws_bytes = plan.ws_bytes + h->retry.ws_bytes;
     if (h->ws_bytes > STATIC_WS_BYTES) {
-        if (replay_plan_for(cfg, h->small, false) != VMS_OK || replay_plan_retry(cfg, h->small, h->small_retry) != VMS_OK ||
-            h->small.ws_bytes + h->small_retry.ws_bytes > STATIC_WS_BYTES)
-            h->small.ws_bytes = 0;
+        replay_plan_small(cfg, STATIC_WS_BYTES, h->small, h->small_retry);
         if (h->small_retry.has_retry)
             for (int pol = 0; pol < 2; pol++) h->small.kp[pol].retry_slots = c.retry_traces;
     }
@@ -310,7 +301,7 @@ static int run_plan(vms_replay *h, const ReplayPlan &plan, const ReplayPlan &ret
     HIP_TRY(h, hipEventRecord(h->ev[1], st));       // the kernel times are those of the first pass
     if ((c.policy_mask & VMS_POLICY_VMS) && retry.has_retry) {
         // second pass: retry_traces wavefronts with larger tables replay the traces whose tables overflowed
-        hipLaunchKernelGGL(pick_vms(retry), dim3(second_pass_waves(c)), dim3(64), retry.kp[1].lds_bytes, st, retry.kp[1],
+        hipLaunchKernelGGL(pick_vms(retry), dim3(plan_second_pass_waves(c)), dim3(64), retry.kp[1].lds_bytes, st, retry.kp[1],
                            d_events, d_n_events, d_dec_vms, h->d_stats, (char *)d_workspace);
         HIP_TRY(h, hipGetLastError());
     }
@@ -322,7 +313,7 @@ static int run_plan(vms_replay *h, const ReplayPlan &plan, const ReplayPlan &ret
     }
     if (!plan.together) HIP_TRY(h, hipEventRecord(h->ev[3], sst));
     if ((c.policy_mask & VMS_POLICY_SPLIT) && retry.has_retry) {
-        hipLaunchKernelGGL(pick_split(retry), dim3(second_pass_waves(c)), dim3(64),
+        hipLaunchKernelGGL(pick_split(retry), dim3(plan_second_pass_waves(c)), dim3(64),
                            retry.kp[0].lds_bytes, sst, retry.kp[0], d_events, d_n_events, d_dec_split, h->d_stats);
         HIP_TRY(h, hipGetLastError());
     }

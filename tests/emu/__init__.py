@@ -34,26 +34,39 @@ def lib():
         _lib.emu_replay.restype = ctypes.c_int
         _lib.emu_replay.argtypes = [vp, vp, vp, vp, vp, vp]
         _lib.emu_selftest.restype = ctypes.c_uint
-        _lib.emu_plan_lds.restype = ctypes.c_int
-        _lib.emu_plan_lds.argtypes = [vp]
+        _lib.emu_plan.restype = ctypes.c_int
+        _lib.emu_plan.argtypes = [vp, vp]
     return _lib
 
 
+class Plan(ctypes.Structure):
+    """What tests ask of a plan; slots: SLOTS_IN_LDS, SLOTS_IN_REGS or SLOTS_IN_MEM."""
+    _fields_ = [("fine", ctypes.c_uint32), ("slots", ctypes.c_uint32), ("tbl_ws", ctypes.c_uint32), ("lds_bytes", ctypes.c_uint32 * 2),
+                ("mem_stride", ctypes.c_uint64 * 2)]
+
+
+SLOTS_IN_LDS, SLOTS_IN_REGS, SLOTS_IN_MEM = 0, 1, 2
+
+
 def plan(cfg):
-    """LDS bytes of a wavefront of the stitching kernel under the plan the library makes for cfg."""
-    return lib().emu_plan_lds(ctypes.byref(cfg))
+    """(VMS_OK or an error code, the plan the library makes for cfg)."""
+    out = Plan()
+    return lib().emu_plan(ctypes.byref(cfg), ctypes.byref(out)), out
 
 
-def replay(events, cfg, stats_dtype, n_events=None, pool_in_mem=False):
+PLAN_OF_LIBRARY, PLAN_POOL_IN_MEM, PLAN_SMALL = 0, 1, 2
+
+
+def replay(events, cfg, stats_dtype, n_events=None, pool_in_mem=False, small=False):
     """events: uint64[n_traces, max_events]; cfg: the binding's vms_config; pool_in_mem: the plan of a large batch with
-    all tables in the workspace (cfg names VMS_TABLES_WORKSPACE_ALL).
+    all tables in the workspace (cfg names VMS_TABLES_WORKSPACE_ALL); small: the plan that needs least workspace.
     Returns (dec_split, dec_vms, stats[2, n_traces])."""
     ev = np.ascontiguousarray(events, dtype=np.uint64)
     assert ev.shape == (cfg.n_traces, cfg.max_events)
     ds, dv = np.zeros_like(ev), np.zeros_like(ev)
     st = np.zeros((2, cfg.n_traces), dtype=stats_dtype)
     ne = None if n_events is None else np.ascontiguousarray(n_events, dtype=np.uint32)
-    lib().emu_pool_in_mem(1 if pool_in_mem else 0)
+    lib().emu_use_plan(PLAN_POOL_IN_MEM if pool_in_mem else PLAN_SMALL if small else PLAN_OF_LIBRARY)
     rc = lib().emu_replay(ctypes.byref(cfg), ev.ctypes.data, None if ne is None else ne.ctypes.data,
                           ds.ctypes.data, dv.ctypes.data, st.ctypes.data)
     if rc != 0:

@@ -142,12 +142,20 @@ void body_selftest(void *tab) { selftest_kernel(&g_selftest_fail, (uint16_t *)ta
 
 }  // namespace
 
-static bool g_pool_in_mem;
+enum { PLAN_OF_LIBRARY, PLAN_POOL_IN_MEM, PLAN_SMALL };
+static int g_plan;
 
 extern "C" {
 
-// the fine-grained variant with all its tables out of the LDS, which the library plans for large batches only
-void emu_pool_in_mem(int on) { g_pool_in_mem = on != 0; }
+// what tests ask of a plan
+struct emu_plan_info {
+    uint32_t fine, slots, tbl_ws, lds_bytes[2];
+    uint64_t mem_stride[2];
+};
+
+// the plan that emu_replay runs: the library's; the fine-grained variant with all its tables out of the LDS, which the
+// library plans for large batches only; the one that needs least workspace
+void emu_use_plan(int which) { g_plan = which; }
 
 // Replays every trace under the policies of cfg->policy_mask with the kernels the library would
 // launch.  dec_split / dec_vms: [n_traces][max_events] or NULL; stats: [2][n_traces].
@@ -156,24 +164,19 @@ void emu_pool_in_mem(int on) { g_pool_in_mem = on != 0; }
 int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_events, uint64_t *dec_split,
                uint64_t *dec_vms, vms_trace_stats *stats)
 {
-    ReplayPlan plan;
+    ReplayPlan plan, again;
     int rc = replay_plan_make(cfg, plan);
-    if (rc == VMS_OK && g_pool_in_mem) rc = replay_plan_for(cfg, plan, true, true);
-    if (rc != VMS_OK) return rc;
-    ReplayPlan again;
-    rc = replay_plan_retry(cfg, plan, again);
+    if (rc == VMS_OK && g_plan == PLAN_POOL_IN_MEM) rc = replay_plan_for(cfg, plan, true, true);
+    if (rc == VMS_OK && g_plan != PLAN_SMALL) rc = replay_plan_retry(cfg, plan, again);
+    if (rc == VMS_OK && g_plan == PLAN_SMALL) replay_plan_small(cfg, ~0ull, plan, again);
     if (rc != VMS_OK) return rc;
     if (again.has_retry)
         for (int pol = 0; pol < 2; pol++) plan.kp[pol].retry_slots = cfg->retry_traces;
     const size_t n = (size_t)cfg->n_traces * cfg->max_events, ws_bytes = plan.ws_bytes + again.ws_bytes;
     Guarded g_dec(n * 8), g_stats(sizeof(vms_trace_stats) * (2 * cfg->n_traces + 1)), g_ws(ws_bytes ? ws_bytes : 256);
     memset(g_stats.ptr(), 0, g_stats.bytes);
-    // tables in global memory: of both passes, each policy's in turn
-    Guarded g_mem[2] = { Guarded(plan.kp[1].mem_stride * cfg->n_traces), Guarded(again.kp[1].mem_stride * cfg->retry_traces) };
-    for (int pol = 0; pol < 2; pol++) {
-        plan.kp[pol].mem = g_mem[0].ptr();
-        again.kp[pol].mem = g_mem[1].ptr();
-    }
+    Guarded g_mem(plan_place_tables(*cfg, plan, again, nullptr));
+    plan_place_tables(*cfg, plan, again, g_mem.ptr());
     for (int pol = 0; pol < 2; pol++) {
         if (!(cfg->policy_mask & (1u << pol))) continue;
         Args a;
@@ -209,19 +212,27 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
         if (!g_dec.intact()) return -102;
         if (!g_stats.intact()) return -103;
         if (!g_ws.intact()) return -104;
-        if (!g_mem[0].intact() || !g_mem[1].intact()) return -105;
+        if (!g_mem.intact()) return -105;
         if (out) memcpy(out, g_dec.ptr(), n * 8);
     }
     memcpy(stats, g_stats.ptr(), sizeof(vms_trace_stats) * 2 * cfg->n_traces);
     return 0;
 }
 
-// LDS bytes of a wavefront of the stitching kernel under the plan the library makes for cfg, or a VMS_E* code
-int emu_plan_lds(const vms_config *cfg)
+// What the library plans for cfg.  Returns VMS_OK or a VMS_E* code.
+int emu_plan(const vms_config *cfg, emu_plan_info *out)
 {
-    ReplayPlan plan;
-    const int rc = replay_plan_make(cfg, plan);
-    return rc == VMS_OK ? (int)plan.kp[1].lds_bytes : rc;
+    ReplayPlan p;
+    const int rc = replay_plan_make(cfg, p);
+    if (rc != VMS_OK) return rc;
+    out->fine = p.fine;
+    out->slots = p.slots;
+    out->tbl_ws = p.tbl_ws;
+    for (int pol = 0; pol < 2; pol++) {
+        out->lds_bytes[pol] = p.kp[pol].lds_bytes;
+        out->mem_stride[pol] = p.kp[pol].mem_stride;
+    }
+    return VMS_OK;
 }
 
 // the wave primitives' self-test kernel on the host lanes: 0, its failure bits, or 0xFFFFFFFF if a guard band was written

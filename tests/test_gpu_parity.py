@@ -120,6 +120,24 @@ def test_slot_tables_too_large_for_global_memory_are_in_lds():
         gpu_util.assert_parity(ev, gpu_util.make_cfg(n, ev.shape[1], slots, variant=variant, max_runs=900), label="variant %d" % variant)
 
 
+def test_slot_tables_that_leave_no_room_in_lds_are_in_global_memory():
+    # 11,800 slots: three words each fit beside the other tables, the flat variant's four do not
+    import torch
+    n, slots = 200, 11800
+    ev, _ = gpu_util.slot_reuse_traces(slots, 64 * 3, seed=4)
+    ev = np.ascontiguousarray(np.tile(ev, (n // 4, 1)))
+    cfg = gpu_util.make_cfg(n, ev.shape[1], slots, variant=1, max_free_blocks=64, max_small_blocks=64, max_pblocks=128,
+                            max_sblocks=520, max_runs=400, max_chunks=640, retry_traces=2)
+    gpu_util.assert_parity(ev, cfg, label="run")
+    rep, d = binding.Replay(cfg), torch.from_numpy(ev.view(np.int64)).to("cuda:0")
+    out = torch.zeros_like(d), torch.zeros_like(d)
+    rep.run_static(d, None, *out)
+    for pol in (oracle.SPLIT, oracle.VMS):
+        dec, _ = oracle.replay(ev[:4], gpu_util.oracle_params(cfg), pol)
+        assert np.array_equal(out[pol].cpu().numpy().view(np.uint64), np.tile(dec, (n // 4, 1)))
+    rep.close()
+
+
 def test_static_run_of_a_batch_whose_own_plan_needs_more_workspace():
     # the library plans this batch on the fine-grained variant, whose lists do not fit the built-in workspace; the flat
     # variant's do

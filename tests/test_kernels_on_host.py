@@ -185,8 +185,8 @@ def test_both_policies_in_one_launch(kind, free):
     (6, 1163, [(64, 50560), (512, 50560), (1024, 31936), (1280, 31936), (1281, 10304), (4096, 6560)])])
 def test_plan_of_a_batch_by_its_size(config, slots, sizes):
     for n, lds in sizes:
-        out = emu.plan(workloads.make_config(binding, config, n, 20000, slots))
-        assert out == lds, (config, n, out)
+        rc, out = emu.plan(workloads.make_config(binding, config, n, 20000, slots))
+        assert rc == 0 and out.lds_bytes[1] == lds, (config, n, rc, out.lds_bytes[1])
 
 
 # slot tables in registers (up to 64 slots), in LDS (flat variant) and in global memory; a capacity that is reached, and an arena that is squeezed often
@@ -335,3 +335,26 @@ def test_fragmentation_limit_of_more_chunks_than_16_bits_count(chunks, variant, 
                             frag_limit_bytes=chunks * 2 * MiB)
     st = check(ev, cfg, label="limit of %d chunks" % chunks, pool_in_mem=place == 4)
     assert st["max_members"][1, 0] <= 1
+
+
+# The list places in the slot table of the flat variant are there for speed only: a slot table that leaves no room for
+# them in LDS (up to about 12,500 slots of three words each beside the smallest other tables) is in global memory,
+# whatever it takes there, and the tables are neither refused nor moved to the fine-grained variant.
+@pytest.mark.parametrize("slots,traces,ok", [(9800, 1, True), (12400, 1, True), (12400, 1 << 16, True), (13700, 1, False)])
+@pytest.mark.parametrize("variant", [binding.VMS_VARIANT_AUTO, binding.VMS_VARIANT_FLAT])
+def test_plan_of_a_slot_table_as_large_as_the_lds(slots, traces, ok, variant):
+    cfg = gpu_util.make_cfg(traces, 9, slots, variant=variant, max_free_blocks=8, max_small_blocks=8, max_pblocks=16, max_sblocks=520,
+                            max_runs=64, max_chunks=640)
+    rc, p = emu.plan(cfg)
+    assert rc == (0 if ok else -6)
+    if ok:
+        assert p.slots == emu.SLOTS_IN_MEM and p.lds_bytes[1] < 20000
+        assert not p.fine or variant == binding.VMS_VARIANT_AUTO
+
+
+@pytest.mark.parametrize("small", [False, True])
+def test_slot_table_as_large_as_the_lds(small):
+    ev, n = gpu_util.slot_reuse_traces(11800, 64 * 9, seed=3)
+    check(ev, gpu_util.make_cfg(4, ev.shape[1], 11800, variant=binding.VMS_VARIANT_FLAT, max_free_blocks=64, max_small_blocks=64,
+                                max_pblocks=128, max_sblocks=520, max_runs=400, max_chunks=640, retry_traces=1),
+          n_events=n, label="11,800 slots", small=small)
