@@ -369,8 +369,10 @@ inline int replay_plan_retry(const vms_config *cfg, const ReplayPlan &first, Rep
     big.max_runs = twice(cfg->max_runs < (1u << 16) ? (1u << 16) : cfg->max_runs, plan_detail::TABLE_MAX);
     big.max_chunks = twice(cfg->max_chunks, plan_detail::TABLE_MAX);
     while ((uint64_t)big.max_chunks * big.chunk_bytes > plan_detail::ENGINE_MAX_BYTES) big.max_chunks /= 2;
-    // shrink towards the first pass's sizes until the tables fit
-    for (int tries = 0; tries < 8; tries++) {
+    // shrink towards the first pass's sizes until the tables fit; that of the multi-chunk pBlocks, of which a handle may
+    // name more than pBlocks, when the others have been
+    const uint32_t multi = first.fine ? first.kp[1].cap_pblocks : 0;
+    for (int tries = 0; tries < 11; tries++) {
         const int rc = replay_plan_for(&big, q, first.slots == SLOTS_IN_MEM);
         if (rc == VMS_OK) {
             q.has_retry = true;
@@ -386,6 +388,7 @@ inline int replay_plan_retry(const vms_config *cfg, const ReplayPlan &first, Rep
         big.max_chunks = big.max_chunks / 2 > cfg->max_chunks ? big.max_chunks / 2 : cfg->max_chunks;
         big.max_sblocks = big.max_sblocks * 3 / 4 > cfg->max_sblocks ? big.max_sblocks * 3 / 4 : cfg->max_sblocks;
         big.max_free_blocks = big.max_free_blocks / 2 > cfg->max_free_blocks ? big.max_free_blocks / 2 : cfg->max_free_blocks;
+        if (tries >= 7 && multi) big.max_multi_pblocks = big.max_multi_pblocks * 3 / 4 > multi ? big.max_multi_pblocks * 3 / 4 : multi;
     }
     memset(&q, 0, sizeof q);
     return VMS_OK;

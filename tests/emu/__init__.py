@@ -41,7 +41,7 @@ def lib():
 
 class Plan(ctypes.Structure):
     """What tests ask of a plan; slots: SLOTS_IN_LDS, SLOTS_IN_REGS or SLOTS_IN_MEM."""
-    _fields_ = [("fine", ctypes.c_uint32), ("slots", ctypes.c_uint32), ("tbl_ws", ctypes.c_uint32), ("lds_bytes", ctypes.c_uint32 * 2),
+    _fields_ = [("fine", ctypes.c_uint32), ("slots", ctypes.c_uint32), ("tbl_ws", ctypes.c_uint32), ("has_retry", ctypes.c_uint32), ("lds_bytes", ctypes.c_uint32 * 2),
                 ("mem_stride", ctypes.c_uint64 * 2)]
 
 

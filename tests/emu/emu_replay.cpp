@@ -149,7 +149,7 @@ extern "C" {
 
 // what tests ask of a plan
 struct emu_plan_info {
-    uint32_t fine, slots, tbl_ws, lds_bytes[2];
+    uint32_t fine, slots, tbl_ws, has_retry, lds_bytes[2];
     uint64_t mem_stride[2];
 };
 
@@ -219,12 +219,14 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
     return 0;
 }
 
-// What the library plans for cfg.  Returns VMS_OK or a VMS_E* code.
+// What the library plans for cfg (has_retry: a second pass too).  Returns VMS_OK or a VMS_E* code.
 int emu_plan(const vms_config *cfg, emu_plan_info *out)
 {
-    ReplayPlan p;
-    const int rc = replay_plan_make(cfg, p);
+    ReplayPlan p, again;
+    int rc = replay_plan_make(cfg, p);
+    if (rc == VMS_OK) rc = replay_plan_retry(cfg, p, again);
     if (rc != VMS_OK) return rc;
+    out->has_retry = again.has_retry;
     out->fine = p.fine;
     out->slots = p.slots;
     out->tbl_ws = p.tbl_ws;

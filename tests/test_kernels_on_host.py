@@ -358,3 +358,11 @@ def test_slot_table_as_large_as_the_lds(small):
     check(ev, gpu_util.make_cfg(4, ev.shape[1], 11800, variant=binding.VMS_VARIANT_FLAT, max_free_blocks=64, max_small_blocks=64,
                                 max_pblocks=128, max_sblocks=520, max_runs=400, max_chunks=640, retry_traces=1),
           n_events=n, label="11,800 slots", small=small)
+
+
+# The second pass shrinks its tables towards the first one's until they fit, the table of multi-chunk pBlocks among them
+def test_second_pass_shrinks_the_table_of_multi_chunk_pblocks():
+    cfg = gpu_util.make_cfg(1, 9, 10099, policy_mask=2, variant=binding.VMS_VARIANT_FINE, max_free_blocks=8, max_small_blocks=8,
+                            max_pblocks=16, max_multi_pblocks=2855, max_sblocks=900, max_runs=64, max_chunks=64, retry_traces=1)
+    rc, p = emu.plan(cfg)
+    assert rc == 0 and p.fine and p.has_retry
