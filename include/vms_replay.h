@@ -188,8 +188,10 @@ void vms_config_default(vms_config *cfg, uint32_t n_traces, uint32_t max_events,
 
 /* Validate cfg, choose the LDS layout and allocate the device statistics
  * buffer (n_traces * 2 records) and, for batches that need the room in LDS, slot
- * tables and pBlock tables (at most 2 GiB per policy and pass) on the current HIP
- * device.  *out is owned by the caller until vms_replay_destroy.               */
+ * tables and pBlock tables (at most 2 GiB per policy and pass; more only for slot
+ * tables that the LDS has no room for) on the current HIP device.  Where the
+ * device has no memory left for these tables they are kept in LDS.  *out is
+ * owned by the caller until vms_replay_destroy.                                */
 int vms_replay_create(const vms_config *cfg, vms_replay **out);
 
 /* Bytes of device scratch memory vms_replay_run needs (may be 0); the caller

@@ -345,9 +345,10 @@ inline int replay_plan_choose(const vms_config *cfg, ReplayPlan &p)
     return VMS_OK;
 }
 
-inline int replay_plan_make(const vms_config *cfg, ReplayPlan &p)
+// in_lds: without tables in global memory (but for those the LDS has no room for), whatever that costs
+inline int replay_plan_make(const vms_config *cfg, ReplayPlan &p, bool in_lds = false)
 {
-    const int rc = replay_plan_choose(cfg, p);
+    const int rc = in_lds ? replay_plan_for(cfg, p, false) : replay_plan_choose(cfg, p);
     if (rc == VMS_OK) p.together = plan_together(p, *cfg);
     return rc;
 }

@@ -186,6 +186,24 @@ void vms_config_default(vms_config *cfg, uint32_t n_traces, uint32_t max_events,
     cfg->max_chunks = 32768;    // 64 GiB of 2 MiB chunks
 }
 
+// The plans of a handle for its cfg: of both passes, and of runs in the built-in workspace (see replay_plan_make)
+static int make_plans(vms_replay *h, bool in_lds)
+{
+    const vms_config &c = h->cfg;
+    int rc = replay_plan_make(&c, h->plan, in_lds);
+    if (rc == VMS_OK) rc = replay_plan_retry(&c, h->plan, h->retry);
+    if (rc != VMS_OK) return rc;
+    h->ws_bytes = h->plan.ws_bytes + h->retry.ws_bytes;
+    memset(&h->small, 0, sizeof h->small);
+    memset(&h->small_retry, 0, sizeof h->small_retry);
+    if (h->ws_bytes > STATIC_WS_BYTES) replay_plan_small(&c, STATIC_WS_BYTES, h->small, h->small_retry);
+    for (int pol = 0; pol < 2; pol++) {     // the first pass resets the second one's count
+        if (h->retry.has_retry) h->plan.kp[pol].retry_slots = c.retry_traces;
+        if (h->small_retry.has_retry) h->small.kp[pol].retry_slots = c.retry_traces;
+    }
+    return VMS_OK;
+}
+
 // One allocation for the tables in global memory of all launches of a run, under whichever plan it goes: a wavefront
 // writes its slice before it reads it, and the runs of a handle do not overlap.
 static hipError_t alloc_tables(vms_replay *h)
@@ -199,7 +217,10 @@ static hipError_t alloc_tables(vms_replay *h)
         }
         if (mem || !bytes) return hipSuccess;
         const hipError_t e = hipMalloc((void **)&h->d_mem, bytes);
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess) {
+            h->d_mem = nullptr;
+            return e;
+        }
         mem = h->d_mem;
     }
 }
@@ -208,28 +229,16 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
 {
     if (!cfg || !out) return VMS_EINVAL;
     *out = nullptr;
-    ReplayPlan plan;
-    const int prc = replay_plan_make(cfg, plan);      // refuses bad or oversized tables before any device call
-    if (prc != VMS_OK) return prc;
-    const vms_config &c = *cfg;
-
+    if (cfg->struct_size != sizeof(vms_config)) return VMS_ESTRUCT;
     vms_replay *h = new (std::nothrow) vms_replay;
     if (!h) return VMS_ENOMEM;
     memset(h, 0, sizeof *h);
-    h->cfg = c;
-    h->plan = plan;
-    const int rrc = replay_plan_retry(cfg, plan, h->retry);
-    if (rrc != VMS_OK) {
+    h->cfg = *cfg;
+    const vms_config &c = h->cfg;
+    const int prc = make_plans(h, false);             // refuses bad or oversized tables before any device call
+    if (prc != VMS_OK) {
         delete h;
-        return rrc;
-    }
-    if (h->retry.has_retry)
-        for (int pol = 0; pol < 2; pol++) h->plan.kp[pol].retry_slots = c.retry_traces;    // the first pass resets the count
-    h->ws_bytes = plan.ws_bytes + h->retry.ws_bytes;
-    if (h->ws_bytes > STATIC_WS_BYTES) {
-        replay_plan_small(cfg, STATIC_WS_BYTES, h->small, h->small_retry);
-        if (h->small_retry.has_retry)
-            for (int pol = 0; pol < 2; pol++) h->small.kp[pol].retry_slots = c.retry_traces;
+        return prc;
     }
 
     if (hipGetDevice(&h->device) != hipSuccess) {
@@ -241,7 +250,11 @@ int vms_replay_create(const vms_config *cfg, vms_replay **out)
     // records of a policy that never runs stay zero; a run rewrites every record of its policies
     if (e == hipSuccess) e = hipMemset(h->d_stats, 0, sizeof(vms_trace_stats) * (2 * (size_t)c.n_traces + 1));
     if (e == hipSuccess) e = hipMalloc((void **)&h->d_summary, sizeof(vms_summary));
-    if (e == hipSuccess) e = alloc_tables(h);
+    if (e == hipSuccess && (e = alloc_tables(h)) == hipErrorOutOfMemory) {
+        // these tables are there for speed: without the memory for them they are in LDS
+        (void)hipGetLastError();
+        e = make_plans(h, true) == VMS_OK ? alloc_tables(h) : hipErrorUnknown;
+    }
     for (int i = 0; i < 6 && e == hipSuccess; i++) e = hipEventCreate(&h->ev[i]);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     // LDS above 64 KB per workgroup has to be requested explicitly

@@ -48,25 +48,27 @@ class Plan(ctypes.Structure):
 SLOTS_IN_LDS, SLOTS_IN_REGS, SLOTS_IN_MEM = 0, 1, 2
 
 
-def plan(cfg):
-    """(VMS_OK or an error code, the plan the library makes for cfg)."""
+def plan(cfg, in_lds=False):
+    """(VMS_OK or an error code, the plan the library makes for cfg; in_lds: where there is no memory for its tables)."""
     out = Plan()
+    lib().emu_use_plan(PLAN_IN_LDS if in_lds else PLAN_OF_LIBRARY)
     return lib().emu_plan(ctypes.byref(cfg), ctypes.byref(out)), out
 
 
-PLAN_OF_LIBRARY, PLAN_POOL_IN_MEM, PLAN_SMALL = 0, 1, 2
+PLAN_OF_LIBRARY, PLAN_POOL_IN_MEM, PLAN_SMALL, PLAN_IN_LDS = 0, 1, 2, 3
 
 
-def replay(events, cfg, stats_dtype, n_events=None, pool_in_mem=False, small=False):
+def replay(events, cfg, stats_dtype, n_events=None, pool_in_mem=False, small=False, in_lds=False):
     """events: uint64[n_traces, max_events]; cfg: the binding's vms_config; pool_in_mem: the plan of a large batch with
-    all tables in the workspace (cfg names VMS_TABLES_WORKSPACE_ALL); small: the plan that needs least workspace.
+    all tables in the workspace (cfg names VMS_TABLES_WORKSPACE_ALL); small: the plan that needs least workspace;
+    in_lds: the one without tables in global memory.
     Returns (dec_split, dec_vms, stats[2, n_traces])."""
     ev = np.ascontiguousarray(events, dtype=np.uint64)
     assert ev.shape == (cfg.n_traces, cfg.max_events)
     ds, dv = np.zeros_like(ev), np.zeros_like(ev)
     st = np.zeros((2, cfg.n_traces), dtype=stats_dtype)
     ne = None if n_events is None else np.ascontiguousarray(n_events, dtype=np.uint32)
-    lib().emu_use_plan(PLAN_POOL_IN_MEM if pool_in_mem else PLAN_SMALL if small else PLAN_OF_LIBRARY)
+    lib().emu_use_plan(PLAN_POOL_IN_MEM if pool_in_mem else PLAN_SMALL if small else PLAN_IN_LDS if in_lds else PLAN_OF_LIBRARY)
     rc = lib().emu_replay(ctypes.byref(cfg), ev.ctypes.data, None if ne is None else ne.ctypes.data,
                           ds.ctypes.data, dv.ctypes.data, st.ctypes.data)
     if rc != 0:

@@ -142,7 +142,7 @@ void body_selftest(void *tab) { selftest_kernel(&g_selftest_fail, (uint16_t *)ta
 
 }  // namespace
 
-enum { PLAN_OF_LIBRARY, PLAN_POOL_IN_MEM, PLAN_SMALL };
+enum { PLAN_OF_LIBRARY, PLAN_POOL_IN_MEM, PLAN_SMALL, PLAN_IN_LDS };
 static int g_plan;
 
 extern "C" {
@@ -153,8 +153,9 @@ struct emu_plan_info {
     uint64_t mem_stride[2];
 };
 
-// the plan that emu_replay runs: the library's; the fine-grained variant with all its tables out of the LDS, which the
-// library plans for large batches only; the one that needs least workspace
+// the plan that emu_replay runs (and emu_plan tells of, if it is the first or the last): the library's; the fine-grained variant with all its tables out of the LDS, which the
+// library plans for large batches only; the one that needs least workspace; the one without
+// tables in global memory
 void emu_use_plan(int which) { g_plan = which; }
 
 // Replays every trace under the policies of cfg->policy_mask with the kernels the library would
@@ -165,7 +166,7 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
                uint64_t *dec_vms, vms_trace_stats *stats)
 {
     ReplayPlan plan, again;
-    int rc = replay_plan_make(cfg, plan);
+    int rc = replay_plan_make(cfg, plan, g_plan == PLAN_IN_LDS);
     if (rc == VMS_OK && g_plan == PLAN_POOL_IN_MEM) rc = replay_plan_for(cfg, plan, true, true);
     if (rc == VMS_OK && g_plan != PLAN_SMALL) rc = replay_plan_retry(cfg, plan, again);
     if (rc == VMS_OK && g_plan == PLAN_SMALL) replay_plan_small(cfg, ~0ull, plan, again);
@@ -223,7 +224,7 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
 int emu_plan(const vms_config *cfg, emu_plan_info *out)
 {
     ReplayPlan p, again;
-    int rc = replay_plan_make(cfg, p);
+    int rc = replay_plan_make(cfg, p, g_plan == PLAN_IN_LDS);
     if (rc == VMS_OK) rc = replay_plan_retry(cfg, p, again);
     if (rc != VMS_OK) return rc;
     out->has_retry = again.has_retry;

@@ -138,6 +138,43 @@ def test_slot_tables_that_leave_no_room_in_lds_are_in_global_memory():
     rep.close()
 
 
+def test_tables_are_in_lds_where_the_device_has_no_memory_left():
+    # 1 GiB of slot tables for the stitching policy and half of that for the other, a handle after the other on a device
+    # with about 1 GiB left (more than it says it has may be given out)
+    import torch
+    n, slots, ne = 16000, 4000, 64 * 3
+    ev, _ = gpu_util.slot_reuse_traces(slots, ne, seed=4)
+    ev = np.ascontiguousarray(np.tile(ev, (n // 4, 1)))
+    cfg = gpu_util.make_cfg(n, ne, slots, variant=1, max_free_blocks=64, max_small_blocks=64, max_pblocks=128, max_sblocks=520,
+                            max_runs=400, max_chunks=640)
+    d = torch.from_numpy(ev.view(np.int64)).cuda()
+    out = torch.zeros_like(d), torch.zeros_like(d)
+    torch.cuda.empty_cache()
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")
+    held = []
+    try:
+        for _ in range(12):
+            held.append(binding.Replay(cfg))
+            if held[-1].lds_bytes()[1] > 64000:
+                break
+    finally:
+        del rest
+        torch.cuda.empty_cache()
+    tight = held.pop()
+    assert tight.lds_bytes()[1] > 64000
+    held.append(binding.Replay(cfg))
+    for rep in held:
+        assert rep.lds_bytes()[1] < 20000
+        rep.close()
+    tight.run(d, None, *out)
+    st = tight.stats()
+    tight.close()
+    for pol in (oracle.SPLIT, oracle.VMS):
+        dec, ost = oracle.replay(ev[:4], gpu_util.oracle_params(cfg), pol)
+        assert np.array_equal(out[pol].cpu().numpy().view(np.uint64), np.tile(dec, (n // 4, 1)))
+        assert np.array_equal(st[pol]["digest"], np.tile(ost["digest"], n // 4))
+
+
 def test_static_run_of_a_batch_whose_own_plan_needs_more_workspace():
     # the library plans this batch on the fine-grained variant, whose lists do not fit the built-in workspace; the flat
     # variant's do

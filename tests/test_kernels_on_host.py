@@ -366,3 +366,25 @@ def test_second_pass_shrinks_the_table_of_multi_chunk_pblocks():
                             max_pblocks=16, max_multi_pblocks=2855, max_sblocks=900, max_runs=64, max_chunks=64, retry_traces=1)
     rc, p = emu.plan(cfg)
     assert rc == 0 and p.fine and p.has_retry
+
+
+# A batch whose tables are in global memory has a plan without them for a device that has no room left: in both passes,
+# for each policy, whichever variant and place the handle names
+@pytest.mark.parametrize("config,slots,traces", [(1, 120, 6000), (2, 64, 4096), (3, 64, 4096), (4, 650, 4096), (4, 650, 700), (6, 1163, 1280)])
+@pytest.mark.parametrize("kw", [dict(), dict(variant=1), dict(variant=2), dict(table_place=3)])
+def test_plan_without_tables_in_global_memory(config, slots, traces, kw):
+    if config == 3 and kw.get("variant") == 1:
+        return
+    cfg = workloads.make_config(binding, config, traces, 20000, slots, **kw)
+    rc, p = emu.plan(cfg, in_lds=True)
+    assert rc == 0 and p.slots != emu.SLOTS_IN_MEM and list(p.mem_stride) == [0, 0] and max(p.lds_bytes) <= 160 * 1024
+    again = emu.plan(workloads.make_config(binding, config, traces, 20000, slots, **kw))[1].has_retry
+    assert p.has_retry == again
+
+
+def test_replay_without_tables_in_global_memory():
+    ev, ms = tg.generate(4, n_traces=3, n_events=1500, seed=9)
+    cfg = workloads.make_config(binding, 4, 900, 1500, ms)
+    ev = np.concatenate([ev, np.zeros((897, 1500), dtype=np.uint64)])
+    assert emu.plan(cfg)[1].slots == emu.SLOTS_IN_MEM
+    check(ev, cfg, n_events=np.array([1500, 1499, 1437] + [0] * 897, dtype=np.uint32), label="in LDS", in_lds=True)
