@@ -21,9 +21,10 @@ TABLES = {
     # variant: single chunks in bitmaps, a table for the pBlocks of two or more chunks, lists in the workspace)
     # (LDS is handed out in 1,280-byte granules, 128 per compute unit.  Multi-chunk pBlocks: 2,421 to 2,824 at most over
     # 13 seeds.  2,848 places are what five wavefronts per compute unit have room for with all tables in LDS, 31,984 B,
-    # where the library puts them for up to 1,280 traces; up to 2,560 the tables of the sBlocks are in the workspace and
+    # where the library puts them for up to 1,280 traces; up to 2,304 the tables of the sBlocks are in the workspace and
     # a wavefront takes 16,144 B; for more traces than that the table of the multi-chunk pBlocks is in global memory too,
-    # 4,432 B, sixteen wavefronts.  With 2,592 places seven of the 13 seeds sent one or two traces through the second pass)
+    # 4,432 B, sixteen wavefronts.  2,592 places would hold 2,560 traces in one round without that, 2500x20000 in 81.8
+    # instead of 88.2 ms, but at 50,000 events seven of the 13 seeds send one or two traces through the second pass)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2848, max_sblocks=2560, max_runs=1 << 18, max_chunks=10240),
     # (up to 512 traces on the flat kernel with the slot table in LDS, 49,616 B, up to 1,024 with it in global memory,
     # 39,184; the fine-grained one beyond that, 14,320 B, and with all its tables in the workspace and global memory 7,504,
@@ -64,10 +65,6 @@ def make_config(binding, config, n_traces, n_events, max_slots, kind=None, **ove
     tables = TABLES_5[kind] if config == 5 else TABLES[config % 10]
     for k, v in tables.items():
         setattr(cfg, k, v)
-    if tables is TABLES[3] and 2304 < n_traces <= 2560:
-        # with 2,592 places a wavefront takes 15,120 B, ten per compute unit instead of nine: the batch in one round
-        # (2500x20000 85 ms instead of 127; a trace that needs more places goes through the second pass)
-        cfg.max_multi_pblocks = 2592
     # the tables hold the high-water marks of the seeded workloads with little headroom; a trace of
     # another seed that outgrows one is replayed a second time with doubled tables
     cfg.retry_traces = min(32, n_traces)

@@ -180,7 +180,7 @@ def test_both_policies_in_one_launch(kind, free):
 # at once beside its splitting kernel, then the fine-grained variant, then its tables in the workspace
 @pytest.mark.parametrize("config,slots,sizes", [
     (2, 64, [(1024, 34832), (2048, 34832), (3072, 8560), (4096, 8560)]),
-    (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2560, 15120), (4096, 4432)]),
+    (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2304, 16144), (2305, 4432), (2560, 4432), (4096, 4432)]),
     (4, 650, [(64, 49616), (512, 49616), (1024, 39184), (1280, 14320), (4096, 7504)]),
     (6, 1163, [(64, 50560), (512, 50560), (1024, 31936), (1280, 31936), (1281, 10304), (4096, 6560)])])
 def test_plan_of_a_batch_by_its_size(config, slots, sizes):
