@@ -4,7 +4,7 @@ Table sizes (per trace) are capacity settings of the replay engine, not paramete
 allocators: a trace that outgrows them is replayed a second time with doubled tables (up to
 retry_traces traces per run), and flagged VMS_ST_TABLE_OVERFLOW, never replayed wrongly, if that
 does not suffice.  The values below hold the high-water marks measured on the full workloads of the
-default seed with headroom (what other seeds need is said beside the table where they were counted);
+default seed with headroom (what other seeds and longer traces need is said beside the tables where they were counted);
 smaller tables mean less LDS per wavefront and therefore more resident wavefronts per compute unit.
 """
 from . import tracegen
@@ -52,6 +52,21 @@ TABLES_5 = {
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=736, max_sblocks=576, max_runs=4224, max_chunks=18432),
 }
 
+# Tables of traces longer than the presets of workloads 2 and 6 are sized for: pBlocks are cut finer the longer a trace
+# runs.  (events up to which the tables before hold its traces, the tables of longer ones.)  With the presets' tables 202
+# of 1,280 ZeRO-3 traces x 50,000 and 53 of 1,024 recomputation traces were replayed again, in turns of retry_traces:
+# 453 and 203 ms for the whole pass, 30.6 and 19.4 with these; at 100,000 events 2,475 and 1,155, 55 and 66.  No trace of 13
+# seeds outgrows them (50,000 events: 721 pBlocks and 622 at most; 100,000: 867 and 625).  Up to 23,000
+# events ZeRO-3 keeps the smaller ones, five traces per compute unit on the flat kernel: one trace of a batch of 1,280 is
+# replayed again for one or two seeds of four (22,000: 21.8 against 13.3 ms), for the others the batch is that much faster
+# (9.1 against 13.3).
+LONGER = {
+    # (40,208 B on the flat kernel, four wavefronts per compute unit like the preset's)
+    2: [(20000, dict(max_free_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=4992, max_chunks=4096)), (50000, TABLES_5[2])],
+    6: [(23000, dict(max_free_blocks=192, max_pblocks=768, max_sblocks=576, max_runs=4352, max_chunks=9408)),
+        (50000, dict(max_free_blocks=192, max_pblocks=896, max_sblocks=688, max_runs=8448, max_chunks=9408))],
+}
+
 
 def shape(config):
     c = tracegen.CONFIGS[config]
@@ -63,6 +78,9 @@ def make_config(binding, config, n_traces, n_events, max_slots, kind=None, **ove
     cfg = binding.vms_config_default(n_traces, n_events, max_slots)
     cfg.capacity_bytes = tracegen.CONFIGS[config]["capacity_bytes"]
     tables = TABLES_5[kind] if config == 5 else TABLES[config % 10]
+    for events, longer in LONGER.get(config % 10, []):
+        if n_events > events:
+            tables = longer
     for k, v in tables.items():
         setattr(cfg, k, v)
     # the tables hold the high-water marks of the seeded workloads with little headroom; a trace of

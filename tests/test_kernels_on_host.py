@@ -257,6 +257,21 @@ def test_zero3_preset_holds_its_traces_in_the_first_pass(seed, trace):
     assert st["max_pblocks"][1, 0] > 512
 
 
+# Presets by the length of the traces: no pool of 320 traces outgrows its tables, and of the first 64 the trace with the
+# most pBlocks is replayed on them without a second pass
+@pytest.mark.parametrize("config,events,worst", [(6, 50000, 49), (2, 50000, 8), (6, 100000, None), (2, 100000, None), (2, 30000, None)])
+def test_presets_hold_longer_traces_in_the_first_pass(config, events, worst):
+    ev, ms = tg.generate(config, n_traces=320, n_events=events, seed=1)
+    cfg = workloads.make_config(binding, config, 320, events, ms)
+    _, st = oracle.replay(ev, gpu_util.oracle_params(cfg), oracle.VMS, want_decisions=False, threads=8)
+    assert st["max_pblocks"].max() < cfg.max_pblocks and st["max_sblocks"].max() + 2 < cfg.max_sblocks
+    assert st["peak_reserved"].max() <= cfg.max_chunks * cfg.chunk_bytes
+    if worst is not None:
+        assert st["max_pblocks"][:64].argmax() == worst
+        cfg = workloads.make_config(binding, config, 1, events, ms, retry_traces=0, policy_mask=2)
+        check(ev[worst : worst + 1], cfg, label="trace %d" % worst)
+
+
 def test_table_overflow_is_flagged_not_fatal():
     ev, ms = tg.generate(3, n_traces=1, n_events=2500, seed=5)
     cfg = gpu_util.make_cfg(1, 2500, ms, policy_mask=2, variant=2, max_pblocks=64, max_sblocks=520, max_chunks=4096)
