@@ -28,7 +28,9 @@ if int(os.environ.get("GPU_MAX_HW_QUEUES", "4") or 4) < 8:
     os.environ["GPU_MAX_HW_QUEUES"] = "8"
 
 HBM_PEAK_GBS = 8000.0
-BYTES_PER_EVENT_PER_KERNEL = 16       # 8 B event word read + 8 B decision word written
+# per launch: 8 B event word read + 8 B decision word written for each policy it replays
+BYTES_PER_EVENT = {"vms": 16, "split": 16, "both": 24}
+POLICY_OF_LAUNCH = {"vms": "stitching policy", "split": "splitting policy", "both": "both policies in one launch"}
 KERNEL_SOURCES = ("replay_kernels.hpp", "replay_fine.hpp", "replay_plan.hpp", "vms_replay.hip", "wave_ops.hpp", "wave_hw.hpp")
 MAPPING_LIMIT = 40000                 # chunk mappings the demo may hold at once (hipMemSetAccess was refused at about 48,000)
 
@@ -54,6 +56,23 @@ def recorded_counters(config):
         return json.loads(fields["counters_json"])
     except (OSError, KeyError, ValueError):
         return {}
+
+
+def dominant_launch(per_batch, counters):
+    """(batch, "vms" / "split" / "both", its milliseconds in this run, its recorded counters) of the launch with the most
+    work.  A batch whose two policies went in one launch has the same time for both.  Side by side every launch lasts
+    about as long as the step, so where the profiled figures exist the launch that takes longest ALONE is named; its
+    duration here is still the one measured in this run."""
+    launches = []
+    for b, ms in enumerate(per_batch):
+        if ms["vms"] == ms["split"]:
+            launches.append((b, "both", ms["vms"]))
+        else:
+            launches += [(b, p, ms[p]) for p in ("vms", "split")]
+    recorded = [counters.get("batch%d_%s" % (b, p), {}) for b, p, _ in launches]
+    alone = all("ms_alone" in r for r in recorded)
+    i = max(range(len(launches)), key=lambda i: recorded[i]["ms_alone"] if alone else launches[i][2])
+    return launches[i] + (recorded[i],)
 
 
 VALU_PEAK_GIPS = 256 * 4 * 2.4 / 4        # G wave64 VALU instructions per second: 614.4
@@ -253,20 +272,10 @@ def main():
     total_events = n_traces * n_events
     ms_per_step = dt / args.steps * 1e3
     counters = recorded_counters(args.config) if n_traces == base["n_traces"] and n_events == base["n_events"] else {}
-    # The dominant kernel: the launch (batch, policy) with the most work.  Side by side every launch
-    # lasts about as long as the step, so where the profiled figures exist the launch that takes
-    # longest ALONE is named; its duration here is still the one measured in this run.
-    launches = [(i, p) for i in range(len(batches)) for p in ("vms", "split")]
-    if all("ms_alone" in counters.get("batch%d_%s" % bp, {}) for bp in launches):
-        dom_b, dom_p = max(launches, key=lambda bp: counters["batch%d_%s" % bp]["ms_alone"])
-    else:
-        dom_b, dom_p = max(launches, key=lambda bp: per_batch[bp[0]][bp[1]])
-    dom_events = batches[dom_b]["events"].size
-    algo_bytes = BYTES_PER_EVENT_PER_KERNEL * dom_events
-    achieved = algo_bytes / (per_batch[dom_b][dom_p] * 1e-3) / 1e9
-    dom_name = "%s policy, batch %d%s" % ("stitching" if dom_p == "vms" else "splitting", dom_b,
-                                          " (generator %d)" % kinds[dom_b] if kinds[dom_b] else "")
-    dom_counters = counters.get("batch%d_%s" % (dom_b, dom_p), {})
+    dom_b, dom_p, dom_ms, dom_counters = dominant_launch(per_batch, counters)
+    algo_bytes = BYTES_PER_EVENT[dom_p] * batches[dom_b]["events"].size
+    achieved = algo_bytes / (dom_ms * 1e-3) / 1e9
+    dom_name = "%s, batch %d%s" % (POLICY_OF_LAUNCH[dom_p], dom_b, " (generator %d)" % kinds[dom_b] if kinds[dom_b] else "")
     lds = [bt["rep"].lds_bytes() for bt in batches]
     summaries = [bt["rep"].summary() for bt in batches]
     sum_res = [sum(int(s.sum_peak_reserved[p]) for s in summaries) for p in (0, 1)]
@@ -292,11 +301,10 @@ def main():
         "roofline": {"bound": "hbm", "kernel": dom_name,
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": dom_counters.get("hbm_bytes"),
-                     "kernel_ms": per_batch[dom_b][dom_p],                    # in this run, beside the other launches
+                     "kernel_ms": dom_ms,                    # in this run, beside the other launches
                      "kernel_ms_alone": dom_counters.get("ms_alone"),        # profiled (--pmc runs the launches one by one)
-                     "note": "algorithmic bytes = 16 B per event (8 B event read + 8 B decision written) x the events of "
-                             "that launch; the path is a serial state machine per trace, bound by instruction issue and "
-                             "LDS / list latency, not by bandwidth: see issue_rate and lds below",
+                     "note": "algorithmic bytes = 8 B event read + 8 B decision written per policy of that launch, x its "
+                             "events; the path is a serial state machine per trace, bound by instruction issue and LDS / list latency, not by bandwidth: see issue_rate and lds below",
                      # from the committed counter summary of this workload (null once the kernels have changed)
                      "issue_rate": dom_counters.get("issue_rate"),           # wave instructions per SIMD cycle
                      "lds": dom_counters.get("lds"),                         # bytes, GB/s and fraction of the measured peak
@@ -305,7 +313,7 @@ def main():
                      # instructions (counted by the profiler; the same for every run of the same kernel on
                      # the same input) over its duration in this run, against one wave64 instruction per
                      # 4 cycles on each of 256 x 4 SIMDs at 2.4 GHz.
-                     "alu": alu_view(dom_counters, per_batch[dom_b][dom_p])},
+                     "alu": alu_view(dom_counters, dom_ms)},
         # the same over the whole step: all launches' instructions over the step time
         "step_alu": step_alu_view(counters, ms_per_step),
         "kernels": counters or None,
