@@ -273,16 +273,25 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 // fine-grained 12.0).
 // A slot table in global memory costs the flat variant 1 to 2 % (one random trace 1.057 -> 1.069 ms, scale-out
 // 320x20000 7.58 -> 7.75).
+// Streams of many small requests are bound by instruction issue from about three wavefronts per SIMD on: a fourth gains
+// them nothing, and leaves the splitting kernel no registers to run beside it (ZeRO-3 4096x20000: 22.3 ms with the tables
+// in LDS, fourteen wavefronts per compute unit, 23.5 with them in the workspace, sixteen; 8,192 traces 38.7 and 43.3;
+// LoRA 4096x20000 with pool[] in global memory 22.0, in LDS, fourteen, 21.4).  Where every request stitches they wait
+// for memory, and sixteen pay (offloading 4096x8000: 42 ms, 60 with nine).
+// What the model cannot know: a stream of more than 64 slots of which every request stitches costs the fine-grained
+// variant 2.4 rounds, not 1.6 (recomputation 1536x8000 with 65 slots 8.8 ms, flat 6.7), and one of 64 or fewer with the
+// default tables is charged more rounds than it takes (4096x8000 on the flat variant 20.7 ms, fine-grained 15.8).
 inline uint64_t plan_cost(const ReplayPlan &x, const vms_config &c)
 {
     const uint64_t round = !x.fine ? 100 + (x.slots == SLOTS_IN_MEM ? 2 : 0)
                                    : (x.slot_regs ? 260 : 160) * (x.tbl_ws == 4 ? 112 : x.tbl_ws ? 106 : 100) / 100;
-    const uint64_t n = c.n_traces, w = plan_waves_per_cu(x), all = (uint64_t)PLAN_CUS * PLAN_GRANULES;
+    const uint64_t most = x.fine && !x.slot_regs ? 12 : 16;     // wavefronts per compute unit that gain anything
+    const uint64_t n = c.n_traces, fit = plan_waves_per_cu(x), w = fit < most ? fit : most, all = (uint64_t)PLAN_CUS * PLAN_GRANULES;
     if (!w) return ~0ull;
-    const uint64_t lds = plan_granules(x.kp[1].lds_bytes), g = lds > PLAN_GRANULES / 16 ? lds : PLAN_GRANULES / 16;
+    const uint64_t lds = plan_granules(x.kp[1].lds_bytes), g3 = lds * most > PLAN_GRANULES ? 3 * lds : 3 * PLAN_GRANULES / most;     // in thirds
     const uint64_t g_split = c.policy_mask & VMS_POLICY_SPLIT ? plan_granules(x.kp[0].lds_bytes) : 0;
     if (n > PLAN_CUS * w) {
-        const uint64_t shares = n * (g * round + g_split * 65) / all + round / 2, rounds = (n + PLAN_CUS * w - 1) / (PLAN_CUS * w);
+        const uint64_t shares = n * (g3 * round + 3 * g_split * 65) / (3 * all) + round / 2, rounds = (n + PLAN_CUS * w - 1) / (PLAN_CUS * w);
         return w > 8 || shares > rounds * round ? shares : rounds * round;
     }
     if (!g_split) return round;

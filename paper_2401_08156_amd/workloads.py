@@ -27,11 +27,10 @@ TABLES = {
     # instead of 88.2 ms, but at 50,000 events seven of the 13 seeds send one or two traces through the second pass)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2848, max_sblocks=2560, max_runs=1 << 18, max_chunks=10240),
     # (up to 512 traces on the flat kernel with the slot table in LDS, 49,616 B, up to 1,024 with it in global memory,
-    # 39,184; the fine-grained one beyond that, 14,320 B, and with all its tables in the workspace and global memory 7,504,
-    # sixteen wavefronts per compute unit, where that saves a round; chunk tables for the 17,699 chunks the largest trace
-    # reserves)
+    # 39,184; the fine-grained one beyond that, 14,320 B, and with the tables of its sBlocks in the workspace 10,384,
+    # beyond 2,560, where that saves a round; chunk tables for the 17,699 chunks the largest trace reserves)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432),
-    # (the same for the scale-out regime, 9,408 chunks at most; 50,560 / 31,936 / 10,304 / 6,560 B.  31,936 B are what five
+    # (the same for the scale-out regime, 9,408 chunks at most; 50,560 / 31,936 / 10,304 B.  31,936 B are what five
     # wavefronts per compute unit have room for, so that the 1,280 traces of the workload are on the flat kernel at once:
     # 8.4 ms, 12.0 on the fine-grained one, which 3,072 list entries, 576 sBlocks, 9,728 chunks and 544 pBlocks made them
     # take.  No trace of 19 seeds outgrows these sizes; with 2,864 list entries one of them sent a trace through the
@@ -47,7 +46,7 @@ TABLES_5 = {
     # unit; for more traces than that the library moves the sBlock tables to the workspace, 14,960 B, ten, and beyond
     # 2,560 the table of the multi-chunk pBlocks too, 3,760 B, sixteen)
     3: dict(max_free_blocks=64, max_pblocks=8192, max_multi_pblocks=2720, max_sblocks=4128, max_runs=1 << 18, max_chunks=8480),
-    # (18,055 chunks is the most a trace of this kind reserves; 7,504 B of LDS per wavefront for the 5,461 traces of the
+    # (18,055 chunks is the most a trace of this kind reserves; 10,768 B of LDS per wavefront for the 5,461 traces of the
     # workload)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=736, max_sblocks=576, max_runs=4224, max_chunks=18432),
 }

@@ -35,24 +35,26 @@ def lib():
         _lib.emu_replay.argtypes = [vp, vp, vp, vp, vp, vp]
         _lib.emu_selftest.restype = ctypes.c_uint
         _lib.emu_plan.restype = ctypes.c_int
-        _lib.emu_plan.argtypes = [vp, vp]
+        _lib.emu_plan.argtypes = [vp, ctypes.c_int, vp]
     return _lib
 
 
 class Plan(ctypes.Structure):
     """What tests ask of a plan; slots: SLOTS_IN_LDS, SLOTS_IN_REGS or SLOTS_IN_MEM."""
-    _fields_ = [("fine", ctypes.c_uint32), ("slots", ctypes.c_uint32), ("tbl_ws", ctypes.c_uint32), ("has_retry", ctypes.c_uint32), ("lds_bytes", ctypes.c_uint32 * 2),
-                ("mem_stride", ctypes.c_uint64 * 2)]
+    _fields_ = [("fine", ctypes.c_uint32), ("slots", ctypes.c_uint32), ("tbl_ws", ctypes.c_uint32), ("has_retry", ctypes.c_uint32),
+                ("lds_bytes", ctypes.c_uint32 * 2), ("mem_stride", ctypes.c_uint64 * 2), ("cost", ctypes.c_uint64)]
 
 
 SLOTS_IN_LDS, SLOTS_IN_REGS, SLOTS_IN_MEM = 0, 1, 2
 
 
-def plan(cfg, in_lds=False):
-    """(VMS_OK or an error code, the plan the library makes for cfg; in_lds: where there is no memory for its tables)."""
+def plan(cfg, in_lds=False, tables_in_mem=-1):
+    """(VMS_OK or an error code, the plan the library makes for cfg; in_lds: where there is no memory for its tables).
+    tables_in_mem: the one plan of the variant and table place that cfg names, with its slot tables (1) and its table of
+    multi-chunk pBlocks (2) in global memory."""
     out = Plan()
     lib().emu_use_plan(PLAN_IN_LDS if in_lds else PLAN_OF_LIBRARY)
-    return lib().emu_plan(ctypes.byref(cfg), ctypes.byref(out)), out
+    return lib().emu_plan(ctypes.byref(cfg), tables_in_mem, ctypes.byref(out)), out
 
 
 PLAN_OF_LIBRARY, PLAN_POOL_IN_MEM, PLAN_SMALL, PLAN_IN_LDS = 0, 1, 2, 3

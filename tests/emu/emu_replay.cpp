@@ -150,7 +150,7 @@ extern "C" {
 // what tests ask of a plan
 struct emu_plan_info {
     uint32_t fine, slots, tbl_ws, has_retry, lds_bytes[2];
-    uint64_t mem_stride[2];
+    uint64_t mem_stride[2], cost;
 };
 
 // the plan that emu_replay runs (and emu_plan tells of, if it is the first or the last): the library's; the fine-grained variant with all its tables out of the LDS, which the
@@ -220,14 +220,17 @@ int emu_replay(const vms_config *cfg, const uint64_t *events, const uint32_t *n_
     return 0;
 }
 
-// What the library plans for cfg (has_retry: a second pass too).  Returns VMS_OK or a VMS_E* code.
-int emu_plan(const vms_config *cfg, emu_plan_info *out)
+// What the library plans for cfg (has_retry: a second pass too); with tables_in_mem >= 0 instead the one plan of the variant
+// and table place that cfg names, with its slot tables (bit 0) and pool[] (bit 1) in global memory.  Returns VMS_OK or a
+// VMS_E* code.
+int emu_plan(const vms_config *cfg, int tables_in_mem, emu_plan_info *out)
 {
     ReplayPlan p, again;
-    int rc = replay_plan_make(cfg, p, g_plan == PLAN_IN_LDS);
+    int rc = tables_in_mem < 0 ? replay_plan_make(cfg, p, g_plan == PLAN_IN_LDS) : replay_plan_for(cfg, p, tables_in_mem & 1, tables_in_mem & 2);
     if (rc == VMS_OK) rc = replay_plan_retry(cfg, p, again);
     if (rc != VMS_OK) return rc;
     out->has_retry = again.has_retry;
+    out->cost = plan_cost(p, *cfg);
     out->fine = p.fine;
     out->slots = p.slots;
     out->tbl_ws = p.tbl_ws;

@@ -176,17 +176,34 @@ def test_both_policies_in_one_launch(kind, free):
           n_events=np.array([1000, 937], dtype=np.uint32), label="generator %d, %d free blocks" % (kind, free))
 
 
-# The library's choices cost no more than the others they were made among: flat while a batch fits the compute units
-# at once beside its splitting kernel, then the fine-grained variant, then its tables in the workspace
+# The library's choice for the presets by the number of traces: flat while a batch fits the compute units at once beside
+# its splitting kernel, then the fine-grained variant, then its tables in the workspace, where that was measured to be
+# the fastest of the plans (ZeRO-3 and LoRA gain nothing from a fourth wavefront per SIMD, offloading does)
 @pytest.mark.parametrize("config,slots,sizes", [
     (2, 64, [(1024, 34832), (2048, 34832), (3072, 8560), (4096, 8560)]),
     (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2304, 16144), (2305, 4432), (2560, 4432), (4096, 4432)]),
-    (4, 650, [(64, 49616), (512, 49616), (1024, 39184), (1280, 14320), (4096, 7504)]),
-    (6, 1163, [(64, 50560), (512, 50560), (1024, 31936), (1280, 31936), (1281, 10304), (4096, 6560)])])
+    (4, 650, [(64, 49616), (512, 49616), (1024, 39184), (1280, 14320), (2560, 14320), (3584, 10384), (4096, 10384), (8192, 10384)]),
+    (6, 1163, [(64, 50560), (512, 50560), (1024, 31936), (1280, 31936), (1281, 10304), (3585, 10304), (4096, 10304), (8192, 10304)])])
 def test_plan_of_a_batch_by_its_size(config, slots, sizes):
     for n, lds in sizes:
         rc, out = emu.plan(workloads.make_config(binding, config, n, 20000, slots))
         assert rc == 0 and out.lds_bytes[1] == lds, (config, n, rc, out.lds_bytes[1])
+
+
+# ... and it costs no more than any other plan there is
+@pytest.mark.parametrize("config,slots", [(1, 110), (1, 650), (2, 64), (2, 65), (3, 64), (4, 650), (6, 1163)])
+@pytest.mark.parametrize("policies", [2, 3])
+def test_plan_of_a_batch_costs_least(config, slots, policies):
+    for n in [1, 64, 300, 512, 768, 1024, 1281, 1600, 2048, 2305, 2561, 3072, 3585, 4096, 5461, 8192, 16384]:
+        cfg = workloads.make_config(binding, config, n, 20000, slots, policy_mask=policies)
+        costs = {}
+        for variant, place, in_mem in [(1, 0, 0), (1, 0, 1), (2, 1, 1), (2, 3, 1), (2, 3, 3)]:
+            rc, p = emu.plan(workloads.make_config(binding, config, n, 20000, slots, policy_mask=policies, variant=variant, table_place=place),
+                             tables_in_mem=in_mem)
+            if rc == 0:
+                costs[variant, place, in_mem] = p.cost
+        rc, p = emu.plan(cfg)
+        assert rc == 0 and len(costs) == (3 if config == 3 else 5) and p.cost == min(costs.values()), (n, p.cost, costs)
 
 
 # slot tables in registers (up to 64 slots), in LDS (flat variant) and in global memory; a capacity that is reached, and an arena that is squeezed often
