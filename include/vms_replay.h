@@ -108,7 +108,8 @@ typedef struct vms_config {
                                     while more than this many are cached (Sec. 4.2.3)        */
     uint32_t max_slots;          /* slots are 0 .. max_slots-1                               */
     /* engine table sizes per trace; a trace that needs more gets VMS_ST_TABLE_OVERFLOW     */
-    uint32_t max_free_blocks;    /* inactive blocks of a splitting pool (up to 320: registers) */
+    uint32_t max_free_blocks;    /* inactive blocks of a splitting pool (the first 320 are in
+                                    registers, the rest in LDS)                              */
     uint32_t max_pblocks;        /* pBlocks (active and inactive)                            */
     uint32_t max_sblocks;        /* cached sBlocks; must exceed spool_threshold + 2          */
     uint32_t max_runs;           /* chunk runs summed over all cached sBlocks                */
@@ -140,7 +141,8 @@ typedef struct vms_config {
                                     per sBlock) or VMS_TABLES_WORKSPACE_ALL (sizes too: 6
                                     bytes less): more wavefronts per compute unit, each of
                                     them slower; at most 63000 chunks.  0: the library
-                                    chooses by the rounds of wavefronts the batch takes      */
+                                    chooses what the batch costs least under, for large
+                                    batches with the pBlocks outside the LDS too             */
 } vms_config;
 
 typedef struct vms_trace_stats {        /* one per (policy, trace) */

@@ -3,7 +3,7 @@
 // one is a single chunk, cache thousands of sBlocks, and stitch a new sBlock from a hundred
 // candidates for every other request.  One wavefront still replays one trace, but its tables are
 // laid out for that regime, in a quarter of the LDS the flat sorted arrays of replay_kernels.hpp
-// would need, so that four such wavefronts share a compute unit:
+// would need or less, so that five to sixteen such wavefronts share a compute unit:
 //
 //   bnd[]   one bit per physical chunk: set where a pBlock starts (and at the end of the last one).
 //           pBlocks are only ever created behind the last chunk (Alloc) or cut in two (Split), so
@@ -64,8 +64,10 @@ struct FineT {
     // trace's workspace slice: then they are read with workgroup-scope loads and moved by gblk_shift_*;
     // IDX is 16 bits wide there.  TH 4: pool[] is in global memory as well, which leaves 4 KB of LDS per trace, so that
     // the vector registers alone limit the wavefronts per compute unit (16; offloading 4096x50000, nine before, 371 ->
-    // 254 ms); its steps are longer, so scans have the next step's keys on their way and moves two steps
-    // before the first read of these tables after they were written (the stores must have arrived)
+    // 254 ms); its steps are longer, so scans have the next step's keys on their way and moves two steps.
+
+    // Before the first read of these tables after they were written.  It orders the accesses for the compiler only: the
+    // memory accesses of one wavefront pass the vector cache in order, so there is nothing to wait for.
     DI void tables_written() const
     {
         if constexpr (TH) tbl_fence();
@@ -104,20 +106,10 @@ DI u32 singles_free(const FineT<IDX, TH> &V, u32 w)
     return b & ((b >> 1) | (bn << 31)) & ~a;
 }
 
-// the chunks of bitmap word w that belong to inactive pBlocks of two or more chunks: the inactive
-// chunks that exist and are not single-chunk pBlocks (an inactive pBlock has none of its bits set)
-template <class IDX, int TH>
-DI u32 multi_free(const FineT<IDX, TH> &V, u32 w)
-{
-    const u32 b = V.bnd[w], bn = V.bnd[w + 1], a = V.bmp[w];
-    const u32 single = b & ((b >> 1) | (bn << 31));
-    const u32 n = V.n_chunks, exist = w * 32 + 32 <= n ? 0xFFFFFFFFu : (w * 32 >= n ? 0u : (1u << (n & 31)) - 1u);
-    return ~a & ~single & exist;
-}
-
-// The same for four consecutive bitmap words per lane (words 4 q .. 4 q + 3, sixteen-byte loads): the
-// free single-chunk pBlocks, the chunks of free multi-chunk pBlocks and the block starts.  One step
-// of the wavefront covers 8192 chunks.
+// For four consecutive bitmap words per lane (words 4 q .. 4 q + 3, sixteen-byte loads): the free
+// single-chunk pBlocks, the chunks of free multi-chunk pBlocks (the inactive chunks that exist and are not
+// single-chunk pBlocks: an inactive pBlock has none of its bits set) and the block starts.  One step of the
+// wavefront covers 8192 chunks.
 struct Quad {
     u32 single[4], multi[4], start[4];
 };

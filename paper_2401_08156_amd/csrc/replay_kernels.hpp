@@ -1,5 +1,5 @@
-// Replay kernels: one wavefront (= one workgroup of 64 lanes) replays one trace
-// under one policy.  All allocator state of the trace lives in that wave's LDS
+// Replay kernels: one wavefront of 64 lanes replays one trace under one policy
+// (a workgroup is one wavefront, or two that share nothing).  All allocator state of the trace lives in that wave's LDS
 // and registers; scalar state (counters, byte totals) stays wave-uniform so the
 // compiler keeps it in SGPRs.  Control flow is wave-uniform throughout: the 64
 // lanes only ever split up to scan / shift / mark the pool arrays in parallel.
@@ -641,8 +641,6 @@ DI u32 arena_put(VmsT &V, u32 at, u32 start, u32 len)
     return n;
 }
 
-DI bool bmp_test(const u32 *bmp, u32 c) { return (bmp[c >> 5] >> (c & 31)) & 1u; }
-
 DI u32 word_mask(u32 w, u32 start, u32 end)    // bits of word w inside [start, end)
 {
     u32 b0 = (w == (start >> 5)) ? (start & 31) : 0u;
@@ -735,25 +733,6 @@ DI u32 list_extract(const VmsT &V, u32 wmin, u32 wmax, u32 at, u32 spare)
     }
     wave_sync();
     return cnt;
-}
-
-// Is sBlock i inactive?  Evaluated by ONE lane for its own index i (lanes work on different
-// sBlocks side by side): the witness first, then the whole list.
-DI bool sblock_inactive_lane(const VmsT &V, u32 i)
-{
-    const u32 wit = V.swit[i];
-    if (V.bmp[ENT_WORD(wit)] & emask(wit)) return false;
-    const auto meta = V.smeta[i];
-    const u32 *list = V.arena + V.off(meta);
-    const u32 cnt = V.cnt(meta);
-    for (u32 r = 0; r < cnt; r++) {
-        const u32 e = list[r];
-        if (V.bmp[ENT_WORD(e)] & emask(e)) {
-            V.swit[i] = e;
-            return false;
-        }
-    }
-    return true;
 }
 
 template <class AcctT>

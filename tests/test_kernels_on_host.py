@@ -224,11 +224,10 @@ def test_ragged_traces_and_nothing_written_past_the_end():
 
 def test_second_pass_replays_traces_that_outgrow_the_tables():
     # tables far too small for the first trace's pools (the other two fit): flagged without a second
-    # pass, replayed in full with doubled tables with one.  (The flat stitching kernel as first pass is
-    # covered on the GPU: its sources carry no lane-switch marks for this host build.)
+    # pass, replayed in full with doubled tables with one
     ev, ms = tg.generate(1, n_traces=3, n_events=900, seed=13)
     ev[1:, 60:] = ev[1:, :1] * 0 + tg.make_events([("A", 0, 2 * MiB), ("F", 0)] * 420)[None, :]
-    for variant in (binding.VMS_VARIANT_FINE,):
+    for variant in (binding.VMS_VARIANT_FINE, binding.VMS_VARIANT_FLAT):
         small = dict(variant=variant, max_free_blocks=24, max_pblocks=40, max_sblocks=560, max_runs=900, max_chunks=8192)
         _, _, st = emu.replay(ev, gpu_util.make_cfg(3, 900, ms, **small), binding.STATS_DTYPE)
         assert (st["status"][:, 0] & binding.VMS_ST_TABLE_OVERFLOW).all() and not (st["status"][:, 1:] & binding.VMS_ST_TABLE_OVERFLOW).any()
@@ -263,6 +262,22 @@ def test_lists_are_compacted_under_a_slot_table_in_lds():
                                 max_pblocks=1024, max_sblocks=92, max_runs=700, max_chunks=20480)
         st = check(ev, cfg, label="compaction, slot table in LDS, tables %d" % place)
         assert st["n_sblock_created"][1, 0] > 400 and st["n_sblock_evicted"][1, 0] > 300
+
+
+# List places take all 16 bits, whatever the slots that hold them: lists of a thousand words each, until they reach
+# behind granule 32,767 of an arena of 43,200, then hits on the sBlocks that have them
+@pytest.mark.parametrize("place", [1, 3])
+@pytest.mark.parametrize("in_lds", [False, True])
+def test_list_places_of_sixteen_bits(place, in_lds):
+    chunk, n = 2 * MiB, 1000
+    ops = [op for i in range(n) for op in (("A", 2 * i, chunk), ("A", 2 * i + 1, 31 * chunk))] + [("F", 2 * i) for i in range(n)]
+    sizes = [n - i for i in range(160)]
+    ops += [op for size in sizes + sizes[::-1] for op in (("A", 0, size * chunk), ("F", 0))]
+    ev = tg.make_events(ops)[None, :]
+    cfg = gpu_util.make_cfg(1, ev.shape[1], 2 * n, policy_mask=2, variant=2, table_place=place, max_pblocks=8192, max_multi_pblocks=1100,
+                            max_sblocks=2560, max_runs=160000, max_chunks=32000)
+    st = check(ev, cfg, label="lists of a thousand words", in_lds=in_lds)
+    assert st["n_code"][1, 0, 1] == 160 and st["max_runs"][1, 0] > 36000
 
 
 @pytest.mark.parametrize("seed,trace", [(1, 300), (12345, 500)])
