@@ -276,8 +276,8 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 // Streams of many small requests are bound by instruction issue from about three wavefronts per SIMD on: a fourth gains
 // them nothing, and leaves the splitting kernel no registers to run beside it (ZeRO-3 4096x20000: 22.3 ms with the tables
 // in LDS, fourteen wavefronts per compute unit, 23.5 with them in the workspace, sixteen; 8,192 traces 38.7 and 43.3;
-// LoRA 4096x20000 with pool[] in global memory 22.0, in LDS, fourteen, 21.4).  Where every request stitches they wait
-// for memory, and sixteen pay (offloading 4096x8000: 42 ms, 60 with nine).
+// LoRA 4096x20000 with pool[] in global memory 22.0, with it in LDS, fourteen, 21.4).  Where every request stitches they
+// wait for memory, and sixteen pay (offloading 4096x8000: 42 ms, 60 with nine).
 // What the model cannot know: a stream of more than 64 slots of which every request stitches costs the fine-grained
 // variant 2.4 rounds, not 1.6 (recomputation 1536x8000 with 65 slots 8.8 ms, flat 6.7), and one of 64 or fewer with the
 // default tables is charged more rounds than it takes (4096x8000 on the flat variant 20.7 ms, fine-grained 15.8).

@@ -16,7 +16,10 @@ TABLES = {
     # config: splitting free list (max_small_blocks: the stitching policy's own, smaller one), pBlocks, sBlocks,
     # chunk-run list entries, chunks (x 2 MiB)
     1: dict(max_free_blocks=512, max_pblocks=1024, max_sblocks=640, max_runs=4096, max_chunks=8192),
-    2: dict(max_free_blocks=192, max_pblocks=544, max_sblocks=576, max_runs=3840, max_chunks=4096),
+    # (40,208 B on the flat kernel: four wavefronts per compute unit have room for as much.  No trace of 120 seeds outgrows
+    # these sizes at 20,000 events, nor of 13 at 50,000 (607 and 622 pBlocks); 544 pBlocks and 3,840 list entries were
+    # too few in one seed of seven, whose batch of 1,024 traces then took 23 ms instead of 8)
+    2: dict(max_free_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=4992, max_chunks=4096),
     # offloading grinds pBlocks down to single chunks: thousands of pBlocks and sBlocks (the fine-grained kernel
     # variant: single chunks in bitmaps, a table for the pBlocks of two or more chunks, lists in the workspace)
     # (LDS is handed out in 1,280-byte granules, 128 per compute unit.  Multi-chunk pBlocks: 2,421 to 2,824 at most over
@@ -30,12 +33,12 @@ TABLES = {
     # 39,184; the fine-grained one beyond that, 14,320 B, and with the tables of its sBlocks in the workspace 10,384,
     # beyond 2,560, where that saves a round; chunk tables for the 17,699 chunks the largest trace reserves)
     4: dict(max_free_blocks=320, max_small_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=3840, max_chunks=18432),
-    # (the same for the scale-out regime, 9,408 chunks at most; 50,560 / 31,936 / 10,304 B.  31,936 B are what five
+    # (the same for the scale-out regime, 9,408 chunks at most; 50,608 / 31,984 / 10,464 B.  31,984 B are what five
     # wavefronts per compute unit have room for, so that the 1,280 traces of the workload are on the flat kernel at once:
     # 8.4 ms, 12.0 on the fine-grained one, which 3,072 list entries, 576 sBlocks, 9,728 chunks and 544 pBlocks made them
-    # take.  No trace of 19 seeds outgrows these sizes; with 2,864 list entries one of them sent a trace through the
-    # second pass)
-    6: dict(max_free_blocks=192, max_pblocks=536, max_sblocks=544, max_runs=2960, max_chunks=9408),
+    # take.  Among what fits there these sizes were outgrown least: by one trace of 220 seeds, which puts the batch at
+    # 21 ms; with 536 pBlocks, 544 sBlocks and 2,960 list entries by one in two seeds of 60)
+    6: dict(max_free_blocks=192, max_pblocks=576, max_sblocks=540, max_runs=2912, max_chunks=9408),
 }
 # config 5 mixes the generators of configs 2, 3 and 4 (trace i uses kind 2 + i mod 3) with twice the
 # events; replayed as three batches, one per kind, each with tables of its own
@@ -52,16 +55,14 @@ TABLES_5 = {
 }
 
 # Tables of traces longer than the presets of workloads 2 and 6 are sized for: pBlocks are cut finer the longer a trace
-# runs.  (events up to which the tables before hold its traces, the tables of longer ones.)  With the presets' tables 202
-# of 1,280 ZeRO-3 traces x 50,000 and 53 of 1,024 recomputation traces were replayed again, in turns of retry_traces:
-# 453 and 203 ms for the whole pass, 30.6 and 19.4 with these; at 100,000 events 2,475 and 1,155, 55 and 66.  No trace of 13
-# seeds outgrows them (50,000 events: 721 pBlocks and 622 at most; 100,000: 867 and 625).  Up to 23,000
-# events ZeRO-3 keeps the smaller ones, five traces per compute unit on the flat kernel: one trace of a batch of 1,280 is
-# replayed again for one or two seeds of four (22,000: 21.8 against 13.3 ms), for the others the batch is that much faster
-# (9.1 against 13.3).
+# runs.  (events up to which the tables before hold its traces, the tables of longer ones.)  With tables for 20,000 events
+# 202 of 1,280 ZeRO-3 traces x 50,000 were replayed again, in turns of retry_traces: 453 ms for the whole pass, 30.6 with
+# these; at 100,000 events 2,475 and 55, recomputation 1,155 and 66.  No trace of 13 seeds outgrows them (ZeRO-3 721 pBlocks
+# at most at 50,000 events, 867 at 100,000; recomputation 625).  Up to 23,000 events ZeRO-3 keeps the smaller ones, five
+# traces per compute unit on the flat kernel: two of 40 seeds have a trace that is replayed again (22,000 events: 21.8
+# against 13.3 ms), for the others the batch is that much faster (9.1 against 13.3).
 LONGER = {
-    # (40,208 B on the flat kernel, four wavefronts per compute unit like the preset's)
-    2: [(20000, dict(max_free_blocks=192, max_pblocks=640, max_sblocks=576, max_runs=4992, max_chunks=4096)), (50000, TABLES_5[2])],
+    2: [(50000, TABLES_5[2])],
     6: [(23000, dict(max_free_blocks=192, max_pblocks=768, max_sblocks=576, max_runs=4352, max_chunks=9408)),
         (50000, dict(max_free_blocks=192, max_pblocks=896, max_sblocks=688, max_runs=8448, max_chunks=9408))],
 }

@@ -180,10 +180,10 @@ def test_both_policies_in_one_launch(kind, free):
 # its splitting kernel, then the fine-grained variant, then its tables in the workspace, where that was measured to be
 # the fastest of the plans (ZeRO-3 and LoRA gain nothing from a fourth wavefront per SIMD, offloading does)
 @pytest.mark.parametrize("config,slots,sizes", [
-    (2, 64, [(1024, 34832), (2048, 34832), (3072, 8560), (4096, 8560)]),
+    (2, 64, [(1024, 40208), (2048, 40208), (3072, 8944), (4096, 8944)]),
     (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2304, 16144), (2305, 4432), (2560, 4432), (4096, 4432)]),
     (4, 650, [(64, 49616), (512, 49616), (1024, 39184), (1280, 14320), (2560, 14320), (3584, 10384), (4096, 10384), (8192, 10384)]),
-    (6, 1163, [(64, 50560), (512, 50560), (1024, 31936), (1280, 31936), (1281, 10304), (3585, 10304), (4096, 10304), (8192, 10304)])])
+    (6, 1163, [(64, 50608), (512, 50608), (1024, 31984), (1280, 31984), (1281, 10464), (3585, 10464), (4096, 10464), (8192, 10464)])])
 def test_plan_of_a_batch_by_its_size(config, slots, sizes):
     for n, lds in sizes:
         rc, out = emu.plan(workloads.make_config(binding, config, n, 20000, slots))
@@ -287,6 +287,15 @@ def test_zero3_preset_holds_its_traces_in_the_first_pass(seed, trace):
     cfg = workloads.make_config(binding, 6, 1, 20000, ms, retry_traces=0, policy_mask=2)
     st = check(ev, cfg, label="seed %d trace %d" % (seed, trace))
     assert st["max_pblocks"][1, 0] > 512
+
+
+# ... and traces of seeds that tables of 536 and 544 places sent through the second pass
+@pytest.mark.parametrize("config,seed,trace,pblocks", [(6, 112, 500, 539), (6, 140, 930, 535), (2, 114, 463, 546)])
+def test_presets_hold_traces_of_other_seeds_in_the_first_pass(config, seed, trace, pblocks):
+    ev, ms = tg.generate(config, n_traces=1, n_events=20000, first_trace=trace, seed=seed)
+    cfg = workloads.make_config(binding, config, 1, 20000, ms, retry_traces=0, policy_mask=2)
+    st = check(ev, cfg, label="seed %d trace %d" % (seed, trace))
+    assert st["max_pblocks"][1, 0] == pblocks
 
 
 # Presets by the length of the traces: no pool of 320 traces outgrows its tables, and of the first 64 the trace with the
