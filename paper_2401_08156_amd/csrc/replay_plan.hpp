@@ -250,12 +250,18 @@ inline int replay_plan_for(const vms_config *cfg, ReplayPlan &p, bool slots_in_m
 const uint32_t PLAN_CUS = 256, PLAN_GRANULES = 128;
 inline uint32_t plan_granules(uint32_t lds_bytes) { return (lds_bytes + 1279) / 1280; }
 
-// Wavefronts of the stitching kernel that share a compute unit: by their LDS, and at most four per SIMD,
-// which is what their vector registers allow.
+// Wavefronts of the stitching kernel that share a compute unit.  By their vector registers: four per SIMD, but three where
+// the fine-grained kernel has its slot table in global memory and tables in the workspace (130 registers) or just two
+// tables there (129 to 135) ...
+inline uint32_t plan_waves_by_registers(const ReplayPlan &x)
+{
+    return x.fine && x.tbl_ws && (x.slots == SLOTS_IN_MEM || x.tbl_ws == 2) ? 12 : 16;
+}
+// ... and by their LDS
 inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 {
-    const uint32_t g = plan_granules(x.kp[1].lds_bytes), w = g ? PLAN_GRANULES / g : 16;
-    return w < 16 ? w : 16;
+    const uint32_t g = plan_granules(x.kp[1].lds_bytes), most = plan_waves_by_registers(x), w = g ? PLAN_GRANULES / g : most;
+    return w < most ? w : most;
 }
 
 // What a batch costs under plan x, in tenths of what one round of wavefronts of the flat variant takes.
@@ -273,11 +279,10 @@ inline uint32_t plan_waves_per_cu(const ReplayPlan &x)
 // fine-grained 12.0).
 // A slot table in global memory costs the flat variant 1 to 2 % (one random trace 1.057 -> 1.069 ms, scale-out
 // 320x20000 7.58 -> 7.75).
-// Streams of many small requests are bound by instruction issue from about three wavefronts per SIMD on: a fourth gains
-// them nothing, and leaves the splitting kernel no registers to run beside it (ZeRO-3 4096x20000: 22.3 ms with the tables
-// in LDS, fourteen wavefronts per compute unit, 23.5 with them in the workspace, sixteen; 8,192 traces 38.7 and 43.3;
-// LoRA 4096x20000 with pool[] in global memory 22.0, with it in LDS, fourteen, 21.4).  Where every request stitches they
-// wait for memory, and sixteen pay (offloading 4096x8000: 42 ms, 60 with nine).
+// (With four wavefronts per SIMD assumed everywhere, ZeRO-3 batches of 3,585 traces and more had their tables moved to
+// the workspace for a fourth that the registers have no room for: 4096x20000 23.4 ms, 21.8 with them in LDS, where
+// fourteen share a compute unit; 8,192 traces 42.7 and 38.9; LoRA 4096x50000 with pool[] in global memory 54.1, without
+// 53.5.)
 // What the model cannot know: a stream of more than 64 slots of which every request stitches costs the fine-grained
 // variant 2.4 rounds, not 1.6 (recomputation 1536x8000 with 65 slots 8.8 ms, flat 6.7), and one of 64 or fewer with the
 // default tables is charged more rounds than it takes (4096x8000 on the flat variant 20.7 ms, fine-grained 15.8).
@@ -285,8 +290,7 @@ inline uint64_t plan_cost(const ReplayPlan &x, const vms_config &c)
 {
     const uint64_t round = !x.fine ? 100 + (x.slots == SLOTS_IN_MEM ? 2 : 0)
                                    : (x.slot_regs ? 260 : 160) * (x.tbl_ws == 4 ? 112 : x.tbl_ws ? 106 : 100) / 100;
-    const uint64_t most = x.fine && !x.slot_regs ? 12 : 16;     // wavefronts per compute unit that gain anything
-    const uint64_t n = c.n_traces, fit = plan_waves_per_cu(x), w = fit < most ? fit : most, all = (uint64_t)PLAN_CUS * PLAN_GRANULES;
+    const uint64_t n = c.n_traces, w = plan_waves_per_cu(x), most = plan_waves_by_registers(x), all = (uint64_t)PLAN_CUS * PLAN_GRANULES;
     if (!w) return ~0ull;
     const uint64_t lds = plan_granules(x.kp[1].lds_bytes), g3 = lds * most > PLAN_GRANULES ? 3 * lds : 3 * PLAN_GRANULES / most;     // in thirds
     const uint64_t g_split = c.policy_mask & VMS_POLICY_SPLIT ? plan_granules(x.kp[0].lds_bytes) : 0;

@@ -178,7 +178,8 @@ def test_both_policies_in_one_launch(kind, free):
 
 # The library's choice for the presets by the number of traces: flat while a batch fits the compute units at once beside
 # its splitting kernel, then the fine-grained variant, then its tables in the workspace, where that was measured to be
-# the fastest of the plans (ZeRO-3 and LoRA gain nothing from a fourth wavefront per SIMD, offloading does)
+# the fastest of the plans (with slot tables in global memory and tables in the workspace the vector registers allow three
+# wavefronts per SIMD, not four: ZeRO-3 stays in LDS)
 @pytest.mark.parametrize("config,slots,sizes", [
     (2, 64, [(1024, 40208), (2048, 40208), (3072, 8944), (4096, 8944)]),
     (3, 64, [(64, 31984), (1280, 31984), (1281, 16144), (2304, 16144), (2305, 4432), (2560, 4432), (4096, 4432)]),
